@@ -100,17 +100,11 @@ struct Slot {
     uint32_t* tile_walk = nullptr;   // list entries walked per tile by the forward blend
     int* order_fwd = nullptr;        // longest-first tile order of the forward blend
     int* order_bwd = nullptr;        // and of the backward blend
-    // chunk-major list of the depth-first binning (without gradient records):
-    // vals[0] holds the (chunk, tile) segments; `walked` the tile-major list,
-    // filled by the forward up to each tile's last staged entry (and in full
-    // by materialise_tile_major for the inspection calls)
-    uint32_t* chist = nullptr;       // [chunk][tile] pairs
-    uint64_t* cmb = nullptr;         // [chunk][tile] first slot in vals[0]
-    uint32_t* ttot = nullptr;        // pairs per tile
-    uint32_t* walked = nullptr;
-    bool chunked = false;
-    bool tile_major_full = false;    // walked holds the whole tile-major list
-    int64_t nchunks = 0;
+    // supers' lists of the depth-first binning (without gradient records):
+    // ids are vals[0]; the walked blocks the forward keeps for the backward
+    SuperDev sup{};
+    int* sorder = nullptr;           // supers, longest list first
+    bool super = false;              // the last render binned into supers
     bool valid = false;
     GaussDev g{};
     CamDev cam{};
@@ -139,6 +133,8 @@ struct gs3_ctx {
     uint32_t* sel_flag = nullptr;    // selection scratch (max_gaussians each)
     uint32_t* sel_pos = nullptr;
     uint64_t* sel_total = nullptr;
+    uint32_t* sup_hist = nullptr;    // entries per (super, chunk)
+    uint64_t* sup_ksum = nullptr;    // pairs per chunk
     uint2* bin_rect = nullptr;       // tile rectangles in depth order
     uint32_t* bin_goff = nullptr;    // first pair slots in depth order (record mode)
     float* accum = nullptr;
@@ -231,6 +227,14 @@ gs3_status gs3_create(const gs3_config* cfg, gs3_ctx** out) {
     c->max_tiles = tiles_of(cfg->max_width, cfg->max_height);
     const int64_t N = cfg->max_gaussians, PK = cfg->max_pairs, PX = (int64_t)cfg->max_width * cfg->max_height;
     const int64_t nchunks = bin_chunks(N);
+    // without gradient records the depth-first binning is by supers
+    const bool supers = cfg->sort_mode == GS3_SORT_DEPTH_FIRST && cfg->grad_record_log2 <= 0;
+    const int nsuper = super_count_of((cfg->max_width + kTile - 1) / kTile) *
+                       super_count_of((cfg->max_height + kTile - 1) / kTile);
+    if (nsuper > kMaxSupers) {
+        delete c;
+        return GS3_EINVAL;
+    }
     bool ok = true;
     c->slots.resize(cfg->num_slots);
     for (auto& s : c->slots) {
@@ -241,9 +245,16 @@ gs3_status gs3_create(const gs3_config* cfg, gs3_ctx** out) {
              c->alloc(&s.order_fwd, c->max_tiles) && c->alloc(&s.order_bwd, c->max_tiles);
         if (ok && cfg->sort_mode == GS3_SORT_RADIX64)
             ok = c->alloc(&s.vals[1], PK) && c->alloc(&s.pkeys[0], PK) && c->alloc(&s.pkeys[1], PK);
-        if (ok && cfg->sort_mode == GS3_SORT_DEPTH_FIRST && cfg->grad_record_log2 <= 0)
-            ok = c->alloc(&s.chist, (int64_t)c->max_tiles * nchunks) && c->alloc(&s.cmb, (int64_t)c->max_tiles * nchunks) &&
-                 c->alloc(&s.ttot, c->max_tiles) && c->alloc(&s.walked, PK);
+        if (ok && supers) {
+            SuperDev& u = s.sup;
+            const int64_t blocks = PK / kWalkBlock + c->max_tiles;
+            ok = c->alloc(&u.masks, PK) && c->alloc(&u.start, nsuper) && c->alloc(&u.len, nsuper) &&
+                 c->alloc(&u.walked, blocks * kWalkBlock) && c->alloc(&u.prev, blocks) &&
+                 c->alloc(&u.tile_blk, c->max_tiles) && c->alloc(&u.pool, 1) && c->alloc(&s.sorder, nsuper);
+            u.ids = s.vals[0];
+            u.cap = (uint32_t)PK;
+            u.max_blocks = (uint32_t)blocks;
+        }
     }
     const int64_t sort_items = cfg->sort_mode == GS3_SORT_RADIX64 ? std::max(N, PK) : N;
     const int64_t hist_words = radix_hist_words(sort_items);
@@ -260,11 +271,13 @@ gs3_status gs3_create(const gs3_config* cfg, gs3_ctx** out) {
         c->grec_cap = std::min<int64_t>(PK, (int64_t)1 << std::min(cfg->grad_record_log2, 30));
         ok = ok && c->alloc(&c->grec, 9 * c->grec_cap);
     }
-    if (ok && cfg->sort_mode == GS3_SORT_DEPTH_FIRST)
+    if (ok && cfg->sort_mode == GS3_SORT_DEPTH_FIRST) ok = c->alloc(&c->bin_ttot, c->max_tiles) && c->alloc(&c->bin_rect, N);
+    if (ok && supers)
+        ok = c->alloc(&c->sup_hist, (int64_t)nsuper * super_chunks(N)) && c->alloc(&c->sup_ksum, super_chunks(N));
+    else if (ok && cfg->sort_mode == GS3_SORT_DEPTH_FIRST)
         ok = c->alloc(&c->bin_hist, bin_words) && c->alloc(&c->bin_base, bin_words) &&
              c->alloc(&c->bin_part, bin_scan_part_words(nchunks, c->max_tiles)) &&
-             c->alloc(&c->bin_ttot, c->max_tiles) && c->alloc(&c->bin_toff, c->max_tiles) && c->alloc(&c->bin_rect, N) &&
-             c->alloc(&c->bin_goff, cfg->grad_record_log2 > 0 ? N : 1);
+             c->alloc(&c->bin_toff, c->max_tiles) && c->alloc(&c->bin_goff, N);
     if (ok && cfg->enable_ntc) {
         const gs3_ntc_config& nc = cfg->ntc;
         if (nc.levels != 16 || nc.feats != 2 || nc.hidden != 64 || nc.log2_T < 10 || nc.log2_T > 22 ||
@@ -692,38 +705,27 @@ gs3_status gs3_render(gs3_ctx* c, int32_t slot, const gs3_gaussians* g, const fl
         if (n > 0) {
             const int r = radix_order_u32(L, sl.key, c->dkeys, c->dvals, n, 32, c->radix_hist, c->scan_tmp);
             const uint32_t* order = c->dvals[r];
-            const int64_t nchunks = bin_chunks(n);
-            const bool rec_mode = c->grec_cap > 0;
-            // first pair slot of each Gaussian: only the record mode's
-            // gradient gather needs it
-            if (rec_mode) scan_u32_to_u64(L, sl.count, n, sl.goff, c->goff_total, c->scan_tmp);
-            bin_gather(L, order, n, sl.rect, sl.count, sl.goff, cap, c->bin_rect, rec_mode ? c->bin_goff : nullptr,
-                       rec_mode ? nullptr : sl.ttot, rec_mode ? 0 : (int64_t)ntiles);
-            if (rec_mode) {
-                // tile-major list (the record gather needs every pair's slot)
-                bin_count(L, order, n, c->bin_rect, cd.tiles_x, cd.tiles_y, c->bin_hist, nullptr);
-                bin_scan(L, c->bin_hist, nchunks, ntiles, (uint32_t)cap, c->bin_base, sl.total, c->bin_part,
-                         c->bin_ttot, c->bin_toff, c->scan_tmp);
-                // gpos (and the first slots bin_gather stored) exist only in
-                // record mode; without it the buffers hold one element
-                bin_scatter(L, order, n, c->bin_rect, rec_mode ? c->bin_goff : nullptr, cd.tiles_x, cd.tiles_y,
-                            c->bin_base, cap, sl.vals[0], rec_mode ? sl.gpos : nullptr);
-                ranges_from_hist(L, c->bin_base, sl.total, ntiles, cap, sl.ranges, c->flags);
+            sl.super = c->grec_cap <= 0;
+            if (sl.super) {
+                sl.sup.supers_x = super_count_of(cd.tiles_x);
+                super_bin(L, order, n, sl.rect, cd.tiles_x, cd.tiles_y, cap, (uint32_t)ntiles, c->bin_rect, c->sup_hist,
+                          c->sup_ksum, sl.total, c->flags, sl.sup, sl.sorder);
             } else {
-                // chunk-major list: every wave writes one run of consecutive
-                // slots; the forward walks each tile's segments
-                bin_count(L, order, n, c->bin_rect, cd.tiles_x, cd.tiles_y, sl.chist, sl.ttot);
-                scan_u32_to_u64(L, sl.chist, (int64_t)ntiles * nchunks, sl.cmb, sl.total, c->scan_tmp);
-                tile_ranges_from_counts(L, sl.ttot, ntiles, cap, sl.total, sl.ranges, c->flags);
-                bin_scatter_chunked(L, order, n, c->bin_rect, cd.tiles_x, cd.tiles_y, sl.cmb, cap, sl.vals[0]);
+                // tile-major list: the record gather needs every pair's slot,
+                // from the first pair slot of each Gaussian
+                scan_u32_to_u64(L, sl.count, n, sl.goff, c->goff_total, c->scan_tmp);
+                bin_gather(L, order, n, sl.rect, sl.count, sl.goff, cap, c->bin_rect, c->bin_goff);
+                bin_count(L, n, c->bin_rect, cd.tiles_x, cd.tiles_y, c->bin_hist);
+                bin_scan(L, c->bin_hist, bin_chunks(n), ntiles, (uint32_t)cap, c->bin_base, sl.total, c->bin_part,
+                         c->bin_ttot, c->bin_toff, c->scan_tmp);
+                bin_scatter(L, order, n, c->bin_rect, c->bin_goff, cd.tiles_x, cd.tiles_y, c->bin_base, cap, sl.vals[0],
+                            sl.gpos);
+                ranges_from_hist(L, c->bin_base, sl.total, ntiles, cap, sl.ranges, c->flags);
             }
-            sl.chunked = !rec_mode;
-            sl.nchunks = nchunks;
         } else {
             fill_u32(L, (uint32_t*)sl.ranges, 0u, 2 * (int64_t)ntiles);
             fill_u32(L, (uint32_t*)sl.total, 0u, 2);
-            sl.chunked = false;
-            sl.nchunks = 0;
+            sl.super = false;
         }
         sl.K_host = -1;
     } else {
@@ -746,15 +748,9 @@ gs3_status gs3_render(gs3_ctx* c, int32_t slot, const gs3_gaussians* g, const fl
             gpos_from_pairs(L, sl.pkeys[sl.cur], sl.vals[sl.cur], (int64_t)K, sl.rect, sl.goff, cd.tiles_x, cap,
                             sl.gpos);
     }
-    tile_order(L, sl.ranges, nullptr, ntiles, sl.order_fwd);
-    sl.tile_major_full = false;
-    if (sl.chunked) {
-        const ChunkDev cl{sl.chist, sl.cmb, sl.nchunks, (uint32_t)cap, sl.walked};
-        blend_forward(L, cd, sl.ranges, sl.vals[0], sl.rec, image, sl.T_final, sl.last, sl.tile_walk, sl.order_fwd, &cl);
-    } else {
-        blend_forward(L, cd, sl.ranges, sl.vals[sl.cur], sl.rec, image, sl.T_final, sl.last, sl.tile_walk, sl.order_fwd,
-                      nullptr);
-    }
+    if (!sl.super) tile_order(L, sl.ranges, nullptr, ntiles, sl.order_fwd);
+    blend_forward(L, cd, sl.ranges, sl.vals[sl.cur], sl.rec, image, sl.T_final, sl.last, sl.tile_walk,
+                  sl.super ? sl.sorder : sl.order_fwd, sl.super ? &sl.sup : nullptr);
     gs3_status st = c->check_launch("render");
     if (st != GS3_OK) return st;
     sl.g = gd;
@@ -779,8 +775,9 @@ gs3_status gs3_render_backward(gs3_ctx* c, int32_t slot, const float* d_image, c
     ga.walk_off = c->walk_off; ga.grec = c->grec; ga.grec_cap = (uint64_t)c->grec_cap;
     ga.cap = (uint64_t)c->cfg.max_pairs;
     tile_order(L, sl.ranges, sl.tile_walk, ntiles, sl.order_bwd);
-    blend_backward(L, sl.cam, sl.ranges, sl.chunked ? sl.walked : sl.vals[sl.cur], sl.rec, d_image, sl.T_final,
-                   sl.last, ga, c->accum, out->d_opacity != nullptr || out->d_opacity_logits != nullptr, sl.order_bwd);
+    blend_backward(L, sl.cam, sl.ranges, sl.vals[sl.cur], sl.rec, d_image, sl.T_final, sl.last, ga, c->accum,
+                   out->d_opacity != nullptr || out->d_opacity_logits != nullptr, sl.order_bwd,
+                   sl.super ? &sl.sup : nullptr);
     GradsDev gd;
     gd.d_means = out->d_means; gd.d_quats = out->d_quats; gd.d_log_scales = out->d_log_scales;
     gd.d_opac = out->d_opacity_logits; gd.d_sh = out->d_sh; gd.d_dmu = sl.g.dmu ? out->d_dmu : nullptr;
@@ -903,6 +900,15 @@ gs3_status gs3_debug_counts(gs3_ctx* c, int32_t slot, int64_t* num_pairs, int64_
     return ov ? c->fail(GS3_ECAPACITY, "pair list overflowed") : GS3_OK;
 }
 
+// Tile ranges of a render that binned into supers (the render itself needs none).
+static void super_ranges(gs3_ctx* c, Slot& sl) {
+    Launch L = c->L();
+    super_tile_counts(L, sl.sup, sl.cam.tiles_x, sl.cam.tiles_y, c->bin_ttot);
+    // flags[2]: the render already reported an overflow
+    tile_ranges_from_counts(L, c->bin_ttot, sl.cam.tiles_x * sl.cam.tiles_y, (uint64_t)c->cfg.max_pairs, sl.total,
+                            sl.ranges, c->flags + 2);
+}
+
 gs3_status gs3_debug_pairs(gs3_ctx* c, int32_t slot, uint64_t* keys, uint32_t* vals, int64_t cap) {
     if (!c) return GS3_EINVAL;
     if (slot < 0 || slot >= (int)c->slots.size()) return c->fail(GS3_EINVAL, "bad slot");
@@ -916,18 +922,11 @@ gs3_status gs3_debug_pairs(gs3_ctx* c, int32_t slot, uint64_t* keys, uint32_t* v
     if (K == 0) return GS3_OK;
     const int ntiles = sl.cam.tiles_x * sl.cam.tiles_y;
     const uint32_t* tm = sl.vals[sl.cur];
-    if (sl.chunked) {
-        // the whole tile-major list from the chunk-major one (its prefix
-        // walked by the forward is unchanged by this)
-        if (!sl.tile_major_full) {
-            Launch L = c->L();
-            bin_scan(L, sl.chist, sl.nchunks, ntiles, (uint32_t)c->cfg.max_pairs, c->bin_base, c->walk_total,
-                     c->bin_part, c->bin_ttot, c->bin_toff, c->scan_tmp);
-            chunked_to_tile_major(L, sl.chist, sl.cmb, c->bin_base, sl.nchunks, ntiles, (uint64_t)c->cfg.max_pairs,
-                                  sl.vals[0], sl.walked);
-            sl.tile_major_full = true;
-        }
-        tm = sl.walked;
+    if (sl.super) {
+        // the tile-major list from the supers' lists, straight into the caller's buffers
+        super_ranges(c, sl);
+        super_pairs(c->L(), sl.sup, sl.cam.tiles_x, sl.cam.tiles_y, sl.ranges, sl.key, keys, vals);
+        return c->check_launch("debug_pairs");
     }
     if (vals && hipMemcpyAsync(vals, tm, (size_t)K * 4, hipMemcpyDeviceToDevice, c->st) != hipSuccess)
         return c->fail(GS3_EHIP, "debug_pairs: copy failed");
@@ -948,6 +947,7 @@ gs3_status gs3_debug_ranges(gs3_ctx* c, int32_t slot, uint32_t* ranges) {
     Slot& sl = c->slots[slot];
     if (!sl.valid) return c->fail(GS3_ESTATE, "no render on this slot");
     const int ntiles = sl.cam.tiles_x * sl.cam.tiles_y;
+    if (sl.super) super_ranges(c, sl);
     if (hipMemcpyAsync(ranges, sl.ranges, (size_t)ntiles * 8, hipMemcpyDeviceToDevice, c->st) != hipSuccess)
         return c->fail(GS3_EHIP, "debug_ranges: copy failed");
     return GS3_OK;

@@ -598,4 +598,14 @@ __device__ __forceinline__ float wave_sum_dpp(float x) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63));
 }
 
+// Half-octave scale of the work a tile or list carries (0..65), for the
+// longest-first schedules.
+constexpr int kOrderBuckets = 66;
+__device__ __forceinline__ int work_bucket(uint32_t w) {
+    if (w == 0u) return 0;
+    const int lz = 31 - __clz(w);
+    const int half = lz >= 1 ? (int)((w >> (lz - 1)) & 1u) : 0;
+    return 1 + 2 * lz + half;
+}
+
 }  // namespace gs3

@@ -57,8 +57,10 @@ void preprocess(const Launch& L, const GaussDev& g, const CamDev& cam, float4* r
 void emit_pairs(const Launch& L, int64_t n, const uint32_t* key, const uint2* rect, const uint64_t* offs,
                 int tiles_x, uint64_t cap, uint64_t* keys, uint32_t* vals);
 void ranges_from_keys(const Launch& L, const uint64_t* keys, int64_t K, int ntiles, uint2* ranges);
-// depth-first path: per-chunk tile histograms of depth-ordered Gaussians,
-// then an order-preserving scatter of Gaussian indices.
+// depth-first path with gradient records: per-chunk tile histograms of
+// depth-ordered Gaussians, then an order-preserving scatter of Gaussian
+// indices into the tile-major pair list (the record gather needs the slot of
+// every pair; without records the Gaussians are binned into supers instead).
 #ifndef GS3_BIN_CHUNK
 #define GS3_BIN_CHUNK 512
 #endif
@@ -67,17 +69,14 @@ constexpr int kMaxTilesX = 256;   // widest image: 4096 pixels
 // chunks of kBinChunk depth-ordered Gaussians for n Gaussians, rounded up to
 // a multiple of 8 (the passes give each XCD an eighth; padding chunks are empty)
 int64_t bin_chunks(int64_t n);
-// tile rectangles (empty for culled Gaussians) and, when sgoff is set, the
-// first pair slots goff, gathered into depth order; also zeroes zero[0,
-// nzero) (the per-tile totals bin_count adds to; null with nzero 0)
+// tile rectangles (empty for culled Gaussians) and the first pair slots
+// goff, gathered into depth order
 void bin_gather(const Launch& L, const uint32_t* order, int64_t n, const uint2* rect, const uint32_t* count,
-                const uint64_t* goff, uint64_t cap, uint2* srect, uint32_t* sgoff, uint32_t* zero, int64_t nzero);
+                const uint64_t* goff, uint64_t cap, uint2* srect, uint32_t* sgoff);
 // Pairs per (chunk, tile), chunk-major: hist[chunk * ntiles + tile] with
 // ntiles = tiles_x * tiles_y, so each pass writes and reads a tile row of one
-// chunk as consecutive words; ttot (optional, zeroed by the caller) receives
-// the pairs per tile.
-void bin_count(const Launch& L, const uint32_t* order, int64_t n, const uint2* srect, int tiles_x, int tiles_y,
-               uint32_t* hist, uint32_t* ttot);
+// chunk as consecutive words.
+void bin_count(const Launch& L, int64_t n, const uint2* srect, int tiles_x, int tiles_y, uint32_t* hist);
 // ranges[t] = [start, start + len[t]) clamped to cap, start the exclusive
 // prefix of len; sets *overflow when *total (the list's length) exceeds cap
 void tile_ranges_from_counts(const Launch& L, const uint32_t* len, int64_t ntiles, uint64_t cap, const uint64_t* total,
@@ -94,27 +93,6 @@ void bin_scan(const Launch& L, const uint32_t* hist, int64_t nchunks, int ntiles
 // pair: gpos[goff[id] + k] (goff = exclusive scan of the tile counts)
 void bin_scatter(const Launch& L, const uint32_t* order, int64_t n, const uint2* srect, const uint32_t* sgoff,
                  int tiles_x, int tiles_y, const uint32_t* base, uint64_t cap, uint32_t* vals, uint32_t* gpos);
-// The chunk-major pair list of the depth-first binning, as the forward
-// blend reads it: segment lengths hist[chunk][tile], segment starts
-// cmb[chunk][tile] (the exclusive scan of hist in that order), and the
-// tile-major list `walked`, into which the forward writes each entry it
-// stages at its tile-major slot (the backward walks that list).
-struct ChunkDev {
-    const uint32_t* hist;
-    const uint64_t* cmb;
-    int64_t nchunks;
-    uint32_t cap;
-    uint32_t* walked;
-};
-// The same into the chunk-major list: cmb = exclusive scan of hist in its
-// [chunk][tile] order (the start of every (chunk, tile) segment).
-void bin_scatter_chunked(const Launch& L, const uint32_t* order, int64_t n, const uint2* srect, int tiles_x,
-                         int tiles_y, const uint64_t* cmb, uint64_t cap, uint32_t* vals);
-// Copy every (chunk, tile) segment of the chunk-major list to its slot in
-// the tile-major list (base_tm: the tile-major first slot of each segment,
-// from bin_scan); slots at or past cap are skipped.
-void chunked_to_tile_major(const Launch& L, const uint32_t* hist, const uint64_t* cmb, const uint32_t* base_tm,
-                           int64_t nchunks, int ntiles, uint64_t cap, const uint32_t* vals_cm, uint32_t* vals_tm);
 void gpos_from_pairs(const Launch& L, const uint64_t* keys, const uint32_t* vals, int64_t K, const uint2* rect,
                      const uint64_t* goff, int tiles_x, uint64_t cap, uint32_t* gpos);
 void ranges_from_hist(const Launch& L, const uint32_t* base, const uint64_t* total, int ntiles, uint64_t cap,
@@ -136,18 +114,59 @@ struct GatherDev {
     uint64_t cap;   // pair capacity (gpos length)
 };
 
+// Supers: blocks of kSuperDim x kSuperDim tiles (supers.hip).  A super's list
+// is ids / masks [start, start + len): the Gaussians whose tile rectangle
+// meets it, in depth order, with the mask of the tiles covered (bit
+// kSuperDim ly + lx).  The forward blend keeps what it walks for the
+// backward in blocks of kWalkBlock entries, `walked`: a tile's first block is
+// the tile's index, later ones come from the counter *pool; prev[b] is the
+// block before block b of the same tile, tile_blk[tile] the block that holds
+// the tile's last contributor.
+constexpr int kSuperShift = 2;
+constexpr int kSuperDim = 1 << kSuperShift;
+constexpr int kSuperChunk = 512;   // depth-ordered Gaussians per workgroup of the binning
+constexpr int kMaxSupers = 1408;   // 16384 tiles, at most 256 columns and 2048 rows, give at most 1365
+constexpr int kWalkBlock = 256;
+struct SuperDev {
+    uint32_t* ids;
+    uint16_t* masks;
+    uint32_t* start;
+    uint32_t* len;
+    int supers_x;
+    uint32_t cap;         // slots of ids and masks
+    uint32_t* walked;     // max_blocks x kWalkBlock
+    uint32_t* prev;
+    uint32_t* tile_blk;
+    uint32_t* pool;
+    uint32_t max_blocks;
+};
+int64_t super_chunks(int64_t n);
+int super_count_of(int tiles);   // supers along one axis
+// Bins the depth-ordered Gaussians into sd's lists; *total receives the
+// number of (Gaussian, tile) pairs, *overflow is set when it exceeds cap.
+// srect: n; hist: supers x super_chunks(n); ksum: super_chunks(n).  sorder
+// (optional, one int per super): the supers, longest list first.
+void super_bin(const Launch& L, const uint32_t* order, int64_t n, const uint2* rect, int tiles_x, int tiles_y,
+               uint64_t cap, uint32_t pool0, uint2* srect, uint32_t* hist, uint64_t* ksum, uint64_t* total,
+               int* overflow, const SuperDev& sd, int* sorder);
+// inspection: the pairs per tile, and the tile-major pair list
+void super_tile_counts(const Launch& L, const SuperDev& sd, int tiles_x, int tiles_y, uint32_t* ttot);
+void super_pairs(const Launch& L, const SuperDev& sd, int tiles_x, int tiles_y, const uint2* ranges,
+                 const uint32_t* key, uint64_t* keys_out, uint32_t* vals_out);
+
 // Longest-first launch order of the tiles: by list length (walk == nullptr)
 // or by walked entries.  `order` holds ntiles ints.
 void tile_order(const Launch& L, const uint2* ranges, const uint32_t* walk, int ntiles, int* order);
-// `order` (optional) maps workgroups to tiles
-// chunks: the chunk-major list (vals is then that list), or NULL for a
-// tile-major list read through ranges.
+// supers: the supers' lists (order then maps places to supers), or NULL for a
+// tile-major list read through ranges (order maps workgroups to tiles).
+// `order` is optional.
 void blend_forward(const Launch& L, const CamDev& cam, const uint2* ranges, const uint32_t* vals, const float4* rec,
                    float* image, float* T_final, uint32_t* last, uint32_t* tile_walk, const int* order,
-                   const ChunkDev* chunks);
+                   const SuperDev* supers);
+// supers: walk the blocks the forward kept, or NULL for the tile-major list
 void blend_backward(const Launch& L, const CamDev& cam, const uint2* ranges, const uint32_t* vals,
                     const float4* rec, const float* d_image, const float* T_final, const uint32_t* last,
-                    const GatherDev& ga, float* accum, bool want_opacity, const int* order);
+                    const GatherDev& ga, float* accum, bool want_opacity, const int* order, const SuperDev* supers);
 
 struct GradsDev {
     float *d_means, *d_quats, *d_log_scales, *d_opac, *d_sh, *d_dmu, *d_dq;

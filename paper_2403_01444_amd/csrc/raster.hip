@@ -3,13 +3,6 @@
 // per-Gaussian kernels.
 #include "kernels.h"
 
-#ifndef GS3_BLEND_ROWS_FWD
-#define GS3_BLEND_ROWS_FWD 1
-#endif
-#ifndef GS3_BLEND_ROWS_BWD
-#define GS3_BLEND_ROWS_BWD 1
-#endif
-
 namespace gs3 {
 
 namespace {
@@ -140,17 +133,13 @@ __device__ __forceinline__ void bin_block(int64_t nchunks, int& rowblock, int64_
 __global__ __launch_bounds__(256) void k_bin_gather(const uint32_t* __restrict__ order, int64_t n,
                                                     const uint2* __restrict__ rect, const uint32_t* __restrict__ count,
                                                     const uint64_t* __restrict__ goff, uint32_t cap,
-                                                    uint2* __restrict__ srect, uint32_t* __restrict__ sgoff,
-                                                    uint32_t* __restrict__ zero, int64_t nzero) {
+                                                    uint2* __restrict__ srect, uint32_t* __restrict__ sgoff) {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e < nzero) zero[e] = 0u;
     if (e >= n) return;
     const uint32_t id = order[e];
     srect[e] = count[id] ? rect[id] : make_uint2(0xFFFF0000u, 0u);   // empty: no row spans
-    if (sgoff) {
-        const uint64_t go = goff[id];
-        sgoff[e] = go < (uint64_t)cap ? (uint32_t)go : cap;
-    }
+    const uint64_t go = goff[id];
+    sgoff[e] = go < (uint64_t)cap ? (uint32_t)go : cap;
 }
 
 // Counting pass of the depth-first binning: for a tile row (one wave) and a
@@ -160,14 +149,11 @@ __global__ __launch_bounds__(256) void k_bin_gather(const uint32_t* __restrict__
 // array; a prefix sum over the row's columns gives the counts (the same
 // coverage test the scatter applies tile by tile).  The counts are stored
 // chunk-major, so a wave writes its row as consecutive words.  A workgroup
-// takes kCountGroup consecutive chunks of one row block and, when ttot is
-// set, adds each tile's count over them to ttot (one atomic per tile and
-// group).
+// takes kCountGroup consecutive chunks of one row block.
 constexpr int kCountGroup = 8;   // bin_chunks is a multiple of 8
 
 __global__ __launch_bounds__(kBinThreads) void k_bin_count(const uint2* __restrict__ srect, int64_t n, int tiles_x,
-                                                           int tiles_y, int64_t nchunks, uint32_t* __restrict__ hist,
-                                                           uint32_t* __restrict__ ttot) {
+                                                           int tiles_y, int64_t nchunks, uint32_t* __restrict__ hist) {
     const int64_t ntiles = (int64_t)tiles_x * tiles_y;
     __shared__ uint2 s_rect[kBinChunk];
     __shared__ int s_diff[kBinRowsPerBlock][kMaxTilesX + 1];
@@ -176,7 +162,6 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_count(const uint2* __restri
     const int64_t group = (int64_t)blockIdx.x % ngroups;
     const int rowblock = (int)((int64_t)blockIdx.x / ngroups);
     const int row = rowblock * kBinRowsPerBlock + w;
-    uint32_t tot[4] = {0u, 0u, 0u, 0u};
     for (int64_t chunk = group * kCountGroup; chunk < (group + 1) * kCountGroup; chunk++) {
         const int64_t e0 = chunk * kBinChunk;
         const int m = (int)min((int64_t)kBinChunk, n - e0);   // <= 0 for the padding chunks
@@ -210,15 +195,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_count(const uint2* __restri
         for (int k = 0; k < 4; k++) {
             const int tx = 4 * lane + k;
             const uint32_t v = (uint32_t)(pre + a[k]);
-            tot[k] += v;
             if (tx < tiles_x) hist[chunk * ntiles + (int64_t)row * tiles_x + tx] = v;
-        }
-    }
-    if (ttot && row < tiles_y) {
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const int tx = 4 * lane + k;
-            if (tx < tiles_x && tot[k]) atomicAdd(&ttot[(int64_t)row * tiles_x + tx], tot[k]);
         }
     }
 }
@@ -286,16 +263,14 @@ __global__ __launch_bounds__(256) void k_bin_scan_base(const uint32_t* __restric
 // instruction therefore fills one segment (about a dozen consecutive
 // words) instead of touching a dozen tiles' lists, and every tile's entries
 // keep the depth order.  The first slot of each (chunk, tile) segment comes
-// from `base` in [chunk][tile] layout: the tile-major list's slots (u32,
-// already clamped to cap) or the chunk-major list's (u64).
+// from `base` in [chunk][tile] layout (clamped to cap).
 constexpr int kBinGroups = kBinChunk / 64;   // register groups of the covering list
 static_assert(kBinChunk % 64 == 0, "the covering list is held in groups of 64");
 
-template <typename B, bool kRec>
 __global__ __launch_bounds__(kBinThreads) void k_bin_rows(const uint32_t* __restrict__ order, int64_t n,
                                                   const uint2* __restrict__ srect, const uint32_t* __restrict__ sgoff,
                                                   int tiles_x, int tiles_y, int64_t nchunks,
-                                                  const B* __restrict__ base, uint32_t cap,
+                                                  const uint32_t* __restrict__ base, uint32_t cap,
                                                   uint32_t* __restrict__ vals, uint32_t* __restrict__ gpos) {
     // A segment's slots start at min(first slot, cap) and run at most
     // kBinChunk past it, so with cap < 2^31 they never wrap; slots at or
@@ -314,7 +289,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_rows(const uint32_t* __rest
     for (int e = threadIdx.x; e < m; e += kBinThreads) {
         s_id[e] = order[e0 + e];
         s_rect[e] = srect[e0 + e];
-        s_goff[e] = kRec ? sgoff[e0 + e] : 0u;
+        s_goff[e] = sgoff[e0 + e];
     }
     __syncthreads();
     if (row >= tiles_y) return;
@@ -336,8 +311,8 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_rows(const uint32_t* __rest
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // 2. the list in registers: column span, index and (record mode) the
-    // slot of column 0 of this row in the Gaussian's own pair range
+    // 2. the list in registers: column span, index and the slot of column 0
+    // of this row in the Gaussian's own pair range
     int lo[kBinGroups], hi[kBinGroups];
     uint32_t gid[kBinGroups], gk[kBinGroups];
     int cmin = 1 << 30, cmax = -1;
@@ -354,9 +329,8 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_rows(const uint32_t* __rest
             lo[gi] = (int)(r.x & 0xFFFFu);
             hi[gi] = (int)(r.y & 0xFFFFu);   // < tiles_x
             gid[gi] = s_id[e];
-            if (kRec)
-                gk[gi] = s_goff[e] + (uint32_t)(row - (int)(r.x >> 16)) * (uint32_t)(hi[gi] - lo[gi] + 1) -
-                         (uint32_t)lo[gi];
+            gk[gi] = s_goff[e] + (uint32_t)(row - (int)(r.x >> 16)) * (uint32_t)(hi[gi] - lo[gi] + 1) -
+                     (uint32_t)lo[gi];
             cmin = min(cmin, lo[gi]);
             cmax = max(cmax, hi[gi]);
         }
@@ -371,13 +345,12 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_rows(const uint32_t* __rest
     const int ngr = (G + 63) >> 6;
     // 3. the columns the list covers; lane l of colb[cg] holds the first
     // slot of column 64 cg + l
-    const B* brow = base + chunk * ((int64_t)tiles_x * tiles_y) + (int64_t)row * tiles_x;
+    const uint32_t* brow = base + chunk * ((int64_t)tiles_x * tiles_y) + (int64_t)row * tiles_x;
     uint32_t colb[kMaxTilesX / 64];
 #pragma unroll
     for (int cg = 0; cg < kMaxTilesX / 64; cg++) {
         const int tx = 64 * cg + lane;
-        const uint64_t b = (tx < tiles_x && cg * 64 <= cmax) ? (uint64_t)brow[tx] : (uint64_t)cap;
-        colb[cg] = b < (uint64_t)cap ? (uint32_t)b : cap;
+        colb[cg] = (tx < tiles_x && cg * 64 <= cmax) ? min(brow[tx], cap) : cap;
     }
 #pragma unroll
     for (int cg = 0; cg < kMaxTilesX / 64; cg++) {
@@ -396,10 +369,8 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_rows(const uint32_t* __rest
                 const uint32_t slot = pos + rank;
                 if (__builtin_amdgcn_inverse_ballot_w64(bal) && slot < cap) {
                     vals[slot] = gid[gi];
-                    if (kRec) {
-                        const uint32_t kk = gk[gi] + (uint32_t)tx;
-                        if (kk < cap) gpos[kk] = slot;
-                    }
+                    const uint32_t kk = gk[gi] + (uint32_t)tx;
+                    if (kk < cap) gpos[kk] = slot;
                 }
                 pos += (uint32_t)__popcll(bal);
             }
@@ -435,14 +406,6 @@ __device__ __forceinline__ int tile_of_block(int b, int ntiles) {
 // scale, heaviest bucket first, so the long tiles start in the first wave of
 // workgroups instead of trailing the launch.  One workgroup; the order inside
 // a bucket is whatever the atomics give (it only affects scheduling).
-constexpr int kOrderBuckets = 66;
-__device__ __forceinline__ int work_bucket(uint32_t w) {
-    if (w == 0u) return 0;
-    const int lz = 31 - __clz(w);
-    const int half = lz >= 1 ? (int)((w >> (lz - 1)) & 1u) : 0;
-    return 1 + 2 * lz + half;
-}
-
 __global__ __launch_bounds__(1024) void k_tile_order(const uint2* __restrict__ ranges,
                                                      const uint32_t* __restrict__ walk, int ntiles,
                                                      int* __restrict__ order) {
@@ -469,155 +432,137 @@ __global__ __launch_bounds__(1024) void k_tile_order(const uint2* __restrict__ r
 }
 
 // ---------------------------------------------------------------------------
-// blend forward (Eq. 4): one workgroup per 16x16 tile; each thread owns R
-// vertically adjacent pixels of one column, so a staged record is read from
-// LDS once per R evaluations and the column terms of the exponent are shared.
-// The tile's Gaussian records are staged through LDS 256/R at a time.
+// blend forward (Eq. 4): one workgroup per 16x16 tile, one pixel per thread;
+// the tile's Gaussian records are staged through LDS 256 at a time.
 //
-// kChunked: the pairs are in the chunk-major list of the depth-first
-// binning (ChunkDev): the tile's entries are its segments of successive
-// depth chunks.  A cursor (chunk, offset) walks them: per batch, the first
-// wave reads the lengths and starts of the tile's segments in the next 64
-// chunks and scans the lengths, and each thread finds its entry's segment
-// by binary search.  Every staged entry's Gaussian index is also written to
-// the tile-major list at the tile's slot (ranges[tile].x + entry), which
-// the backward walks.  The result equals the walk of the tile-major list.
+// kSuper: the tile's entries are those of its super's list whose mask has the
+// tile's bit.  The workgroup filters the list 256 entries at a time into a
+// queue of indices in LDS (the next 256 masks and indices are loaded while
+// the current batch is evaluated) and evaluates the queue in batches of 256
+// (fewer at the end of the list).  Each batch's indices are kept in a walked
+// block for the backward.  Otherwise the entries are vals[ranges[tile]).
 // ---------------------------------------------------------------------------
-template <int R, bool kChunked>
-__global__ __launch_bounds__(kTile * kTile / R) void k_blend_fwd(CamDev cam, int ntiles,
-                                                                 const uint2* __restrict__ ranges,
-                                                                 const uint32_t* __restrict__ vals,
-                                                                 const float4* __restrict__ rec,
-                                                                 float* __restrict__ image, float* __restrict__ T_final,
-                                                                 uint32_t* __restrict__ last_out,
-                                                                 uint32_t* __restrict__ tile_walk,
-                                                                 const int* __restrict__ order, ChunkDev cl) {
-    constexpr int NT = kTile * kTile / R;
-    static_assert(!kChunked || NT >= 64, "the chunk window needs a full wave");
+template <bool kSuper>
+__global__ __launch_bounds__(kBlendThreads) void k_blend_fwd(CamDev cam, int ntiles, const uint2* __restrict__ ranges,
+                                                             const uint32_t* __restrict__ vals,
+                                                             const float4* __restrict__ rec, float* __restrict__ image,
+                                                             float* __restrict__ T_final, uint32_t* __restrict__ last_out,
+                                                             uint32_t* __restrict__ tile_walk,
+                                                             const int* __restrict__ order, SuperDev sd, int nsuper) {
+    constexpr int NT = kBlendThreads, NW = NT / 64;
+    static_assert(kWalkBlock == NT, "a walked block holds one batch");
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    int tx, ty, tile, sup = 0;
+    if (kSuper) {
+        // the tiles of a super on one XCD (workgroup b runs on XCD b mod 8):
+        // they read the same list and mostly the same records
+        constexpr int T = kSuperDim * kSuperDim;
+        const int x = blockIdx.x & 7, k = blockIdx.x >> 3;
+        const int place = (k / T) * 8 + x, local = k % T;
+        if (place >= nsuper) return;
+        sup = order ? order[place] : place;
+        tx = (sup % sd.supers_x) * kSuperDim + local % kSuperDim;
+        ty = (sup / sd.supers_x) * kSuperDim + local / kSuperDim;
+        if (tx >= cam.tiles_x || ty >= cam.tiles_y) return;
+        tile = ty * cam.tiles_x + tx;
+    } else {
+        tile = order ? order[blockIdx.x] : tile_of_block(blockIdx.x, ntiles);
+        if (tile >= ntiles) return;
+        tx = tile % cam.tiles_x;
+        ty = tile / cam.tiles_x;
+    }
     __shared__ uint32_t s_walk;
-    __shared__ uint32_t s_pre[65];   // chunk window: exclusive prefix of the segment lengths
-    __shared__ uint32_t s_sb[64];    // and the slot of each segment's next entry
-    __shared__ int64_t s_cc;         // cursor: first chunk of the window
-    __shared__ uint32_t s_co;        // and the entries of it already staged
-    const int tile = order ? order[blockIdx.x] : tile_of_block(blockIdx.x, ntiles);
     __shared__ float4 s_w0[NT];
     __shared__ float4 s_w1[NT];
     __shared__ float4 s_w2[NT];   // blend_stage_w2 form
-    if (tile >= ntiles) return;
-    const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
+    __shared__ uint32_t s_q[kSuper ? 2 * NT : 1];   // queue of indices
+    __shared__ uint32_t s_n[2][NW];                 // entries each wave adds to it
+    __shared__ uint32_t s_live[NW], s_took[NW], s_blk;
     const int tx0p = tx * kTile, ty0p = ty * kTile;
-    const int px = tx0p + (threadIdx.x & 15), py0 = ty0p + (threadIdx.x >> 4) * R;
+    const int px = tx0p + (tid & 15), py = ty0p + (tid >> 4);
     const float fpx = (float)px;
-    uint32_t sel[R];   // this thread's column and row bits in the box masks
-#pragma unroll
-    for (int k = 0; k < R; k++) sel[k] = (1u << (threadIdx.x & 15)) | (1u << (16 + (threadIdx.x >> 4) * R + k));
-    const uint2 rg = ranges[tile];
-    const uint32_t start = rg.x, end = rg.y;
-    float T[R], c0[R], c1[R], c2[R];
-    uint32_t last[R];
+    const uint32_t sel = (1u << (tid & 15)) | (1u << (16 + (tid >> 4)));   // column and row bits in the box masks
+    float T = 1.0f, c0 = 0.f, c1 = 0.f, c2 = 0.f;
+    uint32_t last = 0u;
     // pixel row coordinate, NaN once the pixel has stopped (and for pixels
     // outside the image): every comparison of its exponent is then false, so
     // a stopped pixel takes no further contribution without a flag test
     const float kStopped = __int_as_float(0x7FC00000);
-    float fpy[R];
-#pragma unroll
-    for (int k = 0; k < R; k++) {
-        T[k] = 1.0f;
-        c0[k] = c1[k] = c2[k] = 0.f;
-        last[k] = 0u;
-        fpy[k] = (px < cam.W && py0 + k < cam.H) ? (float)(py0 + k) : kStopped;
+    float fpy = (px < cam.W && py < cam.H) ? (float)py : kStopped;
+    if (tid == 0) s_walk = 0u;
+    // list cursor: the super's entries [c, cend) are not filtered yet; mk, id
+    // hold this thread's entry c + tid
+    uint32_t c = 0u, cend = 0u, mk = 0u, nid = 0u;
+    uint32_t queued = 0u;
+    int par = 0;
+    uint32_t tbit = 0u;
+    if (kSuper) {
+        c = sd.start[sup];
+        cend = min(sd.cap, c + sd.len[sup]);
+        tbit = 1u << ((ty % kSuperDim) * kSuperDim + tx % kSuperDim);
+        if (c + tid < cend) {
+            mk = sd.masks[c + tid];
+            nid = sd.ids[c + tid];
+        }
+    } else {
+        const uint2 rg = ranges[tile];
+        c = rg.x;
+        cend = rg.y;
     }
-    if (threadIdx.x == 0) {
-        s_walk = 0u;
-        s_cc = 0;
-        s_co = 0u;
-    }
-    const uint32_t total = end - start;
-    for (uint32_t eb = 0; eb < total;) {   // eb: entries staged so far
-        bool all = true;
-#pragma unroll
-        for (int k = 0; k < R; k++) all = all && (fpy[k] != fpy[k]);
-        if (__syncthreads_count(all) == NT) break;
+    uint32_t blk = (uint32_t)tile, lastblk = (uint32_t)tile;   // walked blocks (thread 0 tracks the last contributor's)
+    for (uint32_t eb = 0;;) {   // eb: entries staged so far
+        uint32_t myid = 0u;
         uint32_t cnt_u;
-        if (kChunked) {
-            const int64_t ntl = (int64_t)ntiles;
-            if (threadIdx.x < 64) {
-                const int l = threadIdx.x;
-                const int64_t c = s_cc + l;
-                uint32_t len = 0u, sb = 0u;
-                if (c < cl.nchunks) {
-                    len = cl.hist[c * ntl + tile];
-                    const uint64_t b = cl.cmb[c * ntl + tile];
-                    sb = b < (uint64_t)cl.cap ? (uint32_t)b : cl.cap;
+        if (kSuper) {
+            while (queued < (uint32_t)NT && c < cend) {
+                const bool on = (mk & tbit) != 0u && c + tid < cend;
+                const uint64_t bal = __ballot(on);
+                if (lane == 0) s_n[par][w] = (uint32_t)__popcll(bal);
+                __syncthreads();
+                uint32_t at = queued + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+#pragma unroll
+                for (int k = 0; k < NW; k++) {
+                    if (k < w) at += s_n[par][k];
+                    queued += s_n[par][k];
                 }
-                if (l == 0) {
-                    len -= s_co;
-                    sb += s_co;
+                if (on) s_q[at] = nid;   // at < NT - 1 + NT
+                par ^= 1;
+                c += NT;
+                if (c + tid < cend) {
+                    mk = sd.masks[c + tid];
+                    nid = sd.ids[c + tid];
                 }
-                const uint32_t x = wave_incl_scan_u32(len);   // inclusive scan of the lengths
-                s_pre[l + 1] = x;
-                if (l == 0) s_pre[0] = 0u;
-                s_sb[l] = sb;
             }
+            if (queued == 0u) break;
+            cnt_u = min((uint32_t)NT, queued);
             __syncthreads();
-            const uint32_t avail = s_pre[64];
-            // (avail exceeds the rest of the tile's range only when the pair
-            // list overflowed and the ranges were clamped to cap)
-            cnt_u = min(min((uint32_t)NT, avail), total - eb);
-            const uint32_t e = threadIdx.x;
-            if (e < cnt_u) {
-                int lo = 0, hi = 63;   // the last segment starting at or before entry e
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (s_pre[mid] <= e) lo = mid; else hi = mid - 1;
-                }
-                const uint32_t idx = s_sb[lo] + (e - s_pre[lo]);
-                if (idx < cl.cap) {
-                    const uint32_t id = vals[idx];
-                    const float4 r0 = rec[3 * (int64_t)id + 0], r1 = rec[3 * (int64_t)id + 1];
-                    s_w0[threadIdx.x] = r0;
-                    s_w1[threadIdx.x] = r1;
-                    s_w2[threadIdx.x] = blend_stage_w2<false>(r0, r1, rec[3 * (int64_t)id + 2], tx0p, ty0p);
-                    const uint32_t slot = start + eb + e;
-                    if (slot < cl.cap) cl.walked[slot] = id;
-                } else {
-                    // past the pair capacity (the render reports the overflow):
-                    // an entry no pixel takes
-                    s_w0[threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    s_w1[threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    s_w2[threadIdx.x] = make_float4(0.f, 0.f, 0.f, __uint_as_float(0u));
-                }
-            }
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                // advance past the cnt_u staged entries
-                if (cnt_u == avail) {
-                    s_cc += 64;
-                    s_co = 0u;
-                } else {
-                    int lo = 0, hi = 63;   // the segment holding the next entry
-                    while (lo < hi) {
-                        const int mid = (lo + hi + 1) >> 1;
-                        if (s_pre[mid] <= cnt_u) lo = mid; else hi = mid - 1;
-                    }
-                    s_co = (lo == 0 ? s_co : 0u) + (cnt_u - s_pre[lo]);
-                    s_cc += lo;
-                }
-            }
+            if ((uint32_t)tid < cnt_u) myid = s_q[tid];
         } else {
-            const uint32_t e = start + eb + threadIdx.x;
-            if (e < end) {
-                const uint32_t id = vals[e];
-                const float4 r0 = rec[3 * (int64_t)id + 0], r1 = rec[3 * (int64_t)id + 1];
-                s_w0[threadIdx.x] = r0;
-                s_w1[threadIdx.x] = r1;
-                s_w2[threadIdx.x] = blend_stage_w2<false>(r0, r1, rec[3 * (int64_t)id + 2], tx0p, ty0p);
-            }
-            __syncthreads();
-            cnt_u = min((uint32_t)NT, total - eb);
+            if (c >= cend) break;
+            cnt_u = min((uint32_t)NT, cend - c);
+            if ((uint32_t)tid < cnt_u) myid = vals[c + tid];
+            c += cnt_u;
+        }
+        if ((uint32_t)tid < cnt_u) {
+            const float4 r0 = rec[3 * (int64_t)myid + 0], r1 = rec[3 * (int64_t)myid + 1];
+            s_w0[tid] = r0;
+            s_w1[tid] = r1;
+            s_w2[tid] = blend_stage_w2<false>(r0, r1, rec[3 * (int64_t)myid + 2], tx0p, ty0p);
+        }
+        uint32_t rest = 0u;   // the queue's entries past this batch move to its front
+        if (kSuper && (uint32_t)tid + NT < queued) rest = s_q[NT + tid];
+        __syncthreads();
+        if (kSuper) {
+            if ((uint32_t)tid + NT < queued) s_q[tid] = rest;
+            queued -= cnt_u;
+            // a block for this batch (the first is the tile's own); the
+            // answer is needed only after the evaluation
+            if (tid == 0 && eb != 0u) blk = atomicAdd(sd.pool, 1u);
         }
         const int cnt = (int)cnt_u;
-        if (!all) {
+        bool live = fpy == fpy;
+        uint64_t took = 0ull;
+        if (__builtin_amdgcn_ballot_w64(live)) {
             // branch-free per-pixel body: every lane evaluates, selects keep
             // the state of pixels that do not take the contribution
             auto eval = [&](int j) {
@@ -625,79 +570,79 @@ __global__ __launch_bounds__(kTile * kTile / R) void k_blend_fwd(CamDev cam, int
                 const uint32_t box = __float_as_uint(w2.w);
                 float adx2, bdx;
                 blend_dx_terms(fpx - w0.x, w0, adx2, bdx);
-                // lane masks (wave-uniform): okm[k] the lanes whose pixel k
-                // takes the entry, bm[k] those whose exponent lies in the
-                // band where the exact test decides
-                float power[R];
-                uint64_t okm[R], bm[R];
-                uint64_t any_band = 0ull;
-#pragma unroll
-                for (int k = 0; k < R; k++) {
-                    power[k] = blend_power(adx2, bdx, fpy[k] - w0.y, w1.x);
-                    const uint64_t pm = __builtin_amdgcn_ballot_w64((box & sel[k]) == sel[k]) &
-                                        __builtin_amdgcn_ballot_w64(power[k] <= 0.0f) &
-                                        __builtin_amdgcn_ballot_w64(power[k] >= w2.y);
-                    bm[k] = pm & __builtin_amdgcn_ballot_w64(power[k] < w2.z);
-                    okm[k] = pm & ~bm[k];
-                    any_band |= bm[k];
-                }
-                if (any_band) {
-#pragma unroll
-                    for (int k = 0; k < R; k++)
-                        okm[k] |= bm[k] & __builtin_amdgcn_ballot_w64(blend_exact_test(power[k], w1.y));
-                }
-                uint64_t any_ok = 0ull;   // no pixel of the wave takes the entry: nothing changes
-#pragma unroll
-                for (int k = 0; k < R; k++) any_ok |= okm[k];
-                if (!any_ok) return;
-#pragma unroll
-                for (int k = 0; k < R; k++) {
-                    const bool ok = __builtin_amdgcn_inverse_ballot_w64(okm[k]);
-                    const float alpha = fminf(0.99f, w1.y * __expf(power[k]));
-                    const float Tn = T[k] * (1.0f - alpha);
-                    const bool stop = ok & (Tn < 1e-4f);
-                    const bool take = ok & !stop;
-                    const float wgt = take ? alpha * T[k] : 0.0f;
-                    c0[k] += wgt * w1.z;
-                    c1[k] += wgt * w1.w;
-                    c2[k] += wgt * w2.x;
-                    T[k] = take ? Tn : T[k];
-                    last[k] = take ? eb + (uint32_t)j + 1u : last[k];
-                    fpy[k] = stop ? kStopped : fpy[k];
-                }
+                // lane masks (wave-uniform): okm the lanes whose pixel takes
+                // the entry, bm those whose exponent lies in the band where
+                // the exact test decides
+                const float power = blend_power(adx2, bdx, fpy - w0.y, w1.x);
+                const uint64_t pm = __builtin_amdgcn_ballot_w64((box & sel) == sel) &
+                                    __builtin_amdgcn_ballot_w64(power <= 0.0f) &
+                                    __builtin_amdgcn_ballot_w64(power >= w2.y);
+                const uint64_t bm = pm & __builtin_amdgcn_ballot_w64(power < w2.z);
+                uint64_t okm = pm & ~bm;
+                if (bm) okm |= bm & __builtin_amdgcn_ballot_w64(blend_exact_test(power, w1.y));
+                if (!okm) return;   // no pixel of the wave takes the entry: nothing changes
+                const bool ok = __builtin_amdgcn_inverse_ballot_w64(okm);
+                const float alpha = fminf(0.99f, w1.y * __expf(power));
+                const float Tn = T * (1.0f - alpha);
+                const bool stop = ok & (Tn < 1e-4f);
+                const bool take = ok & !stop;
+                const float wgt = take ? alpha * T : 0.0f;
+                c0 += wgt * w1.z;
+                c1 += wgt * w1.w;
+                c2 += wgt * w2.x;
+                T = take ? Tn : T;
+                last = take ? eb + (uint32_t)j + 1u : last;
+                fpy = stop ? kStopped : fpy;
             };
             // two entries per trip; the wave leaves once all its pixels have stopped
             int j = 0;
             for (; j + 1 < cnt; j += 2) {
                 eval(j);
                 eval(j + 1);
-                bool active = false;
-#pragma unroll
-                for (int k = 0; k < R; k++) active = active | (fpy[k] == fpy[k]);
-                if (!__builtin_amdgcn_ballot_w64(active)) break;
+                if (!__builtin_amdgcn_ballot_w64(fpy == fpy)) break;
             }
             if (j + 1 == cnt) eval(j);
+            live = fpy == fpy;
+            took = __builtin_amdgcn_ballot_w64(last > eb);
+        }
+        const uint64_t alive = __builtin_amdgcn_ballot_w64(live);
+        if (lane == 0) {
+            s_live[w] = alive != 0ull;
+            s_took[w] = took != 0ull;
+        }
+        if (kSuper && tid == 0) {
+            if (blk >= sd.max_blocks) blk = 0xFFFFFFFFu;   // only when the pairs overflowed
+            if (eb != 0u && blk != 0xFFFFFFFFu) sd.prev[blk] = s_blk;
+            s_blk = blk;
+        }
+        __syncthreads();
+        if (kSuper) {
+            const uint32_t b = s_blk;
+            if ((uint32_t)tid < cnt_u && b != 0xFFFFFFFFu) sd.walked[(int64_t)b * kWalkBlock + tid] = myid;
+            if (s_took[0] | s_took[1] | s_took[2] | s_took[3]) lastblk = b;
         }
         eb += cnt_u;
-        __syncthreads();
+        if (!(s_live[0] | s_live[1] | s_live[2] | s_live[3])) break;
     }
     const int64_t P = (int64_t)cam.W * cam.H;
-    uint32_t mx = 0u;
-#pragma unroll
-    for (int k = 0; k < R; k++) {
-        if (px < cam.W && py0 + k < cam.H) {
-            const int64_t p = (int64_t)(py0 + k) * cam.W + px;
-            image[p] = c0[k] + T[k] * cam.bg[0];
-            image[P + p] = c1[k] + T[k] * cam.bg[1];
-            image[2 * P + p] = c2[k] + T[k] * cam.bg[2];
-            T_final[p] = T[k];
-            last_out[p] = last[k];
-        }
-        mx = max(mx, last[k]);
+    if (px < cam.W && py < cam.H) {
+        const int64_t p = (int64_t)py * cam.W + px;
+        image[p] = c0 + T * cam.bg[0];
+        image[P + p] = c1 + T * cam.bg[1];
+        image[2 * P + p] = c2 + T * cam.bg[2];
+        T_final[p] = T;
+        last_out[p] = last;
     }
-    if (mx) atomicMax(&s_walk, mx);
     __syncthreads();
-    if (threadIdx.x == 0) tile_walk[tile] = s_walk;
+    if (last) atomicMax(&s_walk, last);
+    __syncthreads();
+    if (tid == 0) {
+        // no block to walk back through: the backward skips the tile (the
+        // pairs overflowed, which the render reports)
+        const bool lost = kSuper && lastblk == 0xFFFFFFFFu;
+        tile_walk[tile] = lost ? 0u : s_walk;
+        if (kSuper) sd.tile_blk[tile] = lost ? (uint32_t)tile : lastblk;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -719,7 +664,7 @@ __global__ __launch_bounds__(kTile * kTile / R) void k_blend_fwd(CamDev cam, int
 constexpr int kBwdBatch = GS3_BWD_BATCH;   // backward blend: entries staged per batch (LDS: about 200 B each)
 __constant__ float kConicScale[9] = {1.f, 1.f, -0.5f, -1.f, -0.5f, 1.f, 1.f, 1.f, 1.f};
 
-template <int R, bool kRecords, bool kOpacity>
+template <int R, bool kSuper, bool kRecords, bool kOpacity>
 __global__ __launch_bounds__(kTile * kTile / R) void k_blend_bwd(CamDev cam, int ntiles,
                                                                  const uint2* __restrict__ ranges,
                                                                  const uint32_t* __restrict__ vals,
@@ -731,7 +676,7 @@ __global__ __launch_bounds__(kTile * kTile / R) void k_blend_bwd(CamDev cam, int
                                                                  const uint32_t* __restrict__ walk_off,
                                                                  float* __restrict__ grec, uint32_t grec_cap,
                                                                  float* __restrict__ accum,
-                                                                 const int* __restrict__ order) {
+                                                                 const int* __restrict__ order, SuperDev sd) {
     constexpr int NT = kTile * kTile / R, NW = NT / 64;
     constexpr int KB = kBwdBatch < NT ? kBwdBatch : NT;   // entries staged per batch
     static_assert(KB <= 128, "the wave entry masks hold two words");
@@ -751,7 +696,10 @@ __global__ __launch_bounds__(kTile * kTile / R) void k_blend_bwd(CamDev cam, int
     uint32_t sel[R];   // this thread's column and row bits in the box masks
 #pragma unroll
     for (int k = 0; k < R; k++) sel[k] = (1u << (threadIdx.x & 15)) | (1u << (16 + (threadIdx.x >> 4) * R + k));
-    const uint32_t start = ranges[tile].x;
+    // kSuper: the block holding the batch (the forward's tile_blk, then prev)
+    const uint32_t start = kSuper ? 0u : ranges[tile].x;
+    uint32_t blk = kSuper ? sd.tile_blk[tile] : 0u;
+    static_assert(kWalkBlock % KB == 0, "a batch lies in one walked block");
     const uint32_t woff = kRecords ? walk_off[tile] : 0u;
     const int64_t P = (int64_t)cam.W * cam.H;
     // gb: dL/dC . (colour behind the current contributor), the only use of
@@ -791,7 +739,7 @@ __global__ __launch_bounds__(kTile * kTile / R) void k_blend_bwd(CamDev cam, int
     for (int64_t jb = ((int64_t)(maxlast - 1) / KB) * KB; jb >= 0; jb -= KB) {
         const uint32_t e = (uint32_t)jb + threadIdx.x;
         if ((int)threadIdx.x < KB && e < maxlast) {
-            const uint32_t id = vals[start + e];
+            const uint32_t id = kSuper ? sd.walked[(int64_t)blk * kWalkBlock + (e % kWalkBlock)] : vals[start + e];
             const float4 r0 = rec[3 * (int64_t)id + 0], r1 = rec[3 * (int64_t)id + 1];
             s_id[threadIdx.x] = id;
             s_w0[threadIdx.x] = r0;
@@ -966,6 +914,7 @@ __global__ __launch_bounds__(kTile * kTile / R) void k_blend_bwd(CamDev cam, int
                 if (v != 0.f) atomicAdd(accum + 9 * (int64_t)s_id[e] + k, v);
             }
         }
+        if (kSuper && jb > 0 && jb % kWalkBlock == 0) blk = sd.prev[blk];
         __syncthreads();
     }
 }
@@ -1216,11 +1165,11 @@ void ranges_from_keys(const Launch& L, const uint64_t* keys, int64_t K, int ntil
 }
 
 void bin_gather(const Launch& L, const uint32_t* order, int64_t n, const uint2* rect, const uint32_t* count,
-                const uint64_t* goff, uint64_t cap, uint2* srect, uint32_t* sgoff, uint32_t* zero, int64_t nzero) {
+                const uint64_t* goff, uint64_t cap, uint2* srect, uint32_t* sgoff) {
     if (n <= 0) return;
     if (L.prof) L.prof->begin("bin_gather", L.st);
-    hipLaunchKernelGGL(k_bin_gather, dim3(blocks_for(std::max(n, nzero), 256)), dim3(256), 0, L.st, order, n, rect,
-                       count, goff, (uint32_t)std::min<uint64_t>(cap, 0xFFFFFFFFull), srect, sgoff, zero, nzero);
+    hipLaunchKernelGGL(k_bin_gather, dim3(blocks_for(n, 256)), dim3(256), 0, L.st, order, n, rect, count, goff,
+                       (uint32_t)std::min<uint64_t>(cap, 0xFFFFFFFFull), srect, sgoff);
     if (L.prof) L.prof->end(L.st);
 }
 
@@ -1230,17 +1179,14 @@ static dim3 bin_grid(int64_t nchunks, int tiles_y) {
     return dim3((unsigned)(nchunks * ((tiles_y + kBinRowsPerBlock - 1) / kBinRowsPerBlock)));
 }
 
-void bin_count(const Launch& L, const uint32_t* order, int64_t n, const uint2* srect, int tiles_x, int tiles_y,
-               uint32_t* hist, uint32_t* ttot) {
+void bin_count(const Launch& L, int64_t n, const uint2* srect, int tiles_x, int tiles_y, uint32_t* hist) {
     const int64_t nchunks = n > 0 ? bin_chunks(n) : 0;
     if (nchunks == 0) return;
     if (L.prof) L.prof->begin("bin_count", L.st);
     const unsigned grid = (unsigned)((nchunks / kCountGroup) * ((tiles_y + kBinRowsPerBlock - 1) / kBinRowsPerBlock));
-    hipLaunchKernelGGL(k_bin_count, dim3(grid), dim3(kBinThreads), 0, L.st, srect, n, tiles_x, tiles_y, nchunks, hist,
-                       ttot);
+    hipLaunchKernelGGL(k_bin_count, dim3(grid), dim3(kBinThreads), 0, L.st, srect, n, tiles_x, tiles_y, nchunks, hist);
     if (L.prof) L.prof->end(L.st);
 }
-
 
 int64_t bin_scan_part_words(int64_t nchunks, int ntiles) {
     return ((nchunks + kBinScanSeg - 1) / kBinScanSeg) * (int64_t)ntiles;
@@ -1262,52 +1208,14 @@ void bin_scan(const Launch& L, const uint32_t* hist, int64_t nchunks, int ntiles
     if (L.prof) L.prof->end(L.st);
 }
 
-template <typename B>
-static void bin_scatter_impl(const Launch& L, const uint32_t* order, int64_t n, const uint2* srect,
-                             const uint32_t* sgoff, int tiles_x, int tiles_y, const B* base, uint64_t cap,
-                             uint32_t* vals, uint32_t* gpos) {
+void bin_scatter(const Launch& L, const uint32_t* order, int64_t n, const uint2* srect, const uint32_t* sgoff,
+                 int tiles_x, int tiles_y, const uint32_t* base, uint64_t cap, uint32_t* vals, uint32_t* gpos) {
     const int64_t nchunks = n > 0 ? bin_chunks(n) : 0;
     if (nchunks == 0) return;
     if (L.prof) L.prof->begin("bin_scatter", L.st);
-    if (gpos)
-        hipLaunchKernelGGL((k_bin_rows<B, true>), bin_grid(nchunks, tiles_y), dim3(kBinThreads), 0, L.st, order, n,
-                           srect, sgoff, tiles_x, tiles_y, nchunks, base, (uint32_t)cap, vals, gpos);
-    else
-        hipLaunchKernelGGL((k_bin_rows<B, false>), bin_grid(nchunks, tiles_y), dim3(kBinThreads), 0, L.st, order, n,
-                           srect, sgoff, tiles_x, tiles_y, nchunks, base, (uint32_t)cap, vals, gpos);
+    hipLaunchKernelGGL(k_bin_rows, bin_grid(nchunks, tiles_y), dim3(kBinThreads), 0, L.st, order, n, srect, sgoff,
+                       tiles_x, tiles_y, nchunks, base, (uint32_t)cap, vals, gpos);
     if (L.prof) L.prof->end(L.st);
-}
-
-void bin_scatter(const Launch& L, const uint32_t* order, int64_t n, const uint2* srect, const uint32_t* sgoff,
-                 int tiles_x, int tiles_y, const uint32_t* base, uint64_t cap, uint32_t* vals, uint32_t* gpos) {
-    bin_scatter_impl(L, order, n, srect, sgoff, tiles_x, tiles_y, base, cap, vals, gpos);
-}
-
-void bin_scatter_chunked(const Launch& L, const uint32_t* order, int64_t n, const uint2* srect, int tiles_x,
-                         int tiles_y, const uint64_t* cmb, uint64_t cap, uint32_t* vals) {
-    bin_scatter_impl(L, order, n, srect, (const uint32_t*)nullptr, tiles_x, tiles_y, cmb, cap, vals,
-                     (uint32_t*)nullptr);
-}
-
-__global__ __launch_bounds__(256) void k_chunked_to_tile_major(const uint32_t* __restrict__ hist,
-                                                               const uint64_t* __restrict__ cmb,
-                                                               const uint32_t* __restrict__ base_tm, int64_t m,
-                                                               uint64_t cap, const uint32_t* __restrict__ vals_cm,
-                                                               uint32_t* __restrict__ vals_tm) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;   // (chunk, tile) in [chunk][tile] order
-    if (i >= m) return;
-    const uint32_t len = hist[i];
-    const uint64_t src = cmb[i], dst = base_tm[i];
-    for (uint32_t k = 0; k < len; k++)
-        if (src + k < cap && dst + k < cap) vals_tm[dst + k] = vals_cm[src + k];
-}
-
-void chunked_to_tile_major(const Launch& L, const uint32_t* hist, const uint64_t* cmb, const uint32_t* base_tm,
-                           int64_t nchunks, int ntiles, uint64_t cap, const uint32_t* vals_cm, uint32_t* vals_tm) {
-    const int64_t m = nchunks * ntiles;
-    if (m <= 0) return;
-    hipLaunchKernelGGL(k_chunked_to_tile_major, dim3(blocks_for(m, 256)), dim3(256), 0, L.st, hist, cmb, base_tm, m, cap,
-                       vals_cm, vals_tm);
 }
 
 void gpos_from_pairs(const Launch& L, const uint64_t* keys, const uint32_t* vals, int64_t K, const uint2* rect,
@@ -1328,10 +1236,6 @@ void ranges_from_hist(const Launch& L, const uint32_t* base, const uint64_t* tot
 
 static unsigned blend_grid(int ntiles) { return (unsigned)(((ntiles + 7) / 8) * 8); }
 
-// pixels per thread of the blend kernels
-constexpr int kBlendRows = GS3_BLEND_ROWS_FWD;
-constexpr int kBlendRowsBwd = GS3_BLEND_ROWS_BWD;
-
 void tile_order(const Launch& L, const uint2* ranges, const uint32_t* walk, int ntiles, int* order) {
     if (L.prof) L.prof->begin("tile_order", L.st);
     hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(1024), 0, L.st, ranges, walk, ntiles, order);
@@ -1340,32 +1244,36 @@ void tile_order(const Launch& L, const uint2* ranges, const uint32_t* walk, int 
 
 void blend_forward(const Launch& L, const CamDev& cam, const uint2* ranges, const uint32_t* vals, const float4* rec,
                    float* image, float* T_final, uint32_t* last, uint32_t* tile_walk, const int* order,
-                   const ChunkDev* chunks) {
+                   const SuperDev* supers) {
     const int ntiles = cam.tiles_x * cam.tiles_y;
     if (L.prof) L.prof->begin("blend_fwd", L.st);
-    const dim3 grid(order ? (unsigned)ntiles : blend_grid(ntiles));
-    const ChunkDev cl = chunks ? *chunks : ChunkDev{};
-    if (chunks)
-        hipLaunchKernelGGL((k_blend_fwd<kBlendRows, true>), grid, dim3(kTile * kTile / kBlendRows), 0, L.st, cam, ntiles,
-                           ranges, vals, rec, image, T_final, last, tile_walk, order, cl);
-    else
-        hipLaunchKernelGGL((k_blend_fwd<kBlendRows, false>), grid, dim3(kTile * kTile / kBlendRows), 0, L.st, cam,
-                           ntiles, ranges, vals, rec, image, T_final, last, tile_walk, order, cl);
+    if (supers) {
+        const int nsuper = supers->supers_x * super_count_of(cam.tiles_y);
+        const unsigned grid = (unsigned)((nsuper + 7) / 8 * 8 * kSuperDim * kSuperDim);
+        hipLaunchKernelGGL((k_blend_fwd<true>), dim3(grid), dim3(kBlendThreads), 0, L.st, cam, ntiles, ranges, vals,
+                           rec, image, T_final, last, tile_walk, order, *supers, nsuper);
+    } else {
+        hipLaunchKernelGGL((k_blend_fwd<false>), dim3(order ? (unsigned)ntiles : blend_grid(ntiles)),
+                           dim3(kBlendThreads), 0, L.st, cam, ntiles, ranges, vals, rec, image, T_final, last,
+                           tile_walk, order, SuperDev{}, 0);
+    }
     if (L.prof) L.prof->end(L.st);
 }
 
 void blend_backward(const Launch& L, const CamDev& cam, const uint2* ranges, const uint32_t* vals, const float4* rec,
                     const float* d_image, const float* T_final, const uint32_t* last, const GatherDev& ga,
-                    float* accum, bool want_opacity, const int* order) {
+                    float* accum, bool want_opacity, const int* order, const SuperDev* supers) {
     const int ntiles = cam.tiles_x * cam.tiles_y;
     if (L.prof) L.prof->begin("blend_bwd", L.st);
     const bool records = ga.grec_cap > 0;
-    constexpr int R = kBlendRowsBwd;
-    auto kern = records ? (want_opacity ? k_blend_bwd<R, true, true> : k_blend_bwd<R, true, false>)
-                        : (want_opacity ? k_blend_bwd<R, false, true> : k_blend_bwd<R, false, false>);
+    constexpr int R = 1;
+    // gradient records are kept with a tile-major list only
+    auto kern = supers ? (want_opacity ? k_blend_bwd<R, true, false, true> : k_blend_bwd<R, true, false, false>)
+                : records ? (want_opacity ? k_blend_bwd<R, false, true, true> : k_blend_bwd<R, false, true, false>)
+                          : (want_opacity ? k_blend_bwd<R, false, false, true> : k_blend_bwd<R, false, false, false>);
     hipLaunchKernelGGL(kern, dim3(order ? (unsigned)ntiles : blend_grid(ntiles)), dim3(kTile * kTile / R), 0, L.st,
                        cam, ntiles, ranges, vals, rec, d_image, T_final, last, ga.tile_walk, ga.walk_off, ga.grec,
-                       (uint32_t)ga.grec_cap, accum, order);
+                       (uint32_t)ga.grec_cap, accum, order, supers ? *supers : SuperDev{});
     if (L.prof) L.prof->end(L.st);
 }
 

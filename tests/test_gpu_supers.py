@@ -1,0 +1,92 @@
+"""GPU tests of the binning into supers (blocks of 4 x 4 tiles) against the
+general path, the 64-bit sort of every (tile, depth) pair: same pair list,
+ranges, image and per-pixel state bit for bit, and the same gradients, at the
+sizes where the supers, their chunks of 512 Gaussians or the batches of 256
+entries are ragged."""
+import numpy as np
+import pytest
+
+from paper_2403_01444_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+# (n, width, height, log-scale offset, pair capacity).  Offsets make the
+# Gaussians span many supers (a view-filling one takes the whole-wave walk)
+# or less than a tile.
+CASES = [
+    (1, 16, 16, 0.0, 1 << 12),           # one Gaussian, one tile
+    (511, 64, 64, 0.0, 1 << 16),         # one super, a chunk short of one
+    (512, 65, 63, 0.0, 1 << 16),         # one column past a super
+    (513, 130, 17, 0.0, 1 << 16),        # one Gaussian past a chunk, one tile row and a pixel
+    (3000, 48, 48, -0.5, 1 << 18),       # tiles with several batches of 256
+    (2500, 700, 300, 1.2, 1 << 22),      # rectangles of more than 32 supers
+    (700, 4096, 560, 0.3, 1 << 22),      # 64 x 9 supers: two batches of 512 in the scatter
+]
+
+
+def render_all(g, cam, pairs, mode):
+    from paper_2403_01444_amd import gs3
+    ctx = gs3.Context(g.n, pairs, cam.width, cam.height, sort_mode=mode)
+    gg = gs3.GaussiansGPU.from_host(g)
+    img = ctx.render(gg, cam).clone()
+    out = {"image": img}
+    out["T"], out["last"] = ctx.debug_pixels(cam)
+    out["keys"], out["vals"] = ctx.debug_pairs()
+    out["ranges"] = ctx.debug_ranges(cam)
+    rng = np.random.default_rng(3)
+    d = torch.from_numpy(rng.normal(size=(3, cam.height, cam.width)).astype(np.float32)).cuda()
+    grads = {"d_uv": ctx.zeros(g.n, 2), "d_conic": ctx.zeros(g.n, 3), "d_opacity": ctx.zeros(g.n),
+             "d_rgb": ctx.zeros(g.n, 3)}
+    ctx.render_backward(d, grads)
+    sums = ctx.debug_sums()
+    ctx.check_flags()
+    ctx.close()
+    return {k: v.cpu().numpy() for k, v in out.items()}, {k: v.cpu().numpy() for k, v in grads.items()}, sums
+
+
+@pytest.mark.parametrize("n,width,height,offset,pairs", CASES)
+def test_supers_match_the_sorted_pairs(n, width, height, offset, pairs):
+    g = synth.make_gaussians(n, 1, n)
+    g.log_scales += np.float32(offset)
+    cam = synth.look_at_camera(width, height, azimuth_deg=11.0, bg=(0.1, 0.2, 0.3))
+    a, ga, sa = render_all(g, cam, pairs, "depth_first")
+    b, gb, sb = render_all(g, cam, pairs, "radix64")
+    assert a["vals"].size > 0 and sa == sb
+    # an empty tile's range is [s, s) in depth order and [0, 0) from the sorted keys
+    for r in (a["ranges"], b["ranges"]):
+        r[r[:, 0] == r[:, 1]] = 0
+    for k in a:
+        assert np.array_equal(a[k], b[k]), k
+    # The sums over a tile are the same on both paths; they are added to the
+    # Gaussian's total with float atomics in another order.  m addends of sum
+    # S and absolute sum A differ by at most 2 (m - 1) 2^-24 A; with m up to
+    # a few hundred tiles and A up to a few S that is below 2e-4 of the largest.
+    for k in ga:
+        assert np.abs(ga[k] - gb[k]).max() <= 2e-4 * np.abs(gb[k]).max(), k
+
+
+def test_supers_report_an_overflow_and_stay_in_bounds():
+    """More pairs than the capacity: reported like before, the render and its
+    backward stay in bounds, and the pair count is still the true one."""
+    from paper_2403_01444_amd import gs3
+    g = synth.make_gaussians(4000, 0, 5)
+    cam = synth.look_at_camera(96, 80)
+    full = gs3.Context(g.n, 1 << 18, 96, 80)
+    gg = gs3.GaussiansGPU.from_host(g)
+    full.render(gg, cam)
+    K, _ = full.debug_counts()
+    full.check_flags()
+    small = gs3.Context(g.n, K // 50, 96, 80)
+    img = small.render(gg, cam)
+    small.render_backward(torch.ones_like(img), {"d_uv": small.zeros(g.n, 2)})
+    assert small.debug_counts() == (K, 1)
+    with pytest.raises(gs3.GS3Error) as e:
+        small.check_flags()
+    assert e.value.status == gs3.GS3_ECAPACITY
+    with pytest.raises(gs3.GS3Error) as e:
+        small.debug_pairs()
+    assert e.value.status == gs3.GS3_ECAPACITY
+    full.close()
+    small.close()
