@@ -449,6 +449,53 @@ __device__ __forceinline__ float4 blend_stage_w2(const float4& w0, const float4&
     return make_float4(w2.x, w2.w - 1e-4f, w2.w + 1e-4f, __uint_as_float(cm | (rm << 16)));
 }
 
+// Pixel of a blend lane inside its tile: wave w has the 8 x 8 quadrant
+// (w & 1, w >> 1).
+__device__ __forceinline__ int quad_x(int w, int lane) { return 8 * (w & 1) + (lane & 7); }
+__device__ __forceinline__ int quad_y(int w, int lane) { return 8 * (w >> 1) + (lane >> 3); }
+
+// Whether the exponent can reach the band's lower edge (blend_stage_w2)
+// inside the rectangle of offsets [dx0, dx1] x [dy0, dy1] from the mean: the
+// smallest value of the form A dx^2 + 2 B dx dy + C dy^2 there against
+// k = -2 (pthr - 1e-4).  The minimum over the rectangle lies at the mean (0,
+// when it is inside) or on an edge that faces it; on the edge dx = e it is at
+// dy = -B e / C, clamped to the edge.  The offsets of the rectangle's pixels
+// lie in it exactly (rounding x - u is monotone).  The per-pixel exponent and
+// the values here are each within 5 ulp of the sum of the form's absolute
+// terms, which is at most 4 A C / det times the form: with A C <= 250 det
+// that is under 6e-4 of it together, and the comparison leaves 2e-3.
+__device__ __forceinline__ bool conic_reaches(float A, float B, float C, float k, float dx0, float dx1, float dy0,
+                                              float dy1) {
+    const float ex = fminf(fmaxf(0.0f, dx0), dx1), ey = fminf(fmaxf(0.0f, dy0), dy1);
+    const float y = fminf(fmaxf(-B * ex * __builtin_amdgcn_rcpf(C), dy0), dy1);
+    const float x = fminf(fmaxf(-B * ey * __builtin_amdgcn_rcpf(A), dx0), dx1);
+    const float q1 = A * ex * ex + 2.0f * B * ex * y + C * y * y;
+    const float q2 = A * x * x + 2.0f * B * x * ey + C * ey * ey;
+    return !(fminf(q1, q2) > 1.002f * k + 1e-4f);
+}
+
+// Quadrants of the tile at (tx0p, ty0p) in which a pixel can take the record:
+// bit w as wave w of a blend workgroup.  Its pixel box has to meet the
+// quadrant and, where single precision decides it safely (conic_reaches), its
+// exponent has to reach the opacity threshold there.
+__device__ __forceinline__ uint32_t quads_reached(const float4& w0, const float4& w1, const float4& w2, int tx0p,
+                                                  int ty0p) {
+    const uint32_t b0 = __float_as_uint(w2.y), b1 = __float_as_uint(w2.z);
+    const int x0 = (int)(b0 & 0xFFFFu), y0 = (int)(b0 >> 16), x1 = (int)(b1 & 0xFFFFu), y1 = (int)(b1 >> 16);
+    const float A = w0.z, B = w0.w, C = w1.x, k = -2.0f * (w2.w - 1e-4f);
+    const bool cut = A * C <= 250.0f * (A * C - B * B);
+    uint32_t m = 0u;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const int qx = tx0p + 8 * (q & 1), qy = ty0p + 8 * (q >> 1);
+        const int rx0 = max(x0, qx), rx1 = min(x1, qx + 7), ry0 = max(y0, qy), ry1 = min(y1, qy + 7);
+        const bool meets = conic_reaches(A, B, C, k, (float)rx0 - w0.x, (float)rx1 - w0.x, (float)ry0 - w0.y,
+                                         (float)ry1 - w0.y);
+        m |= (uint32_t)((rx0 <= rx1) & (ry0 <= ry1) & (!cut | meets)) << q;
+    }
+    return m;
+}
+
 // Rows of the tile that wave wv of a blend workgroup covers (16 columns x R
 // rows per 16 threads), as bits 16-31 of a box mask.
 template <int R>

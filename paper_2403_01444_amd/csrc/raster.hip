@@ -1,6 +1,8 @@
 // Tile rasterizer of 3D Gaussians for gfx950 (Sec. 3.2: Eq. 2-4), forward
 // and adjoint, plus the Gaussian transform of Sec. 4.1 fused into the
 // per-Gaussian kernels.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace gs3 {
@@ -441,9 +443,21 @@ __global__ __launch_bounds__(1024) void k_tile_order(const uint2* __restrict__ r
 // the current batch is evaluated) and evaluates the queue in batches of 256
 // (fewer at the end of the list).  Each batch's indices are kept in a walked
 // block for the backward.  Otherwise the entries are vals[ranges[tile]).
+//
+// Bound by VALU issue where the launch fills the chip and by the latency of
+// one wave's chain where it does not.  So a wave takes a square of 8 x 8
+// pixels and evaluates only the staged entries that can reach it
+// (quads_reached, a bit per entry and quadrant: at the benchmark scene less
+// than half of the (wave, entry) visits of 16 x 4 pixels without the test),
+// four at a time, since their exponents do not depend on each other (two at a
+// time 0.5-3% slower, eight 2-4% slower on the large views).  Per launch,
+// 16 x 4 pixels and every entry -> this: 300K uniform at 1352 x 1014 227 ->
+// 139 us, 1M at 1920 x 1080 407 -> 228, 300K surfaces 298 -> 168, 50K
+// surfaces at 256 x 256 486 -> 225, 2K at 64 x 64 129 -> 53 us.
 // ---------------------------------------------------------------------------
+constexpr int kFwdGroup = 4;   // entries whose exponents are evaluated together
 template <bool kSuper>
-__global__ __launch_bounds__(kBlendThreads) void k_blend_fwd(CamDev cam, int ntiles, const uint2* __restrict__ ranges,
+__global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int ntiles, const uint2* __restrict__ ranges,
                                                              const uint32_t* __restrict__ vals,
                                                              const float4* __restrict__ rec, float* __restrict__ image,
                                                              float* __restrict__ T_final, uint32_t* __restrict__ last_out,
@@ -477,18 +491,18 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend_fwd(CamDev cam, int nti
     __shared__ float4 s_w2[NT];   // blend_stage_w2 form
     __shared__ uint32_t s_q[kSuper ? 2 * NT : 1];   // queue of indices
     __shared__ uint32_t s_n[2][NW];                 // entries each wave adds to it
+    __shared__ uint64_t s_reach[NW][NW];            // [quadrant][word]: staged entries that can reach its pixels
     __shared__ uint32_t s_live[NW], s_took[NW], s_blk;
     const int tx0p = tx * kTile, ty0p = ty * kTile;
-    const int px = tx0p + (tid & 15), py = ty0p + (tid >> 4);
-    const float fpx = (float)px;
-    const uint32_t sel = (1u << (tid & 15)) | (1u << (16 + (tid >> 4)));   // column and row bits in the box masks
+    // wave w: the 8 x 8 quadrant (w & 1, w >> 1) of the tile
+    const int lx = quad_x(w, lane), ly = quad_y(w, lane);
+    const int px = tx0p + lx, py = ty0p + ly;
+    const float fpx = (float)px, fpy = (float)py;
+    const uint32_t sel = (1u << lx) | (1u << (16 + ly));   // column and row bits in the box masks
     float T = 1.0f, c0 = 0.f, c1 = 0.f, c2 = 0.f;
     uint32_t last = 0u;
-    // pixel row coordinate, NaN once the pixel has stopped (and for pixels
-    // outside the image): every comparison of its exponent is then false, so
-    // a stopped pixel takes no further contribution without a flag test
-    const float kStopped = __int_as_float(0x7FC00000);
-    float fpy = (px < cam.W && py < cam.H) ? (float)py : kStopped;
+    // lanes whose pixel is in the image and has not stopped
+    uint64_t alive = __builtin_amdgcn_ballot_w64(px < cam.W && py < cam.H);
     if (tid == 0) s_walk = 0u;
     // list cursor: the super's entries [c, cend) are not filtered yet; mk, id
     // hold this thread's entry c + tid
@@ -543,11 +557,19 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend_fwd(CamDev cam, int nti
             if ((uint32_t)tid < cnt_u) myid = vals[c + tid];
             c += cnt_u;
         }
+        uint32_t reach = 0u;   // quadrants this thread's entry can reach
         if ((uint32_t)tid < cnt_u) {
             const float4 r0 = rec[3 * (int64_t)myid + 0], r1 = rec[3 * (int64_t)myid + 1];
+            const float4 r2 = rec[3 * (int64_t)myid + 2];
             s_w0[tid] = r0;
             s_w1[tid] = r1;
-            s_w2[tid] = blend_stage_w2<false>(r0, r1, rec[3 * (int64_t)myid + 2], tx0p, ty0p);
+            s_w2[tid] = blend_stage_w2<false>(r0, r1, r2, tx0p, ty0p);
+            reach = quads_reached(r0, r1, r2, tx0p, ty0p);
+        }
+#pragma unroll
+        for (int q = 0; q < NW; q++) {
+            const uint64_t b = __builtin_amdgcn_ballot_w64((reach >> q) & 1u);
+            if (lane == 0) s_reach[q][w] = b;
         }
         uint32_t rest = 0u;   // the queue's entries past this batch move to its front
         if (kSuper && (uint32_t)tid + NT < queued) rest = s_q[NT + tid];
@@ -560,52 +582,89 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend_fwd(CamDev cam, int nti
             if (tid == 0 && eb != 0u) blk = atomicAdd(sd.pool, 1u);
         }
         const int cnt = (int)cnt_u;
-        bool live = fpy == fpy;
-        uint64_t took = 0ull;
-        if (__builtin_amdgcn_ballot_w64(live)) {
-            // branch-free per-pixel body: every lane evaluates, selects keep
-            // the state of pixels that do not take the contribution
-            auto eval = [&](int j) {
-                const float4 w0 = s_w0[j], w1 = s_w1[j], w2 = s_w2[j];
-                const uint32_t box = __float_as_uint(w2.w);
-                float adx2, bdx;
-                blend_dx_terms(fpx - w0.x, w0, adx2, bdx);
-                // lane masks (wave-uniform): okm the lanes whose pixel takes
-                // the entry, bm those whose exponent lies in the band where
-                // the exact test decides
-                const float power = blend_power(adx2, bdx, fpy - w0.y, w1.x);
-                const uint64_t pm = __builtin_amdgcn_ballot_w64((box & sel) == sel) &
-                                    __builtin_amdgcn_ballot_w64(power <= 0.0f) &
-                                    __builtin_amdgcn_ballot_w64(power >= w2.y);
-                const uint64_t bm = pm & __builtin_amdgcn_ballot_w64(power < w2.z);
-                uint64_t okm = pm & ~bm;
-                if (bm) okm |= bm & __builtin_amdgcn_ballot_w64(blend_exact_test(power, w1.y));
-                if (!okm) return;   // no pixel of the wave takes the entry: nothing changes
-                const bool ok = __builtin_amdgcn_inverse_ballot_w64(okm);
-                const float alpha = fminf(0.99f, w1.y * __expf(power));
-                const float Tn = T * (1.0f - alpha);
-                const bool stop = ok & (Tn < 1e-4f);
-                const bool take = ok & !stop;
-                const float wgt = take ? alpha * T : 0.0f;
-                c0 += wgt * w1.z;
-                c1 += wgt * w1.w;
-                c2 += wgt * w2.x;
-                T = take ? Tn : T;
-                last = take ? eb + (uint32_t)j + 1u : last;
-                fpy = stop ? kStopped : fpy;
+        if (alive) {
+            // branch-free per-pixel body over a group of entries: the
+            // exponents and opacities of the group are independent of each
+            // other, so their latencies overlap; only the transmittance
+            // passes from entry to entry.  Every lane evaluates, lane masks
+            // (wave-uniform) keep the state of pixels that do not take the
+            // contribution.
+            auto eval = [&](auto G, const int* j) {
+                constexpr int kG = decltype(G)::value;
+                float power[kG], alpha[kG];
+                float4 w1[kG];
+                float cb[kG];
+                uint64_t okm[kG], bm[kG];
+                uint64_t any = 0ull, band = 0ull;
+#pragma unroll
+                for (int i = 0; i < kG; i++) {
+                    const float4 w0 = s_w0[j[i]], w2 = s_w2[j[i]];
+                    w1[i] = s_w1[j[i]];
+                    cb[i] = w2.x;
+                    const uint32_t box = __float_as_uint(w2.w);
+                    float adx2, bdx;
+                    blend_dx_terms(fpx - w0.x, w0, adx2, bdx);
+                    power[i] = blend_power(adx2, bdx, fpy - w0.y, w1[i].x);
+                    // pixels inside the exponent band at w2.y..w2.z take the exact test
+                    const uint64_t pm = alive & __builtin_amdgcn_ballot_w64((box & sel) == sel) &
+                                        __builtin_amdgcn_ballot_w64(power[i] <= 0.0f) &
+                                        __builtin_amdgcn_ballot_w64(power[i] >= w2.y);
+                    bm[i] = pm & __builtin_amdgcn_ballot_w64(power[i] < w2.z);
+                    okm[i] = pm & ~bm[i];
+                    any |= pm;
+                    band |= bm[i];
+                }
+                if (band) {
+#pragma unroll
+                    for (int i = 0; i < kG; i++)
+                        okm[i] |= bm[i] & __builtin_amdgcn_ballot_w64(blend_exact_test(power[i], w1[i].y));
+                }
+                if (!any) return;   // no pixel of the wave takes an entry: nothing changes
+#pragma unroll
+                for (int i = 0; i < kG; i++) alpha[i] = fminf(0.99f, w1[i].y * __expf(power[i]));
+#pragma unroll
+                for (int i = 0; i < kG; i++) {
+                    const float Tn = T * (1.0f - alpha[i]);
+                    const uint64_t ok = okm[i] & alive;   // a pixel may have stopped inside the group
+                    const uint64_t stop = ok & __builtin_amdgcn_ballot_w64(Tn < 1e-4f);
+                    const bool take = __builtin_amdgcn_inverse_ballot_w64(ok & ~stop);
+                    alive &= ~stop;
+                    const float wgt = take ? alpha[i] * T : 0.0f;
+                    c0 += wgt * w1[i].z;
+                    c1 += wgt * w1[i].w;
+                    c2 += wgt * cb[i];
+                    T = take ? Tn : T;
+                    last = take ? eb + (uint32_t)j[i] + 1u : last;
+                }
             };
-            // two entries per trip; the wave leaves once all its pixels have stopped
-            int j = 0;
-            for (; j + 1 < cnt; j += 2) {
-                eval(j);
-                eval(j + 1);
-                if (!__builtin_amdgcn_ballot_w64(fpy == fpy)) break;
+            // the entries that can reach the wave's pixels, in order; the
+            // wave leaves once all its pixels have stopped
+#pragma unroll 1
+            for (int q = 0; q < NW && alive; q++) {
+                uint64_t m = s_reach[w][q];
+                m = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(m >> 32)) << 32) |
+                    (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)m);
+                auto next = [&]() {
+                    const int b = __builtin_ctzll(m);
+                    m &= m - 1;
+                    return 64 * q + b;
+                };
+                int left = __popcll(m);
+#pragma unroll 1
+                for (; left >= kFwdGroup && alive; left -= kFwdGroup) {
+                    int j[kFwdGroup];
+#pragma unroll
+                    for (int i = 0; i < kFwdGroup; i++) j[i] = next();
+                    eval(std::integral_constant<int, kFwdGroup>{}, j);
+                }
+#pragma unroll 1
+                for (; left > 0 && alive; left--) {
+                    const int j[1] = {next()};
+                    eval(std::integral_constant<int, 1>{}, j);
+                }
             }
-            if (j + 1 == cnt) eval(j);
-            live = fpy == fpy;
-            took = __builtin_amdgcn_ballot_w64(last > eb);
         }
-        const uint64_t alive = __builtin_amdgcn_ballot_w64(live);
+        const uint64_t took = __builtin_amdgcn_ballot_w64(last > eb);
         if (lane == 0) {
             s_live[w] = alive != 0ull;
             s_took[w] = took != 0ull;

@@ -1,0 +1,98 @@
+"""GPU tests of the blend's quadrants: each wave of a tile's workgroup
+evaluates only the entries that can reach its 8 x 8 pixels, so a scene where
+that test could go wrong (thin, tiny, faint and ill-conditioned Gaussians,
+ragged images) is compared with every Gaussian evaluated at every pixel of its
+box: by the oracle, and from the render's own records."""
+import numpy as np
+import pytest
+
+from oracle import raster as orc
+from paper_2403_01444_amd import synth
+from parity import check_grads, check_image
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def scene(kind, n, seed):
+    g = synth.make_gaussians(n, 1, seed)
+    rng = np.random.default_rng(seed + 1)
+    if kind == "thin":            # needles of every direction, aspect up to e^4
+        g.log_scales = rng.choice(np.array([-5.5, -4.0, -1.5], np.float32), size=(n, 3)).astype(np.float32)
+    elif kind == "tiny":          # below a pixel: the low-pass alone decides the footprint
+        g.log_scales -= np.float32(4.0)
+        g.opacity_logits += np.float32(3.0)
+    elif kind == "faint":         # opacities around and below 1/255
+        g.opacity_logits = rng.normal(-5.5, 0.5, n).astype(np.float32)
+    elif kind == "long":          # covariances of condition 1e5 and more: the box alone decides
+        g.log_scales[:, 0] = 0.5
+        g.log_scales[:, 1:] = -7.0
+    return g
+
+
+def blend_records(key, box, rec, width, height, bg):
+    """Eq. 4 from a render's per-Gaussian records: the exponent in single
+    precision in the decision procedure's order, the rest in double.  Returns
+    the image, the transmittance and the pixels where a decision (opacity
+    1/255, the stop at 1e-4) lies within 1e-5 of its threshold."""
+    f = np.float32
+    img, T = np.zeros((3, height, width)), np.ones((height, width))
+    live, near = np.ones((height, width), bool), np.zeros((height, width), bool)
+    order = np.argsort(key, kind="stable")
+    for i in order[: int((key != 0xFFFFFFFF).sum())]:
+        x0, y0, x1, y1 = box[i]
+        u, v, A, B, C, op = rec[i, :6]
+        sl = np.s_[y0:y1 + 1, x0:x1 + 1]
+        dx, dy = np.arange(x0, x1 + 1).astype(f)[None] - u, np.arange(y0, y1 + 1).astype(f)[:, None] - v
+        power = f(-0.5) * ((A * dx) * dx + (C * dy) * dy) - (B * dx) * dy
+        raw = float(op) * np.exp(power.astype(np.float64))
+        ok = (power <= 0) & (raw >= 1 / 255) & live[sl]
+        alpha = np.where(ok, np.minimum(raw, 0.99), 0.0)
+        Tn = T[sl] * (1 - alpha)
+        near[sl] |= live[sl] & (power <= 0) & (np.abs(raw * 255 - 1) < 1e-5)
+        near[sl] |= ok & (np.abs(Tn - 1e-4) < 1e-5 * 1e-4 * 100)
+        stop = ok & (Tn < 1e-4)
+        live[sl] &= ~stop
+        w = np.where(ok & ~stop, alpha * T[sl], 0.0)
+        img[(slice(None),) + sl] += w[None] * rec[i, 6:9].astype(np.float64)[:, None, None]
+        T[sl] = np.where(ok & ~stop, Tn, T[sl])
+    return img + T[None] * np.asarray(bg, np.float64)[:, None, None], T, near
+
+
+@pytest.mark.parametrize("kind,n,width,height", [("thin", 3000, 97, 61), ("tiny", 4000, 64, 64), ("faint", 1500, 50, 37),
+                                                 ("long", 400, 120, 90), ("usual", 1200, 33, 17)])
+def test_quadrants_take_every_contributor(kind, n, width, height):
+    from paper_2403_01444_amd import gs3
+    g = scene(kind, n, n)
+    cam = synth.look_at_camera(width, height, azimuth_deg=20.0, bg=(0.3, 0.1, 0.2))
+    # "long": single precision cannot project condition 1e5 to the oracle's
+    # bar, so only the blend of its records is compared
+    projected = kind != "long"
+    ref = orc.render(g, cam)
+    w = (np.random.default_rng(4).normal(size=(3, height, width)) / (3 * height * width)).astype(np.float32)
+    rb = orc.render_backward(g, cam, w.astype(np.float64))
+    gg = gs3.GaussiansGPU.from_host(g)
+    first = None
+    for mode, log2 in (("depth_first", 0), ("depth_first", 16), ("radix64", 0)):
+        ctx = gs3.Context(g.n, 1 << 20, width, height, sort_mode=mode, grad_record_log2=log2)
+        img = ctx.render(gg, cam).clone()
+        T, last = ctx.debug_pixels(cam)
+        if projected:
+            check_image(img, T, ref, f"{kind} {mode}")
+        if first is None:
+            key, box, rec = (t.cpu().numpy() for t in ctx.debug_gaussians(g.n))
+            want, wantT, near = blend_records(key.view(np.uint32), box, rec, width, height, cam.bg)
+            assert near.mean() < 0.05
+            # the repository's image bar; a contributor left out shows as up to 1/255
+            assert np.abs(img.cpu().numpy() - want)[:, ~near].max() <= 1e-4 * np.abs(want).max()
+            assert np.abs(T.cpu().numpy() - wantT)[~near].max() <= 1e-4
+            first = (img, T, last)
+        else:                     # the same contributors in the same order: bit for bit
+            for a, b in zip(first, (img, T, last)):
+                assert torch.equal(a, b)
+        grads = {"d_means": ctx.zeros(g.n, 3), "d_opacity_logits": ctx.zeros(g.n), "d_rgb": ctx.zeros(g.n, 3)}
+        ctx.render_backward(torch.from_numpy(w).cuda(), grads)
+        if projected:
+            check_grads(grads, rb, f"{kind} {mode}")
+        ctx.close()
