@@ -103,6 +103,7 @@ struct Slot {
     // supers' lists of the depth-first binning (without gradient records):
     // ids are vals[0]; the walked blocks the forward keeps for the backward
     SuperDev sup{};
+    uint64_t* taken = nullptr;       // bit per walked entry and tile quadrant: a pixel there took it
     int* sorder = nullptr;           // supers, longest list first
     bool super = false;              // the last render binned into supers
     bool valid = false;
@@ -248,13 +249,15 @@ gs3_status gs3_create(const gs3_config* cfg, gs3_ctx** out) {
         if (ok && supers) {
             SuperDev& u = s.sup;
             const int64_t blocks = PK / kWalkBlock + c->max_tiles;
-            ok = c->alloc(&u.masks, PK) && c->alloc(&u.start, nsuper) && c->alloc(&u.len, nsuper) &&
+            ok = c->alloc(&s.taken, blocks * (kWalkBlock / 64) * 4) &&
+                 c->alloc(&u.masks, PK) && c->alloc(&u.start, nsuper) && c->alloc(&u.len, nsuper) &&
                  c->alloc(&u.walked, blocks * kWalkBlock) && c->alloc(&u.prev, blocks) &&
                  c->alloc(&u.tile_blk, c->max_tiles) && c->alloc(&u.pool, 1) && c->alloc(&s.sorder, nsuper);
             u.ids = s.vals[0];
             u.cap = (uint32_t)PK;
             u.max_blocks = (uint32_t)blocks;
         }
+        if (ok && !supers) ok = c->alloc(&s.taken, (PK / 64 + c->max_tiles + 1) * 4);
     }
     const int64_t sort_items = cfg->sort_mode == GS3_SORT_RADIX64 ? std::max(N, PK) : N;
     const int64_t hist_words = radix_hist_words(sort_items);
@@ -750,7 +753,7 @@ gs3_status gs3_render(gs3_ctx* c, int32_t slot, const gs3_gaussians* g, const fl
     }
     if (!sl.super) tile_order(L, sl.ranges, nullptr, ntiles, sl.order_fwd);
     blend_forward(L, cd, sl.ranges, sl.vals[sl.cur], sl.rec, image, sl.T_final, sl.last, sl.tile_walk,
-                  sl.super ? sl.sorder : sl.order_fwd, sl.super ? &sl.sup : nullptr);
+                  sl.super ? sl.sorder : sl.order_fwd, sl.taken, sl.super ? &sl.sup : nullptr);
     gs3_status st = c->check_launch("render");
     if (st != GS3_OK) return st;
     sl.g = gd;
@@ -776,7 +779,7 @@ gs3_status gs3_render_backward(gs3_ctx* c, int32_t slot, const float* d_image, c
     ga.cap = (uint64_t)c->cfg.max_pairs;
     tile_order(L, sl.ranges, sl.tile_walk, ntiles, sl.order_bwd);
     blend_backward(L, sl.cam, sl.ranges, sl.vals[sl.cur], sl.rec, d_image, sl.T_final, sl.last, ga, c->accum,
-                   out->d_opacity != nullptr || out->d_opacity_logits != nullptr, sl.order_bwd,
+                   out->d_opacity != nullptr || out->d_opacity_logits != nullptr, sl.order_bwd, sl.taken,
                    sl.super ? &sl.sup : nullptr);
     GradsDev gd;
     gd.d_means = out->d_means; gd.d_quats = out->d_quats; gd.d_log_scales = out->d_log_scales;

@@ -159,14 +159,18 @@ void super_pairs(const Launch& L, const SuperDev& sd, int tiles_x, int tiles_y, 
 void tile_order(const Launch& L, const uint2* ranges, const uint32_t* walk, int ntiles, int* order);
 // supers: the supers' lists (order then maps places to supers), or NULL for a
 // tile-major list read through ranges (order maps workgroups to tiles).
-// `order` is optional.
+// `order` is optional.  taken: for every 64 entries of a tile's list four
+// words, one per quadrant of the tile (quad_x), with a bit for each entry a
+// pixel of the quadrant took; at the walked blocks' places (kWalkBlock / 64
+// each), or at taken_word of a tile-major list.  The words up to the tile's
+// last contributor are written.
 void blend_forward(const Launch& L, const CamDev& cam, const uint2* ranges, const uint32_t* vals, const float4* rec,
-                   float* image, float* T_final, uint32_t* last, uint32_t* tile_walk, const int* order,
+                   float* image, float* T_final, uint32_t* last, uint32_t* tile_walk, const int* order, uint64_t* taken,
                    const SuperDev* supers);
 // supers: walk the blocks the forward kept, or NULL for the tile-major list
 void blend_backward(const Launch& L, const CamDev& cam, const uint2* ranges, const uint32_t* vals,
                     const float4* rec, const float* d_image, const float* T_final, const uint32_t* last,
-                    const GatherDev& ga, float* accum, bool want_opacity, const int* order, const SuperDev* supers);
+                    const GatherDev& ga, float* accum, bool want_opacity, const int* order, const uint64_t* taken, const SuperDev* supers);
 
 struct GradsDev {
     float *d_means, *d_quats, *d_log_scales, *d_opac, *d_sh, *d_dmu, *d_dq;

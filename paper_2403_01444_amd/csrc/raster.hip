@@ -462,7 +462,8 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
                                                              const float4* __restrict__ rec, float* __restrict__ image,
                                                              float* __restrict__ T_final, uint32_t* __restrict__ last_out,
                                                              uint32_t* __restrict__ tile_walk,
-                                                             const int* __restrict__ order, SuperDev sd, int nsuper) {
+                                                             const int* __restrict__ order,
+                                                             uint64_t* __restrict__ taken, SuperDev sd, int nsuper) {
     constexpr int NT = kBlendThreads, NW = NT / 64;
     static_assert(kWalkBlock == NT, "a walked block holds one batch");
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -492,7 +493,8 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
     __shared__ uint32_t s_q[kSuper ? 2 * NT : 1];   // queue of indices
     __shared__ uint32_t s_n[2][NW];                 // entries each wave adds to it
     __shared__ uint64_t s_reach[NW][NW];            // [quadrant][word]: staged entries that can reach its pixels
-    __shared__ uint32_t s_live[NW], s_took[NW], s_blk;
+    __shared__ uint64_t s_taken[NW][NW];            // [word][quadrant]: entries a pixel of the quadrant took
+    __shared__ uint32_t s_live[NW], s_blk;           // bit 0: pixels left, bit 1: took an entry of the batch
     const int tx0p = tx * kTile, ty0p = ty * kTile;
     // wave w: the 8 x 8 quadrant (w & 1, w >> 1) of the tile
     const int lx = quad_x(w, lane), ly = quad_y(w, lane);
@@ -523,10 +525,11 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
         c = rg.x;
         cend = rg.y;
     }
-    uint32_t blk = (uint32_t)tile, lastblk = (uint32_t)tile;   // walked blocks (thread 0 tracks the last contributor's)
+    uint32_t blk = (uint32_t)tile, lastblk = (uint32_t)tile;   // walked blocks
     for (uint32_t eb = 0;;) {   // eb: entries staged so far
         uint32_t myid = 0u;
         uint32_t cnt_u;
+        int64_t word = 0;   // first word of the batch in `taken` (kSuper: the block's, known later)
         if (kSuper) {
             while (queued < (uint32_t)NT && c < cend) {
                 const bool on = (mk & tbit) != 0u && c + tid < cend;
@@ -555,6 +558,7 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
             if (c >= cend) break;
             cnt_u = min((uint32_t)NT, cend - c);
             if ((uint32_t)tid < cnt_u) myid = vals[c + tid];
+            word = taken_word(ranges[tile].x, tile) + (eb >> 6);
             c += cnt_u;
         }
         uint32_t reach = 0u;   // quadrants this thread's entry can reach
@@ -563,7 +567,7 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
             const float4 r2 = rec[3 * (int64_t)myid + 2];
             s_w0[tid] = r0;
             s_w1[tid] = r1;
-            s_w2[tid] = blend_stage_w2<false>(r0, r1, r2, tx0p, ty0p);
+            s_w2[tid] = blend_stage_w2(r2, tx0p, ty0p);
             reach = quads_reached(r0, r1, r2, tx0p, ty0p);
         }
 #pragma unroll
@@ -581,15 +585,15 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
             // answer is needed only after the evaluation
             if (tid == 0 && eb != 0u) blk = atomicAdd(sd.pool, 1u);
         }
-        const int cnt = (int)cnt_u;
-        if (alive) {
+        uint64_t tk = 0ull;   // the word's entries a pixel of the wave takes
+        {
             // branch-free per-pixel body over a group of entries: the
             // exponents and opacities of the group are independent of each
             // other, so their latencies overlap; only the transmittance
             // passes from entry to entry.  Every lane evaluates, lane masks
             // (wave-uniform) keep the state of pixels that do not take the
             // contribution.
-            auto eval = [&](auto G, const int* j) {
+            auto eval = [&](auto G, const int* j, int& tj) {
                 constexpr int kG = decltype(G)::value;
                 float power[kG], alpha[kG];
                 float4 w1[kG];
@@ -628,6 +632,8 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
                     const uint64_t ok = okm[i] & alive;   // a pixel may have stopped inside the group
                     const uint64_t stop = ok & __builtin_amdgcn_ballot_w64(Tn < 1e-4f);
                     const bool take = __builtin_amdgcn_inverse_ballot_w64(ok & ~stop);
+                    tj = (ok & ~stop) != 0ull ? j[i] & 63 : tj;
+                    set_bit(tk, tj);
                     alive &= ~stop;
                     const float wgt = take ? alpha[i] * T : 0.0f;
                     c0 += wgt * w1[i].z;
@@ -640,13 +646,15 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
             // the entries that can reach the wave's pixels, in order; the
             // wave leaves once all its pixels have stopped
 #pragma unroll 1
-            for (int q = 0; q < NW && alive; q++) {
-                uint64_t m = s_reach[w][q];
-                m = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(m >> 32)) << 32) |
-                    (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)m);
+            for (int q = 0; q < NW; q++) {
+                tk = 0ull;
+                uint64_t m = uniform64(alive ? s_reach[w][q] : 0ull);
+                // the last entry taken; until there is one, the first visited
+                // (a bit too many costs the backward a visit)
+                int tj = __builtin_ctzll(m | (1ull << 63));
                 auto next = [&]() {
                     const int b = __builtin_ctzll(m);
-                    m &= m - 1;
+                    clear_bit(m, b);
                     return 64 * q + b;
                 };
                 int left = __popcll(m);
@@ -655,33 +663,38 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
                     int j[kFwdGroup];
 #pragma unroll
                     for (int i = 0; i < kFwdGroup; i++) j[i] = next();
-                    eval(std::integral_constant<int, kFwdGroup>{}, j);
+                    eval(std::integral_constant<int, kFwdGroup>{}, j, tj);
                 }
 #pragma unroll 1
                 for (; left > 0 && alive; left--) {
                     const int j[1] = {next()};
-                    eval(std::integral_constant<int, 1>{}, j);
+                    eval(std::integral_constant<int, 1>{}, j, tj);
                 }
+                if (lane == 0) s_taken[q][w] = tk;
             }
         }
         const uint64_t took = __builtin_amdgcn_ballot_w64(last > eb);
-        if (lane == 0) {
-            s_live[w] = alive != 0ull;
-            s_took[w] = took != 0ull;
-        }
+        if (lane == 0) s_live[w] = (alive != 0ull ? 1u : 0u) | (took != 0ull ? 2u : 0u);
         if (kSuper && tid == 0) {
             if (blk >= sd.max_blocks) blk = 0xFFFFFFFFu;   // only when the pairs overflowed
             if (eb != 0u && blk != 0xFFFFFFFFu) sd.prev[blk] = s_blk;
             s_blk = blk;
         }
         __syncthreads();
+        bool keep = true;   // the batch's taken bits have a place
         if (kSuper) {
             const uint32_t b = s_blk;
-            if ((uint32_t)tid < cnt_u && b != 0xFFFFFFFFu) sd.walked[(int64_t)b * kWalkBlock + tid] = myid;
-            if (s_took[0] | s_took[1] | s_took[2] | s_took[3]) lastblk = b;
+            keep = b != 0xFFFFFFFFu;
+            if ((uint32_t)tid < cnt_u && keep) sd.walked[(int64_t)b * kWalkBlock + tid] = myid;
+            word = (int64_t)b * (kWalkBlock / 64);
         }
+        // a tile-major list's words past the tile's last entry are another tile's
+        if (keep && tid < NW * NW && 64u * (tid / NW) < cnt_u)
+            taken[(word + tid / NW) * NW + tid % NW] = s_taken[tid / NW][tid % NW];
+        const uint32_t state = s_live[0] | s_live[1] | s_live[2] | s_live[3];
+        if (kSuper && (state & 2u)) lastblk = s_blk;   // the last contributor's so far
         eb += cnt_u;
-        if (!(s_live[0] | s_live[1] | s_live[2] | s_live[3])) break;
+        if (!(state & 1u)) break;
     }
     const int64_t P = (int64_t)cam.W * cam.H;
     if (px < cam.W && py < cam.H) {
@@ -708,8 +721,20 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
 // blend backward: walk the tile list from the last contributor of any pixel
 // down to the first, recover T_i = T_{i+1} / (1 - alpha_i), keep the colour
 // accumulated behind each contributor, sum each Gaussian's nine gradient
-// terms over a thread's R pixels, then across the wave (reduce-scatter) and
-// the tile's waves in LDS, before one global atomic per term and tile.
+// terms over a wave's pixels (reduce-scatter), then over the tile's waves in
+// LDS, before one global atomic per term and tile.
+//
+// Bound by VALU issue on large views.  Each wave has the forward's 8 x 8
+// quadrant and visits exactly the entries of which the forward noted that a
+// pixel of the quadrant took them (`taken`, a bit per entry and quadrant), so
+// next to no visit is in vain; kBwdGroup entries are evaluated together
+// (their exponents, opacities and reciprocals do not depend on each other;
+// the transmittance and the colour behind pass from entry to entry).  Four
+// together gain 2-3% where one wave has a SIMD to itself and lose 1-2% on the
+// large views.  Per launch, 16 x 4 pixels with per-wave box tests -> this:
+// 300K uniform at 1352 x 1014 259 -> 214 us, 1M at 1920 x 1080 442 -> 355,
+// 502K surfaces (opacity too) 444 -> 297, 50K surfaces at 256 x 256 619 ->
+// 331, 2K at 64 x 64 161 -> 95 us.
 // ---------------------------------------------------------------------------
 // kRecords: write each walked entry's nine sums to the compact record buffer
 // (fixed summation order; gathered per Gaussian by the preprocess backward),
@@ -717,229 +742,219 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
 // (tile, Gaussian).  kOpacity: also reduce the opacity term.
 // factors of the nine reduced terms: the conic terms are summed as dx^2,
 // dx dy and dy^2 (powers of two: the scaling is exact)
-#ifndef GS3_BWD_BATCH
-#define GS3_BWD_BATCH 128
-#endif
-constexpr int kBwdBatch = GS3_BWD_BATCH;   // backward blend: entries staged per batch (LDS: about 200 B each)
+constexpr int kBwdBatch = 128;   // entries staged per batch (LDS: about 200 B each)
+constexpr int kBwdGroup = 2;     // entries evaluated and reduced together
+static_assert(kBwdGroup % 2 == 0, "entries are reduced two at a time");
 __constant__ float kConicScale[9] = {1.f, 1.f, -0.5f, -1.f, -0.5f, 1.f, 1.f, 1.f, 1.f};
 
-template <int R, bool kSuper, bool kRecords, bool kOpacity>
-__global__ __launch_bounds__(kTile * kTile / R) void k_blend_bwd(CamDev cam, int ntiles,
-                                                                 const uint2* __restrict__ ranges,
-                                                                 const uint32_t* __restrict__ vals,
-                                                                 const float4* __restrict__ rec,
-                                                                 const float* __restrict__ d_image,
-                                                                 const float* __restrict__ T_final,
-                                                                 const uint32_t* __restrict__ last_in,
-                                                                 const uint32_t* __restrict__ tile_walk,
-                                                                 const uint32_t* __restrict__ walk_off,
-                                                                 float* __restrict__ grec, uint32_t grec_cap,
-                                                                 float* __restrict__ accum,
-                                                                 const int* __restrict__ order, SuperDev sd) {
-    constexpr int NT = kTile * kTile / R, NW = NT / 64;
-    constexpr int KB = kBwdBatch < NT ? kBwdBatch : NT;   // entries staged per batch
-    static_assert(KB <= 128, "the wave entry masks hold two words");
+template <bool kSuper, bool kRecords, bool kOpacity>
+__global__ __launch_bounds__(kBlendThreads) void k_blend_bwd(CamDev cam, int ntiles, const uint2* __restrict__ ranges,
+                                                             const uint32_t* __restrict__ vals,
+                                                             const float4* __restrict__ rec,
+                                                             const float* __restrict__ d_image,
+                                                             const float* __restrict__ T_final,
+                                                             const uint32_t* __restrict__ last_in,
+                                                             const uint32_t* __restrict__ tile_walk,
+                                                             const uint32_t* __restrict__ walk_off,
+                                                             float* __restrict__ grec, uint32_t grec_cap,
+                                                             float* __restrict__ accum, const int* __restrict__ order,
+                                                             const uint64_t* __restrict__ taken, SuperDev sd) {
+    constexpr int NT = kBlendThreads, NW = NT / 64;
+    constexpr int KB = kBwdBatch;
+    static_assert(KB == 128, "two mask words per batch");
+    static_assert(kWalkBlock % KB == 0, "a batch lies in one walked block");
     __shared__ float4 s_w0[KB];
     __shared__ float4 s_w1[KB];
     __shared__ float4 s_w2[KB];   // blend_stage_w2 form
     __shared__ uint32_t s_id[KB];
+    __shared__ uint64_t s_taken[2][NW];    // the batch's taken bits, [word][quadrant]
     __shared__ float s_g[NW][9][KB + 1];   // per-wave sums, [wave][term][entry] (padded: term rows on distinct banks)
     const int tile = order ? order[blockIdx.x] : tile_of_block(blockIdx.x, ntiles);
     if (tile >= ntiles) return;
     const uint32_t maxlast = tile_walk[tile];
     if (maxlast == 0) return;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
     const int tx0p = tx * kTile, ty0p = ty * kTile;
-    const int px = tx0p + (threadIdx.x & 15), py0 = ty0p + (threadIdx.x >> 4) * R;
-    const float fpx = (float)px;
-    uint32_t sel[R];   // this thread's column and row bits in the box masks
-#pragma unroll
-    for (int k = 0; k < R; k++) sel[k] = (1u << (threadIdx.x & 15)) | (1u << (16 + (threadIdx.x >> 4) * R + k));
+    const int lx = quad_x(w, lane), ly = quad_y(w, lane);
+    const int px = tx0p + lx, py = ty0p + ly;
+    const float fpx = (float)px, fpy = (float)py;
+    const uint32_t sel = (1u << lx) | (1u << (16 + ly));   // column and row bits in the box masks
     // kSuper: the block holding the batch (the forward's tile_blk, then prev)
     const uint32_t start = kSuper ? 0u : ranges[tile].x;
     uint32_t blk = kSuper ? sd.tile_blk[tile] : 0u;
-    static_assert(kWalkBlock % KB == 0, "a batch lies in one walked block");
     const uint32_t woff = kRecords ? walk_off[tile] : 0u;
     const int64_t P = (int64_t)cam.W * cam.H;
     // gb: dL/dC . (colour behind the current contributor), the only use of
     // that colour (dL/dalpha_i = T_i (dL/dC . c_i - gb)); it starts at the
     // background and moves to alpha c + (1 - alpha) b past each contributor
-    float T[R], g0[R], g1[R], g2[R], gb[R];
-    uint32_t last[R];
-#pragma unroll
-    for (int k = 0; k < R; k++) {
-        T[k] = 1.0f;
-        last[k] = 0u;
-        g0[k] = g1[k] = g2[k] = 0.f;
-        if (px < cam.W && py0 + k < cam.H) {
-            const int64_t p = (int64_t)(py0 + k) * cam.W + px;
-            T[k] = T_final[p];
-            last[k] = last_in[p];
-            g0[k] = d_image[p];
-            g1[k] = d_image[P + p];
-            g2[k] = d_image[2 * P + p];
-        }
-        gb[k] = g0[k] * cam.bg[0] + g1[k] * cam.bg[1] + g2[k] * cam.bg[2];
+    float T = 1.0f, g0 = 0.f, g1 = 0.f, g2 = 0.f;
+    uint32_t last = 0u;
+    if (px < cam.W && py < cam.H) {
+        const int64_t p = (int64_t)py * cam.W + px;
+        T = T_final[p];
+        last = last_in[p];
+        g0 = d_image[p];
+        g1 = d_image[P + p];
+        g2 = d_image[2 * P + p];
     }
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    float gb = g0 * cam.bg[0] + g1 * cam.bg[1] + g2 * cam.bg[2];
     // reduce-scatter terms: the image-space mean terms summed as dp dx and
     // dp dy (the conic is applied to the sums per entry), the conic terms,
     // r, g, b; lane group (lane >> 3) holds term (lane >> 3)
     const int my_term = lane >> 3;
-    // the wave's last contributor: entries past it reach none of its pixels
-    uint32_t wlast = 0u;
-#pragma unroll
-    for (int k = 0; k < R; k++) wlast = max(wlast, last[k]);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) wlast = max(wlast, (uint32_t)__shfl_xor((int)wlast, off));
-    wlast = __builtin_amdgcn_readfirstlane(wlast);
-    const uint32_t wrows = wave_row_bits<R>(wv);
     const int my_slot = my_term < 5 ? my_term : my_term + 1;   // index in the nine-term layout
     for (int64_t jb = ((int64_t)(maxlast - 1) / KB) * KB; jb >= 0; jb -= KB) {
-        const uint32_t e = (uint32_t)jb + threadIdx.x;
-        if ((int)threadIdx.x < KB && e < maxlast) {
+        const uint32_t e = (uint32_t)jb + tid;
+        if (tid < KB && e < maxlast) {
             const uint32_t id = kSuper ? sd.walked[(int64_t)blk * kWalkBlock + (e % kWalkBlock)] : vals[start + e];
             const float4 r0 = rec[3 * (int64_t)id + 0], r1 = rec[3 * (int64_t)id + 1];
-            s_id[threadIdx.x] = id;
-            s_w0[threadIdx.x] = r0;
-            s_w1[threadIdx.x] = r1;
-            s_w2[threadIdx.x] = blend_stage_w2(r0, r1, rec[3 * (int64_t)id + 2], tx0p, ty0p);
+            s_id[tid] = id;
+            s_w0[tid] = r0;
+            s_w1[tid] = r1;
+            s_w2[tid] = blend_stage_w2(rec[3 * (int64_t)id + 2], tx0p, ty0p);
         }
+        if (tid >= KB && tid < KB + 2 * NW) {
+            const int t = tid - KB, wd = t / NW;
+            const int64_t word = (kSuper ? (int64_t)blk * (kWalkBlock / 64) + ((jb % kWalkBlock) >> 6)
+                                         : taken_word(start, tile) + (jb >> 6)) + wd;
+            s_taken[wd][t % NW] = (uint32_t)jb + 64u * wd < maxlast ? taken[word * NW + t % NW] : 0ull;
+        }
+        if (kSuper && jb > 0 && jb % kWalkBlock == 0) blk = sd.prev[blk];
         __syncthreads();
         const int cnt = (int)min((int64_t)KB, (int64_t)maxlast - jb);
-        // the staged entries that can reach a pixel of this wave: box on its
-        // rows, before its last contributor (bit j % 64 of wm0 for j < 64,
-        // of wm1 above)
-        auto bword = [&](int q) -> uint64_t {
-            const int jq = 64 * q + lane;
-            return __builtin_amdgcn_ballot_w64(jq < cnt && (uint32_t)jb + (uint32_t)jq < wlast &&
-                                               box_meets_rows(s_w2[jq].w, wrows));
-        };
-        const uint64_t wm0 = bword(0), wm1 = KB > 64 ? bword(1) : 0ull;
-        // one entry: this thread's R pixels walk back past entry j (their
-        // transmittance and behind-colour state), and gr receives the eight
-        // terms summed over them; returns whether any pixel of the wave
-        // takes the entry (gr and gop are left unset when none does)
-        auto entry = [&](int j, float gr[8], float& gop) -> bool {
-            const uint32_t ej = (uint32_t)jb + (uint32_t)j;
-            gop = 0.f;
-            {
-                const uint64_t mw = (j >> 6) == 0 ? wm0 : wm1;
-                if (!((mw >> (j & 63)) & 1ull)) return false;
-            }
-            uint64_t act = 0ull;
-            const float4 w0 = s_w0[j], w1 = s_w1[j], w2 = s_w2[j];
-            const uint32_t box = __float_as_uint(w2.w);
-            const float cr = w1.z, cg = w1.w, cb = w2.x;
-            const float dx = fpx - w0.x;
-            float adx2, bdx;
-            blend_dx_terms(dx, w0, adx2, bdx);
-            float power[R], dy[R];
-            // lane masks (wave-uniform): okm[k] the lanes whose pixel k takes
-            // the entry, bm[k] those whose exponent lies in the band where
-            // the exact test decides
-            uint64_t okm[R], bm[R];
-            uint64_t any_band = 0ull;
+        // kG entries, last first: this thread's pixel walks back past them
+        // (its transmittance and behind-colour state), and their eight terms
+        // are summed over the wave
+        auto walk = [&](auto G, const int* j) {
+            constexpr int kG = decltype(G)::value;
+            float power[kG], dx[kG], dy[kG], G_[kG], raw[kG], inv[kG], cb[kG];
+            float4 w1[kG];
+            // lane masks (wave-uniform): okm the lanes whose pixel takes the
+            // entry, bm those whose exponent lies in the band where the exact
+            // test decides
+            uint64_t okm[kG], bm[kG], band = 0ull;
 #pragma unroll
-            for (int k = 0; k < R; k++) {
-                dy[k] = (float)(py0 + k) - w0.y;
-                power[k] = blend_power(adx2, bdx, dy[k], w1.x);
-                const uint64_t pm =
-                    __builtin_amdgcn_ballot_w64(ej < last[k]) & __builtin_amdgcn_ballot_w64((box & sel[k]) == sel[k]) &
-                    __builtin_amdgcn_ballot_w64(power[k] <= 0.0f) & __builtin_amdgcn_ballot_w64(power[k] >= w2.y);
-                bm[k] = pm & __builtin_amdgcn_ballot_w64(power[k] < w2.z);
-                okm[k] = pm & ~bm[k];
-                any_band |= bm[k];
+            for (int i = 0; i < kG; i++) {
+                const float4 w0 = s_w0[j[i]], w2 = s_w2[j[i]];
+                w1[i] = s_w1[j[i]];
+                cb[i] = w2.x;
+                const uint32_t box = __float_as_uint(w2.w);
+                dx[i] = fpx - w0.x;
+                dy[i] = fpy - w0.y;
+                float adx2, bdx;
+                blend_dx_terms(dx[i], w0, adx2, bdx);
+                power[i] = blend_power(adx2, bdx, dy[i], w1[i].x);
+                const uint64_t pm = __builtin_amdgcn_ballot_w64((uint32_t)jb + (uint32_t)j[i] < last) &
+                                    __builtin_amdgcn_ballot_w64((box & sel) == sel) &
+                                    __builtin_amdgcn_ballot_w64(power[i] <= 0.0f) &
+                                    __builtin_amdgcn_ballot_w64(power[i] >= w2.y);
+                bm[i] = pm & __builtin_amdgcn_ballot_w64(power[i] < w2.z);
+                okm[i] = pm & ~bm[i];
+                band |= bm[i];
             }
-            if (any_band) {
+            if (band) {
 #pragma unroll
-                for (int k = 0; k < R; k++)
-                    okm[k] |= bm[k] & __builtin_amdgcn_ballot_w64(blend_exact_test(power[k], w1.y));
+                for (int i = 0; i < kG; i++)
+                    okm[i] |= bm[i] & __builtin_amdgcn_ballot_w64(blend_exact_test(power[i], w1[i].y));
             }
 #pragma unroll
-            for (int k = 0; k < R; k++) act |= okm[k];
-            // no pixel of the wave takes the entry: its state and sums stay
-            if (!act) return false;
-            // branch-free per-pixel body: selects keep the state of pixels
-            // that this Gaussian does not reach
-            bool ok[R];
-#pragma unroll
-            for (int k = 0; k < R; k++) ok[k] = __builtin_amdgcn_inverse_ballot_w64(okm[k]);
-#pragma unroll
-            for (int k = 0; k < R; k++) {
-                const float G = __expf(power[k]);
-                const float raw = w1.y * G;
-                const float alpha = fminf(0.99f, raw);
+            for (int i = 0; i < kG; i++) {
+                G_[i] = __expf(power[i]);
+                raw[i] = w1[i].y * G_[i];
                 // T recovery T_i = T_{i+1} / (1 - alpha_i), with the hardware reciprocal (1 ulp)
-                const float Tk = ok[k] ? T[k] * __builtin_amdgcn_rcpf(1.0f - alpha) : T[k];
-                T[k] = Tk;
-                const float aok = ok[k] ? alpha : 0.0f;   // zero: the pixel's state is kept
-                const float wgt = aok * Tk;
-                const float e = (g0[k] * cr + g1[k] * cg + g2[k] * cb) - gb[k];
-                const float dal = Tk * e;
-                gb[k] += aok * e;
-                const bool unclamped = ok[k] && raw < 0.99f;
-                const float dp = unclamped ? dal * raw : 0.0f;
-                gop += unclamped ? dal * G : 0.0f;
+                inv[i] = __builtin_amdgcn_rcpf(1.0f - fminf(0.99f, raw[i]));
+            }
+            float gr[kG][8], gop[kG];
+#pragma unroll
+            for (int i = 0; i < kG; i++) {
+                // branch-free: selects keep the state of pixels that this
+                // Gaussian does not reach
+                const bool ok = __builtin_amdgcn_inverse_ballot_w64(okm[i]);
+                T = ok ? T * inv[i] : T;
+                const float aok = ok ? fminf(0.99f, raw[i]) : 0.0f;   // zero: the pixel's state is kept
+                const float wgt = aok * T;
+                const float d = (g0 * w1[i].z + g1 * w1[i].w + g2 * cb[i]) - gb;
+                const float dal = T * d;
+                gb += aok * d;
+                const bool unclamped =
+                    __builtin_amdgcn_inverse_ballot_w64(okm[i] & __builtin_amdgcn_ballot_w64(raw[i] < 0.99f));
+                const float dp = unclamped ? dal * raw[i] : 0.0f;
+                gop[i] = unclamped ? dal * G_[i] : 0.0f;
                 // d power / d(u, v) = (A dx + B dy, B dx + C dy): the sums of
                 // dp dx and dp dy take A, B, C after the reduction; the conic
                 // terms -dx^2 / 2, -dx dy, -dy^2 / 2 get their constant
                 // factors there too (kConicScale)
-                const float tx = dp * dx, ty = dp * dy[k];
-                const float t8[8] = {tx, ty, tx * dx, tx * dy[k], ty * dy[k], g0[k] * wgt, g1[k] * wgt, g2[k] * wgt};
-#pragma unroll
-                for (int c = 0; c < 8; c++) gr[c] = k == 0 ? t8[c] : gr[c] + t8[c];
+                const float ax = dp * dx[i], ay = dp * dy[i];
+                gr[i][0] = ax;
+                gr[i][1] = ay;
+                gr[i][2] = ax * dx[i];
+                gr[i][3] = ax * dy[i];
+                gr[i][4] = ay * dy[i];
+                gr[i][5] = g0 * wgt;
+                gr[i][6] = g1 * wgt;
+                gr[i][7] = g2 * wgt;
             }
-            return act != 0ull;
-        };
-        // two entries per reduction: their exchanges and DPP chains overlap
-        int j = cnt - 1;
-        for (; j >= 1; j -= 2) {
-            float ga[8], gc[8], opa, opc;
-            const bool anya = entry(j, ga, opa);
-            const bool anyc = entry(j - 1, gc, opc);
-            float ra = 0.f, rc = 0.f;
-            if (anya && anyc)
-                wave_reduce_scatter8x2(ga, gc, lane, ra, rc);
-            else if (anya)
-                ra = wave_reduce_scatter8(ga, lane);
-            else if (anyc)
-                rc = wave_reduce_scatter8(gc, lane);
+            float red[kG];
+            if constexpr (kG == 1) {
+                red[0] = wave_reduce_scatter8(gr[0], lane);
+            } else {
+#pragma unroll
+                for (int i = 0; i < kG; i += 2) wave_reduce_scatter8x2(gr[i], gr[i + 1], lane, red[i], red[i + 1]);
+            }
             if ((lane & 7) == 0) {
-                s_g[wv][my_slot][j] = ra;
-                s_g[wv][my_slot][j - 1] = rc;
+#pragma unroll
+                for (int i = 0; i < kG; i++) s_g[w][my_slot][j[i]] = red[i];
             }
             if (kOpacity) {
-                const float oa = anya ? wave_sum_dpp(opa) : 0.f;
-                const float oc = anyc ? wave_sum_dpp(opc) : 0.f;
-                if (lane == 8) {
-                    s_g[wv][5][j] = oa;
-                    s_g[wv][5][j - 1] = oc;
+#pragma unroll
+                for (int i = 0; i < kG; i++) {
+                    const float o = wave_sum_dpp(gop[i]);
+                    if (lane == 8) s_g[w][5][j[i]] = o;
                 }
             }
-        }
-        if (j == 0) {
-            float ga[8], opa;
-            const bool any = entry(0, ga, opa);
-            float red = 0.f, redop = 0.f;
-            if (any) {
-                red = wave_reduce_scatter8(ga, lane);
-                if (kOpacity) redop = wave_sum_dpp(opa);
+        };
+#pragma unroll 1
+        for (int wd = 1; wd >= 0; wd--) {
+            uint64_t m = uniform64(s_taken[wd][w]);
+            auto next = [&]() {
+                const int b = 63 - __builtin_clzll(m);
+                clear_bit(m, b);
+                return 64 * wd + b;
+            };
+            int left = __popcll(m);
+#pragma unroll 1
+            for (; left >= kBwdGroup; left -= kBwdGroup) {
+                int j[kBwdGroup];
+#pragma unroll
+                for (int i = 0; i < kBwdGroup; i++) j[i] = next();
+                walk(std::integral_constant<int, kBwdGroup>{}, j);
             }
-            if ((lane & 7) == 0) s_g[wv][my_slot][0] = red;
-            if (kOpacity && lane == 8) s_g[wv][5][0] = redop;
+#pragma unroll 1
+            for (; left > 0; left--) {
+                const int j[1] = {next()};
+                walk(std::integral_constant<int, 1>{}, j);
+            }
         }
         __syncthreads();
-        // term k of entry e summed over the waves: the mean terms from the
-        // sums of dp dx and dp dy and the entry's conic (A, B, C)
-        auto entry_term = [&](int k, int e) -> float {
-            float v = s_g[0][k][e];
+        // term k of entry e summed over the waves that took it
+        auto over_waves = [&](int k, int e, uint32_t on) -> float {
+            float v = 0.f;
 #pragma unroll
-            for (int w = 1; w < NW; w++) v += s_g[w][k][e];
+            for (int q = 0; q < NW; q++) v += (on >> q) & 1u ? s_g[q][k][e] : 0.f;
+            return v;
+        };
+        auto taken_by = [&](int e) -> uint32_t {
+            uint32_t on = 0u;
+#pragma unroll
+            for (int q = 0; q < NW; q++) on |= (uint32_t)((s_taken[e >> 6][q] >> (e & 63)) & 1ull) << q;
+            return on;
+        };
+        // the mean terms from the sums of dp dx and dp dy and the entry's conic (A, B, C)
+        auto entry_term = [&](int k, int e, uint32_t on) -> float {
+            const float v = over_waves(k, e, on);
             if (k <= 1) {
-                float o = s_g[0][1 - k][e];
-#pragma unroll
-                for (int w = 1; w < NW; w++) o += s_g[w][1 - k][e];
+                const float o = over_waves(1 - k, e, on);
                 const float4 w0 = s_w0[e];
                 const float C = s_w1[e].x;
                 return k == 0 ? w0.z * v + w0.w * o : w0.w * o + C * v;
@@ -947,33 +962,35 @@ __global__ __launch_bounds__(kTile * kTile / R) void k_blend_bwd(CamDev cam, int
             return v * kConicScale[k];
         };
         if (kRecords) {
-            if ((int)threadIdx.x < cnt) {
-                const uint32_t widx = woff + (uint32_t)jb + threadIdx.x;   // compact index of this walked entry
+            if (tid < cnt) {
+                const uint32_t widx = woff + (uint32_t)jb + tid;   // compact index of this walked entry
                 const bool fits = widx < grec_cap;
+                const uint32_t on = taken_by(tid);
 #pragma unroll
                 for (int k = 0; k < 9; k++) {
                     if (!kOpacity && k == 5) {
                         if (fits) grec[(int64_t)k * grec_cap + widx] = 0.f;
                         continue;
                     }
-                    const float v = entry_term(k, threadIdx.x);
+                    const float v = entry_term(k, tid, on);
                     if (fits)
                         grec[(int64_t)k * grec_cap + widx] = v;
                     else if (v != 0.f)
-                        atomicAdd(accum + 9 * (int64_t)s_id[threadIdx.x] + k, v);
+                        atomicAdd(accum + 9 * (int64_t)s_id[tid] + k, v);
                 }
             }
         } else {
             // lane = (entry, term): the atomics of one entry's terms are
             // adjacent lanes on adjacent addresses (one or two cache lines)
-            for (int q = threadIdx.x; q < 9 * cnt; q += NT) {
+            for (int q = tid; q < 9 * cnt; q += NT) {
                 const int e = q / 9, k = q - 9 * e;
                 if (!kOpacity && k == 5) continue;
-                const float v = entry_term(k, e);
+                const uint32_t on = taken_by(e);
+                if (!on) continue;
+                const float v = entry_term(k, e, on);
                 if (v != 0.f) atomicAdd(accum + 9 * (int64_t)s_id[e] + k, v);
             }
         }
-        if (kSuper && jb > 0 && jb % kWalkBlock == 0) blk = sd.prev[blk];
         __syncthreads();
     }
 }
@@ -1302,7 +1319,7 @@ void tile_order(const Launch& L, const uint2* ranges, const uint32_t* walk, int 
 }
 
 void blend_forward(const Launch& L, const CamDev& cam, const uint2* ranges, const uint32_t* vals, const float4* rec,
-                   float* image, float* T_final, uint32_t* last, uint32_t* tile_walk, const int* order,
+                   float* image, float* T_final, uint32_t* last, uint32_t* tile_walk, const int* order, uint64_t* taken,
                    const SuperDev* supers) {
     const int ntiles = cam.tiles_x * cam.tiles_y;
     if (L.prof) L.prof->begin("blend_fwd", L.st);
@@ -1310,29 +1327,28 @@ void blend_forward(const Launch& L, const CamDev& cam, const uint2* ranges, cons
         const int nsuper = supers->supers_x * super_count_of(cam.tiles_y);
         const unsigned grid = (unsigned)((nsuper + 7) / 8 * 8 * kSuperDim * kSuperDim);
         hipLaunchKernelGGL((k_blend_fwd<true>), dim3(grid), dim3(kBlendThreads), 0, L.st, cam, ntiles, ranges, vals,
-                           rec, image, T_final, last, tile_walk, order, *supers, nsuper);
+                           rec, image, T_final, last, tile_walk, order, taken, *supers, nsuper);
     } else {
         hipLaunchKernelGGL((k_blend_fwd<false>), dim3(order ? (unsigned)ntiles : blend_grid(ntiles)),
                            dim3(kBlendThreads), 0, L.st, cam, ntiles, ranges, vals, rec, image, T_final, last,
-                           tile_walk, order, SuperDev{}, 0);
+                           tile_walk, order, taken, SuperDev{}, 0);
     }
     if (L.prof) L.prof->end(L.st);
 }
 
 void blend_backward(const Launch& L, const CamDev& cam, const uint2* ranges, const uint32_t* vals, const float4* rec,
                     const float* d_image, const float* T_final, const uint32_t* last, const GatherDev& ga,
-                    float* accum, bool want_opacity, const int* order, const SuperDev* supers) {
+                    float* accum, bool want_opacity, const int* order, const uint64_t* taken, const SuperDev* supers) {
     const int ntiles = cam.tiles_x * cam.tiles_y;
     if (L.prof) L.prof->begin("blend_bwd", L.st);
     const bool records = ga.grec_cap > 0;
-    constexpr int R = 1;
     // gradient records are kept with a tile-major list only
-    auto kern = supers ? (want_opacity ? k_blend_bwd<R, true, false, true> : k_blend_bwd<R, true, false, false>)
-                : records ? (want_opacity ? k_blend_bwd<R, false, true, true> : k_blend_bwd<R, false, true, false>)
-                          : (want_opacity ? k_blend_bwd<R, false, false, true> : k_blend_bwd<R, false, false, false>);
-    hipLaunchKernelGGL(kern, dim3(order ? (unsigned)ntiles : blend_grid(ntiles)), dim3(kTile * kTile / R), 0, L.st,
-                       cam, ntiles, ranges, vals, rec, d_image, T_final, last, ga.tile_walk, ga.walk_off, ga.grec,
-                       (uint32_t)ga.grec_cap, accum, order, supers ? *supers : SuperDev{});
+    auto kern = supers ? (want_opacity ? k_blend_bwd<true, false, true> : k_blend_bwd<true, false, false>)
+                : records ? (want_opacity ? k_blend_bwd<false, true, true> : k_blend_bwd<false, true, false>)
+                          : (want_opacity ? k_blend_bwd<false, false, true> : k_blend_bwd<false, false, false>);
+    hipLaunchKernelGGL(kern, dim3(order ? (unsigned)ntiles : blend_grid(ntiles)), dim3(kBlendThreads), 0, L.st, cam,
+                       ntiles, ranges, vals, rec, d_image, T_final, last, ga.tile_walk, ga.walk_off, ga.grec,
+                       (uint32_t)ga.grec_cap, accum, order, taken, supers ? *supers : SuperDev{});
     if (L.prof) L.prof->end(L.st);
 }
 
