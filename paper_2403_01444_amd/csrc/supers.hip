@@ -26,7 +26,7 @@ namespace gs3 {
 
 namespace {
 
-constexpr int kBigRect = 32;     // supers walked by one thread
+constexpr int kBigRect = 32;     // supers walked by one thread (16 or 64: 6% or 1% more render time at 1M Gaussians)
 constexpr int kSupBatch = 512;   // supers whose coverage bits the scatter holds at a time (32 KB of LDS)
 constexpr int kWords = kSuperChunk / 64;
 
@@ -51,17 +51,17 @@ __device__ __forceinline__ uint32_t tile_mask(uint2 r, int sx, int sy) {
     return (cols * 0x1111u) & rows;
 }
 
-// f(e, r, id, sx, sy) for every super of the rectangles of a wave's Gaussians
-// (e: position in the chunk, r: tile rectangle, id: index).
+// f(e, sx, sy) for every super of the rectangles of a wave's Gaussians (e:
+// position in the chunk, r: tile rectangle).
 template <class F>
-__device__ __forceinline__ void for_supers(uint2 r, int e, uint32_t id, int lane, F f) {
+__device__ __forceinline__ void for_supers(uint2 r, int e, int lane, F f) {
     const SRect q = super_rect(r);
     const int w = q.x1 - q.x0 + 1;
     const int cnt = empty_rect(r) ? 0 : w * (q.y1 - q.y0 + 1);
     if (cnt <= kBigRect) {
         int sx = q.x0, sy = q.y0;
         for (int k = 0; k < cnt; k++) {
-            f(e, r, id, sx, sy);
+            f(e, sx, sy);
             if (++sx > q.x1) {
                 sx = q.x0;
                 sy++;
@@ -72,13 +72,11 @@ __device__ __forceinline__ void for_supers(uint2 r, int e, uint32_t id, int lane
     while (big) {
         const int l = __builtin_ctzll(big);
         big &= big - 1;
-        const uint2 br = make_uint2((uint32_t)__builtin_amdgcn_readlane((int)r.x, l),
-                                    (uint32_t)__builtin_amdgcn_readlane((int)r.y, l));
-        const uint32_t bid = (uint32_t)__builtin_amdgcn_readlane((int)id, l);
+        const SRect b = super_rect(make_uint2((uint32_t)__builtin_amdgcn_readlane((int)r.x, l),
+                                              (uint32_t)__builtin_amdgcn_readlane((int)r.y, l)));
         const int be = __builtin_amdgcn_readlane(e, l);
-        const SRect b = super_rect(br);
         const int bw = b.x1 - b.x0 + 1, bc = bw * (b.y1 - b.y0 + 1);
-        for (int k = lane; k < bc; k += 64) f(be, br, bid, b.x0 + k % bw, b.y0 + k / bw);
+        for (int k = lane; k < bc; k += 64) f(be, b.x0 + k % bw, b.y0 + k / bw);
     }
 }
 
@@ -100,8 +98,7 @@ __global__ __launch_bounds__(kSuperChunk) void k_super_count(const uint32_t* __r
     }
     for (int s = threadIdx.x; s < nsuper; s += kSuperChunk) s_cnt[s] = 0u;
     __syncthreads();
-    for_supers(r, 0, 0u, lane,
-               [&](int, uint2, uint32_t, int sx, int sy) { atomicAdd(&s_cnt[sy * supers_x + sx], 1u); });
+    for_supers(r, 0, lane, [&](int, int sx, int sy) { atomicAdd(&s_cnt[sy * supers_x + sx], 1u); });
     uint64_t k = 0;
     if (!empty_rect(r))
         k = (uint64_t)((r.y & 0xFFFFu) - (r.x & 0xFFFFu) + 1u) * (uint64_t)((r.y >> 16) - (r.x >> 16) + 1u);
@@ -160,9 +157,18 @@ __global__ __launch_bounds__(256) void k_super_scan(uint32_t* __restrict__ hist,
 // Scatter of one chunk: entry (id, tile mask) of every super its Gaussians
 // meet, at the super's start + the entries of earlier chunks + the rank
 // among the chunk's Gaussians that meet the super (a bit per Gaussian in
-// LDS, the rank a popcount of the bits below).  The first chunk's workgroup
-// also writes the supers' starts, their longest-first order (sorder, when
-// set: scheduling only) and resets the walked-block counter *pool.
+// LDS, the rank a popcount of the bits below).  The entries are first put
+// in list order in LDS, kEntries at a time, so that consecutive lanes write
+// consecutive slots of a super's segment (a dozen or two entries): stored
+// straight from the Gaussian's thread every lane wrote to another segment,
+// and those requests bounded the kernel (1M Gaussians at 1920 x 1080, 18M
+// entries: 292 -> 129 us; 300K at 1352 x 1014: 49 -> 33 us; with under two
+// entries a Gaussian the detour costs 1-2 us).  What is left is the loops
+// over the supers of the widest Gaussian of each wave.  The first chunk's
+// workgroup also writes the supers' starts, their longest-first order
+// (sorder, when set: scheduling only) and resets the walked-block counter
+// *pool.
+constexpr int kEntries = 6144;   // with the other arrays two workgroups share a CU's LDS
 __global__ __launch_bounds__(kSuperChunk) void k_super_scatter(
     const uint32_t* __restrict__ order, int64_t n, const uint2* __restrict__ srect, int supers_x, int nsuper,
     int64_t nchunks, const uint32_t* __restrict__ hist, const uint32_t* __restrict__ len, uint32_t cap,
@@ -170,19 +176,25 @@ __global__ __launch_bounds__(kSuperChunk) void k_super_scatter(
     uint32_t* __restrict__ pool, uint32_t pool0) {
     __shared__ uint64_t s_cov[kSupBatch][kWords];
     __shared__ uint16_t s_pre[kSupBatch][kWords];
-    __shared__ uint32_t s_base[kSupBatch];
+    __shared__ uint32_t s_base[kSupBatch];   // first slot of this chunk's entries of the super
+    __shared__ uint32_t s_loc[kSupBatch];    // and their first place in the chunk's list
+    __shared__ uint32_t s_xy[kSupBatch];     // the super's column and row
+    __shared__ uint2 s_rect[kSuperChunk];
+    __shared__ uint32_t s_id[kSuperChunk];
+    __shared__ uint32_t s_ent[kEntries];     // chunk position | super << 16
     __shared__ uint64_t s_w[kSuperChunk / 64];
+    __shared__ uint32_t s_l[kSuperChunk / 64];
     static_assert(kSupBatch == kSuperChunk, "one thread per super of a batch");
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t g = (int64_t)blockIdx.x * kSuperChunk + threadIdx.x;
+    const int me = (int)threadIdx.x;
     uint2 r = make_uint2(1u, 0u);
-    uint32_t id = 0u;
     if (g < n) {
         r = srect[g];
-        id = order[g];
+        s_id[me] = order[g];
     }
+    s_rect[me] = r;
     if (blockIdx.x == 0 && threadIdx.x == 0) *pool = pool0;
-    const int me = (int)threadIdx.x;
     uint64_t carry = 0;
     for (int b0 = 0; b0 < nsuper; b0 += kSupBatch) {
         const int s = b0 + me;
@@ -196,6 +208,7 @@ __global__ __launch_bounds__(kSuperChunk) void k_super_scatter(
         if (lane == 63) s_w[w] = x;
 #pragma unroll
         for (int k = 0; k < kWords; k++) s_cov[me][k] = 0;
+        s_xy[me] = (uint32_t)(s % supers_x) | ((uint32_t)(s / supers_x) << 16);
         __syncthreads();
         uint64_t first = carry + x - v;
         for (int k = 0; k < kSuperChunk / 64; k++) {
@@ -208,7 +221,7 @@ __global__ __launch_bounds__(kSuperChunk) void k_super_scatter(
             if (blockIdx.x == 0) start[s] = first < (uint64_t)cap ? (uint32_t)first : cap;
         }
         uint32_t* cov32 = reinterpret_cast<uint32_t*>(&s_cov[0][0]);
-        for_supers(r, me, id, lane, [&](int e, uint2, uint32_t, int sx, int sy) {
+        for_supers(r, me, lane, [&](int e, int sx, int sy) {
             const int q = sy * supers_x + sx - b0;
             if (q >= 0 && q < kSupBatch) atomicOr(&cov32[q * (2 * kWords) + (e >> 5)], 1u << (e & 31));
         });
@@ -219,18 +232,36 @@ __global__ __launch_bounds__(kSuperChunk) void k_super_scatter(
             s_pre[me][k] = (uint16_t)run;
             run += (uint32_t)__popcll(s_cov[me][k]);
         }
+        const uint32_t lx = wave_incl_scan_u32(run);
+        if (lane == 63) s_l[w] = lx;
         __syncthreads();
-        for_supers(r, me, id, lane, [&](int e, uint2 er, uint32_t eid, int sx, int sy) {
-            const int q = sy * supers_x + sx - b0;
-            if (q < 0 || q >= kSupBatch) return;
-            const uint64_t below = s_cov[q][e >> 6] & ((1ull << (e & 63)) - 1ull);
-            // base <= cap < 2^31 and the rank is below kSuperChunk: no wrap
-            const uint32_t slot = s_base[q] + s_pre[q][e >> 6] + (uint32_t)__popcll(below);
-            if (slot < cap) {
-                ids[slot] = eid;
-                masks[slot] = (uint16_t)tile_mask(er, sx, sy);
+        uint32_t loc = lx - run, total = 0u;
+        for (int k = 0; k < kSuperChunk / 64; k++) {
+            if (k < w) loc += s_l[k];
+            total += s_l[k];
+        }
+        s_loc[me] = loc;
+        for (uint32_t w0 = 0; w0 < total; w0 += kEntries) {
+            __syncthreads();   // s_loc written; the previous round's entries are no longer read
+            for_supers(r, me, lane, [&](int e, int sx, int sy) {
+                const int q = sy * supers_x + sx - b0;
+                if (q < 0 || q >= kSupBatch) return;
+                const uint64_t below = s_cov[q][e >> 6] & ((1ull << (e & 63)) - 1ull);
+                const uint32_t at = s_loc[q] + s_pre[q][e >> 6] + (uint32_t)__popcll(below) - w0;
+                if (at < (uint32_t)kEntries) s_ent[at] = (uint32_t)e | ((uint32_t)q << 16);
+            });
+            __syncthreads();
+            const uint32_t m = min((uint32_t)kEntries, total - w0);
+            for (uint32_t i = me; i < m; i += kSuperChunk) {
+                const uint32_t t = s_ent[i], q = t >> 16, e = t & 0xFFFFu, xy = s_xy[q];
+                // base <= cap < 2^31 and the rank is below kSuperChunk: no wrap
+                const uint32_t slot = s_base[q] + (w0 + i - s_loc[q]);
+                if (slot < cap) {
+                    ids[slot] = s_id[e];
+                    masks[slot] = (uint16_t)tile_mask(s_rect[e], (int)(xy & 0xFFFFu), (int)(xy >> 16));
+                }
             }
-        });
+        }
         __syncthreads();   // the next batch of supers reuses the LDS arrays
     }
     if (blockIdx.x == 0 && sorder) {
