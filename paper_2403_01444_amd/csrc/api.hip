@@ -156,6 +156,7 @@ struct gs3_ctx {
     int step = 0;
     float* g_part = nullptr;
     int max_parts = 0;
+    float* scatter_denc = nullptr;   // encoding gradient of a backward on unprepared means
     double* warm_bsum = nullptr;
     // per-frame contribution lists of the table gradient
     void* enc_cache = nullptr;   // encoding of the prepared means from the last forward (n x 32)
@@ -320,7 +321,8 @@ gs3_status gs3_create(const gs3_config* cfg, gs3_ctx** out) {
         c->max_parts = 2 * cus;
         ok = c->alloc(&c->p, c->n_params) && c->alloc(&c->g, c->n_params) && c->alloc(&c->m, c->n_params) &&
              c->alloc(&c->v, c->n_params) && c->alloc((float**)&c->work, c->n_params) &&
-             c->alloc(&c->g_part, (int64_t)c->max_parts * ntc_mlp_params()) && c->alloc(&c->warm_bsum, (N + 255) / 256);
+             c->alloc(&c->g_part, (int64_t)c->max_parts * ntc_mlp_params()) &&
+             c->alloc(&c->scatter_denc, std::min<int64_t>(N, kScatterPoints) * 32) && c->alloc(&c->warm_bsum, (N + 255) / 256);
     }
     if (!ok) {
         gs3_destroy(c);
@@ -566,7 +568,7 @@ gs3_status gs3_ntc_backward(gs3_ctx* c, const float* means, int64_t n, uint64_t 
     const bool prepared = token != 0;
     ntc_backward(c->L(), c->cfg.ntc.precision, c->nd, table, mlp, means, n, d_dmu, d_dq, c->g,
                  c->g + c->n_table_floats, c->g_part, c->max_parts, prepared ? &c->csr : nullptr,
-                 prepared && c->enc_valid ? c->enc_cache : nullptr);
+                 c->scatter_denc, prepared && c->enc_valid ? c->enc_cache : nullptr);
     return c->check_launch("ntc_backward");
 }
 

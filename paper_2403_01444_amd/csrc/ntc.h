@@ -24,6 +24,9 @@ struct NtcCsr {
 };
 
 int ntc_mlp_params();
+// points whose encoding gradient a backward without preparation holds at a
+// time (32 MB of scratch)
+constexpr int64_t kScatterPoints = 1 << 18;
 // keys/vals: two ping-pong buffers of n * 128 u32 each; hist: radix_hist_words(n * 128)
 void ntc_csr_build(const Launch& L, const NtcDev& nd, const float* means, int64_t n, NtcCsr& csr, uint32_t* keys[2],
                    uint32_t* vals[2], uint32_t* hist, uint64_t* tmp);
@@ -31,12 +34,13 @@ void ntc_csr_build(const Launch& L, const NtcDev& nd, const float* means, int64_
 // also stores each point's encoding there
 void ntc_forward(const Launch& L, int precision, const NtcDev& nd, const void* table, const void* mlp,
                  const float* means, int64_t n, float* dmu, float* dq, void* enc_out);
-// g_part holds max_parts x ntc_mlp_params() floats; enc_in (optional): the
+// g_part holds max_parts x ntc_mlp_params() floats; without csr, scratch holds
+// min(n, kScatterPoints) x 32 floats; enc_in (optional, with csr): the
 // encoding a forward with the same parameters and means stored, used instead
 // of recomputing it
 void ntc_backward(const Launch& L, int precision, const NtcDev& nd, const void* table, const void* mlp,
                   const float* means, int64_t n, const float* d_dmu, const float* d_dq, float* g_table, float* g_mlp,
-                  float* g_part, int max_parts, const NtcCsr* csr, const void* enc_in);
+                  float* g_part, int max_parts, const NtcCsr* csr, float* scratch, const void* enc_in);
 void ntc_adam(const Launch& L, int precision, float* p, float* g, float* m, float* v, void* work, int64_t n, float lr,
               float b1, float b2, float eps, float bc1, float bc2);
 // float32 master parameters [table | W1 | W2 | W3] from a counter-based

@@ -330,9 +330,8 @@ __device__ __forceinline__ int pow2_exp(float mx) {
 // 2^-k are exact
 __device__ __forceinline__ int clamp_exp(int k) { return k < -126 ? -126 : (k > 126 ? 126 : k); }
 
-// kCSR: write the encoding gradient (n x 32 floats) to `denc` for the
-// per-entry gather of the prepared contribution lists; otherwise scatter-add
-// it into the table gradient with atomics.
+// The encoding gradient goes to `denc` (level-major, n x 32 floats), for the
+// per-entry gather of the prepared contribution lists or the scatter.
 //
 // Each iteration takes four batches, one per wave.  Phase A (each wave on its
 // own batch): the encoding, the forward layers, the output gradient and the
@@ -343,12 +342,12 @@ __device__ __forceinline__ int clamp_exp(int k) { return k < -126 ? -126 : (k > 
 // rows 16 w.. of dW1 and dW2 and the 16 columns 16 w.. of dW3), so a wave
 // holds 7 accumulator tiles instead of 28 and the register file leaves room
 // for more than one wave per SIMD.
-template <class P, bool kCSR>
+template <class P>
 __global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S* __restrict__ table,
                                                  const typename P::S* __restrict__ mlp, const float* __restrict__ means,
                                                  int64_t n, const float* __restrict__ d_dmu,
-                                                 const float* __restrict__ d_dq, float* __restrict__ g_table,
-                                                 float* __restrict__ g_part, float* __restrict__ denc,
+                                                 const float* __restrict__ d_dq, float* __restrict__ g_part,
+                                                 float* __restrict__ denc,
                                                  const typename P::S* __restrict__ enc_in) {
     using S = typename P::S;
     constexpr int kWElems = 64 * LD32 + 64 * LD64 + 32 * LD64 + 64 * LD64 + 64 * LD16;
@@ -362,7 +361,6 @@ __global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S*
     __shared__ S sX[kWaves][kPts * LD32], sH1[kWaves][kPts * LD64], sH2[kWaves][kPts * LD64];
     __shared__ S sD1[kWaves][kPts * LD64], sD2[kWaves][kPts * LD64];
     __shared__ S sO[kWaves][kPts * LD16];
-    __shared__ float sE[kCSR ? 1 : kWaves][kPts * 33];
     __shared__ int sK[kWaves][3];   // each batch's scale exponents k0, k1, k2
     load_weights<P>(mlp, sW1, sW2, nullptr, sW1t, sW2t, sW3t);
     __syncthreads();
@@ -374,7 +372,6 @@ __global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S*
     S* D1 = sD1[w];
     S* D2 = sD2[w];
     S* O = sO[w];
-    float* E = sE[kCSR ? 0 : w];
     // this wave's weight-gradient tiles: dW1 rows 16 w.. (2 column tiles),
     // dW2 rows 16 w.. (4 column tiles), dW3 columns 16 w..
     f4v gW1[2], gW2[4], gW3;
@@ -383,11 +380,8 @@ __global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S*
     gW3 = f4v{0.f, 0.f, 0.f, 0.f};
     // the level slices this lane writes in the level-major encoding gradient:
     // levels 2 g and 8 + 2 g (and the level after each)
-    float2* dlev[2] = {nullptr, nullptr};
-    if (kCSR) {
-        dlev[0] = reinterpret_cast<float2*>(denc) + (int64_t)(2 * g) * n;
-        dlev[1] = reinterpret_cast<float2*>(denc) + (int64_t)(8 + 2 * g) * n;
-    }
+    float2* const dlev[2] = {reinterpret_cast<float2*>(denc) + (int64_t)(2 * g) * n,
+                             reinterpret_cast<float2*>(denc) + (int64_t)(8 + 2 * g) * n};
     const int64_t nb = (n + kPts - 1) / kPts;
     // the inputs of this wave's batch are loaded one round ahead, so that
     // their latency overlaps the previous round's work
@@ -511,35 +505,12 @@ __global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S*
 #pragma unroll
             for (int mt = 0; mt < 2; mt++) {
                 const f4v e = layer_tile<P, 64>(sW1t, LD64, mt * 16, D1, LD64, lane);
-                if (kCSR) {
-                    // level-major [level][point][2]: one level's slice (8 n bytes)
-                    // stays cache-resident while the gather walks that level
-                    if (valid) {
-                        float2* d = dlev[mt] + pt;
-                        d[0] = make_float2(e[0] * inv, e[1] * inv);
-                        d[n] = make_float2(e[2] * inv, e[3] * inv);   // level lv + 1
-                    }
-                } else {
-                    for (int r = 0; r < 4; r++) E[p * 33 + mt * 16 + 4 * g + r] = e[r] * inv;
-                }
-            }
-        }
-        if (!kCSR) {
-            wave_sync();
-            // 6. scatter-add the encoding gradient into the table gradient
-            if (in) {
-#pragma unroll
-                for (int j = 0; j < 4; j++) {
-                    const int lv = 4 * g + j;
-                    uint32_t ent[8];
-                    float wt[8];
-                    ntc_corners(nd, lv, x, ent, wt);
-                    const float e0 = E[p * 33 + 2 * lv], e1 = E[p * 33 + 2 * lv + 1];
-#pragma unroll
-                    for (int c = 0; c < 8; c++) {
-                        atomicAdd(g_table + 2 * (int64_t)ent[c], wt[c] * e0);
-                        atomicAdd(g_table + 2 * (int64_t)ent[c] + 1, wt[c] * e1);
-                    }
+                // level-major [level][point][2]: one level's slice (8 n bytes)
+                // stays cache-resident while the gather walks that level
+                if (valid) {
+                    float2* d = dlev[mt] + pt;
+                    d[0] = make_float2(e[0] * inv, e[1] * inv);
+                    d[n] = make_float2(e[2] * inv, e[3] * inv);   // level lv + 1
                 }
             }
         }
@@ -741,6 +712,88 @@ __global__ __launch_bounds__(256) void k_csr_gather(GatherLevels gl, const uint2
     }
 }
 
+// Table gradient of means that were not prepared: every (point, level) adds
+// its eight corners' weighted encoding gradient to the level's entries.  A
+// workgroup holds kLdsEntries entries of one level (a part) in LDS, adds the
+// corners of its slice of the points that fall there with LDS atomics, and
+// adds the sums to the table gradient, lane after lane on consecutive
+// addresses.  Global atomics straight from the points each go to a line of
+// their own, and the L2s take only some 20 of those per ns.  The sums are
+// doubles: ds_add_f64 takes 3 to 6 lanes per clock of a CU on random entries
+// where ds_add_f32 takes a third of one (measured).  Neighbouring lanes take
+// points that lie apart, since points in spatial order fall on the same
+// entries and their atomics would queue up.  20,011 points in bf16:
+// 290 -> 45 us for backward and table gradient; 300K points in Morton order in
+// fp16: 4.88 -> 0.40 ms.
+constexpr int kLdsEntries = 8192;   // 128 KB
+constexpr int kLdsParts = 128;      // most parts of the table for which the points are read again
+
+struct TableParts {
+    int level[kLdsParts];
+    int first[kLdsParts];   // first entry of the part in its level
+    int size[kLdsParts];
+    int count = 0;
+};
+
+__global__ __launch_bounds__(1024) void k_table_lds(NtcDev nd, TableParts tp, const float* __restrict__ means, int64_t n,
+                                                    int slices, const float* __restrict__ denc,
+                                                    float* __restrict__ g_table) {
+    __shared__ double s_g[2 * kLdsEntries];
+    const int part = blockIdx.x / slices, slice = blockIdx.x % slices;
+    const int lv = tp.level[part], size = tp.size[part];
+    const uint32_t first = (uint32_t)nd.off[lv] + (uint32_t)tp.first[part];
+    for (int k = threadIdx.x; k < 2 * size; k += 1024) s_g[k] = 0.0;
+    __syncthreads();
+    const int64_t per = (n + slices - 1) / slices, p0 = slice * per, p1 = min(n, p0 + per);
+    const int64_t rows = (per + 1023) / 1024;   // points of one thread, next to each other
+    for (int64_t r = 0; r < rows; r++) {
+        const int64_t pt = p0 + (int64_t)threadIdx.x * rows + r;
+        if (pt >= p1) break;
+        const float mu[3] = {means[3 * pt], means[3 * pt + 1], means[3 * pt + 2]};
+        float xn[3];
+        if (!ntc_normalise(nd, mu, xn)) continue;
+        const float2 e = reinterpret_cast<const float2*>(denc)[(int64_t)lv * n + pt];
+        uint32_t ent[8];
+        float wt[8];
+        ntc_corners(nd, lv, xn, ent, wt);
+#pragma unroll
+        for (int c = 0; c < 8; c++) {
+            const uint32_t k = ent[c] - first;
+            if (k < (uint32_t)size) {
+                atomicAdd(&s_g[2 * k], (double)(wt[c] * e.x));
+                atomicAdd(&s_g[2 * k + 1], (double)(wt[c] * e.y));
+            }
+        }
+    }
+    __syncthreads();
+    float* out = g_table + 2 * (int64_t)first;
+    for (int k = threadIdx.x; k < 2 * size; k += 1024) {
+        const float v = (float)s_g[k];
+        if (v != 0.f) atomicAdd(out + k, v);
+    }
+}
+
+// The same with global atomics, for tables of more than kLdsParts parts.
+__global__ __launch_bounds__(256) void k_table_scatter(NtcDev nd, const float* __restrict__ means, int64_t n,
+                                                       const float* __restrict__ denc, float* __restrict__ g_table) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;   // (level, point)
+    if (t >= 16 * n) return;
+    const int lv = (int)(t / n);
+    const int64_t pt = t - lv * n;
+    const float mu[3] = {means[3 * pt], means[3 * pt + 1], means[3 * pt + 2]};
+    float xn[3];
+    if (!ntc_normalise(nd, mu, xn)) return;
+    const float2 e = reinterpret_cast<const float2*>(denc)[t];
+    uint32_t ent[8];
+    float wt[8];
+    ntc_corners(nd, lv, xn, ent, wt);
+#pragma unroll
+    for (int c = 0; c < 8; c++) {
+        atomicAdd(g_table + 2 * (int64_t)ent[c], wt[c] * e.x);
+        atomicAdd(g_table + 2 * (int64_t)ent[c] + 1, wt[c] * e.y);
+    }
+}
+
 // Sum the per-workgroup weight-gradient rows: blockIdx.y takes a slice of
 // the rows, blockIdx.x a range of columns; one atomic per (slice, column).
 constexpr int kPartSlice = 32;
@@ -861,38 +914,68 @@ void fwd_impl(const Launch& L, const NtcDev& nd, const void* table, const void* 
                        (const typename P::S*)mlp, means, n, dmu, dq, (typename P::S*)enc_out);
 }
 
+// Table gradient from the encoding gradient: per entry over the prepared
+// lists, or scattered.
+void table_grad(const Launch& L, const NtcDev& nd, const float* means, int64_t n, const NtcCsr* csr, const float* denc,
+                float* g_table) {
+    if (!csr) {
+        TableParts tp;
+        bool fits = true;
+        for (int lv = 0; lv < 16; lv++) {
+            const int64_t r1 = (int64_t)nd.res[lv] + 1;
+            const int64_t size = (nd.dense_mask >> lv) & 1u ? r1 * r1 * r1 : (int64_t)nd.T_mask + 1;
+            for (int64_t f = 0; f < size; f += kLdsEntries) {
+                fits = fits && tp.count < kLdsParts;
+                if (!fits) break;
+                tp.level[tp.count] = lv;
+                tp.first[tp.count] = (int)f;
+                tp.size[tp.count++] = (int)std::min<int64_t>(kLdsEntries, size - f);
+            }
+        }
+        if (fits) {
+            // about one workgroup per CU (the LDS holds one) for few points,
+            // a slice per 8192 points for many, so that the coarse levels'
+            // workgroups, whose atomics queue up, do not trail the launch
+            // (300K points: 4 slices 763 us, 8 565, 35 400; 20K: 4 slices 81
+            // us for the whole pass, 8 85, 17 100)
+            const int64_t few = std::min<int64_t>(256 / tp.count, (n + 1023) / 1024);
+            const int slices = (int)std::max<int64_t>(std::max<int64_t>(few, n / 8192), 1);
+            hipLaunchKernelGGL(k_table_lds, dim3((unsigned)(tp.count * slices)), dim3(1024), 0, L.st, nd, tp, means, n,
+                               slices, denc, g_table);
+        } else {
+            hipLaunchKernelGGL(k_table_scatter, dim3((unsigned)((16 * n + 255) / 256)), dim3(256), 0, L.st, nd, means, n,
+                               denc, g_table);
+        }
+        return;
+    }
+    GatherLevels gl;
+    for (int lv = 0; lv < 16; lv++) {
+        gl.begin[lv] = nd.off[lv];
+        gl.end[lv] = lv < 15 ? nd.off[lv + 1] : csr->entries;
+    }
+    int64_t per_xcd = 0;
+    for (int x = 0; x < kXcds; x++) per_xcd = std::max(per_xcd, gather_blocks(gl, x) + gather_blocks(gl, 15 - x));
+    hipLaunchKernelGGL(k_csr_gather, dim3((unsigned)(per_xcd * kXcds)), dim3(256), 0, L.st, gl, csr->rows, csr->pw, denc,
+                       n, g_table);
+}
+
 template <class P>
 void bwd_impl(const Launch& L, const NtcDev& nd, const void* table, const void* mlp, const float* means, int64_t n,
               const float* d_dmu, const float* d_dq, float* g_table, float* g_mlp, float* g_part, int max_parts,
-              const NtcCsr* csr, const void* enc_in) {
+              const NtcCsr* csr, float* denc, const void* enc_in) {
     const int64_t nb = (n + kPts - 1) / kPts;
     // max_parts is two per CU: the half-precision kernels fit two workgroups
     // on a CU, the float32 one (twice the LDS) one
     const int parts = sizeof(typename P::S) == 4 ? max_parts / 2 : max_parts;
     const unsigned grid = (unsigned)std::min<int64_t>((nb + kWaves - 1) / kWaves, parts);
-    if (csr) {
-        hipLaunchKernelGGL((k_ntc_bwd<P, true>), dim3(grid), dim3(256), 0, L.st, nd, (const typename P::S*)table,
-                           (const typename P::S*)mlp, means, n, d_dmu, d_dq, g_table, g_part, csr->denc,
-                           (const typename P::S*)enc_in);
-        if (L.prof) L.prof->end(L.st);
-        if (L.prof) L.prof->begin("ntc_scatter", L.st);
-        GatherLevels gl;
-        for (int lv = 0; lv < 16; lv++) {
-            gl.begin[lv] = nd.off[lv];
-            gl.end[lv] = lv < 15 ? nd.off[lv + 1] : csr->entries;
-        }
-        int64_t per_xcd = 0;
-        for (int x = 0; x < kXcds; x++)
-            per_xcd = std::max(per_xcd, gather_blocks(gl, x) + gather_blocks(gl, 15 - x));
-        hipLaunchKernelGGL(k_csr_gather, dim3((unsigned)(per_xcd * kXcds)), dim3(256), 0, L.st, gl, csr->rows,
-                           csr->pw, csr->denc, n, g_table);
-    } else {
-        hipLaunchKernelGGL((k_ntc_bwd<P, false>), dim3(grid), dim3(256), 0, L.st, nd, (const typename P::S*)table,
-                           (const typename P::S*)mlp, means, n, d_dmu, d_dq, g_table, g_part, (float*)nullptr,
-                           (const typename P::S*)enc_in);
-    }
+    hipLaunchKernelGGL((k_ntc_bwd<P>), dim3(grid), dim3(256), 0, L.st, nd, (const typename P::S*)table,
+                       (const typename P::S*)mlp, means, n, d_dmu, d_dq, g_part, denc, (const typename P::S*)enc_in);
+    if (L.prof) L.prof->end(L.st);
+    if (L.prof) L.prof->begin("ntc_scatter", L.st);
+    table_grad(L, nd, means, n, csr, denc, g_table);
     hipLaunchKernelGGL(k_reduce_parts, dim3(nblk(kMlpParams, 256), (grid + kPartSlice - 1) / kPartSlice), dim3(256), 0,
                        L.st, g_part, (int)grid, kMlpParams, g_mlp);
+    if (L.prof) L.prof->end(L.st);
 }
 
 }  // namespace
@@ -914,16 +997,24 @@ void ntc_forward(const Launch& L, int precision, const NtcDev& nd, const void* t
 
 void ntc_backward(const Launch& L, int precision, const NtcDev& nd, const void* table, const void* mlp,
                   const float* means, int64_t n, const float* d_dmu, const float* d_dq, float* g_table, float* g_mlp,
-                  float* g_part, int max_parts, const NtcCsr* csr, const void* enc_in) {
+                  float* g_part, int max_parts, const NtcCsr* csr, float* scratch, const void* enc_in) {
     if (n <= 0) return;
-    if (L.prof) L.prof->begin("ntc_bwd", L.st);
-    if (precision == 1)
-        bwd_impl<PF16>(L, nd, table, mlp, means, n, d_dmu, d_dq, g_table, g_mlp, g_part, max_parts, csr, enc_in);
-    else if (precision == 2)
-        bwd_impl<PBF16>(L, nd, table, mlp, means, n, d_dmu, d_dq, g_table, g_mlp, g_part, max_parts, csr, enc_in);
-    else
-        bwd_impl<PF32>(L, nd, table, mlp, means, n, d_dmu, d_dq, g_table, g_mlp, g_part, max_parts, csr, enc_in);
-    if (L.prof) L.prof->end(L.st);
+    // without preparation the points go through the scratch a part at a time
+    const int64_t step = csr ? n : kScatterPoints;
+    for (int64_t p0 = 0; p0 < n; p0 += step) {
+        const int64_t m = std::min(step, n - p0);
+        float* denc = csr ? csr->denc : scratch;
+        if (L.prof) L.prof->begin("ntc_bwd", L.st);
+        if (precision == 1)
+            bwd_impl<PF16>(L, nd, table, mlp, means + 3 * p0, m, d_dmu + 3 * p0, d_dq + 4 * p0, g_table, g_mlp, g_part,
+                           max_parts, csr, denc, enc_in);
+        else if (precision == 2)
+            bwd_impl<PBF16>(L, nd, table, mlp, means + 3 * p0, m, d_dmu + 3 * p0, d_dq + 4 * p0, g_table, g_mlp, g_part,
+                            max_parts, csr, denc, enc_in);
+        else
+            bwd_impl<PF32>(L, nd, table, mlp, means + 3 * p0, m, d_dmu + 3 * p0, d_dq + 4 * p0, g_table, g_mlp, g_part,
+                           max_parts, csr, denc, enc_in);
+    }
 }
 
 void ntc_csr_build(const Launch& L, const NtcDev& nd, const float* means, int64_t n, NtcCsr& csr, uint32_t* keys[2],

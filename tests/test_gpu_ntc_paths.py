@@ -1,0 +1,51 @@
+"""GPU tests that the NTC's paths give the same gradient where a rule on sizes
+chooses between them: prepared lists against the table gradient of means that
+were not prepared (parts of the table summed in LDS, global atomics for large
+tables), at and past the number of points processed at a time."""
+import numpy as np
+import pytest
+
+from paper_2403_01444_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def cuda(a):
+    return torch.from_numpy(np.ascontiguousarray(a, np.float32)).cuda()
+
+
+@pytest.mark.parametrize("n,log2_T,precision", [
+    (1025, 15, "f32"),          # a slice of two rows of points
+    (30_000, 10, "f16"),        # every level one part, ragged
+    (70_001, 16, "bf16"),       # 8192-entry parts: more than half of the most
+    (3000, 19, "f32"),          # more parts than the points are read for: global atomics
+    (262_144 + 65, 15, "f16"),  # a second round of points
+])
+def test_unprepared_gradient_matches_the_prepared(n, log2_T, precision):
+    from paper_2403_01444_amd import gs3
+    cfg = synth.NTCConfig(log2_T=log2_T)
+    rng = np.random.default_rng(n)
+    ctx = gs3.Context(n, 1 << 10, 16, 16, ntc=cfg, precision=precision)
+    p = synth.ntc_init_params(cfg, 1)
+    p[: cfg.num_table_params()] *= 1000.0
+    ctx.ntc_load(p)
+    m = cuda(rng.uniform(-1.25, 1.25, size=(n, 3)))
+    gm, gq = cuda(rng.normal(size=(n, 3)) * 1e-3), cuda(rng.normal(size=(n, 4)) * 1e-3)
+    tok = ctx.ntc_prepare(m)
+    ctx.ntc_backward(m, gm, gq, tok)
+    a = ctx.ntc_grads().double()
+    ctx.ntc_zero_grads()
+    ctx.ntc_backward(m, gm, gq)
+    b = ctx.ntc_grads().double()
+    # Both add the same float32 products.  An entry's m addends summed in
+    # float32 are within m 2^-24 of their absolute sum A; the fullest entries
+    # (level 0: 8 n / 4913 addends, a few hundred, of either sign, A up to 20
+    # times the largest sum) stay below 5e-4 of the largest entry.  Rounds of
+    # points scale the half-precision activations batch by batch, alike.
+    t = cfg.num_table_params()
+    assert float((a[:t] - b[:t]).abs().max()) <= 5e-4 * float(a[:t].abs().max())
+    assert float((a[t:] - b[t:]).abs().max()) <= 5e-4 * float(a[t:].abs().max())
+    assert float(a[:t].abs().max()) > 0
+    ctx.close()
