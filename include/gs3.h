@@ -235,7 +235,9 @@ gs3_status gs3_ntc_backward(gs3_ctx* ctx, const float* means, int64_t n, uint64_
  * the prepared lists.  The caller guarantees that the contents of `means`
  * do not change while the token is in use; a later gs3_ntc_prepare makes
  * the previous token stale.  Allocates device memory on first use or growth
- * (about 3.3 KB per mean) and synchronises. */
+ * (about 1.3 KB per mean, and 4 bytes per table entry for every slice of the
+ * means that is counted apart, at most 30 MB at T = 2^15; 3.3 KB per mean
+ * with T above 2^18) and synchronises. */
 gs3_status gs3_ntc_prepare(gs3_ctx* ctx, const float* means, int64_t n, uint64_t* token);
 
 /* One Adam step on the NTC parameters with the accumulated gradients,

@@ -167,10 +167,7 @@ struct gs3_ctx {
     uint64_t csr_token = 0;          // token of the current preparation (0: none)
     uint64_t last_token = 0;         // last token handed out
     std::vector<void*> csr_allocs;
-    uint32_t* csr_keys[2] = {nullptr, nullptr};
-    uint32_t* csr_vals[2] = {nullptr, nullptr};
-    uint32_t* csr_hist = nullptr;
-    uint64_t* csr_tmp = nullptr;
+    CsrScratch csr_work;
     EventProfiler prof;
     bool prof_on = false;
 
@@ -596,12 +593,18 @@ gs3_status gs3_ntc_prepare(gs3_ctx* c, const float* means, int64_t n, uint64_t* 
             return true;
         };
         const int64_t entries = c->n_table_floats / 2;
-        bool ok = get((void**)&c->csr_keys[0], m * 4) && get((void**)&c->csr_keys[1], m * 4) &&
-                  get((void**)&c->csr_vals[0], m * 4) && get((void**)&c->csr_vals[1], m * 4) &&
-                  get((void**)&c->csr_hist, radix_hist_words(m) * 4) &&
-                  get((void**)&c->csr_tmp, (scan_tmp_words(radix_hist_words(m)) + 4) * 8) &&
-                  get((void**)&c->csr.rows, entries * 8) && get((void**)&c->csr.pw, m * 8) &&
+        CsrScratch& w = c->csr_work;
+        const int64_t slices = ntc_csr_slices(c->nd, n);
+        bool ok = get((void**)&c->csr.rows, entries * 8) && get((void**)&c->csr.pw, m * 8) &&
                   get((void**)&c->csr.denc, n * 32 * 4) && get(&c->enc_cache, n * 32 * 4);
+        if (slices > 0)
+            ok = ok && get((void**)&w.cnt, slices * entries * 4) && get((void**)&w.first, entries * 4) &&
+                 get((void**)&w.tmp, (scan_tmp_words(entries) + 4) * 8);
+        else
+            ok = ok && get((void**)&w.keys[0], m * 4) && get((void**)&w.keys[1], m * 4) &&
+                 get((void**)&w.vals[0], m * 4) && get((void**)&w.vals[1], m * 4) &&
+                 get((void**)&w.hist, radix_hist_words(m) * 4) &&
+                 get((void**)&w.tmp, (scan_tmp_words(radix_hist_words(m)) + 4) * 8);
         if (!ok) {
             for (void* p : c->csr_allocs) (void)hipFree(p);
             c->csr_allocs.clear();
@@ -611,7 +614,7 @@ gs3_status gs3_ntc_prepare(gs3_ctx* c, const float* means, int64_t n, uint64_t* 
         c->csr_cap = n;
         c->csr.entries = entries;
     }
-    ntc_csr_build(c->L(), c->nd, means, n, c->csr, c->csr_keys, c->csr_vals, c->csr_hist, c->csr_tmp);
+    ntc_csr_build(c->L(), c->nd, means, n, c->csr, c->csr_work);
     if (hipStreamSynchronize(c->st) != hipSuccess) return c->fail(GS3_EHIP, "ntc_prepare: sync failed");
     gs3_status s = c->check_launch("ntc_prepare");
     if (s != GS3_OK) return s;

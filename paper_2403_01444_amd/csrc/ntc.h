@@ -18,8 +18,7 @@ struct NtcDev {
 struct NtcCsr {
     int64_t entries = 0;      // table entries
     uint2* rows = nullptr;    // [entries]: [start, end) into pw
-    uint32_t* pid = nullptr;  // point << 7 | level << 3 | corner, sorted by entry
-    uint2* pw = nullptr;      // (pid, float bits of the trilinear weight) of each contribution
+    uint2* pw = nullptr;      // (point << 7 | level << 3 | corner, float bits of the trilinear weight), by entry
     float* denc = nullptr;    // [16 levels][n][2] encoding gradient of the current backward
 };
 
@@ -27,9 +26,20 @@ int ntc_mlp_params();
 // points whose encoding gradient a backward without preparation holds at a
 // time (32 MB of scratch)
 constexpr int64_t kScatterPoints = 1 << 18;
-// keys/vals: two ping-pong buffers of n * 128 u32 each; hist: radix_hist_words(n * 128)
-void ntc_csr_build(const Launch& L, const NtcDev& nd, const float* means, int64_t n, NtcCsr& csr, uint32_t* keys[2],
-                   uint32_t* vals[2], uint32_t* hist, uint64_t* tmp);
+// Scratch of the list building: cnt (slices x entries) and first (entries)
+// when ntc_csr_slices gives a number of slices, else (0) the sort's ping-pong
+// buffers of n * 128 u32 each and hist, radix_hist_words(n * 128); tmp holds
+// the scan's words of either + 1.
+struct CsrScratch {
+    uint32_t* cnt = nullptr;
+    uint32_t* first = nullptr;
+    uint32_t* keys[2] = {nullptr, nullptr};
+    uint32_t* vals[2] = {nullptr, nullptr};
+    uint32_t* hist = nullptr;
+    uint64_t* tmp = nullptr;
+};
+int64_t ntc_csr_slices(const NtcDev& nd, int64_t n);
+void ntc_csr_build(const Launch& L, const NtcDev& nd, const float* means, int64_t n, NtcCsr& csr, const CsrScratch& w);
 // enc_out (optional, n x 32 values of the working precision): the forward
 // also stores each point's encoding there
 void ntc_forward(const Launch& L, int precision, const NtcDev& nd, const void* table, const void* mlp,

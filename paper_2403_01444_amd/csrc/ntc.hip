@@ -27,6 +27,11 @@ namespace gs3 {
 
 namespace {
 
+// points of a slice of the contribution lists: whole groups of 256
+__host__ __device__ __forceinline__ int64_t csr_slice(int64_t n, int slices) {
+    return ((n + slices - 1) / slices + 255) / 256 * 256;
+}
+
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef _Float16 h4v __attribute__((ext_vector_type(4)));
 typedef __bf16 b4v __attribute__((ext_vector_type(4)));
@@ -570,13 +575,163 @@ __global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S*
         if (4 * g + r < 7) out[64 * 32 + 64 * 64 + (4 * g + r) * 64 + w * 16 + col] = gW3[r];
 }
 
+// The table cut into parts of one level, for the kernels that hold a part in
+// LDS and read the points again for each.
+constexpr int kLdsEntries = 8192;    // entries of a part: two doubles each (128 KB),
+constexpr int kListEntries = 32768;  // or a counter each (128 KB)
+constexpr int kLdsParts = 128;       // most parts of the table for which the points are read again
+
+struct TableParts {
+    int level[kLdsParts];
+    int first[kLdsParts];   // first entry of the part in its level
+    int size[kLdsParts];
+    int count = 0;
+};
+
+static bool table_parts(const NtcDev& nd, int part, TableParts& tp) {
+    for (int lv = 0; lv < 16; lv++) {
+        const int64_t r1 = (int64_t)nd.res[lv] + 1;
+        const int64_t size = (nd.dense_mask >> lv) & 1u ? r1 * r1 * r1 : (int64_t)nd.T_mask + 1;
+        for (int64_t f = 0; f < size; f += part) {
+            if (tp.count == kLdsParts) return false;
+            tp.level[tp.count] = lv;
+            tp.first[tp.count] = (int)f;
+            tp.size[tp.count++] = (int)std::min<int64_t>(part, size - f);
+        }
+    }
+    return true;
+}
+
 // ---------------------------------------------------------------------------
 // Per-frame contribution lists.  The means are frozen during Stage 1, so
 // every (point, level, corner) contribution to the table gradient has a fixed
 // entry and a fixed trilinear weight for the whole frame.  They are sorted
 // by entry once; each iteration then sums, per entry, weight x encoding
 // gradient of the contributing points (no atomics, fixed summation order).
+//
+// The lists are built by counting: a workgroup counts a slice of the points
+// into the entries of one part of the table in LDS, the counts of (slice,
+// entry) are turned into first slots (entry by entry, slice by slice), and a
+// workgroup per (part, slice) walks its points in order with the slots in LDS
+// and stores each contribution where its entry's counter says.  Its four
+// waves compute the corners of 256 points side by side and then take their
+// slots one wave after the other; a wave's LDS operations are done in order,
+// so a list is ordered by groups of 64 points, then corner, then the order in
+// which the LDS serves the lanes of one instruction, which depends on the
+// addresses alone: the same means give the same lists.  Bound by the
+// scattered 8-byte stores: an entry's list is one of 32768 that a workgroup
+// appends to, more lines than an L2 holds.  300K points, T =
+// 2^15, with the means' Morton reorder: 1.85 ms with a radix sort of (entry,
+// contribution) pairs -> 0.53 ms (parts of 8192 entries and a wave each, the
+// points read four times as often: 0.83 ms).  Tables of more than kLdsParts
+// parts (T above 2^18) still take the sort.
 // ---------------------------------------------------------------------------
+__global__ __launch_bounds__(1024) void k_csr_count(NtcDev nd, TableParts tp, const float* __restrict__ means, int64_t n,
+                                                    int slices, int64_t entries, uint32_t* __restrict__ cnt) {
+    __shared__ uint32_t s_n[kListEntries];
+    const int part = blockIdx.x / slices, slice = blockIdx.x % slices;
+    const int lv = tp.level[part], size = tp.size[part];
+    const uint32_t first = (uint32_t)nd.off[lv] + (uint32_t)tp.first[part];
+    for (int k = threadIdx.x; k < size; k += 1024) s_n[k] = 0u;
+    __syncthreads();
+    const int64_t per = csr_slice(n, slices), p0 = slice * per, p1 = min(n, p0 + per);
+    const int64_t rows = (per + 1023) / 1024;   // points of one thread, next to each other: see k_table_lds
+    for (int64_t r = 0; r < rows; r++) {
+        const int64_t pt = p0 + (int64_t)threadIdx.x * rows + r;
+        if (pt >= p1) break;
+        const float mu[3] = {means[3 * pt], means[3 * pt + 1], means[3 * pt + 2]};
+        float x[3];
+        if (!ntc_normalise(nd, mu, x)) continue;
+        uint32_t ent[8];
+        float wt[8];
+        ntc_corners(nd, lv, x, ent, wt);
+#pragma unroll
+        for (int c = 0; c < 8; c++) {
+            const uint32_t k = ent[c] - first;
+            if (k < (uint32_t)size) atomicAdd(&s_n[k], 1u);
+        }
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < size; k += 1024) cnt[(int64_t)slice * entries + first + k] = s_n[k];
+}
+
+// contributions per entry
+__global__ __launch_bounds__(256) void k_csr_totals(const uint32_t* __restrict__ cnt, int slices, int64_t entries,
+                                                    uint32_t* __restrict__ total) {
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= entries) return;
+    uint32_t s = 0u;
+    for (int k = 0; k < slices; k++) s += cnt[k * entries + e];
+    total[e] = s;
+}
+
+// first[e] (exclusive scan of the totals) -> rows[e] and, in place of each
+// (slice, entry) count, its first slot
+__global__ __launch_bounds__(256) void k_csr_slots(uint32_t* __restrict__ cnt, int slices, int64_t entries,
+                                                   const uint32_t* __restrict__ first, uint2* __restrict__ rows) {
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= entries) return;
+    uint32_t run = first[e];
+    const uint32_t begin = run;
+    for (int k = 0; k < slices; k++) {
+        const uint32_t v = cnt[k * entries + e];
+        cnt[k * entries + e] = run;
+        run += v;
+    }
+    rows[e] = make_uint2(begin, run);
+}
+
+__global__ __launch_bounds__(256) void k_csr_place(NtcDev nd, TableParts tp, const float* __restrict__ means, int64_t n,
+                                                   int slices, int64_t entries, const uint32_t* __restrict__ slot,
+                                                   uint2* __restrict__ pw) {
+    __shared__ uint32_t s_at[kListEntries];
+    const int part = blockIdx.x / slices, slice = blockIdx.x % slices;
+    const int lv = tp.level[part], size = tp.size[part];
+    const uint32_t first = (uint32_t)nd.off[lv] + (uint32_t)tp.first[part];
+    const uint32_t* src = slot + (int64_t)slice * entries + first;
+    for (int k = threadIdx.x; k < size; k += 256) s_at[k] = src[k];
+    __syncthreads();
+    const int64_t per = csr_slice(n, slices), p0 = slice * per, p1 = min(n, p0 + per);
+    const int w = threadIdx.x >> 6;
+    float mu[3] = {0.f, 0.f, 0.f};
+    auto load = [&](int64_t pt) {
+        if (pt < p1) {
+            mu[0] = means[3 * pt];
+            mu[1] = means[3 * pt + 1];
+            mu[2] = means[3 * pt + 2];
+        }
+    };
+    load(p0 + threadIdx.x);
+    for (int64_t b = p0; b < p1; b += 256) {
+        const int64_t pt = b + threadIdx.x;
+        float x[3];
+        const bool in = ntc_normalise(nd, mu, x) && pt < p1;
+        load(pt + 256);   // the next group's means arrive during this one's work
+        uint32_t ent[8];
+        float wt[8];
+        ntc_corners(nd, lv, x, ent, wt);
+        uint32_t at[8];
+        for (int turn = 0; turn < 4; turn++) {
+            if (w == turn) {
+#pragma unroll
+                for (int c = 0; c < 8; c++) {
+                    const uint32_t k = ent[c] - first;
+                    at[c] = 0u;
+                    if (in && k < (uint32_t)size) at[c] = atomicAdd(&s_at[k], 1u);
+                }
+            }
+            __syncthreads();   // waits for the wave's LDS operations
+        }
+#pragma unroll
+        for (int c = 0; c < 8; c++) {
+            const uint32_t k = ent[c] - first;
+            if (in && k < (uint32_t)size)
+                pw[at[c]] = make_uint2(((uint32_t)pt << 7) | ((uint32_t)lv << 3) | (uint32_t)c, __float_as_uint(wt[c]));
+        }
+    }
+}
+
+// The sort, for large tables: contributions keyed by entry.
 __global__ __launch_bounds__(256) void k_csr_contrib(NtcDev nd, const float* __restrict__ means, int64_t n,
                                                      uint32_t sentinel, uint32_t* __restrict__ key,
                                                      uint32_t* __restrict__ pid) {
@@ -725,15 +880,6 @@ __global__ __launch_bounds__(256) void k_csr_gather(GatherLevels gl, const uint2
 // entries and their atomics would queue up.  20,011 points in bf16:
 // 290 -> 45 us for backward and table gradient; 300K points in Morton order in
 // fp16: 4.88 -> 0.40 ms.
-constexpr int kLdsEntries = 8192;   // 128 KB
-constexpr int kLdsParts = 128;      // most parts of the table for which the points are read again
-
-struct TableParts {
-    int level[kLdsParts];
-    int first[kLdsParts];   // first entry of the part in its level
-    int size[kLdsParts];
-    int count = 0;
-};
 
 __global__ __launch_bounds__(1024) void k_table_lds(NtcDev nd, TableParts tp, const float* __restrict__ means, int64_t n,
                                                     int slices, const float* __restrict__ denc,
@@ -920,18 +1066,7 @@ void table_grad(const Launch& L, const NtcDev& nd, const float* means, int64_t n
                 float* g_table) {
     if (!csr) {
         TableParts tp;
-        bool fits = true;
-        for (int lv = 0; lv < 16; lv++) {
-            const int64_t r1 = (int64_t)nd.res[lv] + 1;
-            const int64_t size = (nd.dense_mask >> lv) & 1u ? r1 * r1 * r1 : (int64_t)nd.T_mask + 1;
-            for (int64_t f = 0; f < size; f += kLdsEntries) {
-                fits = fits && tp.count < kLdsParts;
-                if (!fits) break;
-                tp.level[tp.count] = lv;
-                tp.first[tp.count] = (int)f;
-                tp.size[tp.count++] = (int)std::min<int64_t>(kLdsEntries, size - f);
-            }
-        }
+        const bool fits = table_parts(nd, kLdsEntries, tp);
         if (fits) {
             // about one workgroup per CU (the LDS holds one) for few points,
             // a slice per 8192 points for many, so that the coarse levels'
@@ -1017,21 +1152,43 @@ void ntc_backward(const Launch& L, int precision, const NtcDev& nd, const void* 
     }
 }
 
-void ntc_csr_build(const Launch& L, const NtcDev& nd, const float* means, int64_t n, NtcCsr& csr, uint32_t* keys[2],
-                   uint32_t* vals[2], uint32_t* hist, uint64_t* tmp) {
+int64_t ntc_csr_slices(const NtcDev& nd, int64_t n) {
+    TableParts tp;
+    if (!table_parts(nd, kListEntries, tp)) return 0;
+    // one workgroup per CU (the LDS holds one), a slice of at least 1024 points
+    return std::max<int64_t>(1, std::min<int64_t>(256 / tp.count, (n + 1023) / 1024));
+}
+
+void ntc_csr_build(const Launch& L, const NtcDev& nd, const float* means, int64_t n, NtcCsr& csr, const CsrScratch& w) {
+    if (L.prof) L.prof->begin("ntc_prepare", L.st);
+    Launch inner{L.st, nullptr};
+    TableParts tp;
+    if (table_parts(nd, kListEntries, tp)) {
+        const int slices = (int)ntc_csr_slices(nd, n);
+        const unsigned grid = (unsigned)(tp.count * slices);
+        hipLaunchKernelGGL(k_csr_count, dim3(grid), dim3(1024), 0, L.st, nd, tp, means, n, slices, csr.entries, w.cnt);
+        hipLaunchKernelGGL(k_csr_totals, dim3(nblk(csr.entries, 256)), dim3(256), 0, L.st, w.cnt, slices, csr.entries,
+                           w.first);
+        scan_u32_to_u32(inner, w.first, csr.entries, w.first, w.tmp, w.tmp + 1);
+        hipLaunchKernelGGL(k_csr_slots, dim3(nblk(csr.entries, 256)), dim3(256), 0, L.st, w.cnt, slices, csr.entries,
+                           w.first, csr.rows);
+        hipLaunchKernelGGL(k_csr_place, dim3(grid), dim3(256), 0, L.st, nd, tp, means, n, slices, csr.entries, w.cnt,
+                           csr.pw);
+        if (L.prof) L.prof->end(L.st);
+        return;
+    }
     const int64_t m = n * 128;
     const uint32_t sentinel = (uint32_t)csr.entries;
     int bits = 1;
     while (((int64_t)1 << bits) <= csr.entries) bits++;
-    if (L.prof) L.prof->begin("ntc_prepare", L.st);
+    uint32_t* keys[2] = {w.keys[0], w.keys[1]};
+    uint32_t* vals[2] = {w.vals[0], w.vals[1]};
     hipLaunchKernelGGL(k_csr_contrib, dim3(nblk(n * 16, 256)), dim3(256), 0, L.st, nd, means, n, sentinel, keys[0],
                        vals[0]);
-    Launch inner{L.st, nullptr};
-    const int r = radix_sort_u32(inner, keys, vals, m, bits, hist, tmp);
-    csr.pid = vals[r];
+    const int r = radix_sort_u32(inner, keys, vals, m, bits, w.hist, w.tmp);
     fill_u32(inner, reinterpret_cast<uint32_t*>(csr.rows), 0u, 2 * csr.entries);
     hipLaunchKernelGGL(k_csr_rows, dim3(nblk(m, 256)), dim3(256), 0, L.st, keys[r], m, sentinel, csr.rows);
-    hipLaunchKernelGGL(k_csr_weights, dim3(nblk(m, 256)), dim3(256), 0, L.st, nd, means, keys[r], csr.pid, m, sentinel,
+    hipLaunchKernelGGL(k_csr_weights, dim3(nblk(m, 256)), dim3(256), 0, L.st, nd, means, keys[r], vals[r], m, sentinel,
                        csr.pw);
     if (L.prof) L.prof->end(L.st);
 }

@@ -20,7 +20,8 @@ def cuda(a):
     (1025, 15, "f32"),          # a slice of two rows of points
     (30_000, 10, "f16"),        # every level one part, ragged
     (70_001, 16, "bf16"),       # 8192-entry parts: more than half of the most
-    (3000, 19, "f32"),          # more parts than the points are read for: global atomics
+    (3000, 18, "f32"),          # global atomics against counted lists of several parts a level
+    (3000, 19, "f32"),          # more parts than the points are read for: global atomics, sorted lists
     (262_144 + 65, 15, "f16"),  # a second round of points
 ])
 def test_unprepared_gradient_matches_the_prepared(n, log2_T, precision):
@@ -49,3 +50,33 @@ def test_unprepared_gradient_matches_the_prepared(n, log2_T, precision):
     assert float((a[t:] - b[t:]).abs().max()) <= 5e-4 * float(a[t:].abs().max())
     assert float(a[:t].abs().max()) > 0
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [1, 255, 257, 4099])
+def test_prepared_lists_repeat(n):
+    """The contribution lists and their order depend on the means alone: two
+    contexts that prepare the same means give the same gradient bit for bit,
+    whatever was prepared before."""
+    from paper_2403_01444_amd import gs3
+    cfg = synth.NTCConfig()
+    rng = np.random.default_rng(n)
+    pts = rng.uniform(-1.2, 1.2, size=(n, 3)).astype(np.float32)
+    pts[: n // 2] = pts[0]                       # one cell: every lane on the same entries
+    m, other = cuda(pts), cuda(rng.uniform(-1, 1, size=(5000, 3)))
+    gm, gq = cuda(rng.normal(size=(n, 3)) * 1e-3), cuda(rng.normal(size=(n, 4)) * 1e-3)
+    out = []
+    for first in (False, True):
+        ctx = gs3.Context(5000, 1 << 10, 16, 16, ntc=cfg, precision="f32")
+        p = synth.ntc_init_params(cfg, 1)
+        p[: cfg.num_table_params()] *= 1000.0
+        ctx.ntc_load(p)
+        if first:
+            ctx.ntc_prepare(other)
+        tok = ctx.ntc_prepare(m)
+        for _ in range(2):
+            ctx.ntc_zero_grads()
+            ctx.ntc_backward(m, gm, gq, tok)
+            out.append(ctx.ntc_grads()[: cfg.num_table_params()].clone())
+        ctx.close()
+    assert all(torch.equal(out[0], o) for o in out[1:])
+    assert float(out[0].abs().max()) > 0
