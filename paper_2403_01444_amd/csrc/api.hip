@@ -717,7 +717,7 @@ gs3_status gs3_render(gs3_ctx* c, int32_t slot, const gs3_gaussians* g, const fl
             if (sl.super) {
                 sl.sup.supers_x = super_count_of(cd.tiles_x);
                 super_bin(L, order, n, sl.rect, cd.tiles_x, cd.tiles_y, cap, (uint32_t)ntiles, c->bin_rect, c->sup_hist,
-                          c->sup_ksum, sl.total, c->flags, sl.sup, sl.sorder);
+                          c->sup_ksum, sl.total, c->flags, sl.sup, narrow_tiles(ntiles) ? nullptr : sl.sorder);
             } else {
                 // tile-major list: the record gather needs every pair's slot,
                 // from the first pair slot of each Gaussian
@@ -756,7 +756,7 @@ gs3_status gs3_render(gs3_ctx* c, int32_t slot, const gs3_gaussians* g, const fl
             gpos_from_pairs(L, sl.pkeys[sl.cur], sl.vals[sl.cur], (int64_t)K, sl.rect, sl.goff, cd.tiles_x, cap,
                             sl.gpos);
     }
-    if (!sl.super) tile_order(L, sl.ranges, nullptr, ntiles, sl.order_fwd);
+    if (!sl.super && !narrow_tiles(ntiles)) tile_order(L, sl.ranges, nullptr, ntiles, sl.order_fwd);
     blend_forward(L, cd, sl.ranges, sl.vals[sl.cur], sl.rec, image, sl.T_final, sl.last, sl.tile_walk,
                   sl.super ? sl.sorder : sl.order_fwd, sl.taken, sl.super ? &sl.sup : nullptr);
     gs3_status st = c->check_launch("render");
@@ -782,7 +782,7 @@ gs3_status gs3_render_backward(gs3_ctx* c, int32_t slot, const float* d_image, c
     ga.rect = sl.rect; ga.goff = sl.goff; ga.gpos = sl.gpos; ga.ranges = sl.ranges; ga.tile_walk = sl.tile_walk;
     ga.walk_off = c->walk_off; ga.grec = c->grec; ga.grec_cap = (uint64_t)c->grec_cap;
     ga.cap = (uint64_t)c->cfg.max_pairs;
-    tile_order(L, sl.ranges, sl.tile_walk, ntiles, sl.order_bwd);
+    if (!narrow_tiles(ntiles)) tile_order(L, sl.ranges, sl.tile_walk, ntiles, sl.order_bwd);
     blend_backward(L, sl.cam, sl.ranges, sl.vals[sl.cur], sl.rec, d_image, sl.T_final, sl.last, ga, c->accum,
                    out->d_opacity != nullptr || out->d_opacity_logits != nullptr, sl.order_bwd, sl.taken,
                    sl.super ? &sl.sup : nullptr);

@@ -157,6 +157,9 @@ void super_pairs(const Launch& L, const SuperDev& sd, int tiles_x, int tiles_y, 
 // Longest-first launch order of the tiles: by list length (walk == nullptr)
 // or by walked entries.  `order` holds ntiles ints.
 void tile_order(const Launch& L, const uint2* ranges, const uint32_t* walk, int ntiles, int* order);
+// Whether a view of ntiles tiles takes the narrow blends, whose workgroups
+// are all in flight at once: no order of the tiles is needed then.
+bool narrow_tiles(int ntiles);
 // supers: the supers' lists (order then maps places to supers), or NULL for a
 // tile-major list read through ranges (order maps workgroups to tiles).
 // `order` is optional.  taken: for every 64 entries of a tile's list four

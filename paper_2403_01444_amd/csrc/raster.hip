@@ -995,6 +995,482 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend_bwd(CamDev cam, int nti
     }
 }
 
+// ---------------------------------------------------------------------------
+// Narrow blends, for views of few tiles.  With a tile to a CU or fewer, the
+// 8 x 8 blends above leave one wave to a SIMD and run at the latency of its
+// chain, entry after entry.  Here a tile has 16 waves: a wave takes a block of
+// 4 x 4 pixels, and its four 16-lane rows evaluate four entries (slots) at a
+// time, one entry to a row, each lane one pixel of it.  The opacities of the
+// four slots are then exchanged between the rows (permlane swaps), and every
+// row walks the four in order for the transmittance, so the results are the
+// same as entry by entry.  A block of 16 pixels is reached by half as many
+// entries as a quadrant of 64 where the Gaussians are small, and the
+// exponents, tests and gradient terms of four entries cost one evaluation.
+// Bound by VALU issue of the tile's one CU.  Per launch, 8 x 8 -> narrow, 50K
+// surfaces at 256 x 256: forward 226 -> 118 us, backward 331 -> 196; 2K
+// uniform at 64 x 64: 54 -> 32, 95 -> 55.  Where it is chosen: narrow_tiles.
+// ---------------------------------------------------------------------------
+constexpr int kNarrowThreads = 1024;
+constexpr int kNarrowWaves = kNarrowThreads / 64;   // one per 4 x 4 block: block w at (w & 3, w >> 2)
+constexpr int kSlots = 4;
+
+// x of the four rows (slots) of a wave, each in every row: s[k] holds, in lane
+// l, the value of lane 16 k + (l & 15).
+__device__ __forceinline__ void rows_all(float x, float s[kSlots]) {
+    float a = x, b = x;
+    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));   // rows 0 1 0 1, rows 2 3 2 3
+    float a1 = a, b1 = b;
+    asm volatile(
+        "s_nop 1\n\t"
+        "v_permlane16_swap_b32 %0, %1\n\t"
+        "v_permlane16_swap_b32 %2, %3"
+        : "+v"(a), "+v"(a1), "+v"(b), "+v"(b1));
+    s[0] = a;
+    s[1] = a1;
+    s[2] = b;
+    s[3] = b1;
+}
+
+// Eight values per lane -> their sums over each row of 16 lanes: afterwards
+// lane i of the row holds the sum of term row_term(i).
+__device__ __forceinline__ int row_term(int i) { return ((i >> 3) & 1) * 4 + ((i >> 2) & 1) * 2 + ((i >> 1) & 1); }
+template <int kCtrl>
+__device__ __forceinline__ float row_halve(float lo, float hi, bool up) {
+    const float keep = up ? hi : lo, send = up ? lo : hi;
+    return keep + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), kCtrl, 0xF,
+                                                                        0xF, false));
+}
+__device__ __forceinline__ float row_reduce_scatter8(const float v[8], int i) {
+    float a[4], b[2];
+#pragma unroll
+    for (int k = 0; k < 4; k++) a[k] = row_halve<0x128>(v[k], v[4 + k], i & 8);        // row_ror:8, lane i ^ 8
+#pragma unroll
+    for (int k = 0; k < 2; k++) b[k] = row_halve<0x141>(a[k], a[2 + k], i & 4);        // row_half_mirror, lane i ^ 7
+    const float c = row_halve<0x4E>(b[0], b[1], i & 2);                                // quad_perm [2,3,0,1]
+    return dpp_add<0xB1, 0xF>(c);                                                      // quad_perm [1,0,3,2]
+}
+
+// Whether an entry in LDS form (s_a, s_b of the narrow blends, box mask) can
+// reach 4 x 4 block b of the tile: quads_reached for a block.
+__device__ __forceinline__ bool block_reached(const float4& a, const float4& b, uint32_t box, int blk, int tx0p, int ty0p) {
+    const int bx = 4 * (blk & 3), by = 4 * (blk >> 2);
+    const uint32_t cols = (box >> bx) & 15u, rows = (box >> (16 + by)) & 15u;
+    const float A = a.z, B = a.w, C = b.x, k = -2.0f * b.z;
+    const bool cut = A * C <= 250.0f * (A * C - B * B);
+    // spans of the box inside the block (the bits are contiguous)
+    const int x0 = tx0p + bx + __ffs(cols) - 1, x1 = tx0p + bx + 31 - __clz(cols);
+    const int y0 = ty0p + by + __ffs(rows) - 1, y1 = ty0p + by + 31 - __clz(rows);
+    const bool meets = conic_reaches(A, B, C, k, (float)x0 - a.x, (float)x1 - a.x, (float)y0 - a.y, (float)y1 - a.y);
+    return (cols != 0u) & (rows != 0u) & (!cut | meets);
+}
+
+// The records of the narrow blends in LDS: (u, v, A, B), (C, opacity, band
+// lower edge, band upper edge), colour, box mask; one past the last is an
+// entry no pixel takes.
+template <int N>
+struct NarrowRecs {
+    float4 a[N + 1], b[N + 1], col[N + 1];
+    uint32_t box[N + 1];
+    __device__ __forceinline__ void put(int j, const float4* __restrict__ rec, uint32_t id, int tx0p, int ty0p) {
+        const float4 r0 = rec[3 * (int64_t)id], r1 = rec[3 * (int64_t)id + 1], r2 = rec[3 * (int64_t)id + 2];
+        const float4 w2 = blend_stage_w2(r2, tx0p, ty0p);
+        a[j] = r0;
+        b[j] = make_float4(r1.x, r1.y, w2.y, w2.z);
+        col[j] = make_float4(r1.z, r1.w, w2.x, 0.f);
+        box[j] = __float_as_uint(w2.w);
+    }
+    __device__ __forceinline__ void put_none(int j) {
+        a[j] = b[j] = col[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+        box[j] = 0u;
+    }
+};
+
+template <bool kSuper>
+__global__ __launch_bounds__(kNarrowThreads) void k_blend_fwd_narrow(CamDev cam, int ntiles,
+                                                                     const uint2* __restrict__ ranges,
+                                                                     const uint32_t* __restrict__ vals,
+                                                                     const float4* __restrict__ rec,
+                                                                     float* __restrict__ image,
+                                                                     float* __restrict__ T_final,
+                                                                     uint32_t* __restrict__ last_out,
+                                                                     uint32_t* __restrict__ tile_walk, SuperDev sd) {
+    constexpr int NT = kNarrowThreads, NW = kNarrowWaves, NB = kWalkBlock;   // NB entries a batch
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tile = blockIdx.x;
+    if (tile >= ntiles) return;
+    const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
+    __shared__ NarrowRecs<NB> s_r;
+    __shared__ uint32_t s_q[kSuper ? NB + NT : 1];   // queue of indices
+    __shared__ uint32_t s_n[2][NW];
+    __shared__ uint64_t s_reach[NW][NB / 64];        // [block][word]
+    __shared__ uint16_t s_list[NW][NB + kSlots];     // entries that reach the wave's block, in order
+    __shared__ uint32_t s_live[2], s_blk, s_walk;
+    const int tx0p = tx * kTile, ty0p = ty * kTile;
+    const int row = lane >> 4, pix = lane & 15;
+    const int lx = 4 * (w & 3) + (pix & 3), ly = 4 * (w >> 2) + (pix >> 2);
+    const int px = tx0p + lx, py = ty0p + ly;
+    const float fpx = (float)px, fpy = (float)py;
+    const uint32_t sel = (1u << lx) | (1u << (16 + ly));
+    float T = 1.0f, c = 0.f;                          // c: the channel of the lane's row (none in row 3)
+    uint32_t last = 0u;                               // of the lane's slot
+    uint64_t alive = __builtin_amdgcn_ballot_w64(px < cam.W && py < cam.H);
+    if (tid == 0) {
+        s_walk = 0u;
+        s_r.put_none(NB);
+    }
+    uint32_t cur, cend, mk = 0u, nid = 0u, queued = 0u, tbit = 0u;
+    int par = 0;
+    if (kSuper) {
+        const int sup = (ty >> kSuperShift) * sd.supers_x + (tx >> kSuperShift);
+        cur = sd.start[sup];
+        cend = min(sd.cap, cur + sd.len[sup]);
+        tbit = 1u << ((ty % kSuperDim) * kSuperDim + tx % kSuperDim);
+        if (cur + tid < cend) {
+            mk = sd.masks[cur + tid];
+            nid = sd.ids[cur + tid];
+        }
+    } else {
+        const uint2 rg = ranges[tile];
+        cur = rg.x;
+        cend = rg.y;
+    }
+    uint32_t blk = (uint32_t)tile, lastblk = (uint32_t)tile;
+    for (uint32_t eb = 0;;) {
+        uint32_t myid = 0u, cnt_u;
+        if (tid < 2) s_live[tid] = 0u;
+        if (kSuper) {
+            while (queued < (uint32_t)NB && cur < cend) {
+                const bool on = (mk & tbit) != 0u && cur + tid < cend;
+                const uint64_t bal = __ballot(on);
+                if (lane == 0) s_n[par][w] = (uint32_t)__popcll(bal);
+                __syncthreads();
+                uint32_t at = queued + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+#pragma unroll
+                for (int k = 0; k < NW; k++) {
+                    const uint32_t v = s_n[par][k];
+                    if (k < w) at += v;
+                    queued += v;
+                }
+                if (on) s_q[at] = nid;   // at < NB - 1 + NT
+                par ^= 1;
+                cur += NT;
+                if (cur + tid < cend) {
+                    mk = sd.masks[cur + tid];
+                    nid = sd.ids[cur + tid];
+                }
+            }
+            if (queued == 0u) break;
+            cnt_u = min((uint32_t)NB, queued);
+            __syncthreads();
+            if ((uint32_t)tid < cnt_u) myid = s_q[tid];
+        } else {
+            if (cur >= cend) break;
+            cnt_u = min((uint32_t)NB, cend - cur);
+            if ((uint32_t)tid < cnt_u) myid = vals[cur + tid];
+            cur += cnt_u;
+        }
+        if ((uint32_t)tid < cnt_u) s_r.put(tid, rec, myid, tx0p, ty0p);
+        // the queue's entries past this batch move to its front
+        uint32_t rest = 0u;
+        if (kSuper && (uint32_t)tid + NB < queued) rest = s_q[NB + tid];
+        __syncthreads();
+        if (kSuper) {
+            if ((uint32_t)tid + NB < queued) s_q[tid] = rest;
+            queued -= cnt_u;
+            if (tid == 0 && eb != 0u) blk = atomicAdd(sd.pool, 1u);   // a walked block, see k_blend_fwd
+        }
+        {
+            // entry 64 (w & 3) + lane against blocks 4 (w >> 2) .. + 3
+            const int j = 64 * (w & 3) + lane;
+            const float4 ra = s_r.a[j], rb = s_r.b[j];
+            const uint32_t box = s_r.box[j];
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const int b = 4 * (w >> 2) + k;
+                const uint64_t m =
+                    __builtin_amdgcn_ballot_w64((uint32_t)j < cnt_u && block_reached(ra, rb, box, b, tx0p, ty0p));
+                if (lane == 0) s_reach[b][w & 3] = m;
+            }
+        }
+        __syncthreads();
+        uint64_t took = 0ull;
+        if (alive) {
+            int listed = 0;
+#pragma unroll
+            for (int q = 0; q < NB / 64; q++) {
+                const uint64_t m = uniform64(s_reach[w][q]);
+                if ((m >> lane) & 1ull)
+                    s_list[w][listed + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(64 * q + lane);
+                listed += __popcll(m);
+            }
+            if (lane < kSlots) s_list[w][listed + lane] = (uint16_t)NB;   // a last group of fewer entries
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll 1
+            for (int g = 0; g < listed && alive; g += kSlots) {
+                const uint16_t* l = &s_list[w][g];
+                const int j = l[row];
+                const float4 ra = s_r.a[j], rb = s_r.b[j];
+                const uint32_t box = s_r.box[j];
+                // the colours of the four slots, this row's channel
+                float col[kSlots];
+#pragma unroll
+                for (int s = 0; s < kSlots; s++) col[s] = reinterpret_cast<const float*>(&s_r.col[l[s]])[row];
+                float adx2, bdx;
+                blend_dx_terms(fpx - ra.x, ra, adx2, bdx);
+                const float power = blend_power(adx2, bdx, fpy - ra.y, rb.x);
+                const uint64_t pm = alive & __builtin_amdgcn_ballot_w64((box & sel) == sel) &
+                                    __builtin_amdgcn_ballot_w64(power <= 0.0f) &
+                                    __builtin_amdgcn_ballot_w64(power >= rb.z);
+                const uint64_t bm = pm & __builtin_amdgcn_ballot_w64(power < rb.w);
+                uint64_t okm = pm & ~bm;
+                if (bm) okm |= bm & __builtin_amdgcn_ballot_w64(blend_exact_test(power, rb.y));
+                if (!okm) continue;
+                // opacity 0 in the lanes that do not take their entry: it
+                // leaves the transmittance and the colour as they are (T is
+                // never below the stop's 1e-4)
+                const float al =
+                    __builtin_amdgcn_inverse_ballot_w64(okm) ? fminf(0.99f, rb.y * __expf(power)) : 0.0f;
+                float as[kSlots];
+                rows_all(al, as);
+                uint64_t own = 0ull;   // lanes whose own slot's entry is taken
+#pragma unroll
+                for (int s = 0; s < kSlots; s++) {
+                    const float Tn = T * (1.0f - as[s]);
+                    const uint64_t stop = alive & __builtin_amdgcn_ballot_w64(Tn < 1e-4f);
+                    const uint64_t takem = alive & ~stop;
+                    const bool take = __builtin_amdgcn_inverse_ballot_w64(takem);
+                    const float wgt = take ? as[s] * T : 0.0f;
+                    c += wgt * col[s];
+                    T = take ? Tn : T;
+                    alive = takem;
+                    own |= takem & (0xFFFFull << (16 * s));
+                }
+                own &= okm;
+                took |= own;
+                last = __builtin_amdgcn_inverse_ballot_w64(own) ? eb + (uint32_t)j + 1u : last;
+            }
+        }
+        if (lane == 0) {
+            if (alive) s_live[0] = 1u;
+            if (took) s_live[1] = 1u;
+        }
+        if (kSuper && tid == 0) {
+            if (blk >= sd.max_blocks) blk = 0xFFFFFFFFu;   // only when the pairs overflowed
+            if (eb != 0u && blk != 0xFFFFFFFFu) sd.prev[blk] = s_blk;
+            s_blk = blk;
+        }
+        __syncthreads();
+        if (kSuper) {
+            const uint32_t b = s_blk;
+            if ((uint32_t)tid < cnt_u && b != 0xFFFFFFFFu) sd.walked[(int64_t)b * kWalkBlock + tid] = myid;
+            if (s_live[1]) lastblk = b;   // the last contributor's so far
+        }
+        eb += cnt_u;
+        const bool more = s_live[0] != 0u;
+        __syncthreads();   // s_live is cleared for the next batch
+        if (!more) break;
+    }
+    const int64_t P = (int64_t)cam.W * cam.H;
+    if (px < cam.W && py < cam.H) {
+        const int64_t p = (int64_t)py * cam.W + px;
+        if (row < 3) image[row * P + p] = c + T * (row == 0 ? cam.bg[0] : row == 1 ? cam.bg[1] : cam.bg[2]);
+        else T_final[p] = T;
+    }
+    // the pixel's last contributor: the latest of its four slots
+    last = max(last, (uint32_t)__shfl_xor((int)last, 16));
+    last = max(last, (uint32_t)__shfl_xor((int)last, 32));
+    if (row == 3 && px < cam.W && py < cam.H) last_out[(int64_t)py * cam.W + px] = last;
+    __syncthreads();
+    if (last && row == 0) atomicMax(&s_walk, last);
+    __syncthreads();
+    if (tid == 0) {
+        const bool lost = kSuper && lastblk == 0xFFFFFFFFu;   // see k_blend_fwd
+        tile_walk[tile] = lost ? 0u : s_walk;
+        if (kSuper) sd.tile_blk[tile] = lost ? (uint32_t)tile : lastblk;
+    }
+}
+
+template <bool kSuper, bool kRecords, bool kOpacity>
+__global__ __launch_bounds__(kNarrowThreads) void k_blend_bwd_narrow(
+    CamDev cam, int ntiles, const uint2* __restrict__ ranges, const uint32_t* __restrict__ vals,
+    const float4* __restrict__ rec, const float* __restrict__ d_image, const float* __restrict__ T_final,
+    const uint32_t* __restrict__ last_in, const uint32_t* __restrict__ tile_walk, const uint32_t* __restrict__ walk_off,
+    float* __restrict__ grec, uint32_t grec_cap, float* __restrict__ accum, SuperDev sd) {
+    constexpr int NT = kNarrowThreads, NW = kNarrowWaves, KB = kBwdBatch;
+    static_assert(KB == 128 && kWalkBlock % KB == 0, "two words, and a batch lies in one walked block");
+    __shared__ NarrowRecs<KB> s_r;
+    __shared__ uint32_t s_id[KB];
+    __shared__ uint64_t s_reach[NW][2];
+    __shared__ uint16_t s_list[NW][KB + kSlots];
+    __shared__ float s_g[NW][9][KB + 1];   // per-wave sums, [wave][term][entry]; the last is no entry's
+    const int tile = blockIdx.x;
+    if (tile >= ntiles) return;
+    const uint32_t maxlast = tile_walk[tile];
+    if (maxlast == 0) return;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
+    const int tx0p = tx * kTile, ty0p = ty * kTile;
+    const int row = lane >> 4, pix = lane & 15;
+    const int lx = 4 * (w & 3) + (pix & 3), ly = 4 * (w >> 2) + (pix >> 2);
+    const int px = tx0p + lx, py = ty0p + ly;
+    const float fpx = (float)px, fpy = (float)py;
+    const uint32_t sel = (1u << lx) | (1u << (16 + ly));
+    const uint32_t start = kSuper ? 0u : ranges[tile].x;
+    uint32_t blk = kSuper ? sd.tile_blk[tile] : 0u;
+    const uint32_t woff = kRecords ? walk_off[tile] : 0u;
+    const int64_t P = (int64_t)cam.W * cam.H;
+    float T = 1.0f, g0 = 0.f, g1 = 0.f, g2 = 0.f;
+    uint32_t last = 0u;
+    if (px < cam.W && py < cam.H) {
+        const int64_t p = (int64_t)py * cam.W + px;
+        T = T_final[p];
+        last = last_in[p];
+        g0 = d_image[p];
+        g1 = d_image[P + p];
+        g2 = d_image[2 * P + p];
+    }
+    float gb = g0 * cam.bg[0] + g1 * cam.bg[1] + g2 * cam.bg[2];   // see k_blend_bwd
+    uint32_t wlast = last;   // the block's last contributor
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) wlast = max(wlast, (uint32_t)__shfl_xor((int)wlast, off));
+    wlast = __builtin_amdgcn_readfirstlane(wlast);
+    const int term = row_term(pix);
+    const int slot9 = term < 5 ? term : term + 1;   // index in the nine-term layout
+    if (tid == 0) s_r.put_none(KB);
+    for (int64_t jb = ((int64_t)(maxlast - 1) / KB) * KB; jb >= 0; jb -= KB) {
+        const uint32_t e = (uint32_t)jb + tid;
+        const int cnt = (int)min((int64_t)KB, (int64_t)maxlast - jb);
+        if (tid < cnt) {
+            const uint32_t id = kSuper ? sd.walked[(int64_t)blk * kWalkBlock + (e % kWalkBlock)] : vals[start + e];
+            s_id[tid] = id;
+            s_r.put(tid, rec, id, tx0p, ty0p);
+        }
+        if (kSuper && jb > 0 && jb % kWalkBlock == 0) blk = sd.prev[blk];
+        __syncthreads();
+        {
+            // entry 64 (w & 1) + lane against blocks 2 (w >> 1), + 1
+            const int j = 64 * (w & 1) + lane;
+            const float4 ra = s_r.a[j], rb = s_r.b[j];
+            const uint32_t box = s_r.box[j];
+#pragma unroll
+            for (int k = 0; k < 2; k++) {
+                const int b = 2 * (w >> 1) + k;
+                const uint64_t m = __builtin_amdgcn_ballot_w64(j < cnt && block_reached(ra, rb, box, b, tx0p, ty0p));
+                if (lane == 0) s_reach[b][w & 1] = m;
+            }
+        }
+        __syncthreads();
+        // the block's entries, last first, up to its last contributor; the
+        // words keep the entries that are visited
+        int listed = 0;
+        const int64_t before = (int64_t)wlast - jb;
+#pragma unroll
+        for (int q = 1; q >= 0; q--) {
+            uint64_t m = uniform64(s_reach[w][q]);
+            const int64_t left = before - 64 * q;
+            m = left <= 0 ? 0ull : left >= 64 ? m : m & ((1ull << left) - 1ull);
+            const int n = __popcll(m);
+            if ((m >> lane) & 1ull)
+                s_list[w][listed + n - 1 - __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(64 * q + lane);
+            listed += n;
+            if (lane == 0) s_reach[w][q] = m;
+        }
+        if (lane < kSlots) s_list[w][listed + lane] = (uint16_t)KB;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll 1
+        for (int g = 0; g < listed; g += kSlots) {
+            const int j = s_list[w][g + row];
+            const float4 ra = s_r.a[j], rb = s_r.b[j], rc = s_r.col[j];
+            const uint32_t box = s_r.box[j];
+            const float dx = fpx - ra.x, dy = fpy - ra.y;
+            float adx2, bdx;
+            blend_dx_terms(dx, ra, adx2, bdx);
+            const float power = blend_power(adx2, bdx, dy, rb.x);
+            const uint64_t pm = __builtin_amdgcn_ballot_w64((uint32_t)jb + (uint32_t)j < last) &
+                                __builtin_amdgcn_ballot_w64((box & sel) == sel) &
+                                __builtin_amdgcn_ballot_w64(power <= 0.0f) & __builtin_amdgcn_ballot_w64(power >= rb.z);
+            const uint64_t bm = pm & __builtin_amdgcn_ballot_w64(power < rb.w);
+            uint64_t okm = pm & ~bm;
+            if (bm) okm |= bm & __builtin_amdgcn_ballot_w64(blend_exact_test(power, rb.y));
+            float red = 0.f, redop = 0.f;
+            if (okm) {
+                const bool ok = __builtin_amdgcn_inverse_ballot_w64(okm);
+                const float G = __expf(power), raw = rb.y * G;
+                const float al = ok ? fminf(0.99f, raw) : 0.0f;   // zero: the pixel's state is kept
+                float as[kSlots], ds[kSlots];
+                rows_all(al, as);
+                rows_all(g0 * rc.x + g1 * rc.y + g2 * rc.z, ds);
+                float To = 0.f, d = 0.f;   // transmittance before, and colour term of, the lane's own slot
+#pragma unroll
+                for (int s = 0; s < kSlots; s++) {
+                    // T recovery T_i = T_{i+1} / (1 - alpha_i), with the hardware reciprocal (1 ulp)
+                    T *= __builtin_amdgcn_rcpf(1.0f - as[s]);
+                    const float di = ds[s] - gb;
+                    gb += as[s] * di;
+                    To = row == s ? T : To;
+                    d = row == s ? di : d;
+                }
+                const float wgt = al * To;
+                const float dal = To * d;
+                const bool unclamped =
+                    __builtin_amdgcn_inverse_ballot_w64(okm & __builtin_amdgcn_ballot_w64(raw < 0.99f));
+                const float dp = unclamped ? dal * raw : 0.0f;
+                const float ax = dp * dx, ay = dp * dy;   // terms: see k_blend_bwd
+                const float t8[8] = {ax, ay, ax * dx, ax * dy, ay * dy, g0 * wgt, g1 * wgt, g2 * wgt};
+                red = row_reduce_scatter8(t8, pix);
+                if (kOpacity) {
+                    float o = unclamped ? dal * G : 0.0f;
+                    o = dpp_add<0xB1, 0xF>(o);
+                    o = dpp_add<0x4E, 0xF>(o);
+                    o = dpp_add<0x141, 0xF>(o);
+                    redop = dpp_add<0x140, 0xF>(o);   // row_mirror
+                }
+            }
+            if ((pix & 1) == 0) s_g[w][slot9][j] = red;
+            if (kOpacity && pix == 1) s_g[w][5][j] = redop;
+        }
+        __syncthreads();
+        auto visited_by = [&](int e) -> uint32_t {
+            uint32_t on = 0u;
+#pragma unroll
+            for (int q = 0; q < NW; q++) on |= (uint32_t)((s_reach[q][e >> 6] >> (e & 63)) & 1ull) << q;
+            return on;
+        };
+        auto over_waves = [&](int k, int e, uint32_t on) -> float {
+            float v = 0.f;
+            for (; on; on &= on - 1u) v += s_g[__builtin_ctz(on)][k][e];
+            return v;
+        };
+        auto entry_term = [&](int k, int e, uint32_t on) -> float {
+            const float v = over_waves(k, e, on);
+            if (k <= 1) {
+                const float o = over_waves(1 - k, e, on);
+                const float4 w0 = s_r.a[e];
+                const float C = s_r.b[e].x;
+                return k == 0 ? w0.z * v + w0.w * o : w0.w * o + C * v;
+            }
+            return v * kConicScale[k];
+        };
+        for (int q = tid; q < 9 * cnt; q += NT) {
+            const int e = q / 9, k = q - 9 * e;
+            const bool none = !kOpacity && k == 5;
+            if (!kRecords && none) continue;
+            const uint32_t on = visited_by(e);
+            const float v = none ? 0.f : entry_term(k, e, on);
+            const uint32_t widx = woff + (uint32_t)jb + e;   // compact index of this walked entry
+            if (kRecords && widx < grec_cap)
+                grec[(int64_t)k * grec_cap + widx] = v;
+            else if (v != 0.f)
+                atomicAdd(accum + 9 * (int64_t)s_id[e] + k, v);
+        }
+        __syncthreads();
+    }
+}
+
 __device__ __forceinline__ void quat_rot_adj(const float q[4], const float g[9], float d[4]) {
     const float w = q[0], x = q[1], y = q[2], z = q[3];
     d[0] += 2.f * (-z * g[1] + y * g[2] + z * g[3] - x * g[5] - y * g[6] + x * g[7]);
@@ -1318,12 +1794,25 @@ void tile_order(const Launch& L, const uint2* ranges, const uint32_t* walk, int 
     if (L.prof) L.prof->end(L.st);
 }
 
+// Views of at most a tile per CU take the narrow blends.  Render / backward of
+// 50K surface Gaussians (us), 8 x 8 against narrow: 100 tiles 396 / 480
+// against 242 / 280, 256 tiles 290 / 336 against 192 / 202; of 50K uniform
+// ones: 100 tiles 150 / 94 against 120 / 82, 256 tiles 109 / 75 against 94 /
+// 60, but 400 tiles 108 / 71 against 114 / 88 and 1024 tiles 109 / 72 against
+// 150 / 147: with more tiles than CUs the 8 x 8 blends fill the SIMDs, and
+// evaluate a large Gaussian's pixels 64 at a time.
+bool narrow_tiles(int ntiles) { return ntiles <= 256; }
+
 void blend_forward(const Launch& L, const CamDev& cam, const uint2* ranges, const uint32_t* vals, const float4* rec,
                    float* image, float* T_final, uint32_t* last, uint32_t* tile_walk, const int* order, uint64_t* taken,
                    const SuperDev* supers) {
     const int ntiles = cam.tiles_x * cam.tiles_y;
     if (L.prof) L.prof->begin("blend_fwd", L.st);
-    if (supers) {
+    if (narrow_tiles(ntiles)) {
+        hipLaunchKernelGGL(supers ? k_blend_fwd_narrow<true> : k_blend_fwd_narrow<false>, dim3((unsigned)ntiles),
+                           dim3(kNarrowThreads), 0, L.st, cam, ntiles, ranges, vals, rec, image, T_final, last,
+                           tile_walk, supers ? *supers : SuperDev{});
+    } else if (supers) {
         const int nsuper = supers->supers_x * super_count_of(cam.tiles_y);
         const unsigned grid = (unsigned)((nsuper + 7) / 8 * 8 * kSuperDim * kSuperDim);
         hipLaunchKernelGGL((k_blend_fwd<true>), dim3(grid), dim3(kBlendThreads), 0, L.st, cam, ntiles, ranges, vals,
@@ -1342,6 +1831,17 @@ void blend_backward(const Launch& L, const CamDev& cam, const uint2* ranges, con
     const int ntiles = cam.tiles_x * cam.tiles_y;
     if (L.prof) L.prof->begin("blend_bwd", L.st);
     const bool records = ga.grec_cap > 0;
+    if (narrow_tiles(ntiles)) {
+        auto kern =
+            supers ? (want_opacity ? k_blend_bwd_narrow<true, false, true> : k_blend_bwd_narrow<true, false, false>)
+            : records ? (want_opacity ? k_blend_bwd_narrow<false, true, true> : k_blend_bwd_narrow<false, true, false>)
+                      : (want_opacity ? k_blend_bwd_narrow<false, false, true> : k_blend_bwd_narrow<false, false, false>);
+        hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(kNarrowThreads), 0, L.st, cam, ntiles, ranges, vals, rec,
+                           d_image, T_final, last, ga.tile_walk, ga.walk_off, ga.grec, (uint32_t)ga.grec_cap, accum,
+                           supers ? *supers : SuperDev{});
+        if (L.prof) L.prof->end(L.st);
+        return;
+    }
     // gradient records are kept with a tile-major list only
     auto kern = supers ? (want_opacity ? k_blend_bwd<true, false, true> : k_blend_bwd<true, false, false>)
                 : records ? (want_opacity ? k_blend_bwd<false, true, true> : k_blend_bwd<false, true, false>)

@@ -1,5 +1,6 @@
-"""GPU tests of the blend's quadrants: each wave of a tile's workgroup
-evaluates only the entries that can reach its 8 x 8 pixels, so a scene where
+"""GPU tests of the blend's quadrants and blocks: each wave of a tile's
+workgroup evaluates only the entries that can reach its 8 x 8 pixels (its
+4 x 4, in views of at most 256 tiles), so a scene where
 that test could go wrong (thin, tiny, faint and ill-conditioned Gaussians,
 ragged images) is compared with every Gaussian evaluated at every pixel of its
 box: by the oracle, and from the render's own records."""
@@ -61,7 +62,11 @@ def blend_records(key, box, rec, width, height, bg):
 
 
 @pytest.mark.parametrize("kind,n,width,height", [("thin", 3000, 97, 61), ("tiny", 4000, 64, 64), ("faint", 1500, 50, 37),
-                                                 ("long", 400, 120, 90), ("usual", 1200, 33, 17)])
+                                                 ("long", 400, 120, 90), ("usual", 1200, 33, 17),
+                                                 # past 256 tiles: the 8 x 8 quadrants
+                                                 ("thin", 2000, 257, 256), ("tiny", 3000, 300, 290),
+                                                 ("faint", 1500, 262, 259), ("long", 300, 272, 257),
+                                                 ("usual", 1000, 256, 256), ("usual", 1000, 258, 270)])
 def test_quadrants_take_every_contributor(kind, n, width, height):
     from paper_2403_01444_amd import gs3
     g = scene(kind, n, n)
