@@ -339,6 +339,10 @@ gs3_status gs3_adam(gs3_ctx* ctx, float* param, const float* grad, float* m, flo
  * clear gradient outputs between iterations. */
 gs3_status gs3_zero(gs3_ctx* ctx, float* dev, int64_t n);
 
+/* gs3_zero of `count` arrays, dev[k] with n[k] floats (dev and n: HOST
+ * arrays), in one launch per 16 of them. */
+gs3_status gs3_zero_many(gs3_ctx* ctx, float* const* dev, const int64_t* n, int32_t count);
+
 /* ---- Inspection (parity tests, benchmarks) ------------------------------- */
 
 /* Counts of the slot's last render (any pointer may be NULL): the number of

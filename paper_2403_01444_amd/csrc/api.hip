@@ -138,7 +138,7 @@ struct gs3_ctx {
     uint64_t* sup_ksum = nullptr;    // pairs per chunk
     uint2* bin_rect = nullptr;       // tile rectangles in depth order
     uint32_t* bin_goff = nullptr;    // first pair slots in depth order (record mode)
-    float* accum = nullptr;
+    float* accum = nullptr;          // 2D gradient terms, 9 per Gaussian; zero between backwards (its reader clears it)
     uint32_t* walk_off = nullptr;
     uint64_t* walk_total = nullptr;
     uint64_t* goff_total = nullptr;
@@ -327,6 +327,7 @@ gs3_status gs3_create(const gs3_config* cfg, gs3_ctx** out) {
     }
     Launch L{nullptr, nullptr};
     fill_u32(L, (uint32_t*)c->flags, 0u, 4);
+    fill_f32(L, c->accum, 0.f, 9 * N);
     if (c->n_params) {
         fill_f32(L, c->p, 0.f, c->n_params);
         fill_f32(L, c->g, 0.f, c->n_params);
@@ -367,8 +368,8 @@ gs3_status gs3_morton_order(gs3_ctx* c, const float* means, int64_t n, const flo
         return c->fail(GS3_EINVAL, "morton_order: bad arguments");
     if (n == 0) return GS3_OK;
     Launch L = c->L();
-    morton_codes(L, means, n, aabb_min, inv_extent, c->dkeys[0], c->dvals[0]);
-    const int r = radix_sort_u32(L, c->dkeys, c->dvals, n, 30, c->radix_hist, c->scan_tmp);
+    morton_codes(L, means, n, aabb_min, inv_extent, c->dkeys[0]);
+    const int r = radix_order_u32(L, c->dkeys[0], c->dkeys, c->dvals, n, 30, c->radix_hist, c->scan_tmp);
     if (hipMemcpyAsync(perm, c->dvals[r], (size_t)n * 4, hipMemcpyDeviceToDevice, c->st) != hipSuccess)
         return c->fail(GS3_EHIP, "morton_order: copy failed");
     return c->check_launch("morton_order");
@@ -774,9 +775,9 @@ gs3_status gs3_render_backward(gs3_ctx* c, int32_t slot, const float* d_image, c
     Slot& sl = c->slots[slot];
     if (!sl.valid) return c->fail(GS3_ESTATE, "render_backward before a successful render on this slot");
     Launch L = c->L();
-    const int64_t n = sl.g.n;
+    if ((out->vspace_grad == nullptr) != (out->vspace_count == nullptr))
+        return c->fail(GS3_EINVAL, "render_backward: vspace_grad and vspace_count go together");
     const int ntiles = sl.cam.tiles_x * sl.cam.tiles_y;
-    fill_f32(L, c->accum, 0.f, 9 * n);
     if (c->grec_cap > 0) scan_u32_to_u32(L, sl.tile_walk, ntiles, c->walk_off, c->walk_total, c->scan_tmp);
     GatherDev ga;
     ga.rect = sl.rect; ga.goff = sl.goff; ga.gpos = sl.gpos; ga.ranges = sl.ranges; ga.tile_walk = sl.tile_walk;
@@ -791,8 +792,6 @@ gs3_status gs3_render_backward(gs3_ctx* c, int32_t slot, const float* d_image, c
     gd.d_opac = out->d_opacity_logits; gd.d_sh = out->d_sh; gd.d_dmu = sl.g.dmu ? out->d_dmu : nullptr;
     gd.d_dq = sl.g.dq ? out->d_dq : nullptr; gd.d_uv = out->d_uv; gd.d_conic = out->d_conic;
     gd.d_opacity = out->d_opacity; gd.d_rgb = out->d_rgb;
-    if ((out->vspace_grad == nullptr) != (out->vspace_count == nullptr))
-        return c->fail(GS3_EINVAL, "render_backward: vspace_grad and vspace_count go together");
     gd.vgrad = out->vspace_grad; gd.vcount = out->vspace_count;
     preprocess_backward(L, sl.g, sl.cam, c->accum, ga, gd);
     return c->check_launch("render_backward");
@@ -880,6 +879,15 @@ gs3_status gs3_zero(gs3_ctx* c, float* dev, int64_t n) {
     if (n < 0 || (n > 0 && !dev)) return c->fail(GS3_EINVAL, "zero: bad arguments");
     fill_f32(c->L(), dev, 0.f, n);
     return c->check_launch("zero");
+}
+
+gs3_status gs3_zero_many(gs3_ctx* c, float* const* dev, const int64_t* n, int32_t count) {
+    if (!c) return GS3_EINVAL;
+    if (count < 0 || (count > 0 && (!dev || !n))) return c->fail(GS3_EINVAL, "zero_many: bad arguments");
+    for (int32_t k = 0; k < count; k++)
+        if (n[k] < 0 || (n[k] > 0 && !dev[k])) return c->fail(GS3_EINVAL, "zero_many: bad arguments");
+    for (int32_t k = 0; k < count; k += kZeroMany) zero_many(c->L(), dev + k, n + k, std::min(count - k, kZeroMany));
+    return c->check_launch("zero_many");
 }
 
 /* ---- inspection ----------------------------------------------------------- */

@@ -35,17 +35,21 @@ int radix_sort_u32(const Launch& L, uint32_t* keys[2], uint32_t* vals[2], int64_
                    uint64_t* tmp);
 int radix_sort_u64(const Launch& L, uint64_t* keys[2], uint32_t* vals[2], int64_t n, int bits, uint32_t* hist,
                    uint64_t* tmp);
-// The same sort of keys_in (left unchanged) with the positions 0..n-1 as
-// values: the order that sorts keys_in, without copying the keys first.
+// The same sort of keys_in with the positions 0..n-1 as values: the order
+// that sorts keys_in, in vals[the result] (the sorted keys may not be
+// written).  keys_in is left unchanged unless it is keys[0].
 int radix_order_u32(const Launch& L, const uint32_t* keys_in, uint32_t* keys[2], uint32_t* vals[2], int64_t n,
                     int bits, uint32_t* hist, uint64_t* tmp);
 
 void morton_codes(const Launch& L, const float* means, int64_t n, const float lo[3], const float inv[3],
-                  uint32_t* code, uint32_t* idx);
+                  uint32_t* code);
 void gather_rows(const Launch& L, const float* src, const uint32_t* perm, int64_t n, int rf, float* dst);
 
 void fill_u32(const Launch& L, uint32_t* p, uint32_t v, int64_t n);
 void fill_f32(const Launch& L, float* p, float v, int64_t n);
+// p[k][0, n[k]) = 0 for k < count <= kZeroMany, in one launch
+constexpr int kZeroMany = 16;
+void zero_many(const Launch& L, float* const* p, const int64_t* n, int count);
 void iota_u32(const Launch& L, uint32_t* p, int64_t n);
 // *out (one u64, device) = sum of the n values
 void sum_u32(const Launch& L, const uint32_t* a, int64_t n, uint64_t* out);
@@ -180,7 +184,8 @@ struct GradsDev {
     float *d_uv, *d_conic, *d_opacity, *d_rgb;
     float *vgrad, *vcount;   // view-space gradient norm and visibility count (accumulated)
 };
-void preprocess_backward(const Launch& L, const GaussDev& g, const CamDev& cam, const float* accum,
+// accum (9 per Gaussian) is read and cleared
+void preprocess_backward(const Launch& L, const GaussDev& g, const CamDev& cam, float* accum,
                          const GatherDev& ga, const GradsDev& out);
 void debug_keys(const Launch& L, const uint2* ranges, const uint32_t* vals, const uint32_t* key, int ntiles,
                 uint64_t* keys_out);

@@ -1484,18 +1484,22 @@ __device__ __forceinline__ void quat_rot_adj(const float q[4], const float g[9],
 // inverse, EWA (with J depending on the camera-space mean), the covariance,
 // the colour (SH and its view direction) and the transform.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_preprocess_bwd(GaussDev g, CamDev cam, const float* __restrict__ accum,
+__global__ __launch_bounds__(256) void k_preprocess_bwd(GaussDev g, CamDev cam, float* __restrict__ accum,
                                                         GatherDev ga, GradsDev out) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= g.n) return;
+    // the blend's sums, left zero for the next backward
+    float a9[9];
+    for (int k = 0; k < 9; k++) {
+        a9[k] = accum[9 * i + k];
+        accum[9 * i + k] = 0.f;
+    }
     Geo o;
     if (!geo_forward(g, cam, i, o)) return;
     ColourCtx cc;
     colour_forward(g, cam, i, o, cc);
-    // the nine 2D gradient terms: fallback atomics plus this Gaussian's walked
-    // entries, visited in its tile-rectangle order
-    float a9[9];
-    for (int k = 0; k < 9; k++) a9[k] = accum[9 * i + k];
+    // the nine 2D gradient terms: the sums (records: those past the buffer)
+    // plus this Gaussian's walked entries, visited in its tile-rectangle order
     if (ga.grec_cap > 0) {
         const uint2 r = ga.rect[i];
         const int tx0 = r.x & 0xFFFF, ty0 = r.x >> 16, tx1 = r.y & 0xFFFF, ty1 = r.y >> 16;
@@ -1852,7 +1856,7 @@ void blend_backward(const Launch& L, const CamDev& cam, const uint2* ranges, con
     if (L.prof) L.prof->end(L.st);
 }
 
-void preprocess_backward(const Launch& L, const GaussDev& g, const CamDev& cam, const float* accum,
+void preprocess_backward(const Launch& L, const GaussDev& g, const CamDev& cam, float* accum,
                          const GatherDev& ga, const GradsDev& out) {
     if (g.n <= 0) return;
     if (L.prof) L.prof->begin("preprocess_bwd", L.st);

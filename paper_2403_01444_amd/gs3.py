@@ -70,7 +70,7 @@ EXPORTED = ("gs3_create", "gs3_destroy", "gs3_last_error", "gs3_set_stream", "gs
             "gs3_ntc_load", "gs3_ntc_save", "gs3_ntc_init", "gs3_ntc_state_bytes", "gs3_ntc_save_state",
             "gs3_ntc_load_state", "gs3_ntc_forward", "gs3_ntc_backward", "gs3_ntc_prepare", "gs3_ntc_step",
             "gs3_ntc_grads", "gs3_ntc_zero_grads", "gs3_warmup_loss", "gs3_render", "gs3_render_backward", "gs3_transform_bake", "gs3_select", "gs3_spawn",
-            "gs3_loss", "gs3_loss_noalloc", "gs3_adam", "gs3_zero", "gs3_debug_counts", "gs3_debug_pairs", "gs3_debug_ranges",
+            "gs3_loss", "gs3_loss_noalloc", "gs3_adam", "gs3_zero", "gs3_zero_many", "gs3_debug_counts", "gs3_debug_pairs", "gs3_debug_ranges",
             "gs3_debug_gaussians", "gs3_debug_pixels", "gs3_check_flags", "gs3_workspace_bytes", "gs3_profile_enable",
             "gs3_profile_only", "gs3_profile_reset", "gs3_profile_query")
 
@@ -116,6 +116,7 @@ def lib():
         "gs3_loss_noalloc": [vp, vp, i32, i32, f32, vp, vp, vp],
         "gs3_adam": [vp, vp, vp, vp, vp, i64, i32, f32, f32, f32, f32],
         "gs3_zero": [vp, vp, i64],
+        "gs3_zero_many": [vp, C.POINTER(vp), C.POINTER(i64), i32],
         "gs3_debug_counts": [vp, i32, C.POINTER(i64), C.POINTER(i64), C.POINTER(i64), C.POINTER(i32)],
         "gs3_debug_pairs": [vp, i32, vp, vp, i64],
         "gs3_debug_ranges": [vp, i32, vp],
@@ -391,6 +392,13 @@ def gs3_zero(h, t):
     _check(h, lib().gs3_zero(h, _ptr(t, name="zero target"), t.numel()))
 
 
+def gs3_zero_many(h, tensors):
+    k = len(tensors)
+    ptrs = (C.c_void_p * k)(*[_ptr(t, name="zero target") for t in tensors])
+    counts = (C.c_int64 * k)(*[t.numel() for t in tensors])
+    _check(h, lib().gs3_zero_many(h, ptrs, counts, k))
+
+
 def gs3_debug_counts(h, slot):
     """(pairs K, overflow flag, sum over pixels of n_contrib, sum over tiles
     of the longest walk); the sums are -1 when the slot holds no render."""
@@ -645,8 +653,7 @@ class Context:
         gs3_adam(self.h, param, grad, m, v, step, lr, beta1, beta2, eps)
 
     def zero(self, *tensors):
-        for t in tensors:
-            gs3_zero(self.h, t)
+        gs3_zero_many(self.h, tensors)
 
     # -- inspection
     def debug_counts(self, slot=0):
