@@ -818,7 +818,11 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend_bwd(CamDev cam, int nti
             const int t = tid - KB, wd = t / NW;
             const int64_t word = (kSuper ? (int64_t)blk * (kWalkBlock / 64) + ((jb % kWalkBlock) >> 6)
                                          : taken_word(start, tile) + (jb >> 6)) + wd;
-            s_taken[wd][t % NW] = (uint32_t)jb + 64u * wd < maxlast ? taken[word * NW + t % NW] : 0ull;
+            // entries past the last contributor are not staged: the forward's
+            // bit for an entry it visited before any was taken may lie there
+            const int64_t left = (int64_t)maxlast - jb - 64 * wd;
+            const uint64_t some = left >= 64 ? ~0ull : left > 0 ? (1ull << left) - 1ull : 0ull;
+            s_taken[wd][t % NW] = some ? taken[word * NW + t % NW] & some : 0ull;
         }
         if (kSuper && jb > 0 && jb % kWalkBlock == 0) blk = sd.prev[blk];
         __syncthreads();

@@ -29,6 +29,18 @@ def scene(kind, n, seed):
     elif kind == "long":          # covariances of condition 1e5 and more: the box alone decides
         g.log_scales[:, 0] = 0.5
         g.log_scales[:, 1:] = -7.0
+    elif kind == "wall":          # every pixel stops at the last of them, a tile's quadrants at different entries
+        cam = synth.look_at_camera(64, 64, azimuth_deg=-9.0)
+        zc = cam.world_to_cam[2, :3]
+        depth = np.concatenate([np.linspace(2.0, 2.3, 64), rng.uniform(2.5, 3.5, n - 65), [4.0]])
+        off = rng.uniform(-1.5, 1.5, (n, 3)) * (np.arange(n) >= 64)[:, None] * (np.arange(n) < n - 1)[:, None]
+        off -= (off @ zc)[:, None] * zc
+        g.means = (cam.cam_pos + depth[:, None] * zc + off).astype(np.float32)
+        big = (np.arange(n) < 64) | (np.arange(n) == n - 1)
+        g.log_scales = np.where(big, 3.4, -4.0)[:, None].repeat(3, 1).astype(np.float32)
+        p = np.where(big, 0.125, 0.02)
+        p[-1] = 0.995
+        g.opacity_logits = np.log(p / (1 - p)).astype(np.float32)
     return g
 
 
@@ -101,3 +113,36 @@ def test_quadrants_take_every_contributor(kind, n, width, height):
         if projected:
             check_grads(grads, rb, f"{kind} {mode}")
         ctx.close()
+
+
+@pytest.mark.parametrize("log2", [0, 18])
+@pytest.mark.parametrize("scene_name,n,width,height", [("surfaces", 6000, 330, 300), ("usual", 3000, 330, 300),
+                                                       ("wall", 900, 330, 300), ("thin", 900, 330, 300),
+                                                       ("surfaces", 6000, 120, 100), ("wall", 300, 120, 100)])
+def test_blends_read_only_what_they_stage(scene_name, n, width, height, log2):
+    """The blends do not depend on what earlier kernels left in LDS: with LDS
+    full of NaN (the loss of NaN images leaves them there) the image and the
+    gradients are the ones without."""
+    from paper_2403_01444_amd import gs3
+    g = synth.surface_scene(n, 1, 3).gaussians if scene_name == "surfaces" else scene(scene_name, n, 3)
+    cam = synth.look_at_camera(width, height, azimuth_deg=-9.0)
+    ctx = gs3.Context(g.n, 1 << 20, 1024, 1024, grad_record_log2=log2)
+    gg = gs3.GaussiansGPU.from_host(g)
+    nan = torch.full((3, 1024, 1024), float("nan"), device="cuda")
+    clean = torch.rand((3, 1024, 1024), device="cuda")
+    d = torch.from_numpy(np.random.default_rng(2).normal(size=(3, height, width)).astype(np.float32)).cuda()
+    out = []
+    for image in (clean, nan, nan, nan):
+        ctx.loss(image, image)
+        img = ctx.render(gg, cam).clone()
+        grads = {"d_uv": ctx.zeros(n, 2), "d_conic": ctx.zeros(n, 3), "d_opacity": ctx.zeros(n), "d_rgb": ctx.zeros(n, 3)}
+        torch.cuda.synchronize()
+        ctx.loss(image, image)
+        ctx.render_backward(d, grads)
+        out.append((img, grads))
+    for img, grads in out[1:]:
+        assert torch.equal(img, out[0][0])
+        for k, v in grads.items():
+            # the sums' order varies (float atomics): see test_gpu_supers.py
+            assert float((v - out[0][1][k]).abs().max()) <= 2e-4 * float(out[0][1][k].abs().max()), k
+    ctx.close()
