@@ -3,16 +3,23 @@
 // SSIM uses an 11 x 11 Gaussian window (sigma 1.5) with zero padding, per
 // channel, means over 3 x H x W.  The window is separable: each workgroup
 // loads a 42 x 42 halo tile for a 32 x 32 output tile into LDS, filters the
-// rows (a thread takes four adjacent outputs of a halo row, so it reads 14
-// inputs and forms their products once), then the columns (a thread takes
-// four outputs of one column from 14 row-filtered values).  Forward: five
-// filtered maps (the two means, then the three second moments, through the
-// same LDS) -> SSIM and its partial derivatives with respect to the
-// filtered mean, E[x^2] and E[xy] at each pixel.  Backward: the adjoint of a
-// zero-padded correlation with a symmetric window is the same correlation,
-// so the three partial maps are filtered again (one at a time) and combined
-// with x and y.  Keeping few row-filtered maps in LDS at once lets five
-// workgroups share a CU.
+// rows (a thread takes eight adjacent outputs of a halo row), then the columns
+// (a thread takes four outputs of one column from 14 row-filtered values).
+// Forward: five filtered maps (the two means and the three second moments) ->
+// SSIM and its partial derivatives with respect to the filtered mean, E[x^2]
+// and E[xy] at each pixel.  Backward: the adjoint of a zero-padded correlation
+// with a symmetric window is the same correlation, so the three partial maps
+// are filtered again and combined with x and y.  A workgroup's time is its
+// chain of loads, passes and barriers, so the loads are all in flight
+// together, every map is filtered between the same three barriers, and
+// row-filtered maps take the halo tiles' place in LDS, which leaves room for
+// five workgroups on a CU.  Each XCD takes a band of the image (tile_pos).
+// 1352 x 1014: forward 54 -> 39, backward 36 -> 23 us against maps filtered in
+// turns, a load round at a time and tiles dealt round the XCDs (the band
+// alone: 63 -> 53 for the two; tiles of 24, 40 and 54 rows were 15, 11 and
+// 10% slower).  The 60 B a pixel and channel read and written take 52 us at
+// the rate of a large copy; the forward's products, about 170 a pixel and
+// channel with the halo rows, take it past its share of that.
 #include <mutex>
 
 #include "../../include/gs3.h"
@@ -27,10 +34,63 @@ constexpr int kTH = 32;              // output tile height
 constexpr int kR = 5;                // window radius
 constexpr int kHW = kTW + 2 * kR;    // halo tile width (42)
 constexpr int kHH = kTH + 2 * kR;    // halo tile height (42)
-constexpr int kQ = 4;                // outputs per thread in each filter pass
-constexpr int kIn = kQ + 2 * kR;     // inputs per thread in each filter pass (14)
-constexpr int kQR = 8;               // outputs per task of the row filters: 42 x 4 tasks, one round of 256 threads
+constexpr int kQ = 4;                // outputs per thread of the column filters
+constexpr int kIn = kQ + 2 * kR;     // their inputs (14)
+constexpr int kQR = 8;               // outputs per task of the row filters
 constexpr int kInR = kQR + 2 * kR;   // their inputs (18)
+static_assert(kHH * (kTW / kQR) <= 256, "at most a row task for each thread");
+static_assert(256 / kTW * kQ == kTH, "the column filters cover the tile");
+constexpr int kLR = 256 / kHW;                // halo rows loaded at a time: 252 threads, one per (row, column)
+constexpr int kLN = (kHH + kLR - 1) / kLR;    // rounds, all in flight together
+
+// Output tile of workgroup b on the 1-D grid of tile_grid(tx, ty) workgroups:
+// workgroup b runs on XCD b mod 8, which gets a contiguous eighth of the
+// tiles, so that most of a halo tile's overlap with its neighbours (1.7 times
+// the tile) is in the XCD's L2.  False past the last tile.
+struct TilePos {
+    int bx, by, ch, t;
+};
+__device__ __forceinline__ bool tile_pos(int tx, int ty, TilePos& p) {
+    const int per = gridDim.x >> 3;
+    p.t = (int)(blockIdx.x & 7u) * per + (int)(blockIdx.x >> 3);
+    p.bx = p.t % tx;
+    p.by = p.t / tx % ty;
+    p.ch = p.t / (tx * ty);
+    return p.t < 3 * tx * ty;
+}
+unsigned tile_grid(int tx, int ty) { return (unsigned)((3 * tx * ty + 7) / 8 * 8); }
+
+// The halo tiles of NM planes around output tile (bx, by), zero outside the
+// image.  Every load is issued before the first is stored to LDS: with a load
+// and its store per round the rounds' latencies add up, half of a workgroup's
+// time.
+template <int NM>
+__device__ __forceinline__ void load_halo(const float* const (&src)[NM], int H, int W, int bx, int by,
+                                          float (*dst)[kHH][kHW + 1]) {
+    const int c = threadIdx.x % kHW, r0 = threadIdx.x / kHW;
+    if (r0 >= kLR) return;
+    const int gx = bx * kTW + c - kR, gy0 = by * kTH + r0 - kR;
+    const bool inx = gx >= 0 && gx < W;
+    float v[NM][kLN];
+#pragma unroll
+    for (int k = 0; k < kLN; k++) {
+        const int gy = gy0 + kLR * k;
+        const bool in = inx && gy >= 0 && gy < H;
+        const int64_t p = in ? (int64_t)gy * W + gx : 0;   // pixel 0 is always there
+#pragma unroll
+        for (int m = 0; m < NM; m++) v[m][k] = src[m][p];
+#pragma unroll
+        for (int m = 0; m < NM; m++) v[m][k] = in ? v[m][k] : 0.f;
+    }
+#pragma unroll
+    for (int k = 0; k < kLN; k++) {
+        const int r = r0 + kLR * k;
+        if (r < kHH) {
+#pragma unroll
+            for (int m = 0; m < NM; m++) dst[m][r][c] = v[m][k];
+        }
+    }
+}
 constexpr float kC1 = 0.01f * 0.01f;
 constexpr float kC2 = 0.03f * 0.03f;
 
@@ -110,62 +170,21 @@ __global__ __launch_bounds__(256) void k_l1(const float* __restrict__ x, const f
     block_sum2(l1, 0.0, bsum + 2 * (int64_t)blockIdx.x);
 }
 
-// Row filter: for the tasks t = threadIdx.x, threadIdx.x + 256, ... of the
-// 42 x 4 (halo row r, column octet q) tasks, outputs at columns 8 q .. 8 q + 7
-// of the NM maps src[m] -> dst[m] (one round of tasks: 168 of the 256
-// threads, each reading 18 inputs per map).
-template <int NM>
-__device__ __forceinline__ void row_filter(const Win& win, const float (*src)[kHH][kHW + 1],
-                                           float (*dst)[kHH][kTW + 1]) {
-    for (int t = threadIdx.x; t < kHH * (kTW / kQR); t += 256) {
-        const int r = t / (kTW / kQR), c0 = (t % (kTW / kQR)) * kQR;
+// Row filter: out[o] for the eight outputs that start at in[0].
+__device__ __forceinline__ void row_filter(const Win& win, const float in[kInR], float out[kQR]) {
 #pragma unroll
-        for (int m = 0; m < NM; m++) {
-            float u[kInR];
+    for (int o = 0; o < kQR; o++) {
+        float a = 0.f;
 #pragma unroll
-            for (int i = 0; i < kInR; i++) u[i] = src[m][r][c0 + i];
-#pragma unroll
-            for (int o = 0; o < kQR; o++) {
-                float a = 0.f;
-#pragma unroll
-                for (int j = 0; j < 11; j++) a += win.g[j] * u[o + j];
-                dst[m][r][c0 + o] = a;
-            }
-        }
+        for (int j = 0; j < 11; j++) a += win.g[j] * in[o + j];
+        out[o] = a;
     }
 }
 
-// Row filter of the three second moments x^2, y^2, x y of src[0] = x and
-// src[1] = y (same task layout as row_filter).
-__device__ __forceinline__ void row_filter_second(const Win& win, const float (*src)[kHH][kHW + 1],
-                                                  float (*dst)[kHH][kTW + 1]) {
-    for (int t = threadIdx.x; t < kHH * (kTW / kQR); t += 256) {
-        const int r = t / (kTW / kQR), c0 = (t % (kTW / kQR)) * kQR;
-        float u[kInR], v[kInR];
-#pragma unroll
-        for (int i = 0; i < kInR; i++) {
-            u[i] = src[0][r][c0 + i];
-            v[i] = src[1][r][c0 + i];
-        }
-#pragma unroll
-        for (int o = 0; o < kQR; o++) {
-            float a2 = 0.f, a3 = 0.f, a4 = 0.f;
-#pragma unroll
-            for (int j = 0; j < 11; j++) {
-                const float uj = u[o + j], vj = v[o + j], wj = win.g[j];
-                a2 += wj * uj * uj;
-                a3 += wj * vj * vj;
-                a4 += wj * uj * vj;
-            }
-            dst[0][r][c0 + o] = a2;
-            dst[1][r][c0 + o] = a3;
-            dst[2][r][c0 + o] = a4;
-        }
-    }
-}
-
-// column filter of map m: outputs rows 4 g .. 4 g + 3 of column c
-__device__ __forceinline__ void col_filter(const Win& win, const float (*src)[kTW + 1], int g, int c, float out[kQ]) {
+// column filter of a map with rows of S floats: outputs rows 4 g .. 4 g + 3 of
+// column c
+template <int S>
+__device__ __forceinline__ void col_filter(const Win& win, const float (*src)[S], int g, int c, float out[kQ]) {
     float u[kIn];
 #pragma unroll
     for (int i = 0; i < kIn; i++) u[i] = src[kQ * g + i][c];
@@ -180,34 +199,64 @@ __device__ __forceinline__ void col_filter(const Win& win, const float (*src)[kT
 
 __global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ x, const float* __restrict__ y, int H,
                                                   int W, Win win, float* __restrict__ maps, double* __restrict__ bsum) {
-    __shared__ float s_img[2][kHH][kHW + 1];   // x, y halo tiles
-    __shared__ float sh[3][kHH][kTW + 1];      // row-filtered maps, three at a time
+    __shared__ float s_img[2][kHH][kHW + 1];   // x, y halo tiles, then the row-filtered means
+    __shared__ float sh[3][kHH][kTW + 1];      // row-filtered x^2, y^2 and x y
     __shared__ float s_w[2][4];
-    const int ch = blockIdx.z;
-    const int bx = blockIdx.x, by = blockIdx.y;
+    TilePos tp;
+    if (!tile_pos((W + kTW - 1) / kTW, (H + kTH - 1) / kTH, tp)) return;
+    const int ch = tp.ch, bx = tp.bx, by = tp.by;
     const int64_t P = (int64_t)H * W;
     const float* xc = x + ch * P;
     const float* yc = y + ch * P;
-    for (int k = threadIdx.x; k < kHH * kHW; k += 256) {
-        const int r = k / kHW, c = k % kHW;
-        const int gy = by * kTH + r - kR, gx = bx * kTW + c - kR;
-        const bool in = gy >= 0 && gy < H && gx >= 0 && gx < W;
-        s_img[0][r][c] = in ? xc[(int64_t)gy * W + gx] : 0.f;
-        s_img[1][r][c] = in ? yc[(int64_t)gy * W + gx] : 0.f;
+    const float* const planes[2] = {xc, yc};
+    load_halo(planes, H, W, bx, by, s_img);
+    __syncthreads();
+    const int c = threadIdx.x % kTW, g = threadIdx.x / kTW;
+    float ad[kQ];   // |x - y| at the thread's pixels, before their tile gives way to the means
+#pragma unroll
+    for (int o = 0; o < kQ; o++)
+        ad[o] = fabsf(s_img[0][kQ * g + o + kR][c + kR] - s_img[1][kQ * g + o + kR][c + kR]);
+    {
+        const int r = threadIdx.x / (kTW / kQR), c0 = (threadIdx.x % (kTW / kQR)) * kQR;
+        const bool task = r < kHH;
+        float fx[kQR], fy[kQR];
+        if (task) {
+            float u[kInR], v[kInR];
+#pragma unroll
+            for (int i = 0; i < kInR; i++) {
+                u[i] = s_img[0][r][c0 + i];
+                v[i] = s_img[1][r][c0 + i];
+            }
+            row_filter(win, u, fx);
+            row_filter(win, v, fy);
+#pragma unroll
+            for (int o = 0; o < kQR; o++) {
+                float a2 = 0.f, a3 = 0.f, a4 = 0.f;
+#pragma unroll
+                for (int j = 0; j < 11; j++) {
+                    const float uj = u[o + j], vj = v[o + j], wj = win.g[j];
+                    a2 += wj * uj * uj;
+                    a3 += wj * vj * vj;
+                    a4 += wj * uj * vj;
+                }
+                sh[0][r][c0 + o] = a2;
+                sh[1][r][c0 + o] = a3;
+                sh[2][r][c0 + o] = a4;
+            }
+        }
+        __syncthreads();
+        if (task) {
+#pragma unroll
+            for (int o = 0; o < kQR; o++) {
+                s_img[0][r][c0 + o] = fx[o];
+                s_img[1][r][c0 + o] = fy[o];
+            }
+        }
     }
     __syncthreads();
-    // the means first, then the second moments through the same LDS maps
-    // (their products formed in the second row pass): three maps of LDS
-    // instead of five leave room for five workgroups per CU
-    const int c = threadIdx.x % kTW, g = threadIdx.x / kTW;
     float mx[kQ], my[kQ], exx[kQ], eyy[kQ], exy[kQ];
-    row_filter<2>(win, s_img, sh);
-    __syncthreads();
-    col_filter(win, sh[0], g, c, mx);
-    col_filter(win, sh[1], g, c, my);
-    __syncthreads();
-    row_filter_second(win, s_img, sh);
-    __syncthreads();
+    col_filter(win, s_img[0], g, c, mx);
+    col_filter(win, s_img[1], g, c, my);
     col_filter(win, sh[0], g, c, exx);
     col_filter(win, sh[1], g, c, eyy);
     col_filter(win, sh[2], g, c, exy);
@@ -233,7 +282,7 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ x, c
             maps[N + p] = dS_db2;
             maps[2 * N + p] = 2.f * dS_da2;
             s_sum += S;
-            l1 += fabsf(s_img[0][r + kR][c + kR] - s_img[1][r + kR][c + kR]);
+            l1 += ad[o];
         }
     }
     // block sums: float within a wave, double across the four waves
@@ -248,7 +297,7 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ x, c
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        const int64_t blk = ((int64_t)ch * gridDim.y + by) * gridDim.x + bx;
+        const int64_t blk = tp.t;
         bsum[2 * blk] = ((double)s_w[0][0] + (double)s_w[0][1]) + ((double)s_w[0][2] + (double)s_w[0][3]);
         bsum[2 * blk + 1] = ((double)s_w[1][0] + (double)s_w[1][1]) + ((double)s_w[1][2] + (double)s_w[1][3]);
     }
@@ -258,30 +307,41 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(const float* __restrict__ x, c
                                                   int W, Win win, float lam, const float* __restrict__ maps,
                                                   float* __restrict__ d, const double* __restrict__ bsum,
                                                   int64_t nblk, float* __restrict__ loss, int* __restrict__ nonfinite) {
-    __shared__ float sm[3][kHH][kHW + 1];
-    __shared__ float sh[1][kHH][kTW + 1];   // one row-filtered map at a time
-    const int ch = blockIdx.z;
-    const int bx = blockIdx.x, by = blockIdx.y;
+    __shared__ float sm[3][kHH][kHW + 1];   // the partial maps' halo tiles, then their row-filtered forms
+    TilePos tp;
+    if (!tile_pos((W + kTW - 1) / kTW, (H + kTH - 1) / kTH, tp)) return;
+    const int ch = tp.ch, bx = tp.bx, by = tp.by;
     const int64_t P = (int64_t)H * W, N = 3 * P;
-    for (int k = threadIdx.x; k < kHH * kHW; k += 256) {
-        const int r = k / kHW, c = k % kHW;
-        const int gy = by * kTH + r - kR, gx = bx * kTW + c - kR;
-        const bool in = gy >= 0 && gy < H && gx >= 0 && gx < W;
-        const int64_t p = ch * P + (int64_t)gy * W + gx;
-        sm[0][r][c] = in ? maps[p] : 0.f;
-        sm[1][r][c] = in ? maps[N + p] : 0.f;
-        sm[2][r][c] = in ? maps[2 * N + p] : 0.f;
-    }
+    const float* const planes[3] = {maps + ch * P, maps + N + ch * P, maps + 2 * N + ch * P};
+    load_halo(planes, H, W, bx, by, sm);
+    __syncthreads();
     const int c = threadIdx.x % kTW, g = threadIdx.x / kTW;
-    float fm[kQ], fe[kQ], ff[kQ];
-    float* const fout[3] = {fm, fe, ff};
+    {
+        const int r = threadIdx.x / (kTW / kQR), c0 = (threadIdx.x % (kTW / kQR)) * kQR;
+        const bool task = r < kHH;
+        float f[3][kQR];
+        if (task) {
 #pragma unroll
-    for (int m = 0; m < 3; m++) {
+            for (int m = 0; m < 3; m++) {
+                float u[kInR];
+#pragma unroll
+                for (int i = 0; i < kInR; i++) u[i] = sm[m][r][c0 + i];
+                row_filter(win, u, f[m]);
+            }
+        }
         __syncthreads();
-        row_filter<1>(win, sm + m, sh);
-        __syncthreads();
-        col_filter(win, sh[0], g, c, fout[m]);
+        if (task) {
+#pragma unroll
+            for (int m = 0; m < 3; m++)
+#pragma unroll
+                for (int o = 0; o < kQR; o++) sm[m][r][c0 + o] = f[m][o];
+        }
     }
+    __syncthreads();
+    float fm[kQ], fe[kQ], ff[kQ];
+    col_filter(win, sm[0], g, c, fm);
+    col_filter(win, sm[1], g, c, fe);
+    col_filter(win, sm[2], g, c, ff);
     const int gx = bx * kTW + c;
     const float invN = 1.0f / (float)N;
 #pragma unroll
@@ -295,7 +355,7 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(const float* __restrict__ x, c
     }
     // the loss value: the forward wrote every block's sums before this
     // launch, so one block adds them up here instead of a launch of its own
-    if (bx == 0 && by == 0 && ch == 0) finalize_sums(bsum, nblk, N, lam, loss, nonfinite);
+    if (tp.t == 0) finalize_sums(bsum, nblk, N, lam, loss, nonfinite);
 }
 
 
@@ -336,9 +396,10 @@ void loss_forward_backward(const Launch& L, const float* x, const float* y, int 
                            nonfinite);
     } else {
         const Win win = make_window();
-        dim3 grid((W + kTW - 1) / kTW, (H + kTH - 1) / kTH, 3);
+        const int tx = (W + kTW - 1) / kTW, ty = (H + kTH - 1) / kTH;
+        const dim3 grid(tile_grid(tx, ty));
         hipLaunchKernelGGL(k_ssim_fwd, grid, dim3(256), 0, L.st, x, y, H, W, win, w.partial_maps, w.block_sums);
-        const int64_t nblk = (int64_t)grid.x * grid.y * grid.z;
+        const int64_t nblk = 3 * (int64_t)tx * ty;
         hipLaunchKernelGGL(k_ssim_bwd, grid, dim3(256), 0, L.st, x, y, H, W, win, lambda, w.partial_maps, d_image,
                            (const double*)w.block_sums, nblk, loss_dev, nonfinite);
     }
