@@ -12,6 +12,10 @@ struct NtcDev {
     uint32_t T_mask;       // 2^log2_T - 1
     float aabb_min[3];
     float inv_ext[3];
+    __host__ __device__ int64_t level_size(int lv) const {
+        const int64_t r = (int64_t)res[lv] + 1;
+        return (dense_mask >> lv) & 1u ? r * r * r : (int64_t)T_mask + 1;
+    }
 };
 
 // Per-frame contribution lists of the table gradient (see ntc.hip).
@@ -41,9 +45,10 @@ struct CsrScratch {
 int64_t ntc_csr_slices(const NtcDev& nd, int64_t n);
 void ntc_csr_build(const Launch& L, const NtcDev& nd, const float* means, int64_t n, NtcCsr& csr, const CsrScratch& w);
 // enc_out (optional, n x 32 values of the working precision): the forward
-// also stores each point's encoding there
+// also stores the points' encoding there, in the order that the backward reads;
+// without it, scratch (min(n, kScatterPoints) x 32 floats) takes it for the call
 void ntc_forward(const Launch& L, int precision, const NtcDev& nd, const void* table, const void* mlp,
-                 const float* means, int64_t n, float* dmu, float* dq, void* enc_out);
+                 const float* means, int64_t n, float* dmu, float* dq, void* enc_out, void* scratch);
 // g_part holds max_parts x ntc_mlp_params() floats; without csr, scratch holds
 // min(n, kScatterPoints) x 32 floats; enc_in (optional, with csr): the
 // encoding a forward with the same parameters and means stored, used instead

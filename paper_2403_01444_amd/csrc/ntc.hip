@@ -234,24 +234,97 @@ __device__ __forceinline__ void encode_lane(const NtcDev& nd, const typename P::
     }
 }
 
-// A lane's eight encoding values (levels 4 g .. 4 g + 3) of point pt:
-// LDS row X[p] <-> the cached encoding enc[pt][8 g .. 8 g + 7].
+// The encoding in memory: [level][point][2], so that a wave that encodes one
+// level stores consecutive words.
 template <class P>
-__device__ __forceinline__ void enc_to_cache(const typename P::S* X, int p, int g, typename P::S* enc, int64_t pt) {
-#pragma unroll
-    for (int j = 0; j < 8; j++) enc[pt * 32 + 8 * g + j] = X[p * LD32 + 8 * g + j];
+using EncPair = typename P::S __attribute__((ext_vector_type(2)));
+template <class P>
+__device__ __forceinline__ void enc_put(typename P::S* enc, int64_t n, int lv, int64_t pt, typename P::S a,
+                                        typename P::S b) {
+    reinterpret_cast<EncPair<P>*>(enc)[lv * n + pt] = EncPair<P>{a, b};
 }
+// a lane's eight values: levels 4 g .. 4 g + 3 of point pt
 template <class P>
-__device__ __forceinline__ void enc_from_cache(typename P::S* X, int p, int g, const typename P::S* enc, int64_t pt) {
+__device__ __forceinline__ void enc_get(const typename P::S* enc, int64_t n, int g, int64_t pt, typename P::S v[8]) {
 #pragma unroll
-    for (int j = 0; j < 8; j++) X[p * LD32 + 8 * g + j] = enc[pt * 32 + 8 * g + j];
+    for (int j = 0; j < 4; j++) {
+        const EncPair<P> w = reinterpret_cast<const EncPair<P>*>(enc)[(4 * g + j) * n + pt];
+        v[2 * j] = w.x;
+        v[2 * j + 1] = w.y;
+    }
 }
 
+// The encoding of many points: a workgroup holds one level of the table in
+// LDS, an entry a word, and encodes its slice of the points from there.  From
+// global memory a point's 128 corners are that many L2 requests, some 320 a
+// ns; LDS serves them several times faster, and what bounds the kernel now is
+// the arithmetic of the corners.  300K points in fp16, encoding and MLP: 109
+// us with points in random order and 58 in Morton order -> 44 (encoding 24,
+// MLP 20); 50K 27 and 19 -> 16.  The float table's levels do not fit: as two
+// passes over a feature each, 300K points took 115 us for 123 and 95.
+constexpr int kEncEntries = 32768;   // entries of a level in LDS (128 KB)
 template <class P>
+__global__ __launch_bounds__(1024) void k_ntc_encode(NtcDev nd, const typename P::S* __restrict__ table,
+                                                     const float* __restrict__ means, int64_t n, int slices,
+                                                     typename P::S* __restrict__ enc) {
+    static_assert(sizeof(EncPair<P>) == 4, "an entry is a word");
+    __shared__ uint32_t s_t[kEncEntries];
+    // a slice's workgroups have the same blockIdx.x mod 8, hence the same XCD,
+    // whose L2 then holds the slice's means (slices is a multiple of 8)
+    const int slice = blockIdx.x % slices, lv = blockIdx.x / slices;
+    const int size = (int)nd.level_size(lv);
+    const uint32_t first = (uint32_t)nd.off[lv];
+    {
+        const uint32_t* src = reinterpret_cast<const uint32_t*>(table) + first;
+        int k = threadIdx.x;
+        for (; k + 7 * 1024 < size; k += 8 * 1024) {
+            uint32_t v[8];
+#pragma unroll
+            for (int u = 0; u < 8; u++) v[u] = src[k + 1024 * u];
+#pragma unroll
+            for (int u = 0; u < 8; u++) s_t[k + 1024 * u] = v[u];
+        }
+        for (; k < size; k += 1024) s_t[k] = src[k];
+    }
+    __syncthreads();
+    const int64_t per = (n + slices - 1) / slices, p1 = min(n, (slice + 1) * per);
+    int64_t pt = slice * per + threadIdx.x;
+    float mu[3] = {0.f, 0.f, 0.f};
+    auto load = [&](int64_t q) {
+        if (q < p1) {
+            mu[0] = means[3 * q];
+            mu[1] = means[3 * q + 1];
+            mu[2] = means[3 * q + 2];
+        }
+    };
+    load(pt);
+    for (; pt < p1; pt += 1024) {
+        float x[3];
+        const bool in = ntc_normalise(nd, mu, x);
+        load(pt + 1024);   // a round ahead
+        float e0 = 0.f, e1 = 0.f;
+        if (in) {
+            uint32_t ent[8];
+            float wt[8];
+            ntc_corners(nd, lv, x, ent, wt);
+#pragma unroll
+            for (int c = 0; c < 8; c++) {
+                const EncPair<P> v = __builtin_bit_cast(EncPair<P>, s_t[ent[c] - first]);
+                e0 += wt[c] * P::tof(v.x);
+                e1 += wt[c] * P::tof(v.y);
+            }
+        }
+        enc_put<P>(enc, n, lv, pt, P::cvt(e0), P::cvt(e1));
+    }
+}
+
+// kGiven: enc holds the points' encoding; else they are encoded here, and the
+// encoding is stored in enc, if given, for the backward.
+template <class P, bool kGiven>
 __global__ __launch_bounds__(256) void k_ntc_fwd(NtcDev nd, const typename P::S* __restrict__ table,
                                                  const typename P::S* __restrict__ mlp, const float* __restrict__ means,
                                                  int64_t n, float* __restrict__ dmu, float* __restrict__ dq,
-                                                 typename P::S* __restrict__ enc_out) {
+                                                 typename P::S* __restrict__ enc) {
     using S = typename P::S;
     __shared__ S sW1[64 * LD32], sW2[64 * LD64], sW3[16 * LD64];
     __shared__ S sX[kWaves][kPts * LD32], sH1[kWaves][kPts * LD64], sH2[kWaves][kPts * LD64];
@@ -263,14 +336,16 @@ __global__ __launch_bounds__(256) void k_ntc_fwd(NtcDev nd, const typename P::S*
     S* H1 = sH1[w];
     S* H2 = sH2[w];
     const int64_t nb = (n + kPts - 1) / kPts;
-    // each batch's means are loaded one round ahead
+    // each batch's inputs are loaded one round ahead
     float nmu[3] = {0.f, 0.f, 0.f};
+    S nenc[8];
     auto prefetch = [&](int64_t bb) {
         const int64_t q = (bb + w) * kPts + p;
         if (bb < nb && q < n) {
             nmu[0] = means[3 * q];
             nmu[1] = means[3 * q + 1];
             nmu[2] = means[3 * q + 2];
+            if constexpr (kGiven) enc_get<P>(enc, n, g, q, nenc);
         }
     };
     prefetch((int64_t)blockIdx.x * kWaves);
@@ -280,15 +355,23 @@ __global__ __launch_bounds__(256) void k_ntc_fwd(NtcDev nd, const typename P::S*
         float x[3] = {0.f, 0.f, 0.f};
         bool in = false;
         if (valid) in = ntc_normalise(nd, nmu, x);
-        prefetch(b0 + (int64_t)gridDim.x * kWaves);
+        if constexpr (!kGiven) prefetch(b0 + (int64_t)gridDim.x * kWaves);
         wave_sync();   // previous batch's reads of X done
-        if (in) {
+        if (kGiven && valid) {
+#pragma unroll
+            for (int j = 0; j < 8; j++) X[p * LD32 + 8 * g + j] = nenc[j];
+        } else if (!kGiven && in) {
             encode_lane<P>(nd, table, x, g, X, p);
         } else {
             for (int j = 0; j < 8; j++) X[p * LD32 + 8 * g + j] = P::cvt(0.f);
         }
+        if constexpr (kGiven) prefetch(b0 + (int64_t)gridDim.x * kWaves);
         wave_sync();
-        if (enc_out && valid) enc_to_cache<P>(X, p, g, enc_out, pt);   // kept for the backward
+        if (!kGiven && enc && valid) {
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+                enc_put<P>(enc, n, 4 * g + j, pt, X[p * LD32 + 8 * g + 2 * j], X[p * LD32 + 8 * g + 2 * j + 1]);
+        }
 #pragma unroll
         for (int mt = 0; mt < 4; mt++) {
             const f4v a = layer_tile<P, 32>(sW1, LD32, mt * 16, X, LD32, lane);
@@ -398,10 +481,7 @@ __global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S*
             nmu[0] = means[3 * q];
             nmu[1] = means[3 * q + 1];
             nmu[2] = means[3 * q + 2];
-            if (enc_in) {
-#pragma unroll
-                for (int j = 0; j < 8; j++) nenc[j] = enc_in[q * 32 + 8 * g + j];
-            }
+            if (enc_in) enc_get<P>(enc_in, n, g, q, nenc);
             if (g == 0) {
                 ndv[0] = d_dmu[3 * q];
                 ndv[1] = d_dmu[3 * q + 1];
@@ -590,8 +670,7 @@ struct TableParts {
 
 static bool table_parts(const NtcDev& nd, int part, TableParts& tp) {
     for (int lv = 0; lv < 16; lv++) {
-        const int64_t r1 = (int64_t)nd.res[lv] + 1;
-        const int64_t size = (nd.dense_mask >> lv) & 1u ? r1 * r1 * r1 : (int64_t)nd.T_mask + 1;
+        const int64_t size = nd.level_size(lv);
         for (int64_t f = 0; f < size; f += part) {
             if (tp.count == kLdsParts) return false;
             tp.level[tp.count] = lv;
@@ -1049,15 +1128,42 @@ __global__ __launch_bounds__(256) void k_warmup_finalize(const double* __restric
 
 inline unsigned nblk(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
+// Whether the encoding gets a launch of its own: the half types' levels, where
+// they fit in its LDS, from so many points that the loads of the tables and
+// the launch pay (fp16, random and Morton order: 8192 points 11 and 10 us in
+// one launch, 11 in two; 20,011 16 and 13, 12 in two).
+constexpr int64_t kEncPoints = 16384;
+bool encode_apart(const NtcDev& nd, int64_t n) {
+    bool fits = n >= kEncPoints;
+    for (int lv = 0; lv < 16; lv++) fits = fits && nd.level_size(lv) <= kEncEntries;
+    return fits;
+}
+
 template <class P>
 void fwd_impl(const Launch& L, const NtcDev& nd, const void* table, const void* mlp, const float* means, int64_t n,
-              float* dmu, float* dq, void* enc_out) {
-    const int64_t nb = (n + kPts - 1) / kPts;
+              float* dmu, float* dq, void* enc_out, void* scratch) {
+    using S = typename P::S;
+    const S* t = (const S*)table;
+    const S* w = (const S*)mlp;
     // four workgroups per CU are resident (LDS-bound) on 256 CUs: one round of
     // workgroups, each looping over its share of the batches
-    const unsigned grid = (unsigned)std::min<int64_t>((nb + kWaves - 1) / kWaves, 1024);
-    hipLaunchKernelGGL((k_ntc_fwd<P>), dim3(grid), dim3(256), 0, L.st, nd, (const typename P::S*)table,
-                       (const typename P::S*)mlp, means, n, dmu, dq, (typename P::S*)enc_out);
+    auto grid = [](int64_t m) { return dim3((unsigned)std::min<int64_t>((m + kPts * kWaves - 1) / (kPts * kWaves), 1024)); };
+    if constexpr (sizeof(S) == 2) {
+        if (encode_apart(nd, n)) {
+            constexpr int kSlices = 16;   // times 16 levels: one workgroup per CU (the LDS holds one)
+            const int64_t step = enc_out ? n : 2 * kScatterPoints;
+            S* enc = (S*)(enc_out ? enc_out : scratch);
+            for (int64_t p0 = 0; p0 < n; p0 += step) {
+                const int64_t m = std::min(step, n - p0);
+                hipLaunchKernelGGL((k_ntc_encode<P>), dim3(16 * kSlices), dim3(1024), 0, L.st, nd, t, means + 3 * p0, m,
+                                   kSlices, enc);
+                hipLaunchKernelGGL((k_ntc_fwd<P, true>), grid(m), dim3(256), 0, L.st, nd, t, w, means + 3 * p0, m,
+                                   dmu + 3 * p0, dq + 4 * p0, enc);
+            }
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_ntc_fwd<P, false>), grid(n), dim3(256), 0, L.st, nd, t, w, means, n, dmu, dq, (S*)enc_out);
 }
 
 // Table gradient from the encoding gradient: per entry over the prepared
@@ -1118,15 +1224,15 @@ void bwd_impl(const Launch& L, const NtcDev& nd, const void* table, const void* 
 int ntc_mlp_params() { return kMlpParams; }
 
 void ntc_forward(const Launch& L, int precision, const NtcDev& nd, const void* table, const void* mlp,
-                 const float* means, int64_t n, float* dmu, float* dq, void* enc_out) {
+                 const float* means, int64_t n, float* dmu, float* dq, void* enc_out, void* scratch) {
     if (n <= 0) return;
     if (L.prof) L.prof->begin("ntc_fwd", L.st);
     if (precision == 1)
-        fwd_impl<PF16>(L, nd, table, mlp, means, n, dmu, dq, enc_out);
+        fwd_impl<PF16>(L, nd, table, mlp, means, n, dmu, dq, enc_out, scratch);
     else if (precision == 2)
-        fwd_impl<PBF16>(L, nd, table, mlp, means, n, dmu, dq, enc_out);
+        fwd_impl<PBF16>(L, nd, table, mlp, means, n, dmu, dq, enc_out, scratch);
     else
-        fwd_impl<PF32>(L, nd, table, mlp, means, n, dmu, dq, enc_out);
+        fwd_impl<PF32>(L, nd, table, mlp, means, n, dmu, dq, enc_out, scratch);
     if (L.prof) L.prof->end(L.st);
 }
 

@@ -80,3 +80,45 @@ def test_prepared_lists_repeat(n):
         ctx.close()
     assert all(torch.equal(out[0], o) for o in out[1:])
     assert float(out[0].abs().max()) > 0
+
+
+@pytest.mark.parametrize("n,log2_T,precision", [
+    (16_384, 15, "f16"), (16_385, 15, "bf16"), (17_407, 10, "f16"),
+    (20_000, 16, "f16"),          # levels that do not fit: encoded in the MLP's launch
+    (524_288 + 77, 15, "bf16"),   # a second round of points
+])
+def test_encoding_apart_is_the_same(n, log2_T, precision):
+    """Many points are encoded in a launch of their own, few in the MLP's: the
+    same bits either way, for points on and past the box's faces too, and a
+    backward takes the kept encoding of either as it would compute it."""
+    from paper_2403_01444_amd import gs3
+    cfg = synth.NTCConfig(log2_T=log2_T)
+    rng = np.random.default_rng(n)
+    ctx = gs3.Context(n, 1 << 10, 16, 16, ntc=cfg, precision=precision)
+    p = synth.ntc_init_params(cfg, 1)
+    p[: cfg.num_table_params()] *= 1000.0
+    ctx.ntc_load(p)
+    x = rng.uniform(-1.25, 1.25, size=(n, 3)).astype(np.float32)
+    x[:3] = [[1.2, -1.2, 0.0], [1.2, 1.2, 1.2], [-1.2, -1.2, -1.2]]
+    x[3:6] = [[np.nan, 0, 0], [np.inf, 0, 0], [0, -np.inf, 0]]
+    x[-1] = [0.3, 1.2, -0.4]
+    m = cuda(x)
+    piece = 8000
+    parts = [ctx.ntc_forward(m[k:k + piece].contiguous()) for k in range(0, n, piece)]
+    dmu, dq = ctx.ntc_forward(m)
+    assert torch.equal(dmu, torch.cat([a for a, _ in parts])) and torch.equal(dq, torch.cat([b for _, b in parts]))
+    gm, gq = cuda(rng.normal(size=(n, 3)) * 1e-3), cuda(rng.normal(size=(n, 4)) * 1e-3)
+    tok = ctx.ntc_prepare(m)
+    grads = []
+    for forward in (False, True):
+        if forward:
+            got = ctx.ntc_forward(m, token=tok)
+            assert torch.equal(got[0], dmu) and torch.equal(got[1], dq)
+        ctx.ntc_zero_grads()
+        ctx.ntc_backward(m, gm, gq, tok)
+        grads.append(ctx.ntc_grads())
+    t = cfg.num_table_params()
+    assert torch.equal(grads[0][:t], grads[1][:t])
+    # the weights' partial sums meet in float atomics: at most 16 of them in any order
+    assert float((grads[0][t:] - grads[1][t:]).abs().max()) <= 16 * 2 ** -24 * 16 * float(grads[0][t:].abs().max())
+    ctx.close()
