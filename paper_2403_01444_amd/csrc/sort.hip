@@ -16,7 +16,8 @@
 // rank is the number of earlier lanes with its digit plus the wave's running
 // count for that digit.  Items keep their order (block, wave, round, lane),
 // so each pass is stable and the sort orders ties by their input position.
-// Orders of up to 8192 keys take one launch of one workgroup (k_sort_one).
+// Orders of up to 8192 keys take one launch of one workgroup (k_sort_one),
+// those of up to 2M keys two launches per pass (k_order_hist, k_order_scatter).
 #include "kernels.h"
 
 namespace gs3 {
@@ -425,6 +426,176 @@ __global__ __launch_bounds__(kOneThreads) void k_sort_one(const uint32_t* __rest
         if (base + 64 * r < n) order[base + 64 * r] = pos[r];
 }
 
+// Orders of more keys, up to kOrderBlocks blocks of I x 1024: a histogram and
+// a scatter per pass, and no scan between them.  hist holds a block's 256
+// counts next to each other; every block of the scatter adds up the rows
+// itself (those before its own, and all for the digits' first places), which
+// its L2 serves in less than a launch takes; a launch behind another costs
+// some 4.5 us however little it does, and that bounds the smaller sorts.  The
+// block's pairs are put in order in LDS, so that a digit's are stored next to
+// each other.  A block takes the fewest items with which the blocks are at
+// most one per CU, since each reads all rows.  Four passes, against a scan of
+// the counts between the two kernels: 50K keys 64 -> 45 us, 300K 81 -> 57, 1M 135 ->
+// 81; the render they are part of, 8 items a thread for one CU's worth of
+// blocks against 4 with twice the blocks: 2M 3304 and 3338 us (the scan: 3409).
+constexpr int64_t kOrderBlocks = 256;   // one per CU
+template <int I>
+__global__ __launch_bounds__(kOneThreads) void k_order_hist(const uint32_t* __restrict__ keys, int64_t n, int shift,
+                                                            uint32_t* __restrict__ hist) {
+    __shared__ uint32_t s_h[256];
+    const int tid = threadIdx.x;
+    if (tid < 256) s_h[tid] = 0u;
+    const int64_t first = (int64_t)blockIdx.x * (I * kOneThreads);
+    uint32_t key[I];
+#pragma unroll
+    for (int r = 0; r < I; r++) {
+        const int64_t i = first + r * kOneThreads + tid;
+        key[r] = i < n ? keys[i] : 0u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < I; r++) {
+        const bool valid = first + r * kOneThreads + tid < n;
+        const uint32_t d = (key[r] >> shift) & 0xFFu;
+        // one add for a wave of one digit (the high bits of the depths), whose
+        // lanes' adds would queue up on the counter
+        const uint64_t on = __ballot(valid), same = __ballot(valid && d == __builtin_amdgcn_readfirstlane(d));
+        if (on == same) {
+            if (on && (tid & 63) == 0) atomicAdd(&s_h[d], (uint32_t)__popcll(on));
+        } else if (valid) {
+            atomicAdd(&s_h[d], 1u);
+        }
+    }
+    __syncthreads();
+    if (tid < 256) hist[(int64_t)blockIdx.x * 256 + tid] = s_h[tid];
+}
+
+template <int I>
+__global__ __launch_bounds__(kOneThreads) void k_order_scatter(const uint32_t* __restrict__ kin,
+                                                               const uint32_t* __restrict__ vin,
+                                                               uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
+                                                               int64_t n, int shift, const uint32_t* __restrict__ hist,
+                                                               int nb) {
+    constexpr int N = I * kOneThreads;
+    __shared__ uint32_t s_key[N], s_val[N];
+    __shared__ uint32_t s_cnt[kOneWaves][256];
+    __shared__ uint32_t s_before[4][256], s_all[4][256];
+    __shared__ uint32_t s_to[256];   // a digit's first place in the output less its first place in LDS
+    __shared__ uint32_t s_dw[2][4];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int64_t first = (int64_t)blockIdx.x * N;
+    const int m = (int)min((int64_t)N, n - first);
+    const int base = w * (64 * I) + lane;
+    uint32_t key[I], val[I], rank[I];
+#pragma unroll
+    for (int r = 0; r < I; r++) {
+        const int i = base + 64 * r;
+        key[r] = i < m ? kin[first + i] : 0u;
+        val[r] = i < m ? (vin ? vin[first + i] : (uint32_t)(first + i)) : 0u;   // no values: the input positions
+    }
+    {
+        const int d = tid & 255, q = tid >> 8;   // a quarter of the rows each
+        const int per = (nb + 3) / 4, b1 = min(nb, (q + 1) * per);
+        uint32_t before = 0u, all = 0u;
+        int b = q * per;
+        for (; b + 8 <= b1; b += 8) {
+            uint32_t v[8];
+#pragma unroll
+            for (int u = 0; u < 8; u++) v[u] = hist[(b + u) * 256 + d];
+#pragma unroll
+            for (int u = 0; u < 8; u++) {
+                all += v[u];
+                before += b + u < (int)blockIdx.x ? v[u] : 0u;
+            }
+        }
+        for (; b < b1; b++) {
+            const uint32_t v = hist[b * 256 + d];
+            all += v;
+            before += b < (int)blockIdx.x ? v : 0u;
+        }
+        s_before[q][d] = before;
+        s_all[q][d] = all;
+    }
+    for (int k = tid; k < kOneWaves * 256; k += kOneThreads) (&s_cnt[0][0])[k] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < I; r++) {
+        const bool valid = base + 64 * r < m;
+        const uint32_t d = (key[r] >> shift) & 0xFFu;
+        const uint64_t peers = match_digit(d) & __ballot(valid);
+        const uint32_t earlier = (uint32_t)__popcll(peers & ((1ull << lane) - 1ull));
+        const uint32_t cur = s_cnt[w][d];
+        rank[r] = cur + earlier;
+        if (valid && earlier == 0) s_cnt[w][d] = cur + (uint32_t)__popcll(peers);
+    }
+    __syncthreads();
+    uint32_t v = 0u, x = 0u, gv = 0u, gx = 0u;   // digit tid: the block's count and all blocks', and their scans
+    if (tid < 256) {
+        for (int k = 0; k < kOneWaves; k++) v += s_cnt[k][tid];
+        gv = (s_all[0][tid] + s_all[1][tid]) + (s_all[2][tid] + s_all[3][tid]);
+        x = wave_incl_scan_u32(v);
+        gx = wave_incl_scan_u32(gv);
+        if (lane == 63) {
+            s_dw[0][w] = x;
+            s_dw[1][w] = gx;
+        }
+    }
+    __syncthreads();
+    if (tid < 256) {
+        uint32_t run = x - v, to = gx - gv;
+        for (int k = 0; k < w; k++) {
+            run += s_dw[0][k];
+            to += s_dw[1][k];
+        }
+        to += (s_before[0][tid] + s_before[1][tid]) + (s_before[2][tid] + s_before[3][tid]);
+        s_to[tid] = to - run;
+        for (int k = 0; k < kOneWaves; k++) {
+            const uint32_t c = s_cnt[k][tid];
+            s_cnt[k][tid] = run;
+            run += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < I; r++) {
+        if (base + 64 * r < m) {
+            const uint32_t at = s_cnt[w][(key[r] >> shift) & 0xFFu] + rank[r];
+            s_key[at] = key[r];
+            s_val[at] = val[r];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < I; r++) {
+        const int i = r * kOneThreads + tid;
+        if (i < m) {
+            const uint32_t k = s_key[i], pos = s_to[(k >> shift) & 0xFFu] + (uint32_t)i;
+            if (pos < (uint64_t)n) {   // always holds for consistent counts
+                kout[pos] = k;
+                vout[pos] = s_val[i];
+            }
+        }
+    }
+}
+
+template <int I>
+int order_passes(const Launch& L, const uint32_t* first, uint32_t* keys[2], uint32_t* vals[2], int64_t n, int bits,
+                 uint32_t* hist) {
+    int cur = 0;
+    const int nb = (int)((n + I * kOneThreads - 1) / (I * kOneThreads));
+    for (int shift = 0; shift < bits; shift += 8) {
+        if (L.prof) L.prof->begin("radix_pass", L.st);
+        const uint32_t* kin = shift == 0 ? first : keys[cur];
+        const uint32_t* vin = shift == 0 ? nullptr : vals[cur];
+        hipLaunchKernelGGL((k_order_hist<I>), dim3((unsigned)nb), dim3(kOneThreads), 0, L.st, kin, n, shift, hist);
+        hipLaunchKernelGGL((k_order_scatter<I>), dim3((unsigned)nb), dim3(kOneThreads), 0, L.st, kin, vin, keys[cur ^ 1],
+                           vals[cur ^ 1], n, shift, hist, nb);
+        if (L.prof) L.prof->end(L.st);
+        cur ^= 1;
+    }
+    return cur;
+}
+
 // One wave per digit d: exclusive scan over the blocks of hist[d][0..nb) in
 // place, the digit's total to dtotal[d].  With the totals, the scatter adds
 // the digit's base (the totals of the smaller digits) itself.
@@ -618,6 +789,13 @@ int radix_order_u32(const Launch& L, const uint32_t* keys_in, uint32_t* keys[2],
         hipLaunchKernelGGL(kern[(n - 1) / kOneThreads], dim3(1), dim3(kOneThreads), 0, L.st, keys_in, (int)n, bits, vals[0]);
         if (L.prof) L.prof->end(L.st);
         return 0;
+    }
+    if (n > 1 && n <= 8 * kOrderBlocks * kOneThreads) {
+        const int64_t per = (n + kOrderBlocks * kOneThreads - 1) / (kOrderBlocks * kOneThreads);
+        return per <= 1   ? order_passes<1>(L, keys_in, keys, vals, n, bits, hist)
+               : per <= 2 ? order_passes<2>(L, keys_in, keys, vals, n, bits, hist)
+               : per <= 4 ? order_passes<4>(L, keys_in, keys, vals, n, bits, hist)
+                          : order_passes<8>(L, keys_in, keys, vals, n, bits, hist);
     }
     return radix_impl<uint32_t>(L, keys_in, true, keys, vals, n, bits, hist, tmp);
 }

@@ -30,6 +30,27 @@ def test_order_around_the_one_workgroup_sort(n):
     ctx.close()
 
 
+@pytest.mark.parametrize("n", [65_537, 262_143, 262_144, 262_145, 524_289, 1_048_577, 2_097_152, 2_097_153])
+def test_order_around_the_block_sizes(n):
+    """Morton order on both sides of the sizes at which a block takes more
+    keys, and past the last of them: whole and ragged last blocks, waves of
+    one digit, many ties."""
+    from paper_2403_01444_amd import gs3
+    rng = np.random.default_rng(n)
+    ctx = gs3.Context(n, 1 << 10, 16, 16)
+    pts = rng.integers(0, 6, size=(n, 3)).astype(np.float32) / np.float32(8)
+    pts[n // 3:] = rng.uniform(0, 1, size=pts[n // 3:].shape).astype(np.float32)
+    pts[-1] = 0
+    perm = ctx.morton_order(torch.from_numpy(pts).cuda(), (0, 0, 0), (1, 1, 1)).cpu().numpy()
+    q = np.minimum((pts * np.float32(1024)).astype(np.int64), 1023)
+    code = np.zeros(n, np.int64)
+    for b in range(10):
+        for a in range(3):
+            code |= ((q[:, a] >> b) & 1) << (3 * b + a)
+    assert np.array_equal(perm, np.argsort(code, kind="stable"))
+    ctx.close()
+
+
 def test_zero_many_clears_each_array_and_nothing_else():
     from paper_2403_01444_amd import gs3
     ctx = gs3.Context(10, 1 << 10, 16, 16)
