@@ -173,29 +173,45 @@ __device__ __forceinline__ void ntc_corners(const NtcDev& nd, int lv, const floa
 }
 
 template <class P>
+using Pair = typename P::S __attribute__((ext_vector_type(2)));
+
+// The weights to LDS, by 256 threads.  Every load is issued before the first
+// store (pairs: what the parameters' alignment allows); with a load and its
+// store per round, the rounds' latencies add up to a third of a launch on few
+// points.
+template <class P>
 __device__ __forceinline__ void load_weights(const typename P::S* __restrict__ mlp, typename P::S* sW1,
                                              typename P::S* sW2, typename P::S* sW3, typename P::S* sW1t,
                                              typename P::S* sW2t, typename P::S* sW3t) {
     using S = typename P::S;
-    const S* W1 = mlp;
-    const S* W2 = mlp + 64 * 32;
-    const S* W3 = mlp + 64 * 32 + 64 * 64;
-    for (int k = threadIdx.x; k < 64 * 32; k += blockDim.x) {
-        const int r = k / 32, c = k % 32;
-        if (sW1) sW1[r * LD32 + c] = W1[k];
-        if (sW1t) sW1t[c * LD64 + r] = W1[k];
+    constexpr int kPairs = kMlpParams / 2, kN = (kPairs + 255) / 256;
+    constexpr int kW2 = 64 * 32 / 2 / 256, kW3 = kW2 + 64 * 64 / 2 / 256;   // first rounds of W2 and W3
+    static_assert(kW2 * 256 == 64 * 32 / 2 && (kW3 - kW2) * 256 == 64 * 64 / 2 && kN == kW3 + 1, "whole rounds");
+    const int t = threadIdx.x;
+    Pair<P> v[kN];
+#pragma unroll
+    for (int u = 0; u < kN; u++)
+        v[u] = t + 256 * u < kPairs ? reinterpret_cast<const Pair<P>*>(mlp)[t + 256 * u] : Pair<P>{P::cvt(0.f), P::cvt(0.f)};
+    auto put = [](S* a, S* at, int r, int c, int ld, int ldt, Pair<P> x) {
+        if (a) {
+            a[r * ld + c] = x.x;
+            a[r * ld + c + 1] = x.y;
+        }
+        if (at) {
+            at[c * ldt + r] = x.x;
+            at[(c + 1) * ldt + r] = x.y;
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < kW2; u++) put(sW1, sW1t, (t + 256 * u) / 16, (t + 256 * u) % 16 * 2, LD32, LD64, v[u]);
+#pragma unroll
+    for (int u = kW2; u < kW3; u++) {
+        const int k = t + 256 * (u - kW2);
+        put(sW2, sW2t, k / 32, k % 32 * 2, LD64, LD64, v[u]);
     }
-    for (int k = threadIdx.x; k < 64 * 64; k += blockDim.x) {
-        const int r = k / 64, c = k % 64;
-        if (sW2) sW2[r * LD64 + c] = W2[k];
-        if (sW2t) sW2t[c * LD64 + r] = W2[k];
-    }
-    for (int k = threadIdx.x; k < 16 * 64; k += blockDim.x) {
-        const int r = k / 64, c = k % 64;
-        const S v = r < 7 ? W3[r * 64 + c] : P::cvt(0.0f);
-        if (sW3) sW3[r * LD64 + c] = v;
-        if (sW3t) sW3t[c * LD16 + r] = v;
-    }
+    // W3 has 7 rows; rows 7 .. 15 are zero
+    put(sW3, sW3t, t / 32, t % 32 * 2, LD64, LD16, v[kW3]);
+    put(sW3, sW3t, 8 + t / 32, t % 32 * 2, LD64, LD16, Pair<P>{P::cvt(0.f), P::cvt(0.f)});
 }
 
 // D (16 x 16, rows m0.., cols = points) += W[m0..m0+15][0..K) X[p][0..K)
@@ -237,18 +253,16 @@ __device__ __forceinline__ void encode_lane(const NtcDev& nd, const typename P::
 // The encoding in memory: [level][point][2], so that a wave that encodes one
 // level stores consecutive words.
 template <class P>
-using EncPair = typename P::S __attribute__((ext_vector_type(2)));
-template <class P>
 __device__ __forceinline__ void enc_put(typename P::S* enc, int64_t n, int lv, int64_t pt, typename P::S a,
                                         typename P::S b) {
-    reinterpret_cast<EncPair<P>*>(enc)[lv * n + pt] = EncPair<P>{a, b};
+    reinterpret_cast<Pair<P>*>(enc)[lv * n + pt] = Pair<P>{a, b};
 }
 // a lane's eight values: levels 4 g .. 4 g + 3 of point pt
 template <class P>
 __device__ __forceinline__ void enc_get(const typename P::S* enc, int64_t n, int g, int64_t pt, typename P::S v[8]) {
 #pragma unroll
     for (int j = 0; j < 4; j++) {
-        const EncPair<P> w = reinterpret_cast<const EncPair<P>*>(enc)[(4 * g + j) * n + pt];
+        const Pair<P> w = reinterpret_cast<const Pair<P>*>(enc)[(4 * g + j) * n + pt];
         v[2 * j] = w.x;
         v[2 * j + 1] = w.y;
     }
@@ -267,7 +281,7 @@ template <class P>
 __global__ __launch_bounds__(1024) void k_ntc_encode(NtcDev nd, const typename P::S* __restrict__ table,
                                                      const float* __restrict__ means, int64_t n, int slices,
                                                      typename P::S* __restrict__ enc) {
-    static_assert(sizeof(EncPair<P>) == 4, "an entry is a word");
+    static_assert(sizeof(Pair<P>) == 4, "an entry is a word");
     __shared__ uint32_t s_t[kEncEntries];
     // a slice's workgroups have the same blockIdx.x mod 8, hence the same XCD,
     // whose L2 then holds the slice's means (slices is a multiple of 8)
@@ -309,7 +323,7 @@ __global__ __launch_bounds__(1024) void k_ntc_encode(NtcDev nd, const typename P
             ntc_corners(nd, lv, x, ent, wt);
 #pragma unroll
             for (int c = 0; c < 8; c++) {
-                const EncPair<P> v = __builtin_bit_cast(EncPair<P>, s_t[ent[c] - first]);
+                const Pair<P> v = __builtin_bit_cast(Pair<P>, s_t[ent[c] - first]);
                 e0 += wt[c] * P::tof(v.x);
                 e1 += wt[c] * P::tof(v.y);
             }
@@ -883,6 +897,54 @@ struct GatherLevels {
     int64_t end[16];     // one past its last entry
 };
 
+// The weighted encoding gradients of contributions k, k + G, ... below end,
+// four independent loads in flight per lane.
+template <int G>
+__device__ __forceinline__ float2 gather_stride(const uint2* __restrict__ pw, const float* __restrict__ denc, int64_t n,
+                                                uint32_t k, uint32_t end) {
+    float a0 = 0.f, a1 = 0.f;
+    auto enc = [&](uint32_t c) {
+        return *reinterpret_cast<const float2*>(denc + 2 * ((int64_t)((c >> 3) & 15) * n + (c >> 7)));
+    };
+    for (; k + 3 * G < end; k += 4 * G) {
+        const uint2 c0 = pw[k], c1 = pw[k + G], c2 = pw[k + 2 * G], c3 = pw[k + 3 * G];
+        const float2 d0 = enc(c0.x), d1 = enc(c1.x), d2 = enc(c2.x), d3 = enc(c3.x);
+        const float w0 = __uint_as_float(c0.y), w1 = __uint_as_float(c1.y);
+        const float w2 = __uint_as_float(c2.y), w3 = __uint_as_float(c3.y);
+        a0 += w0 * d0.x;
+        a1 += w0 * d0.y;
+        a0 += w1 * d1.x;
+        a1 += w1 * d1.y;
+        a0 += w2 * d2.x;
+        a1 += w2 * d2.y;
+        a0 += w3 * d3.x;
+        a1 += w3 * d3.y;
+    }
+    for (; k < end; k += G) {
+        const uint2 c = pw[k];
+        const float2 d = enc(c.x);
+        const float wk = __uint_as_float(c.y);
+        a0 += wk * d.x;
+        a1 += wk * d.y;
+    }
+    return make_float2(a0, a1);
+}
+
+// Row r summed by 16 lanes; lane 0 of them (sub 0) holds the sum.
+__device__ __forceinline__ float2 gather_row16(const uint2* __restrict__ pw, const float* __restrict__ denc, int64_t n,
+                                               uint2 r, int sub) {
+    float2 a = gather_stride<16>(pw, denc, n, r.x + sub, r.y);
+    a.x = dpp_add<0xB1, 0xF>(a.x);    // quad_perm [1,0,3,2]
+    a.x = dpp_add<0x4E, 0xF>(a.x);    // quad_perm [2,3,0,1]
+    a.x = dpp_add<0x141, 0xF>(a.x);   // row_half_mirror
+    a.x = dpp_add<0x140, 0xF>(a.x);   // row_mirror: lane 0 of the row holds the sum
+    a.y = dpp_add<0xB1, 0xF>(a.y);
+    a.y = dpp_add<0x4E, 0xF>(a.y);
+    a.y = dpp_add<0x141, 0xF>(a.y);
+    a.y = dpp_add<0x140, 0xF>(a.y);
+    return a;
+}
+
 static int64_t gather_blocks(const GatherLevels& gl, int lv) {
     return (gl.end[lv] - gl.begin[lv] + kGatherEntries - 1) / kGatherEntries;
 }
@@ -903,46 +965,51 @@ __global__ __launch_bounds__(256) void k_csr_gather(GatherLevels gl, const uint2
     const int sub = threadIdx.x % kGatherLanes;
     uint2 r = make_uint2(0u, 0u);
     if (valid) r = rows[e];
-    float a0 = 0.f, a1 = 0.f;
-    auto enc = [&](uint32_t c) {
-        return *reinterpret_cast<const float2*>(denc + 2 * ((int64_t)((c >> 3) & 15) * n + (c >> 7)));
-    };
-    uint32_t k = r.x + sub;
-    // four independent contribution loads in flight per lane; the sum keeps
-    // the order k, k + 16, k + 32, ...
-    constexpr int G = kGatherLanes;
-    for (; k + 3 * G < r.y; k += 4 * G) {
-        const uint2 c0 = pw[k], c1 = pw[k + G], c2 = pw[k + 2 * G], c3 = pw[k + 3 * G];
-        const float2 d0 = enc(c0.x), d1 = enc(c1.x), d2 = enc(c2.x), d3 = enc(c3.x);
-        const float w0 = __uint_as_float(c0.y), w1 = __uint_as_float(c1.y);
-        const float w2 = __uint_as_float(c2.y), w3 = __uint_as_float(c3.y);
-        a0 += w0 * d0.x;
-        a1 += w0 * d0.y;
-        a0 += w1 * d1.x;
-        a1 += w1 * d1.y;
-        a0 += w2 * d2.x;
-        a1 += w2 * d2.y;
-        a0 += w3 * d3.x;
-        a1 += w3 * d3.y;
-    }
-    for (; k < r.y; k += G) {
-        const uint2 c = pw[k];
-        const float2 d = enc(c.x);
-        const float wk = __uint_as_float(c.y);
-        a0 += wk * d.x;
-        a1 += wk * d.y;
-    }
-    a0 = dpp_add<0xB1, 0xF>(a0);    // quad_perm [1,0,3,2]
-    a0 = dpp_add<0x4E, 0xF>(a0);    // quad_perm [2,3,0,1]
-    a0 = dpp_add<0x141, 0xF>(a0);   // row_half_mirror
-    a0 = dpp_add<0x140, 0xF>(a0);   // row_mirror: lane 0 of the row holds the sum
-    a1 = dpp_add<0xB1, 0xF>(a1);
-    a1 = dpp_add<0x4E, 0xF>(a1);
-    a1 = dpp_add<0x141, 0xF>(a1);
-    a1 = dpp_add<0x140, 0xF>(a1);
+    const float2 a = gather_row16(pw, denc, n, r, sub);
     if (sub == 0 && valid && r.y > r.x) {
-        g_table[2 * e] += a0;
-        g_table[2 * e + 1] += a1;
+        g_table[2 * e] += a.x;
+        g_table[2 * e + 1] += a.y;
+    }
+}
+
+// The same for few points, where most entries have a contribution or none: a
+// lane sums an entry of up to kShortRow contributions alone, and the longer
+// ones of a wave then take 16 lanes each.  Bound by the latency of loads that
+// follow each other, in a quarter of the waves.  Not more entries to a wave,
+// or its long ones queue up: backwards of 2000 and 4096 points in fp16, points
+// all over the box, on surfaces and in a corner of it: 32 30 32 and 35 32 43
+// us with 16 lanes an entry, 18 22 29 and 23 26 46 with 32 entries to a wave,
+// 21 20 28 and 24 24 42 with 16.  8192 points 37 35 70 and 31 30 71, and from
+// there on the corner loses (14000: 113 and 141), hence the line at two
+// contributions an entry (6900 points at T = 2^15).
+constexpr uint32_t kShortRow = 8;
+constexpr int64_t kShortMean = 2;   // mean contributions of an entry up to which lanes take entries alone
+constexpr int kShortEntries = 16;   // entries of a wave
+__global__ __launch_bounds__(256) void k_csr_gather_short(int64_t entries, const uint2* __restrict__ rows,
+                                                          const uint2* __restrict__ pw, const float* __restrict__ denc,
+                                                          int64_t n, float* __restrict__ g_table) {
+    const int lane = threadIdx.x & 63;
+    const int64_t e0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kShortEntries, e = e0 + lane;
+    const uint2 r = lane < kShortEntries && e < entries ? rows[e] : make_uint2(0u, 0u);
+    float2* const out = reinterpret_cast<float2*>(g_table);
+    const bool lone = r.y - r.x <= kShortRow;
+    if (lone && r.y > r.x) {
+        const float2 a = gather_stride<1>(pw, denc, n, r.x, r.y), o = out[e];
+        out[e] = make_float2(o.x + a.x, o.y + a.y);
+    }
+    const int sub = lane & 15, q = lane >> 4;
+    for (uint64_t m = __ballot(!lone); m;) {   // the wave's next four long rows
+        uint64_t t = m;
+        for (int k = 0; k < q; k++) t &= t - 1;
+        const int src = t ? __builtin_ctzll(t) : 0;
+        uint2 l = make_uint2((uint32_t)__shfl((int)r.x, src), (uint32_t)__shfl((int)r.y, src));
+        if (!t) l.y = l.x;
+        const float2 a = gather_row16(pw, denc, n, l, sub);
+        if (sub == 0 && t) {
+            const float2 o = out[e0 + src];
+            out[e0 + src] = make_float2(o.x + a.x, o.y + a.y);
+        }
+        for (int k = 0; k < 4; k++) m &= m - 1;
     }
 }
 
@@ -1187,6 +1254,11 @@ void table_grad(const Launch& L, const NtcDev& nd, const float* means, int64_t n
             hipLaunchKernelGGL(k_table_scatter, dim3((unsigned)((16 * n + 255) / 256)), dim3(256), 0, L.st, nd, means, n,
                                denc, g_table);
         }
+        return;
+    }
+    if (128 * n <= kShortMean * csr->entries) {
+        hipLaunchKernelGGL(k_csr_gather_short, dim3(nblk(csr->entries, 4 * kShortEntries)), dim3(256), 0, L.st, csr->entries, csr->rows,
+                           csr->pw, denc, n, g_table);
         return;
     }
     GatherLevels gl;

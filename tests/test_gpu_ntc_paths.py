@@ -122,3 +122,34 @@ def test_encoding_apart_is_the_same(n, log2_T, precision):
     # the weights' partial sums meet in float atomics: at most 16 of them in any order
     assert float((grads[0][t:] - grads[1][t:]).abs().max()) <= 16 * 2 ** -24 * 16 * float(grads[0][t:].abs().max())
     ctx.close()
+
+
+@pytest.mark.parametrize("n,log2_T,spread", [(1, 15, 1.25), (17, 15, 1.25), (2000, 15, 1.25), (3000, 15, 0.01),
+                                             (100, 10, 1.25), (6000, 16, 0.3)])
+def test_few_points_gather(n, log2_T, spread):
+    """The gather of few points (a lane an entry, longer lists 16 lanes) gives
+    the table gradient of the scattered one, and the same bits each time."""
+    from paper_2403_01444_amd import gs3
+    cfg = synth.NTCConfig(log2_T=log2_T)
+    rng = np.random.default_rng(n)
+    ctx = gs3.Context(n, 1 << 10, 16, 16, ntc=cfg)
+    p = synth.ntc_init_params(cfg, 1)
+    p[: cfg.num_table_params()] *= 1000.0
+    ctx.ntc_load(p)
+    m = cuda(rng.uniform(-spread, spread, size=(n, 3)))
+    gm, gq = cuda(rng.normal(size=(n, 3)) * 1e-3), cuda(rng.normal(size=(n, 4)) * 1e-3)
+    tok = ctx.ntc_prepare(m)
+    t = cfg.num_table_params()
+    got = []
+    for token in (tok, tok, 0):
+        ctx.ntc_zero_grads()
+        ctx.ntc_backward(m, gm, gq, token)
+        got.append(ctx.ntc_grads()[:t].double())
+    assert torch.equal(got[0], got[1])
+    # the same float32 products in another order: an entry's up to 8 n addends
+    # (all points in a cell or two) differ by their number times 2^-24 of their
+    # absolute sum, a walk of either sign that stays below the bound of the
+    # tests above by far
+    scale = float(got[0].abs().max())
+    assert float((got[0] - got[2]).abs().max()) <= 5e-4 * scale
+    ctx.close()
