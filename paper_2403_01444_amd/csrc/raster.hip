@@ -1494,10 +1494,8 @@ __global__ __launch_bounds__(256) void k_preprocess_bwd(GaussDev g, CamDev cam, 
     if (i >= g.n) return;
     // the blend's sums, left zero for the next backward
     float a9[9];
-    for (int k = 0; k < 9; k++) {
-        a9[k] = accum[9 * i + k];
-        accum[9 * i + k] = 0.f;
-    }
+    for (int k = 0; k < 9; k++) a9[k] = accum[9 * i + k];
+    for (int k = 0; k < 9; k++) accum[9 * i + k] = 0.f;
     Geo o;
     if (!geo_forward(g, cam, i, o)) return;
     ColourCtx cc;
@@ -1542,7 +1540,6 @@ __global__ __launch_bounds__(256) void k_preprocess_bwd(GaussDev g, CamDev cam, 
     // colour
     float gch[3];
     for (int k = 0; k < 3; k++) gch[k] = cc.raw[k] > 0.f ? drgb[k] : 0.f;
-    const int K = (g.sh_degree + 1) * (g.sh_degree + 1);
     float wk[16];
     switch (g.sh_degree) {
         case 3: sh_weights<16>(g.sh + i * 48, gch, wk); break;
@@ -1550,14 +1547,15 @@ __global__ __launch_bounds__(256) void k_preprocess_bwd(GaussDev g, CamDev cam, 
         case 2: sh_weights<9>(g.sh + i * 27, gch, wk); break;
         default: sh_weights<1>(g.sh + i * 3, gch, wk); break;
     }
-    if (out.d_sh) {
+    // a Gaussian that no pixel saw leaves its row as it is
+    if (out.d_sh && (gch[0] != 0.f || gch[1] != 0.f || gch[2] != 0.f)) {
         float Y[16];
         sh_basis(g.sh_degree, cc.dl[0], cc.dl[1], cc.dl[2], Y);
-        for (int k = 0; k < K; k++) {
-            float* ds = out.d_sh + i * (int64_t)K * 3 + 3 * k;
-            ds[0] += gch[0] * Y[k];
-            ds[1] += gch[1] * Y[k];
-            ds[2] += gch[2] * Y[k];
+        switch (g.sh_degree) {
+            case 3: sh_accumulate<16>(out.d_sh + i * 48, gch, Y); break;
+            case 1: sh_accumulate<4>(out.d_sh + i * 12, gch, Y); break;
+            case 2: sh_accumulate<9>(out.d_sh + i * 27, gch, Y); break;
+            default: sh_accumulate<1>(out.d_sh + i * 3, gch, Y); break;
         }
     }
     float gdl[3];
