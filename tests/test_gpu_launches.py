@@ -97,3 +97,21 @@ def test_backwards_start_from_cleared_sums(log2):
         # twice the sum; each run's float atomics add a Gaussian's few tiles in another order
         assert float((two[k] - 2 * one[k]).abs().max()) <= 1e-5 * float(one[k].abs().max())
     ctx.close()
+
+
+@pytest.mark.parametrize("n,rows,rf", [(1, 3, 1), (257, 300, 3), (1000, 1700, 4), (333, 333, 12), (129, 200, 27),
+                                       (700, 1000, 48), (5, 9, 1000)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_gathered_rows(n, rows, rf, shift):
+    """Rows by index, four floats at a time where rows and arrays allow it
+    (shift: arrays that start one float past an aligned address)."""
+    from paper_2403_01444_amd import gs3
+    rng = np.random.default_rng(n)
+    ctx = gs3.Context(max(n, rows), 1 << 10, 16, 16)
+    src = torch.rand(rows * rf + 1, device="cuda")[shift:shift + rows * rf].view(rows, rf)
+    dst = torch.full((n * rf + 2,), -1.0, device="cuda")
+    perm = torch.from_numpy(rng.integers(0, rows, n).astype(np.int32)).cuda()
+    gs3.gs3_gather_rows(ctx.h, src, perm, n, rf, dst[shift:shift + n * rf])
+    assert torch.equal(dst[shift:shift + n * rf].view(n, rf), src[perm.long()])
+    assert float(dst[shift + n * rf]) == -1.0
+    ctx.close()
