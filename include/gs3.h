@@ -236,8 +236,10 @@ gs3_status gs3_ntc_backward(gs3_ctx* ctx, const float* means, int64_t n, uint64_
  * do not change while the token is in use; a later gs3_ntc_prepare makes
  * the previous token stale.  Allocates device memory on first use or growth
  * (about 1.3 KB per mean, and 4 bytes per table entry for every slice of the
- * means that is counted apart, at most 30 MB at T = 2^15; 3.3 KB per mean
- * with T above 2^18) and synchronises. */
+ * means that is counted apart, at most 30 MB at T = 2^15; 12 bytes per table
+ * entry and slice, 85 MB per 323,584 means, where the lists are kept slice by
+ * slice: from 220,000 means with T up to 2^15; 3.3 KB per mean with T above
+ * 2^18) and synchronises. */
 gs3_status gs3_ntc_prepare(gs3_ctx* ctx, const float* means, int64_t n, uint64_t* token);
 
 /* One Adam step on the NTC parameters with the accumulated gradients,

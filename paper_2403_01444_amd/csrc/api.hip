@@ -599,8 +599,9 @@ gs3_status gs3_ntc_prepare(gs3_ctx* c, const float* means, int64_t n, uint64_t* 
         bool ok = get((void**)&c->csr.rows, entries * 8) && get((void**)&c->csr.pw, m * 8) &&
                   get((void**)&c->csr.denc, n * 32 * 4) && get(&c->enc_cache, n * 32 * 4);
         if (slices > 0)
-            ok = ok && get((void**)&w.cnt, slices * entries * 4) && get((void**)&w.first, entries * 4) &&
-                 get((void**)&w.tmp, (scan_tmp_words(entries) + 4) * 8);
+            ok = ok && get((void**)&w.cnt, (slices * entries + 1) * 4) && get((void**)&w.first, entries * 4) &&
+                 get((void**)&w.tmp, (scan_tmp_words(slices * entries + 1) + 4) * 8) &&
+                 (!ntc_csr_chunked(c->nd, n) || get((void**)&c->csr.part, slices * entries * 8));
         else
             ok = ok && get((void**)&w.keys[0], m * 4) && get((void**)&w.keys[1], m * 4) &&
                  get((void**)&w.vals[0], m * 4) && get((void**)&w.vals[1], m * 4) &&

@@ -24,13 +24,18 @@ struct NtcCsr {
     uint2* rows = nullptr;    // [entries]: [start, end) into pw
     uint2* pw = nullptr;      // (point << 7 | level << 3 | corner, float bits of the trilinear weight), by entry
     float* denc = nullptr;    // [16 levels][n][2] encoding gradient of the current backward
+    // lists kept slice by slice (many points), instead of rows: starts[slice][entry] of them
+    // in pw and the lists' end, and the slices' sums of the current backward
+    int slices = 0;
+    uint32_t* starts = nullptr;
+    float2* part = nullptr;
 };
 
 int ntc_mlp_params();
 // points whose encoding gradient a backward without preparation holds at a
 // time (32 MB of scratch)
 constexpr int64_t kScatterPoints = 1 << 18;
-// Scratch of the list building: cnt (slices x entries) and first (entries)
+// Scratch of the list building: cnt (slices x entries + 1) and first (entries)
 // when ntc_csr_slices gives a number of slices, else (0) the sort's ping-pong
 // buffers of n * 128 u32 each and hist, radix_hist_words(n * 128); tmp holds
 // the scan's words of either + 1.
@@ -43,6 +48,7 @@ struct CsrScratch {
     uint64_t* tmp = nullptr;
 };
 int64_t ntc_csr_slices(const NtcDev& nd, int64_t n);
+bool ntc_csr_chunked(const NtcDev& nd, int64_t n);   // lists slice by slice
 void ntc_csr_build(const Launch& L, const NtcDev& nd, const float* means, int64_t n, NtcCsr& csr, const CsrScratch& w);
 // enc_out (optional, n x 32 values of the working precision): the forward
 // also stores the points' encoding there, in the order that the backward reads;

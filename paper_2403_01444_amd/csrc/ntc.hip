@@ -719,6 +719,18 @@ static bool table_parts(const NtcDev& nd, int part, TableParts& tp) {
 // points read four times as often: 0.83 ms).  Tables of more than kLdsParts
 // parts (T above 2^18) still take the sort.
 // ---------------------------------------------------------------------------
+// Points from which the lists are kept slice by slice (backward of points in
+// Morton order all over the box, on surfaces, and in random order; entry by
+// entry and slice by slice: 100K 81 78 86 and 86 85 88 us, 150K 105 96 117 and
+// 120 115 123, 200K 142 130 163 and 136 136 134, 300K 210 204 264 and 176 178
+// 174, 600K 427 398 572 and 338 336 342).
+constexpr int64_t kChunkMin = 220000;
+constexpr int kChunkPoints = 79 * 256;   // points of a slice at most: 158 KB of LDS in k_csr_chunk
+static_assert(kChunkPoints <= 1 << 15 && kListEntries <= 1 << 15, "chunk_word");
+
+// a contribution's word in lists kept slice by slice: entry of the level, point of the slice
+__device__ __forceinline__ uint32_t chunk_word(uint32_t entry, uint32_t point) { return entry << 15 | point; }
+
 __global__ __launch_bounds__(1024) void k_csr_count(NtcDev nd, TableParts tp, const float* __restrict__ means, int64_t n,
                                                     int slices, int64_t entries, uint32_t* __restrict__ cnt) {
     __shared__ uint32_t s_n[kListEntries];
@@ -746,6 +758,7 @@ __global__ __launch_bounds__(1024) void k_csr_count(NtcDev nd, TableParts tp, co
     }
     __syncthreads();
     for (int k = threadIdx.x; k < size; k += 1024) cnt[(int64_t)slice * entries + first + k] = s_n[k];
+    if (blockIdx.x == 0 && threadIdx.x == 0) cnt[slices * entries] = 0u;   // the lists' end, once scanned
 }
 
 // contributions per entry
@@ -776,7 +789,7 @@ __global__ __launch_bounds__(256) void k_csr_slots(uint32_t* __restrict__ cnt, i
 
 __global__ __launch_bounds__(256) void k_csr_place(NtcDev nd, TableParts tp, const float* __restrict__ means, int64_t n,
                                                    int slices, int64_t entries, const uint32_t* __restrict__ slot,
-                                                   uint2* __restrict__ pw) {
+                                                   bool chunked, uint2* __restrict__ pw) {
     __shared__ uint32_t s_at[kListEntries];
     const int part = blockIdx.x / slices, slice = blockIdx.x % slices;
     const int lv = tp.level[part], size = tp.size[part];
@@ -819,7 +832,9 @@ __global__ __launch_bounds__(256) void k_csr_place(NtcDev nd, TableParts tp, con
         for (int c = 0; c < 8; c++) {
             const uint32_t k = ent[c] - first;
             if (in && k < (uint32_t)size)
-                pw[at[c]] = make_uint2(((uint32_t)pt << 7) | ((uint32_t)lv << 3) | (uint32_t)c, __float_as_uint(wt[c]));
+                pw[at[c]] = make_uint2(chunked ? chunk_word(k, (uint32_t)(pt - p0))
+                                               : ((uint32_t)pt << 7) | ((uint32_t)lv << 3) | (uint32_t)c,
+                                       __float_as_uint(wt[c]));
         }
     }
 }
@@ -896,6 +911,7 @@ struct GatherLevels {
     int64_t begin[16];   // first entry of each level
     int64_t end[16];     // one past its last entry
 };
+
 
 // The weighted encoding gradients of contributions k, k + G, ... below end,
 // four independent loads in flight per lane.
@@ -1011,6 +1027,200 @@ __global__ __launch_bounds__(256) void k_csr_gather_short(int64_t entries, const
         }
         for (int k = 0; k < 4; k++) m &= m - 1;
     }
+}
+
+// The same for many points, whose lists are kept slice by slice: a workgroup
+// holds a slice of the points of one level in LDS and sums the level's entries
+// over it into the slice's row of part.  The list is read in order, so the
+// next part of it is in flight while one is summed: a lane takes kRun
+// contributions that follow each other, stores the sums of the entries that
+// lie inside them, and the entries that reach over lanes, rounds and waves are
+// put together from the ends (a segmented scan over the lanes, a carry per
+// wave, thread 0 over the waves).  A fixed order throughout.  k_csr_gather's 8
+// bytes a contribution come from all over the level, a 128-byte line of the L2
+// each; here they are read once, and the list's 8 bytes a contribution (65 us
+// of 300K points' 97, at the rate of a large copy) are what is left.  300K
+// points with k_chunk_sum, random and Morton order: 198 and 148 -> 110 and 118
+// us.
+constexpr int kRun = 8;
+constexpr uint32_t kNoEntry = 0x1FFFFu;   // past the end of the list, with a point that is there
+typedef uint32_t pw2 __attribute__((ext_vector_type(4), aligned(8)));   // two contributions
+
+template <int kCtrl, int kRows>
+__device__ __forceinline__ void seg_step(float& x, float& y, uint32_t& f) {
+    const float px = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, kRows, 0xF, false));
+    const float py = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(y), kCtrl, kRows, 0xF, false));
+    const uint32_t pf = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)f, kCtrl, kRows, 0xF, false);
+    x += f ? 0.f : px;
+    y += f ? 0.f : py;
+    f |= pf;
+}
+
+__global__ __launch_bounds__(1024) void k_csr_chunk(NtcDev nd, int64_t n, int slices, int64_t entries,
+                                                    const uint32_t* __restrict__ starts, const uint2* __restrict__ pw,
+                                                    const float* __restrict__ denc, float2* __restrict__ part) {
+    constexpr int NW = 16;
+    __shared__ float2 s_d[kChunkPoints];
+    __shared__ uint32_t s_first[NW], s_last[NW];    // a wave's first and last entry
+    __shared__ float2 s_fsum[NW], s_lsum[NW];       // and their sums
+    const int slice = blockIdx.x % slices, lv = blockIdx.x / slices;
+    const int64_t per = csr_slice(n, slices), p0 = slice * per;
+    const int m = (int)max((int64_t)0, min(n, p0 + per) - p0);
+    const int size = (int)nd.level_size(lv), tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const uint32_t* const st = starts + slice * entries + nd.off[lv];
+    float2* const out = part + slice * entries + nd.off[lv];
+    // the waves take equal parts of the list, in whole rounds
+    constexpr uint32_t kRound = 64 * kRun;
+    const uint32_t A = st[0], B = st[size], perw = (B - A + NW * kRound - 1) / (NW * kRound) * kRound;
+    const uint32_t a = min(B, A + w * perw), b = min(B, a + perw);
+    uint32_t nx[kRun];
+    float nw[kRun];
+    auto load = [&](uint32_t r) {   // the lane's contributions of the round at r
+        const uint32_t k = r + lane * kRun;
+        if (k + kRun <= b) {
+#pragma unroll
+            for (int i = 0; i < kRun; i += 2) {
+                const pw2 v = *reinterpret_cast<const pw2*>(pw + k + i);
+                nx[i] = v.x;
+                nw[i] = __uint_as_float(v.y);
+                nx[i + 1] = v.z;
+                nw[i + 1] = __uint_as_float(v.w);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < kRun; i++) {
+                const bool in = k + i < b;
+                const uint2 v = in ? pw[k + i] : make_uint2(chunk_word(kNoEntry, 0u), 0u);
+                nx[i] = v.x;
+                nw[i] = __uint_as_float(v.y);
+            }
+        }
+    };
+    load(a);
+    {
+        const float2* src = reinterpret_cast<const float2*>(denc) + lv * n + p0;
+        int k = tid;
+        for (; k + 3 * 1024 < m; k += 4 * 1024) {
+            float2 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) v[u] = src[k + 1024 * u];
+#pragma unroll
+            for (int u = 0; u < 4; u++) s_d[k + 1024 * u] = v[u];
+        }
+        for (; k < m; k += 1024) s_d[k] = src[k];
+    }
+    for (int k = tid; k < size; k += 1024) out[k] = make_float2(0.f, 0.f);   // entries without a contribution
+    __syncthreads();
+    uint32_t first = kNoEntry, ckey = kNoEntry;
+    float cx = 0.f, cy = 0.f;
+    auto store = [&](uint32_t e, float x, float y) {   // an entry's whole sum in this wave
+        if (e == first)
+            s_fsum[w] = make_float2(x, y);   // it may have begun in the wave before
+        else
+            out[e] = make_float2(x, y);
+    };
+    for (uint32_t r = a; r < b; r += kRound) {
+        uint32_t key[kRun];
+        float px[kRun], py[kRun];
+#pragma unroll
+        for (int i = 0; i < kRun; i++) {
+            key[i] = nx[i] >> 15;
+            const float2 d = s_d[nx[i] & 0x7FFFu];
+            px[i] = nw[i] * d.x;
+            py[i] = nw[i] * d.y;
+        }
+        load(min(r + kRound, b));
+        if (r == a) first = (uint32_t)__builtin_amdgcn_readfirstlane((int)key[0]);
+        float x = px[0], y = py[0], hx = 0.f, hy = 0.f;
+        bool pass = true;   // one entry so far
+#pragma unroll
+        for (int i = 1; i < kRun; i++) {
+            const bool cut = key[i] != key[i - 1];
+            if (cut && !pass) out[key[i - 1]] = make_float2(x, y);
+            hx = cut && pass ? x : hx;
+            hy = cut && pass ? y : hy;
+            pass = pass && !cut;
+            x = (cut ? 0.f : x) + px[i];
+            y = (cut ? 0.f : y) + py[i];
+        }
+        const uint32_t tail = key[kRun - 1];
+        uint32_t before = (uint32_t)__shfl_up((int)tail, 1);   // the last entry of the lane before
+        before = lane == 0 ? ckey : before;
+        const bool cont = key[0] == before;
+        uint32_t f = pass && cont ? 0u : 1u;
+        if (lane == 0 && !f) {
+            x += cx;
+            y += cy;
+        }
+        seg_step<0x111, 0xF>(x, y, f);   // row_shr 1, 2, 4, 8
+        seg_step<0x112, 0xF>(x, y, f);
+        seg_step<0x114, 0xF>(x, y, f);
+        seg_step<0x118, 0xF>(x, y, f);
+        seg_step<0x142, 0xA>(x, y, f);   // row_bcast 15 into rows 1 and 3
+        seg_step<0x143, 0xC>(x, y, f);   // row_bcast 31 into rows 2 and 3
+        float bx = __shfl_up(x, 1), by = __shfl_up(y, 1);
+        bx = lane == 0 ? cx : bx;
+        by = lane == 0 ? cy : by;
+        if (!cont && before != kNoEntry) store(before, bx, by);
+        if (!pass) store(key[0], hx + (cont ? bx : 0.f), hy + (cont ? by : 0.f));
+        ckey = (uint32_t)__builtin_amdgcn_readlane((int)tail, 63);
+        cx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+        cy = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(y), 63));
+    }
+    if (lane == 0) {
+        s_first[w] = first;
+        s_last[w] = ckey;
+        s_lsum[w] = make_float2(cx, cy);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        uint32_t key = kNoEntry;
+        float2 sum = make_float2(0.f, 0.f);
+        for (int k = 0; k < NW; k++) {
+            if (s_first[k] == kNoEntry) break;   // no contributions here and after
+            const bool one = s_first[k] == s_last[k];   // a single entry in the wave
+            const float2 head = one ? s_lsum[k] : s_fsum[k];
+            if (key == s_first[k]) {
+                sum = make_float2(sum.x + head.x, sum.y + head.y);
+            } else {
+                if (key != kNoEntry) out[key] = sum;
+                key = s_first[k];
+                sum = head;
+            }
+            if (!one) {
+                out[key] = sum;
+                key = s_last[k];
+                sum = s_lsum[k];
+            }
+        }
+        if (key != kNoEntry) out[key] = sum;
+    }
+}
+
+// The slices' sums added to the table gradient, slice by slice.
+__global__ __launch_bounds__(256) void k_chunk_sum(const float2* __restrict__ part, int slices, int64_t entries,
+                                                   float2* __restrict__ g_table) {
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= entries) return;
+    float2 a = make_float2(0.f, 0.f);
+    int k = 0;
+    for (; k + 8 <= slices; k += 8) {
+        float2 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) v[u] = part[(k + u) * entries + e];
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            a.x += v[u].x;
+            a.y += v[u].y;
+        }
+    }
+    for (; k < slices; k++) {
+        const float2 v = part[k * entries + e];
+        a.x += v.x;
+        a.y += v.y;
+    }
+    const float2 o = g_table[e];
+    g_table[e] = make_float2(o.x + a.x, o.y + a.y);
 }
 
 // Table gradient of means that were not prepared: every (point, level) adds
@@ -1256,6 +1466,13 @@ void table_grad(const Launch& L, const NtcDev& nd, const float* means, int64_t n
         }
         return;
     }
+    if (csr->slices > 0) {
+        hipLaunchKernelGGL(k_csr_chunk, dim3((unsigned)(16 * csr->slices)), dim3(1024), 0, L.st, nd, n, csr->slices,
+                           csr->entries, csr->starts, csr->pw, denc, csr->part);
+        hipLaunchKernelGGL(k_chunk_sum, dim3(nblk(csr->entries, 256)), dim3(256), 0, L.st, csr->part, csr->slices,
+                           csr->entries, reinterpret_cast<float2*>(g_table));
+        return;
+    }
     if (128 * n <= kShortMean * csr->entries) {
         hipLaunchKernelGGL(k_csr_gather_short, dim3(nblk(csr->entries, 4 * kShortEntries)), dim3(256), 0, L.st, csr->entries, csr->rows,
                            csr->pw, denc, n, g_table);
@@ -1330,7 +1547,15 @@ void ntc_backward(const Launch& L, int precision, const NtcDev& nd, const void* 
     }
 }
 
+bool ntc_csr_chunked(const NtcDev& nd, int64_t n) {
+    bool fits = n >= kChunkMin;
+    for (int lv = 0; lv < 16; lv++) fits = fits && nd.level_size(lv) <= kListEntries;
+    return fits;
+}
+
 int64_t ntc_csr_slices(const NtcDev& nd, int64_t n) {
+    // a workgroup per level and slice, whole rounds of one per CU
+    if (ntc_csr_chunked(nd, n)) return 16 * ((n + 16 * kChunkPoints - 1) / (16 * kChunkPoints));
     TableParts tp;
     if (!table_parts(nd, kListEntries, tp)) return 0;
     // one workgroup per CU (the LDS holds one), a slice of at least 1024 points
@@ -1345,16 +1570,24 @@ void ntc_csr_build(const Launch& L, const NtcDev& nd, const float* means, int64_
         const int slices = (int)ntc_csr_slices(nd, n);
         const unsigned grid = (unsigned)(tp.count * slices);
         hipLaunchKernelGGL(k_csr_count, dim3(grid), dim3(1024), 0, L.st, nd, tp, means, n, slices, csr.entries, w.cnt);
-        hipLaunchKernelGGL(k_csr_totals, dim3(nblk(csr.entries, 256)), dim3(256), 0, L.st, w.cnt, slices, csr.entries,
-                           w.first);
-        scan_u32_to_u32(inner, w.first, csr.entries, w.first, w.tmp, w.tmp + 1);
-        hipLaunchKernelGGL(k_csr_slots, dim3(nblk(csr.entries, 256)), dim3(256), 0, L.st, w.cnt, slices, csr.entries,
-                           w.first, csr.rows);
+        csr.slices = 0;
+        if (ntc_csr_chunked(nd, n)) {
+            csr.slices = slices;
+            csr.starts = w.cnt;
+            scan_u32_to_u32(inner, w.cnt, slices * csr.entries + 1, w.cnt, w.tmp, w.tmp + 1);
+        } else {
+            hipLaunchKernelGGL(k_csr_totals, dim3(nblk(csr.entries, 256)), dim3(256), 0, L.st, w.cnt, slices,
+                               csr.entries, w.first);
+            scan_u32_to_u32(inner, w.first, csr.entries, w.first, w.tmp, w.tmp + 1);
+            hipLaunchKernelGGL(k_csr_slots, dim3(nblk(csr.entries, 256)), dim3(256), 0, L.st, w.cnt, slices,
+                               csr.entries, w.first, csr.rows);
+        }
         hipLaunchKernelGGL(k_csr_place, dim3(grid), dim3(256), 0, L.st, nd, tp, means, n, slices, csr.entries, w.cnt,
-                           csr.pw);
+                           csr.slices > 0, csr.pw);
         if (L.prof) L.prof->end(L.st);
         return;
     }
+    csr.slices = 0;
     const int64_t m = n * 128;
     const uint32_t sentinel = (uint32_t)csr.entries;
     int bits = 1;

@@ -153,3 +153,52 @@ def test_few_points_gather(n, log2_T, spread):
     scale = float(got[0].abs().max())
     assert float((got[0] - got[2]).abs().max()) <= 5e-4 * scale
     ctx.close()
+
+
+@pytest.mark.parametrize("n,kind", [(220_000, "box"), (323_584, "box"), (323_585, "box"), (220_001, "cell"),
+                                    (230_000, "corner"), (260_003, "out")])
+def test_lists_by_slices(n, kind):
+    """The lists of many points, kept slice by slice: the table gradient of the
+    scattered one, and the same bits each time.  cell: an entry's list reaches
+    over lanes, rounds and waves; corner: most entries have none; out: slices
+    without a contribution."""
+    from paper_2403_01444_amd import gs3
+    cfg = synth.NTCConfig()
+    rng = np.random.default_rng(n)
+    x = rng.uniform(-1.25, 1.25, size=(n, 3))
+    if kind == "cell":
+        x = 0.01 + 0.0005 * rng.uniform(size=(n, 3))
+    elif kind == "corner":
+        x = -1.2 + 0.3 * rng.uniform(size=(n, 3))
+    elif kind == "out":
+        x[30_000:90_000] = 2.0
+        x[-70_000:] = -3.0
+    m = cuda(x)
+    gm, gq = cuda(rng.normal(size=(n, 3)) * 1e-3), cuda(rng.normal(size=(n, 4)) * 1e-3)
+    t = cfg.num_table_params()
+    p = synth.ntc_init_params(cfg, 1)
+    p[:t] *= 1000.0
+    got = []
+    for again in range(2):
+        ctx = gs3.Context(n, 1 << 10, 16, 16, ntc=cfg, precision="f16")
+        ctx.ntc_load(p)
+        if again:
+            ctx.ntc_prepare(cuda(rng.uniform(-1, 1, size=(n // 2, 3))))   # other lists before
+        tok = ctx.ntc_prepare(m)
+        ctx.ntc_backward(m, gm, gq, tok)
+        got.append(ctx.ntc_grads()[:t])
+        if again:
+            ctx.ntc_backward(m, gm, gq, tok)       # adds to what is there
+            twice = ctx.ntc_grads()[:t]
+            ctx.ntc_zero_grads()
+            ctx.ntc_backward(m, gm, gq)
+            got.append(ctx.ntc_grads()[:t])
+        ctx.close()
+    assert torch.equal(got[0], got[1]) and torch.equal(twice, got[0] + got[1])
+    # float32 sums of the same products against sums in double of 8192 points
+    # and less: the fullest entry adds up to 8 n products ("cell"), of random
+    # sign, in runs of a few hundred, so 1000 roundings of 2^-24 relative to
+    # sums that are as large as the result within a factor of a few
+    a, b = got[0].double(), got[2].double()
+    assert float(a.abs().max()) > 0
+    assert float((a - b).abs().max()) <= 5e-4 * float(a.abs().max())
