@@ -81,17 +81,28 @@ __device__ __forceinline__ typename P::AF frag_k_contig(const typename P::S* bas
     }
     return f;
 }
-// fragment with elements base[(k0 + i) * ld + col] (strided in k)
+// Fragment with elements base[(k0 + i) * ld + c0 + (lane & 15)] (strided in
+// k), k0 the same for the 16 lanes of a group: in the half types one
+// transposing read, to which lane j of a group gives the place of four columns
+// of row j / 4.
 template <class P>
-__device__ __forceinline__ typename P::AF frag_k_strided(const typename P::S* base, int ld, int col, int k0) {
-    typename P::AF f;
+__device__ __forceinline__ typename P::AF frag_k_strided(const typename P::S* base, int ld, int c0, int k0, int lane) {
+    const int j = lane & 15;
     if constexpr (P::KPL == 1) {
-        f = base[k0 * ld + col];
+        return base[k0 * ld + c0 + j];
     } else {
-#pragma unroll
-        for (int i = 0; i < P::KPL; i++) f[i] = base[(k0 + i) * ld + col];
+        typedef short s4v __attribute__((ext_vector_type(4)));
+        typedef __attribute__((address_space(3))) s4v lds_s4v;
+        const typename P::S* at = base + (k0 + (j >> 2)) * ld + c0 + 4 * (j & 3);   // 8-byte aligned
+        return __builtin_bit_cast(typename P::AF, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v*)at));
     }
-    return f;
+}
+
+// four consecutive elements, 4-element aligned
+template <class P>
+__device__ __forceinline__ void store4(typename P::S* at, const typename P::S v[4]) {
+    typedef typename P::S s4 __attribute__((ext_vector_type(4)));
+    *reinterpret_cast<s4*>(at) = s4{v[0], v[1], v[2], v[3]};
 }
 
 // Inside the batch loops each wave works on its own activation arrays in LDS
@@ -227,6 +238,28 @@ __device__ __forceinline__ f4v layer_tile(const typename P::S* W, int ldw, int m
     }
     return acc;
 }
+// The same with W^T, from W in the half types and from a transposed copy Wt in
+// float, whose transposed reads would meet on the banks.
+template <class P, int K>
+__device__ __forceinline__ f4v layer_tile_t(const typename P::S* W, int ldw, const typename P::S* Wt, int ldt, int m0,
+                                            const typename P::S* X, int ldx, int lane) {
+    if constexpr (P::KPL == 1) return layer_tile<P, K>(Wt, ldt, m0, X, ldx, lane);
+    f4v acc = {0.f, 0.f, 0.f, 0.f};
+    const int row = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int ks = 0; ks < K / P::KSTEP; ks++) {
+        const int k0 = ks * P::KSTEP + P::KPL * g;
+        acc = P::mfma(frag_k_strided<P>(W, ldw, m0, k0, lane), frag_k_contig<P>(X, ldx, row, k0), acc);
+    }
+    return acc;
+}
+// A layer's outputs (ReLU, rounded) of a lane, to LDS and kept in v.
+template <class P>
+__device__ __forceinline__ void relu_out(const f4v& a, typename P::S* at, typename P::S v[4]) {
+#pragma unroll
+    for (int r = 0; r < 4; r++) v[r] = P::cvt(fmaxf(a[r], 0.f));
+    store4<P>(at, v);
+}
 
 // encode this lane's 4 levels of its point into X[p][8 g .. 8 g + 7]
 template <class P>
@@ -335,13 +368,13 @@ __global__ __launch_bounds__(1024) void k_ntc_encode(NtcDev nd, const typename P
 // kGiven: enc holds the points' encoding; else they are encoded here, and the
 // encoding is stored in enc, if given, for the backward.
 template <class P, bool kGiven>
-__global__ __launch_bounds__(256) void k_ntc_fwd(NtcDev nd, const typename P::S* __restrict__ table,
+__global__ __launch_bounds__(256, 4) void k_ntc_fwd(NtcDev nd, const typename P::S* __restrict__ table,
                                                  const typename P::S* __restrict__ mlp, const float* __restrict__ means,
                                                  int64_t n, float* __restrict__ dmu, float* __restrict__ dq,
                                                  typename P::S* __restrict__ enc) {
     using S = typename P::S;
-    __shared__ S sW1[64 * LD32], sW2[64 * LD64], sW3[16 * LD64];
-    __shared__ S sX[kWaves][kPts * LD32], sH1[kWaves][kPts * LD64], sH2[kWaves][kPts * LD64];
+    __shared__ __align__(16) S sW1[64 * LD32], sW2[64 * LD64], sW3[16 * LD64];
+    __shared__ __align__(16) S sX[kWaves][kPts * LD32], sH1[kWaves][kPts * LD64], sH2[kWaves][kPts * LD64];
     load_weights<P>(mlp, sW1, sW2, sW3, nullptr, nullptr, nullptr);
     __syncthreads();
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -389,13 +422,15 @@ __global__ __launch_bounds__(256) void k_ntc_fwd(NtcDev nd, const typename P::S*
 #pragma unroll
         for (int mt = 0; mt < 4; mt++) {
             const f4v a = layer_tile<P, 32>(sW1, LD32, mt * 16, X, LD32, lane);
-            for (int r = 0; r < 4; r++) H1[p * LD64 + mt * 16 + 4 * g + r] = P::cvt(fmaxf(a[r], 0.f));
+            S v[4];
+            relu_out<P>(a, H1 + p * LD64 + mt * 16 + 4 * g, v);
         }
         wave_sync();
 #pragma unroll
         for (int mt = 0; mt < 4; mt++) {
             const f4v a = layer_tile<P, 64>(sW2, LD64, mt * 16, H1, LD64, lane);
-            for (int r = 0; r < 4; r++) H2[p * LD64 + mt * 16 + 4 * g + r] = P::cvt(fmaxf(a[r], 0.f));
+            S v[4];
+            relu_out<P>(a, H2 + p * LD64 + mt * 16 + 4 * g, v);
         }
         wave_sync();
         const f4v o = layer_tile<P, 64>(sW3, LD64, 0, H2, LD64, lane);
@@ -414,9 +449,20 @@ __global__ __launch_bounds__(256) void k_ntc_fwd(NtcDev nd, const typename P::S*
     }
 }
 
-__device__ __forceinline__ float wave_max(float v) {
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    return v;
+// v or its neighbour's by a DPP pattern, the larger (lanes without one keep v)
+template <int kCtrl, int kRows>
+__device__ __forceinline__ float dpp_max(float v) {
+    const int i = __float_as_int(v);
+    return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(i, i, kCtrl, kRows, 0xF, false)));
+}
+__device__ __forceinline__ float wave_max(float v) {   // patterns as in wave_sum_dpp
+    v = dpp_max<0xB1, 0xF>(v);
+    v = dpp_max<0x4E, 0xF>(v);
+    v = dpp_max<0x141, 0xF>(v);
+    v = dpp_max<0x140, 0xF>(v);
+    v = dpp_max<0x142, 0xA>(v);
+    v = dpp_max<0x143, 0xC>(v);
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
 // exponent k of the power of two 2^k with max * 2^k in [2^12, 2^13); 0 when
@@ -444,25 +490,32 @@ __device__ __forceinline__ int clamp_exp(int k) { return k < -126 ? -126 : (k > 
 // rows 16 w.. of dW1 and dW2 and the 16 columns 16 w.. of dW3), so a wave
 // holds 7 accumulator tiles instead of 28 and the register file leaves room
 // for more than one wave per SIMD.
+// Two workgroups' registers per SIMD and LDS per CU; bound by instructions
+// issued, so fragments strided in the points are read transposed (four 2-byte
+// reads and their packing each, else), W1 and W2 are read either way from one
+// copy, a lane keeps its activations for the masks, and with two waves to a
+// SIMD the accumulators need no AGPRs (184 moves from them): 300K points fp16
+// 62 -> 47 us, 20,011 bf16 with the encoding 22 -> 19.
 template <class P>
-__global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S* __restrict__ table,
+__global__ __launch_bounds__(256, 2) void k_ntc_bwd(NtcDev nd, const typename P::S* __restrict__ table,
                                                  const typename P::S* __restrict__ mlp, const float* __restrict__ means,
                                                  int64_t n, const float* __restrict__ d_dmu,
                                                  const float* __restrict__ d_dq, float* __restrict__ g_part,
                                                  float* __restrict__ denc,
                                                  const typename P::S* __restrict__ enc_in) {
     using S = typename P::S;
-    constexpr int kWElems = 64 * LD32 + 64 * LD64 + 32 * LD64 + 64 * LD64 + 64 * LD16;
+    constexpr bool kCopies = P::KPL == 1;   // transposed copies of W1 and W2: see layer_tile_t
+    constexpr int kWElems = 64 * LD32 + 64 * LD64 + 64 * LD16 + (kCopies ? 32 * LD64 + 64 * LD64 : 0);
     __shared__ __align__(16) S sWraw[kWElems];
     S* sW1 = sWraw;
     S* sW2 = sW1 + 64 * LD32;
-    S* sW1t = sW2 + 64 * LD64;
-    S* sW2t = sW1t + 32 * LD64;
-    S* sW3t = sW2t + 64 * LD64;
+    S* sW3t = sW2 + 64 * LD64;
+    S* sW1t = kCopies ? sW3t + 64 * LD16 : nullptr;
+    S* sW2t = kCopies ? sW1t + 32 * LD64 : nullptr;
     // per wave: encoding, activations, their gradients, output gradient
-    __shared__ S sX[kWaves][kPts * LD32], sH1[kWaves][kPts * LD64], sH2[kWaves][kPts * LD64];
-    __shared__ S sD1[kWaves][kPts * LD64], sD2[kWaves][kPts * LD64];
-    __shared__ S sO[kWaves][kPts * LD16];
+    __shared__ __align__(16) S sX[kWaves][kPts * LD32], sH1[kWaves][kPts * LD64], sH2[kWaves][kPts * LD64];
+    __shared__ __align__(16) S sD1[kWaves][kPts * LD64], sD2[kWaves][kPts * LD64];
+    __shared__ __align__(16) S sO[kWaves][kPts * LD16];
     __shared__ int sK[kWaves][3];   // each batch's scale exponents k0, k1, k2
     load_weights<P>(mlp, sW1, sW2, nullptr, sW1t, sW2t, sW3t);
     __syncthreads();
@@ -538,19 +591,24 @@ __global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S*
         if (P::kScaled)
             k0 = clamp_exp(pow2_exp(wave_max(fmaxf(fmaxf(fabsf(dv[0]), fabsf(dv[1])), fmaxf(fabsf(dv[2]), fabsf(dv[3]))))));
         const float s0 = ldexpf(1.0f, k0);
-        for (int r = 0; r < 4; r++) O[p * LD16 + 4 * g + r] = P::cvt(dv[r] * s0);   // rows 8..15 stay zero
+        {
+            S v[4];
+            for (int r = 0; r < 4; r++) v[r] = P::cvt(dv[r] * s0);   // rows 8..15 stay zero
+            store4<P>(O + p * LD16 + 4 * g, v);
+        }
         wave_sync();
-        // 2. forward recompute
+        // 2. forward recompute; a lane's activations stay for the masks
+        S h1[4][4], h2[4][4];
 #pragma unroll
         for (int mt = 0; mt < 4; mt++) {
             const f4v a = layer_tile<P, 32>(sW1, LD32, mt * 16, X, LD32, lane);
-            for (int r = 0; r < 4; r++) H1[p * LD64 + mt * 16 + 4 * g + r] = P::cvt(fmaxf(a[r], 0.f));
+            relu_out<P>(a, H1 + p * LD64 + mt * 16 + 4 * g, h1[mt]);
         }
         wave_sync();
 #pragma unroll
         for (int mt = 0; mt < 4; mt++) {
             const f4v a = layer_tile<P, 64>(sW2, LD64, mt * 16, H1, LD64, lane);
-            for (int r = 0; r < 4; r++) H2[p * LD64 + mt * 16 + 4 * g + r] = P::cvt(fmaxf(a[r], 0.f));
+            relu_out<P>(a, H2 + p * LD64 + mt * 16 + 4 * g, h2[mt]);
         }
         wave_sync();
         // 3. dH2 = (W3^T dO) * [H2 > 0]
@@ -560,7 +618,7 @@ __global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S*
         for (int mt = 0; mt < 4; mt++) {
             d2[mt] = layer_tile<P, 16>(sW3t, LD16, mt * 16, O, LD16, lane);
             for (int r = 0; r < 4; r++) {
-                const bool on = P::tof(H2[p * LD64 + mt * 16 + 4 * g + r]) > 0.f;
+                const bool on = P::tof(h2[mt][r]) > 0.f;
                 d2[mt][r] = on ? d2[mt][r] : 0.f;
                 m2 = fmaxf(m2, fabsf(d2[mt][r]));
             }
@@ -569,8 +627,11 @@ __global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S*
         if (P::kScaled) k1 = clamp_exp(k0 + pow2_exp(wave_max(m2)));
         {
             const float f = ldexpf(1.0f, k1 - k0);
-            for (int mt = 0; mt < 4; mt++)
-                for (int r = 0; r < 4; r++) D2[p * LD64 + mt * 16 + 4 * g + r] = P::cvt(d2[mt][r] * f);
+            for (int mt = 0; mt < 4; mt++) {
+                S v[4];
+                for (int r = 0; r < 4; r++) v[r] = P::cvt(d2[mt][r] * f);
+                store4<P>(D2 + p * LD64 + mt * 16 + 4 * g, v);
+            }
         }
         wave_sync();
         // 4. dH1 = (W2^T dH2) * [H1 > 0]
@@ -578,9 +639,9 @@ __global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S*
         float m1 = 0.f;
 #pragma unroll
         for (int mt = 0; mt < 4; mt++) {
-            d1[mt] = layer_tile<P, 64>(sW2t, LD64, mt * 16, D2, LD64, lane);
+            d1[mt] = layer_tile_t<P, 64>(sW2, LD64, sW2t, LD64, mt * 16, D2, LD64, lane);
             for (int r = 0; r < 4; r++) {
-                const bool on = P::tof(H1[p * LD64 + mt * 16 + 4 * g + r]) > 0.f;
+                const bool on = P::tof(h1[mt][r]) > 0.f;
                 d1[mt][r] = on ? d1[mt][r] : 0.f;
                 m1 = fmaxf(m1, fabsf(d1[mt][r]));
             }
@@ -589,8 +650,11 @@ __global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S*
         if (P::kScaled) k2 = clamp_exp(k1 + pow2_exp(wave_max(m1)));
         {
             const float f = ldexpf(1.0f, k2 - k1);
-            for (int mt = 0; mt < 4; mt++)
-                for (int r = 0; r < 4; r++) D1[p * LD64 + mt * 16 + 4 * g + r] = P::cvt(d1[mt][r] * f);
+            for (int mt = 0; mt < 4; mt++) {
+                S v[4];
+                for (int r = 0; r < 4; r++) v[r] = P::cvt(d1[mt][r] * f);
+                store4<P>(D1 + p * LD64 + mt * 16 + 4 * g, v);
+            }
         }
         if (lane == 0) {
             sK[w][0] = k0;
@@ -603,7 +667,7 @@ __global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S*
             const float inv = ldexpf(1.0f, -k2);
 #pragma unroll
             for (int mt = 0; mt < 2; mt++) {
-                const f4v e = layer_tile<P, 64>(sW1t, LD64, mt * 16, D1, LD64, lane);
+                const f4v e = layer_tile_t<P, 64>(sW1, LD32, sW1t, LD64, mt * 16, D1, LD64, lane);
                 // level-major [level][point][2]: one level's slice (8 n bytes)
                 // stays cache-resident while the gather walks that level
                 if (valid) {
@@ -626,8 +690,8 @@ __global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S*
 #pragma unroll
                 for (int ks = 0; ks < kPts / P::KSTEP; ks++) {
                     const int kk = ks * P::KSTEP + P::KPL * g;
-                    t = P::mfma(frag_k_strided<P>(sO[b], LD16, col, kk),
-                                frag_k_strided<P>(sH2[b], LD64, w * 16 + col, kk), t);
+                    t = P::mfma(frag_k_strided<P>(sO[b], LD16, 0, kk, lane),
+                                frag_k_strided<P>(sH2[b], LD64, w * 16, kk, lane), t);
                 }
                 gW3 += t * inv0;
             }
@@ -638,8 +702,8 @@ __global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S*
 #pragma unroll
                 for (int ks = 0; ks < kPts / P::KSTEP; ks++) {
                     const int kk = ks * P::KSTEP + P::KPL * g;
-                    t = P::mfma(frag_k_strided<P>(sD2[b], LD64, w * 16 + col, kk),
-                                frag_k_strided<P>(sH1[b], LD64, nt * 16 + col, kk), t);
+                    t = P::mfma(frag_k_strided<P>(sD2[b], LD64, w * 16, kk, lane),
+                                frag_k_strided<P>(sH1[b], LD64, nt * 16, kk, lane), t);
                 }
                 gW2[nt] += t * inv1;
             }
@@ -650,8 +714,8 @@ __global__ __launch_bounds__(256) void k_ntc_bwd(NtcDev nd, const typename P::S*
 #pragma unroll
                 for (int ks = 0; ks < kPts / P::KSTEP; ks++) {
                     const int kk = ks * P::KSTEP + P::KPL * g;
-                    t = P::mfma(frag_k_strided<P>(sD1[b], LD64, w * 16 + col, kk),
-                                frag_k_strided<P>(sX[b], LD32, nt * 16 + col, kk), t);
+                    t = P::mfma(frag_k_strided<P>(sD1[b], LD64, w * 16, kk, lane),
+                                frag_k_strided<P>(sX[b], LD32, nt * 16, kk, lane), t);
                 }
                 gW1[nt] += t * inv2;
             }
