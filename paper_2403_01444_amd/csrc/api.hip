@@ -103,6 +103,7 @@ struct Slot {
     // supers' lists of the depth-first binning (without gradient records):
     // ids are vals[0]; the walked blocks the forward keeps for the backward
     SuperDev sup{};
+    uint2* narrow_ranges = nullptr;  // views of few tiles: their lists in the walked blocks' room
     uint64_t* taken = nullptr;       // bit per walked entry and tile quadrant: a pixel there took it
     int* sorder = nullptr;           // supers, longest list first
     bool super = false;              // the last render binned into supers
@@ -250,7 +251,8 @@ gs3_status gs3_create(const gs3_config* cfg, gs3_ctx** out) {
             ok = c->alloc(&s.taken, blocks * (kWalkBlock / 64) * 4) &&
                  c->alloc(&u.masks, PK) && c->alloc(&u.start, nsuper) && c->alloc(&u.len, nsuper) &&
                  c->alloc(&u.walked, blocks * kWalkBlock) && c->alloc(&u.prev, blocks) &&
-                 c->alloc(&u.tile_blk, c->max_tiles) && c->alloc(&u.pool, 1) && c->alloc(&s.sorder, nsuper);
+                 c->alloc(&u.tile_blk, c->max_tiles) && c->alloc(&u.pool, 2) && c->alloc(&s.sorder, nsuper) &&
+                 c->alloc(&s.narrow_ranges, kNarrowTiles);
             u.ids = s.vals[0];
             u.cap = (uint32_t)PK;
             u.max_blocks = (uint32_t)blocks;
@@ -706,6 +708,7 @@ gs3_status gs3_render(gs3_ctx* c, int32_t slot, const gs3_gaussians* g, const fl
     gd.means = g->means; gd.quats = g->quats; gd.log_scales = g->log_scales; gd.opac = g->opacity_logits;
     gd.sh = g->sh; gd.dmu = dmu; gd.dq = dq; gd.n = g->n; gd.sh_degree = g->sh_degree;
     const int ntiles = cd.tiles_x * cd.tiles_y;
+    const bool narrow = narrow_tiles(ntiles, c->grec_cap > 0);
     const uint64_t cap = (uint64_t)c->cfg.max_pairs;
     Launch L = c->L();
     const int64_t n = g->n;
@@ -718,8 +721,9 @@ gs3_status gs3_render(gs3_ctx* c, int32_t slot, const gs3_gaussians* g, const fl
             sl.super = c->grec_cap <= 0;
             if (sl.super) {
                 sl.sup.supers_x = super_count_of(cd.tiles_x);
-                super_bin(L, order, n, sl.rect, cd.tiles_x, cd.tiles_y, cap, (uint32_t)ntiles, c->bin_rect, c->sup_hist,
-                          c->sup_ksum, sl.total, c->flags, sl.sup, narrow_tiles(ntiles) ? nullptr : sl.sorder);
+                super_bin(L, order, n, sl.rect, cd.tiles_x, cd.tiles_y, cap, narrow ? 0u : (uint32_t)ntiles, c->bin_rect,
+                          c->sup_hist, c->sup_ksum, sl.total, c->flags, sl.sup, narrow ? nullptr : sl.sorder);
+                if (narrow) super_lists(L, sl.sup, cd.tiles_x, ntiles, sl.narrow_ranges, sl.tile_walk);
             } else {
                 // tile-major list: the record gather needs every pair's slot,
                 // from the first pair slot of each Gaussian
@@ -758,9 +762,14 @@ gs3_status gs3_render(gs3_ctx* c, int32_t slot, const gs3_gaussians* g, const fl
             gpos_from_pairs(L, sl.pkeys[sl.cur], sl.vals[sl.cur], (int64_t)K, sl.rect, sl.goff, cd.tiles_x, cap,
                             sl.gpos);
     }
-    if (!sl.super && !narrow_tiles(ntiles)) tile_order(L, sl.ranges, nullptr, ntiles, sl.order_fwd);
-    blend_forward(L, cd, sl.ranges, sl.vals[sl.cur], sl.rec, image, sl.T_final, sl.last, sl.tile_walk,
-                  sl.super ? sl.sorder : sl.order_fwd, sl.taken, sl.super ? &sl.sup : nullptr);
+    if (!sl.super) {
+        // the narrow forward's quarters of a tile meet in tile_walk
+        if (narrow) fill_u32(L, sl.tile_walk, 0u, ntiles);
+        else tile_order(L, sl.ranges, nullptr, ntiles, sl.order_fwd);
+    }
+    const bool listed = sl.super && narrow;
+    blend_forward(L, cd, listed ? sl.narrow_ranges : sl.ranges, listed ? sl.sup.walked : sl.vals[sl.cur], sl.rec, image, sl.T_final, sl.last, sl.tile_walk,
+                  sl.super ? sl.sorder : sl.order_fwd, sl.taken, sl.super ? &sl.sup : nullptr, narrow);
     gs3_status st = c->check_launch("render");
     if (st != GS3_OK) return st;
     sl.g = gd;
@@ -784,10 +793,12 @@ gs3_status gs3_render_backward(gs3_ctx* c, int32_t slot, const float* d_image, c
     ga.rect = sl.rect; ga.goff = sl.goff; ga.gpos = sl.gpos; ga.ranges = sl.ranges; ga.tile_walk = sl.tile_walk;
     ga.walk_off = c->walk_off; ga.grec = c->grec; ga.grec_cap = (uint64_t)c->grec_cap;
     ga.cap = (uint64_t)c->cfg.max_pairs;
-    if (!narrow_tiles(ntiles)) tile_order(L, sl.ranges, sl.tile_walk, ntiles, sl.order_bwd);
-    blend_backward(L, sl.cam, sl.ranges, sl.vals[sl.cur], sl.rec, d_image, sl.T_final, sl.last, ga, c->accum,
+    const bool narrow = narrow_tiles(ntiles, c->grec_cap > 0);
+    if (!narrow) tile_order(L, sl.ranges, sl.tile_walk, ntiles, sl.order_bwd);
+    const bool listed = sl.super && narrow;
+    blend_backward(L, sl.cam, listed ? sl.narrow_ranges : sl.ranges, listed ? sl.sup.walked : sl.vals[sl.cur], sl.rec, d_image, sl.T_final, sl.last, ga, c->accum,
                    out->d_opacity != nullptr || out->d_opacity_logits != nullptr, sl.order_bwd, sl.taken,
-                   sl.super ? &sl.sup : nullptr);
+                   sl.super ? &sl.sup : nullptr, narrow);
     GradsDev gd;
     gd.d_means = out->d_means; gd.d_quats = out->d_quats; gd.d_log_scales = out->d_log_scales;
     gd.d_opac = out->d_opacity_logits; gd.d_sh = out->d_sh; gd.d_dmu = sl.g.dmu ? out->d_dmu : nullptr;

@@ -125,7 +125,8 @@ struct GatherDev {
 // backward in blocks of kWalkBlock entries, `walked`: a tile's first block is
 // the tile's index, later ones come from the counter *pool; prev[b] is the
 // block before block b of the same tile, tile_blk[tile] the block that holds
-// the tile's last contributor.
+// the tile's last contributor.  For the narrow blends `walked` holds tile-major
+// lists instead (super_lists), and *pool counts their entries.
 constexpr int kSuperShift = 2;
 constexpr int kSuperDim = 1 << kSuperShift;
 constexpr int kSuperChunk = 512;   // depth-ordered Gaussians per workgroup of the binning
@@ -141,7 +142,7 @@ struct SuperDev {
     uint32_t* walked;     // max_blocks x kWalkBlock
     uint32_t* prev;
     uint32_t* tile_blk;
-    uint32_t* pool;
+    uint32_t* pool;       // two words, the second zero
     uint32_t max_blocks;
 };
 int64_t super_chunks(int64_t n);
@@ -153,6 +154,9 @@ int super_count_of(int tiles);   // supers along one axis
 void super_bin(const Launch& L, const uint32_t* order, int64_t n, const uint2* rect, int tiles_x, int tiles_y,
                uint64_t cap, uint32_t pool0, uint2* srect, uint32_t* hist, uint64_t* ksum, uint64_t* total,
                int* overflow, const SuperDev& sd, int* sorder);
+// tile-major lists in sd.walked (ranges: ntiles) for the narrow blends, after
+// super_bin with pool0 = 0; clears tile_walk
+void super_lists(const Launch& L, const SuperDev& sd, int tiles_x, int ntiles, uint2* ranges, uint32_t* tile_walk);
 // inspection: the pairs per tile, and the tile-major pair list
 void super_tile_counts(const Launch& L, const SuperDev& sd, int tiles_x, int tiles_y, uint32_t* ttot);
 void super_pairs(const Launch& L, const SuperDev& sd, int tiles_x, int tiles_y, const uint2* ranges,
@@ -163,7 +167,8 @@ void super_pairs(const Launch& L, const SuperDev& sd, int tiles_x, int tiles_y, 
 void tile_order(const Launch& L, const uint2* ranges, const uint32_t* walk, int ntiles, int* order);
 // Whether a view of ntiles tiles takes the narrow blends, whose workgroups
 // are all in flight at once: no order of the tiles is needed then.
-bool narrow_tiles(int ntiles);
+bool narrow_tiles(int ntiles, bool records);
+constexpr int kNarrowTiles = 512;
 // supers: the supers' lists (order then maps places to supers), or NULL for a
 // tile-major list read through ranges (order maps workgroups to tiles).
 // `order` is optional.  taken: for every 64 entries of a tile's list four
@@ -173,11 +178,12 @@ bool narrow_tiles(int ntiles);
 // last contributor are written.
 void blend_forward(const Launch& L, const CamDev& cam, const uint2* ranges, const uint32_t* vals, const float4* rec,
                    float* image, float* T_final, uint32_t* last, uint32_t* tile_walk, const int* order, uint64_t* taken,
-                   const SuperDev* supers);
+                   const SuperDev* supers, bool narrow);
 // supers: walk the blocks the forward kept, or NULL for the tile-major list
 void blend_backward(const Launch& L, const CamDev& cam, const uint2* ranges, const uint32_t* vals,
                     const float4* rec, const float* d_image, const float* T_final, const uint32_t* last,
-                    const GatherDev& ga, float* accum, bool want_opacity, const int* order, const uint64_t* taken, const SuperDev* supers);
+                    const GatherDev& ga, float* accum, bool want_opacity, const int* order, const uint64_t* taken, const SuperDev* supers,
+                    bool narrow);
 
 struct GradsDev {
     float *d_means, *d_quats, *d_log_scales, *d_opac, *d_sh, *d_dmu, *d_dq;

@@ -747,6 +747,45 @@ constexpr int kBwdGroup = 2;     // entries evaluated and reduced together
 static_assert(kBwdGroup % 2 == 0, "entries are reduced two at a time");
 __constant__ float kConicScale[9] = {1.f, 1.f, -0.5f, -1.f, -0.5f, 1.f, 1.f, 1.f, 1.f};
 
+// A batch's sums of the waves (s_g, [wave][term][entry]; on: the entries each
+// wave visited, [word][wave]) added to accum.  A lane has one term of an entry
+// throughout and a wave seven entries at a time, so the rounds need no
+// divisions, a round's LDS reads are independent, and an entry's nine atomics
+// are adjacent lanes on adjacent addresses (one or two cache lines).  The mean
+// terms come from the sums of dp dx and dp dy (the neighbouring lane's) and
+// the entry's conic (A, B, C).  Against a division, the wave masks one by one
+// and a branch for the mean terms in every round, the whole backward went from
+// 156 to 128 us at 50K Gaussians and 256 x 256, from 220 to 208 at 300K and
+// 1352 x 1014, from 295 to 288 at 502K and 1080p (rounds unrolled: 214 and
+// 305, for the registers).
+template <int NW, int KB, bool kOpacity, class Conic>
+__device__ __forceinline__ void add_batch(int cnt, int w, int lane, const uint64_t (&on)[2][NW],
+                                          const float (&s_g)[NW][9][KB + 1], const uint32_t* s_id, Conic conic,
+                                          float* __restrict__ accum) {
+    constexpr int kPer = 7, kRounds = (KB + kPer * NW - 1) / (kPer * NW);
+    const int l = min(lane, 62) / 9, k = min(lane, 62) - 9 * l;
+    const bool mine = lane < 63 && (kOpacity || k != 5);
+    const float scale = kConicScale[k];
+    const int other = k == 0 ? lane + 1 : k == 1 ? lane - 1 : lane;
+#pragma unroll 1
+    for (int i = 0; i < kRounds; i++) {
+        if (kPer * NW * i >= cnt) break;
+        const int e0 = (i * NW + w) * kPer + l, e = min(e0, KB - 1);
+        const uint32_t* words = reinterpret_cast<const uint32_t*>(&on[e >> 6][0]) + ((e >> 5) & 1);
+        float v = 0.f;
+#pragma unroll
+        for (int q = 0; q < NW; q++) {
+            const float g = s_g[q][k][e];
+            v += (words[2 * q] >> (e & 31)) & 1u ? g : 0.f;
+        }
+        const float o = __shfl(v, other);
+        const float3 c = conic(e);
+        const float m = c.y * o + (k == 0 ? c.x : c.z) * v;
+        v = k <= 1 ? m : v * scale;
+        if (mine && e0 < cnt && v != 0.f) atomicAdd(accum + 9 * (int64_t)s_id[e] + k, v);
+    }
+}
+
 template <bool kSuper, bool kRecords, bool kOpacity>
 __global__ __launch_bounds__(kBlendThreads) void k_blend_bwd(CamDev cam, int ntiles, const uint2* __restrict__ ranges,
                                                              const uint32_t* __restrict__ vals,
@@ -984,16 +1023,9 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend_bwd(CamDev cam, int nti
                 }
             }
         } else {
-            // lane = (entry, term): the atomics of one entry's terms are
-            // adjacent lanes on adjacent addresses (one or two cache lines)
-            for (int q = tid; q < 9 * cnt; q += NT) {
-                const int e = q / 9, k = q - 9 * e;
-                if (!kOpacity && k == 5) continue;
-                const uint32_t on = taken_by(e);
-                if (!on) continue;
-                const float v = entry_term(k, e, on);
-                if (v != 0.f) atomicAdd(accum + 9 * (int64_t)s_id[e] + k, v);
-            }
+            add_batch<NW, KB, kOpacity>(
+                cnt, w, lane, s_taken, s_g, s_id, [&](int e) { return make_float3(s_w0[e].z, s_w0[e].w, s_w1[e].x); },
+                accum);
         }
         __syncthreads();
     }
@@ -1010,13 +1042,25 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend_bwd(CamDev cam, int nti
 // same as entry by entry.  A block of 16 pixels is reached by half as many
 // entries as a quadrant of 64 where the Gaussians are small, and the
 // exponents, tests and gradient terms of four entries cost one evaluation.
-// Bound by VALU issue of the tile's one CU.  Per launch, 8 x 8 -> narrow, 50K
-// surfaces at 256 x 256: forward 226 -> 118 us, backward 331 -> 196; 2K
-// uniform at 64 x 64: 54 -> 32, 95 -> 55.  Where it is chosen: narrow_tiles.
+// A workgroup takes a quarter of a tile (8 x 8 pixels, four waves), so that
+// the longest tile, which bounds such launches, is spread over four CUs: at 50K
+// surfaces and 256 x 256 a tile walks 388 entries on average and 2742 at most.
+// The quarters read tile-major lists (k_super_lists writes them for views of
+// few tiles) and stop each by itself.  Only the backward with gradient records
+// keeps a tile to a workgroup, for a record holds the whole tile's sums.  What
+// is left is the latency of the longest quarter's one wave per SIMD.  Per
+// launch, 8 x 8 pixels a wave -> a workgroup a tile -> a quarter, 50K surfaces
+// at 256 x 256: forward 226 -> 118 -> 82 us (and 8 for the lists), backward 331
+// -> 196 -> 128; 2K uniform at 64 x 64: 54 -> 32 -> 20 (and 5), 95 -> 55 -> 33.
+// Where they are chosen: narrow_tiles.
 // ---------------------------------------------------------------------------
-constexpr int kNarrowThreads = 1024;
-constexpr int kNarrowWaves = kNarrowThreads / 64;   // one per 4 x 4 block: block w at (w & 3, w >> 2)
+constexpr int kNarrowThreads = 1024;    // a workgroup a tile: a wave per 4 x 4 block, block w at (w & 3, w >> 2)
+constexpr int kQuarterThreads = 256;    // a workgroup a quarter, four blocks
+constexpr int kQuarterWaves = kQuarterThreads / 64;
 constexpr int kSlots = 4;
+__device__ __forceinline__ int quarter_block(int quarter, int w) {
+    return (2 * (quarter >> 1) + (w >> 1)) * 4 + 2 * (quarter & 1) + (w & 1);
+}
 
 // x of the four rows (slots) of a wave, each in every row: s[k] holds, in lane
 // l, the value of lane 16 k + (l & 15).
@@ -1075,8 +1119,7 @@ template <int N>
 struct NarrowRecs {
     float4 a[N + 1], b[N + 1], col[N + 1];
     uint32_t box[N + 1];
-    __device__ __forceinline__ void put(int j, const float4* __restrict__ rec, uint32_t id, int tx0p, int ty0p) {
-        const float4 r0 = rec[3 * (int64_t)id], r1 = rec[3 * (int64_t)id + 1], r2 = rec[3 * (int64_t)id + 2];
+    __device__ __forceinline__ void put(int j, const float4& r0, const float4& r1, const float4& r2, int tx0p, int ty0p) {
         const float4 w2 = blend_stage_w2(r2, tx0p, ty0p);
         a[j] = r0;
         b[j] = make_float4(r1.x, r1.y, w2.y, w2.z);
@@ -1089,138 +1132,109 @@ struct NarrowRecs {
     }
 };
 
-template <bool kSuper>
-__global__ __launch_bounds__(kNarrowThreads) void k_blend_fwd_narrow(CamDev cam, int ntiles,
-                                                                     const uint2* __restrict__ ranges,
-                                                                     const uint32_t* __restrict__ vals,
-                                                                     const float4* __restrict__ rec,
-                                                                     float* __restrict__ image,
-                                                                     float* __restrict__ T_final,
-                                                                     uint32_t* __restrict__ last_out,
-                                                                     uint32_t* __restrict__ tile_walk, SuperDev sd) {
-    constexpr int NT = kNarrowThreads, NW = kNarrowWaves, NB = kWalkBlock;   // NB entries a batch
+// A batch's records on their way from a tile-major list to LDS: the ids are
+// loaded two batches ahead and the records one, so neither is waited for.
+struct Ahead {
+    float4 r0, r1, r2;
+    uint32_t id, next;   // of the records, and of the batch after
+    __device__ __forceinline__ void records(const float4* __restrict__ rec) {
+        r0 = rec[3 * (int64_t)id];
+        r1 = rec[3 * (int64_t)id + 1];
+        r2 = rec[3 * (int64_t)id + 2];
+    }
+};
+
+__global__ __launch_bounds__(kQuarterThreads) void k_blend_fwd_narrow(CamDev cam, const uint2* __restrict__ ranges,
+                                                                      const uint32_t* __restrict__ vals,
+                                                                      const float4* __restrict__ rec,
+                                                                      float* __restrict__ image,
+                                                                      float* __restrict__ T_final,
+                                                                      uint32_t* __restrict__ last_out,
+                                                                      uint32_t* __restrict__ tile_walk) {
+    constexpr int NB = kQuarterThreads, NW = kQuarterWaves;   // NB entries a batch
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int tile = blockIdx.x;
-    if (tile >= ntiles) return;
+    const int tile = blockIdx.x >> 2, quarter = blockIdx.x & 3;
     const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
     __shared__ NarrowRecs<NB> s_r;
-    __shared__ uint32_t s_q[kSuper ? NB + NT : 1];   // queue of indices
-    __shared__ uint32_t s_n[2][NW];
-    __shared__ uint64_t s_reach[NW][NB / 64];        // [block][word]
-    __shared__ uint16_t s_list[NW][NB + kSlots];     // entries that reach the wave's block, in order
-    __shared__ uint32_t s_live[2], s_blk, s_walk;
+    __shared__ __align__(8) uint16_t s_list[NW][NB + 3 * kSlots];   // entries that reach the wave's block, in order
+    __shared__ uint32_t s_live[2];
     const int tx0p = tx * kTile, ty0p = ty * kTile;
-    const int row = lane >> 4, pix = lane & 15;
-    const int lx = 4 * (w & 3) + (pix & 3), ly = 4 * (w >> 2) + (pix >> 2);
+    const int row = lane >> 4, pix = lane & 15, block = quarter_block(quarter, w);
+    const int lx = 4 * (block & 3) + (pix & 3), ly = 4 * (block >> 2) + (pix >> 2);
     const int px = tx0p + lx, py = ty0p + ly;
     const float fpx = (float)px, fpy = (float)py;
     const uint32_t sel = (1u << lx) | (1u << (16 + ly));
     float T = 1.0f, c = 0.f;                          // c: the channel of the lane's row (none in row 3)
     uint32_t last = 0u;                               // of the lane's slot
     uint64_t alive = __builtin_amdgcn_ballot_w64(px < cam.W && py < cam.H);
-    if (tid == 0) {
-        s_walk = 0u;
-        s_r.put_none(NB);
+    const uint2 rg = ranges[tile];
+    const uint32_t n = rg.y - rg.x;
+    const uint32_t* const list = vals + rg.x;
+    Ahead ahead;
+    if ((uint32_t)tid < n) {
+        ahead.id = list[tid];
+        if ((uint32_t)tid + NB < n) ahead.next = list[tid + NB];
+        ahead.records(rec);
     }
-    uint32_t cur, cend, mk = 0u, nid = 0u, queued = 0u, tbit = 0u;
+    if (tid == 0) s_r.put_none(NB);
     int par = 0;
-    if (kSuper) {
-        const int sup = (ty >> kSuperShift) * sd.supers_x + (tx >> kSuperShift);
-        cur = sd.start[sup];
-        cend = min(sd.cap, cur + sd.len[sup]);
-        tbit = 1u << ((ty % kSuperDim) * kSuperDim + tx % kSuperDim);
-        if (cur + tid < cend) {
-            mk = sd.masks[cur + tid];
-            nid = sd.ids[cur + tid];
-        }
-    } else {
-        const uint2 rg = ranges[tile];
-        cur = rg.x;
-        cend = rg.y;
-    }
-    uint32_t blk = (uint32_t)tile, lastblk = (uint32_t)tile;
-    for (uint32_t eb = 0;;) {
-        uint32_t myid = 0u, cnt_u;
-        if (tid < 2) s_live[tid] = 0u;
-        if (kSuper) {
-            while (queued < (uint32_t)NB && cur < cend) {
-                const bool on = (mk & tbit) != 0u && cur + tid < cend;
-                const uint64_t bal = __ballot(on);
-                if (lane == 0) s_n[par][w] = (uint32_t)__popcll(bal);
-                __syncthreads();
-                uint32_t at = queued + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-#pragma unroll
-                for (int k = 0; k < NW; k++) {
-                    const uint32_t v = s_n[par][k];
-                    if (k < w) at += v;
-                    queued += v;
-                }
-                if (on) s_q[at] = nid;   // at < NB - 1 + NT
-                par ^= 1;
-                cur += NT;
-                if (cur + tid < cend) {
-                    mk = sd.masks[cur + tid];
-                    nid = sd.ids[cur + tid];
-                }
-            }
-            if (queued == 0u) break;
-            cnt_u = min((uint32_t)NB, queued);
-            __syncthreads();
-            if ((uint32_t)tid < cnt_u) myid = s_q[tid];
-        } else {
-            if (cur >= cend) break;
-            cnt_u = min((uint32_t)NB, cend - cur);
-            if ((uint32_t)tid < cnt_u) myid = vals[cur + tid];
-            cur += cnt_u;
-        }
-        if ((uint32_t)tid < cnt_u) s_r.put(tid, rec, myid, tx0p, ty0p);
-        // the queue's entries past this batch move to its front
-        uint32_t rest = 0u;
-        if (kSuper && (uint32_t)tid + NB < queued) rest = s_q[NB + tid];
-        __syncthreads();
-        if (kSuper) {
-            if ((uint32_t)tid + NB < queued) s_q[tid] = rest;
-            queued -= cnt_u;
-            if (tid == 0 && eb != 0u) blk = atomicAdd(sd.pool, 1u);   // a walked block, see k_blend_fwd
-        }
-        {
-            // entry 64 (w & 3) + lane against blocks 4 (w >> 2) .. + 3
-            const int j = 64 * (w & 3) + lane;
-            const float4 ra = s_r.a[j], rb = s_r.b[j];
-            const uint32_t box = s_r.box[j];
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                const int b = 4 * (w >> 2) + k;
-                const uint64_t m =
-                    __builtin_amdgcn_ballot_w64((uint32_t)j < cnt_u && block_reached(ra, rb, box, b, tx0p, ty0p));
-                if (lane == 0) s_reach[b][w & 3] = m;
-            }
+    for (uint32_t eb = 0; eb < n; eb += NB, par ^= 1) {
+        const uint32_t cnt_u = min((uint32_t)NB, n - eb);
+        if ((uint32_t)tid < cnt_u) s_r.put(tid, ahead.r0, ahead.r1, ahead.r2, tx0p, ty0p);
+        if (tid == 0) s_live[par] = 0u;
+        if (eb + NB + tid < n) {
+            ahead.id = ahead.next;
+            if (eb + 2 * NB + tid < n) ahead.next = list[eb + 2 * NB + tid];
+            ahead.records(rec);
         }
         __syncthreads();
-        uint64_t took = 0ull;
         if (alive) {
             int listed = 0;
 #pragma unroll
             for (int q = 0; q < NB / 64; q++) {
-                const uint64_t m = uniform64(s_reach[w][q]);
-                if ((m >> lane) & 1ull)
-                    s_list[w][listed + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(64 * q + lane);
+                const int j = 64 * q + lane;
+                const float4 ra = s_r.a[j], rb = s_r.b[j];
+                const uint64_t m = __builtin_amdgcn_ballot_w64((uint32_t)j < cnt_u &&
+                                                               block_reached(ra, rb, s_r.box[j], block, tx0p, ty0p));
+                if ((m >> lane) & 1ull) s_list[w][listed + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)j;
                 listed += __popcll(m);
             }
-            if (lane < kSlots) s_list[w][listed + lane] = (uint16_t)NB;   // a last group of fewer entries
+            if (lane < 3 * kSlots) s_list[w][listed + lane] = (uint16_t)NB;   // a last group of fewer entries, and two more
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll 1
-            for (int g = 0; g < listed && alive; g += kSlots) {
-                const uint16_t* l = &s_list[w][g];
-                const int j = l[row];
-                const float4 ra = s_r.a[j], rb = s_r.b[j];
-                const uint32_t box = s_r.box[j];
-                // the colours of the four slots, this row's channel
-                float col[kSlots];
+            // four entries' opacities; the next four's records are on their
+            // way from LDS meanwhile (a heavy quarter has a wave per SIMD)
+            struct Four {
+                float as[kSlots], col[kSlots];   // opacity 0 in the lanes that do not take their entry
+                uint64_t ok;
+                int j;
+            };
+            struct Rec {
+                float4 ra, rb;
+                float col[kSlots];   // the colours of the four slots, this row's channel
+                uint32_t box;
+                int j;
+            };
+            auto four_at = [&](int g) { return *reinterpret_cast<const uint64_t*>(&s_list[w][g]); };
+            auto load = [&](uint64_t l) {
+                Rec v;
+                v.j = (int)((l >> (16 * row)) & 0xFFFFu);
+                v.ra = s_r.a[v.j];
+                v.rb = s_r.b[v.j];
+                v.box = s_r.box[v.j];
 #pragma unroll
-                for (int s = 0; s < kSlots; s++) col[s] = reinterpret_cast<const float*>(&s_r.col[l[s]])[row];
+                for (int s = 0; s < kSlots; s++)
+                    v.col[s] = reinterpret_cast<const float*>(&s_r.col[(l >> (16 * s)) & 0xFFFFu])[row];
+                return v;
+            };
+            auto eval = [&](const Rec& r) {
+                Four v;
+                v.j = r.j;
+                const float4 ra = r.ra, rb = r.rb;
+                const uint32_t box = r.box;
+#pragma unroll
+                for (int s = 0; s < kSlots; s++) v.col[s] = r.col[s];
                 float adx2, bdx;
                 blend_dx_terms(fpx - ra.x, ra, adx2, bdx);
                 const float power = blend_power(adx2, bdx, fpy - ra.y, rb.x);
@@ -1228,53 +1242,52 @@ __global__ __launch_bounds__(kNarrowThreads) void k_blend_fwd_narrow(CamDev cam,
                                     __builtin_amdgcn_ballot_w64(power <= 0.0f) &
                                     __builtin_amdgcn_ballot_w64(power >= rb.z);
                 const uint64_t bm = pm & __builtin_amdgcn_ballot_w64(power < rb.w);
-                uint64_t okm = pm & ~bm;
-                if (bm) okm |= bm & __builtin_amdgcn_ballot_w64(blend_exact_test(power, rb.y));
-                if (!okm) continue;
-                // opacity 0 in the lanes that do not take their entry: it
-                // leaves the transmittance and the colour as they are (T is
-                // never below the stop's 1e-4)
-                const float al =
-                    __builtin_amdgcn_inverse_ballot_w64(okm) ? fminf(0.99f, rb.y * __expf(power)) : 0.0f;
-                float as[kSlots];
-                rows_all(al, as);
-                uint64_t own = 0ull;   // lanes whose own slot's entry is taken
+                v.ok = pm & ~bm;
+                if (bm) v.ok |= bm & __builtin_amdgcn_ballot_w64(blend_exact_test(power, rb.y));
+                rows_all(__builtin_amdgcn_inverse_ballot_w64(v.ok) ? fminf(0.99f, rb.y * __expf(power)) : 0.0f, v.as);
+                return v;
+            };
+            Rec ahead4 = load(four_at(0));
+            uint64_t l = four_at(kSlots);
+#pragma unroll 1
+            for (int g = 0; g < listed && alive; g += kSlots) {
+                const Four cur = eval(ahead4);
+                ahead4 = load(l);
+                l = four_at(g + 2 * kSlots);
+                if (!cur.ok) continue;
+                // opacity 0 leaves the transmittance and the colour as they
+                // are (T is never below the stop's 1e-4)
+                float Ts[kSlots + 1];
+                Ts[0] = T;
 #pragma unroll
-                for (int s = 0; s < kSlots; s++) {
-                    const float Tn = T * (1.0f - as[s]);
-                    const uint64_t stop = alive & __builtin_amdgcn_ballot_w64(Tn < 1e-4f);
-                    const uint64_t takem = alive & ~stop;
-                    const bool take = __builtin_amdgcn_inverse_ballot_w64(takem);
-                    const float wgt = take ? as[s] * T : 0.0f;
-                    c += wgt * col[s];
-                    T = take ? Tn : T;
-                    alive = takem;
-                    own |= takem & (0xFFFFull << (16 * s));
+                for (int s = 0; s < kSlots; s++) Ts[s + 1] = Ts[s] * (1.0f - cur.as[s]);
+                uint64_t own = cur.ok;   // lanes whose own slot's entry is taken
+                if ((alive & __builtin_amdgcn_ballot_w64(Ts[kSlots] < 1e-4f)) == 0ull) {
+#pragma unroll
+                    for (int s = 0; s < kSlots; s++) c += (cur.as[s] * Ts[s]) * cur.col[s];
+                    T = Ts[kSlots];
+                } else {   // a pixel stops among the four
+                    uint64_t taken = 0ull;
+#pragma unroll
+                    for (int s = 0; s < kSlots; s++) {
+                        const float Tn = T * (1.0f - cur.as[s]);
+                        const uint64_t stop = alive & __builtin_amdgcn_ballot_w64(Tn < 1e-4f);
+                        const uint64_t takem = alive & ~stop;
+                        const bool take = __builtin_amdgcn_inverse_ballot_w64(takem);
+                        const float wgt = take ? cur.as[s] * T : 0.0f;
+                        c += wgt * cur.col[s];
+                        T = take ? Tn : T;
+                        alive = takem;
+                        taken |= takem & (0xFFFFull << (16 * s));
+                    }
+                    own &= taken;
                 }
-                own &= okm;
-                took |= own;
-                last = __builtin_amdgcn_inverse_ballot_w64(own) ? eb + (uint32_t)j + 1u : last;
+                last = __builtin_amdgcn_inverse_ballot_w64(own) ? eb + (uint32_t)cur.j + 1u : last;
             }
         }
-        if (lane == 0) {
-            if (alive) s_live[0] = 1u;
-            if (took) s_live[1] = 1u;
-        }
-        if (kSuper && tid == 0) {
-            if (blk >= sd.max_blocks) blk = 0xFFFFFFFFu;   // only when the pairs overflowed
-            if (eb != 0u && blk != 0xFFFFFFFFu) sd.prev[blk] = s_blk;
-            s_blk = blk;
-        }
+        if (lane == 0 && alive) s_live[par] = 1u;
         __syncthreads();
-        if (kSuper) {
-            const uint32_t b = s_blk;
-            if ((uint32_t)tid < cnt_u && b != 0xFFFFFFFFu) sd.walked[(int64_t)b * kWalkBlock + tid] = myid;
-            if (s_live[1]) lastblk = b;   // the last contributor's so far
-        }
-        eb += cnt_u;
-        const bool more = s_live[0] != 0u;
-        __syncthreads();   // s_live is cleared for the next batch
-        if (!more) break;
+        if (s_live[par] == 0u) break;
     }
     const int64_t P = (int64_t)cam.W * cam.H;
     if (px < cam.W && py < cam.H) {
@@ -1286,43 +1299,35 @@ __global__ __launch_bounds__(kNarrowThreads) void k_blend_fwd_narrow(CamDev cam,
     last = max(last, (uint32_t)__shfl_xor((int)last, 16));
     last = max(last, (uint32_t)__shfl_xor((int)last, 32));
     if (row == 3 && px < cam.W && py < cam.H) last_out[(int64_t)py * cam.W + px] = last;
-    __syncthreads();
-    if (last && row == 0) atomicMax(&s_walk, last);
-    __syncthreads();
-    if (tid == 0) {
-        const bool lost = kSuper && lastblk == 0xFFFFFFFFu;   // see k_blend_fwd
-        tile_walk[tile] = lost ? 0u : s_walk;
-        if (kSuper) sd.tile_blk[tile] = lost ? (uint32_t)tile : lastblk;
-    }
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) last = max(last, (uint32_t)__shfl_xor((int)last, off));
+    if (lane == 0 && last) atomicMax(tile_walk + tile, last);
 }
 
-template <bool kSuper, bool kRecords, bool kOpacity>
-__global__ __launch_bounds__(kNarrowThreads) void k_blend_bwd_narrow(
-    CamDev cam, int ntiles, const uint2* __restrict__ ranges, const uint32_t* __restrict__ vals,
-    const float4* __restrict__ rec, const float* __restrict__ d_image, const float* __restrict__ T_final,
-    const uint32_t* __restrict__ last_in, const uint32_t* __restrict__ tile_walk, const uint32_t* __restrict__ walk_off,
-    float* __restrict__ grec, uint32_t grec_cap, float* __restrict__ accum, SuperDev sd) {
-    constexpr int NT = kNarrowThreads, NW = kNarrowWaves, KB = kBwdBatch;
-    static_assert(KB == 128 && kWalkBlock % KB == 0, "two words, and a batch lies in one walked block");
+// kRecords: a workgroup a tile (its entries' records hold the whole tile's
+// sums); else a quarter.
+template <bool kRecords, bool kOpacity>
+__global__ __launch_bounds__(kRecords ? kNarrowThreads : kQuarterThreads) void k_blend_bwd_narrow(
+    CamDev cam, const uint2* __restrict__ ranges, const uint32_t* __restrict__ vals, const float4* __restrict__ rec,
+    const float* __restrict__ d_image, const float* __restrict__ T_final, const uint32_t* __restrict__ last_in,
+    const uint32_t* __restrict__ walk_off, float* __restrict__ grec, uint32_t grec_cap, float* __restrict__ accum) {
+    constexpr int NT = kRecords ? kNarrowThreads : kQuarterThreads, NW = NT / 64, KB = kBwdBatch;
+    static_assert(KB == 128 && KB <= NT, "two words, and a thread per entry");
     __shared__ NarrowRecs<KB> s_r;
     __shared__ uint32_t s_id[KB];
-    __shared__ uint64_t s_reach[NW][2];
-    __shared__ uint16_t s_list[NW][KB + kSlots];
+    __shared__ uint64_t s_reach[2][NW];
+    __shared__ uint16_t s_list[NW][KB + 3 * kSlots];
     __shared__ float s_g[NW][9][KB + 1];   // per-wave sums, [wave][term][entry]; the last is no entry's
-    const int tile = blockIdx.x;
-    if (tile >= ntiles) return;
-    const uint32_t maxlast = tile_walk[tile];
-    if (maxlast == 0) return;
+    __shared__ uint32_t s_last[NW];
+    const int tile = kRecords ? blockIdx.x : blockIdx.x >> 2;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
     const int tx0p = tx * kTile, ty0p = ty * kTile;
-    const int row = lane >> 4, pix = lane & 15;
-    const int lx = 4 * (w & 3) + (pix & 3), ly = 4 * (w >> 2) + (pix >> 2);
+    const int row = lane >> 4, pix = lane & 15, block = kRecords ? w : quarter_block(blockIdx.x & 3, w);
+    const int lx = 4 * (block & 3) + (pix & 3), ly = 4 * (block >> 2) + (pix >> 2);
     const int px = tx0p + lx, py = ty0p + ly;
     const float fpx = (float)px, fpy = (float)py;
     const uint32_t sel = (1u << lx) | (1u << (16 + ly));
-    const uint32_t start = kSuper ? 0u : ranges[tile].x;
-    uint32_t blk = kSuper ? sd.tile_blk[tile] : 0u;
     const uint32_t woff = kRecords ? walk_off[tile] : 0u;
     const int64_t P = (int64_t)cam.W * cam.H;
     float T = 1.0f, g0 = 0.f, g1 = 0.f, g2 = 0.f;
@@ -1342,28 +1347,33 @@ __global__ __launch_bounds__(kNarrowThreads) void k_blend_bwd_narrow(
     wlast = __builtin_amdgcn_readfirstlane(wlast);
     const int term = row_term(pix);
     const int slot9 = term < 5 ? term : term + 1;   // index in the nine-term layout
+    if (lane == 0) s_last[w] = wlast;
     if (tid == 0) s_r.put_none(KB);
-    for (int64_t jb = ((int64_t)(maxlast - 1) / KB) * KB; jb >= 0; jb -= KB) {
-        const uint32_t e = (uint32_t)jb + tid;
+    __syncthreads();
+    uint32_t maxlast = 0u;
+#pragma unroll
+    for (int k = 0; k < NW; k++) maxlast = max(maxlast, s_last[k]);
+    if (maxlast == 0) return;
+    const uint32_t* const list = vals + ranges[tile].x;
+    const int64_t top = ((int64_t)(maxlast - 1) / KB) * KB;
+    Ahead ahead;   // walking back: the batch below is the next
+    if (tid < KB) {
+        if (top >= KB) ahead.next = list[top - KB + tid];
+        if (top + tid < (int64_t)maxlast) {
+            ahead.id = list[top + tid];
+            ahead.records(rec);
+        }
+    }
+    for (int64_t jb = top; jb >= 0; jb -= KB) {
         const int cnt = (int)min((int64_t)KB, (int64_t)maxlast - jb);
         if (tid < cnt) {
-            const uint32_t id = kSuper ? sd.walked[(int64_t)blk * kWalkBlock + (e % kWalkBlock)] : vals[start + e];
-            s_id[tid] = id;
-            s_r.put(tid, rec, id, tx0p, ty0p);
+            s_id[tid] = ahead.id;
+            s_r.put(tid, ahead.r0, ahead.r1, ahead.r2, tx0p, ty0p);
         }
-        if (kSuper && jb > 0 && jb % kWalkBlock == 0) blk = sd.prev[blk];
-        __syncthreads();
-        {
-            // entry 64 (w & 1) + lane against blocks 2 (w >> 1), + 1
-            const int j = 64 * (w & 1) + lane;
-            const float4 ra = s_r.a[j], rb = s_r.b[j];
-            const uint32_t box = s_r.box[j];
-#pragma unroll
-            for (int k = 0; k < 2; k++) {
-                const int b = 2 * (w >> 1) + k;
-                const uint64_t m = __builtin_amdgcn_ballot_w64(j < cnt && block_reached(ra, rb, box, b, tx0p, ty0p));
-                if (lane == 0) s_reach[b][w & 1] = m;
-            }
+        if (tid < KB && jb >= KB) {
+            ahead.id = ahead.next;
+            if (jb >= 2 * KB) ahead.next = list[jb - 2 * KB + tid];
+            ahead.records(rec);
         }
         __syncthreads();
         // the block's entries, last first, up to its last contributor; the
@@ -1372,104 +1382,130 @@ __global__ __launch_bounds__(kNarrowThreads) void k_blend_bwd_narrow(
         const int64_t before = (int64_t)wlast - jb;
 #pragma unroll
         for (int q = 1; q >= 0; q--) {
-            uint64_t m = uniform64(s_reach[w][q]);
-            const int64_t left = before - 64 * q;
-            m = left <= 0 ? 0ull : left >= 64 ? m : m & ((1ull << left) - 1ull);
+            const int j = 64 * q + lane;
+            const int64_t left = min(before, (int64_t)cnt) - 64 * q;
+            uint64_t m = 0ull;
+            if (left > 0) {
+                const float4 ra = s_r.a[j], rb = s_r.b[j];
+                m = __builtin_amdgcn_ballot_w64(lane < left && block_reached(ra, rb, s_r.box[j], block, tx0p, ty0p));
+            }
             const int n = __popcll(m);
             if ((m >> lane) & 1ull)
-                s_list[w][listed + n - 1 - __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(64 * q + lane);
+                s_list[w][listed + n - 1 - __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)j;
             listed += n;
-            if (lane == 0) s_reach[w][q] = m;
+            if (lane == 0) s_reach[q][w] = m;
         }
-        if (lane < kSlots) s_list[w][listed + lane] = (uint16_t)KB;
+        if (lane < 3 * kSlots) s_list[w][listed + lane] = (uint16_t)KB;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll 1
-        for (int g = 0; g < listed; g += kSlots) {
-            const int j = s_list[w][g + row];
-            const float4 ra = s_r.a[j], rb = s_r.b[j], rc = s_r.col[j];
-            const uint32_t box = s_r.box[j];
-            const float dx = fpx - ra.x, dy = fpy - ra.y;
+        // four entries up to their opacities and colour terms; see the forward
+        struct Four {
+            float as[kSlots], ds[kSlots];   // opacity zero: the pixel's state is kept
+            float al, raw, G, dx, dy;       // the lane's own slot
+            uint64_t ok;
+            int j;
+        };
+        struct Rec {
+            float4 ra, rb, rc;
+            uint32_t box;
+            int j;
+        };
+        auto load = [&](int j) { return Rec{s_r.a[j], s_r.b[j], s_r.col[j], s_r.box[j], j}; };
+        auto eval = [&](const Rec& r) {
+            Four v;
+            v.j = r.j;
+            const float4 ra = r.ra, rb = r.rb, rc = r.rc;
+            const uint32_t box = r.box;
+            v.dx = fpx - ra.x;
+            v.dy = fpy - ra.y;
             float adx2, bdx;
-            blend_dx_terms(dx, ra, adx2, bdx);
-            const float power = blend_power(adx2, bdx, dy, rb.x);
-            const uint64_t pm = __builtin_amdgcn_ballot_w64((uint32_t)jb + (uint32_t)j < last) &
+            blend_dx_terms(v.dx, ra, adx2, bdx);
+            const float power = blend_power(adx2, bdx, v.dy, rb.x);
+            const uint64_t pm = __builtin_amdgcn_ballot_w64((uint32_t)jb + (uint32_t)v.j < last) &
                                 __builtin_amdgcn_ballot_w64((box & sel) == sel) &
                                 __builtin_amdgcn_ballot_w64(power <= 0.0f) & __builtin_amdgcn_ballot_w64(power >= rb.z);
             const uint64_t bm = pm & __builtin_amdgcn_ballot_w64(power < rb.w);
-            uint64_t okm = pm & ~bm;
-            if (bm) okm |= bm & __builtin_amdgcn_ballot_w64(blend_exact_test(power, rb.y));
+            v.ok = pm & ~bm;
+            if (bm) v.ok |= bm & __builtin_amdgcn_ballot_w64(blend_exact_test(power, rb.y));
+            v.G = __expf(power);
+            v.raw = rb.y * v.G;
+            v.al = __builtin_amdgcn_inverse_ballot_w64(v.ok) ? fminf(0.99f, v.raw) : 0.0f;
+            rows_all(v.al, v.as);
+            rows_all(g0 * rc.x + g1 * rc.y + g2 * rc.z, v.ds);
+            return v;
+        };
+        Rec ahead4 = load(s_list[w][row]);
+        int j = s_list[w][kSlots + row];
+#pragma unroll 1
+        for (int g = 0; g < listed; g += kSlots) {
+            const Four cur = eval(ahead4);
+            ahead4 = load(j);
+            j = s_list[w][g + 2 * kSlots + row];
             float red = 0.f, redop = 0.f;
-            if (okm) {
-                const bool ok = __builtin_amdgcn_inverse_ballot_w64(okm);
-                const float G = __expf(power), raw = rb.y * G;
-                const float al = ok ? fminf(0.99f, raw) : 0.0f;   // zero: the pixel's state is kept
-                float as[kSlots], ds[kSlots];
-                rows_all(al, as);
-                rows_all(g0 * rc.x + g1 * rc.y + g2 * rc.z, ds);
+            if (cur.ok) {
                 float To = 0.f, d = 0.f;   // transmittance before, and colour term of, the lane's own slot
 #pragma unroll
                 for (int s = 0; s < kSlots; s++) {
                     // T recovery T_i = T_{i+1} / (1 - alpha_i), with the hardware reciprocal (1 ulp)
-                    T *= __builtin_amdgcn_rcpf(1.0f - as[s]);
-                    const float di = ds[s] - gb;
-                    gb += as[s] * di;
+                    T *= __builtin_amdgcn_rcpf(1.0f - cur.as[s]);
+                    const float di = cur.ds[s] - gb;
+                    gb += cur.as[s] * di;
                     To = row == s ? T : To;
                     d = row == s ? di : d;
                 }
-                const float wgt = al * To;
+                const float wgt = cur.al * To;
                 const float dal = To * d;
                 const bool unclamped =
-                    __builtin_amdgcn_inverse_ballot_w64(okm & __builtin_amdgcn_ballot_w64(raw < 0.99f));
-                const float dp = unclamped ? dal * raw : 0.0f;
-                const float ax = dp * dx, ay = dp * dy;   // terms: see k_blend_bwd
-                const float t8[8] = {ax, ay, ax * dx, ax * dy, ay * dy, g0 * wgt, g1 * wgt, g2 * wgt};
+                    __builtin_amdgcn_inverse_ballot_w64(cur.ok & __builtin_amdgcn_ballot_w64(cur.raw < 0.99f));
+                const float dp = unclamped ? dal * cur.raw : 0.0f;
+                const float ax = dp * cur.dx, ay = dp * cur.dy;   // terms: see k_blend_bwd
+                const float t8[8] = {ax, ay, ax * cur.dx, ax * cur.dy, ay * cur.dy, g0 * wgt, g1 * wgt, g2 * wgt};
                 red = row_reduce_scatter8(t8, pix);
                 if (kOpacity) {
-                    float o = unclamped ? dal * G : 0.0f;
+                    float o = unclamped ? dal * cur.G : 0.0f;
                     o = dpp_add<0xB1, 0xF>(o);
                     o = dpp_add<0x4E, 0xF>(o);
                     o = dpp_add<0x141, 0xF>(o);
                     redop = dpp_add<0x140, 0xF>(o);   // row_mirror
                 }
             }
-            if ((pix & 1) == 0) s_g[w][slot9][j] = red;
-            if (kOpacity && pix == 1) s_g[w][5][j] = redop;
+            if ((pix & 1) == 0) s_g[w][slot9][cur.j] = red;
+            if (kOpacity && pix == 1) s_g[w][5][cur.j] = redop;
         }
         __syncthreads();
-        auto visited_by = [&](int e) -> uint32_t {
-            uint32_t on = 0u;
+        if constexpr (!kRecords) {
+            add_batch<NW, KB, kOpacity>(
+                cnt, w, lane, s_reach, s_g, s_id, [&](int e) { return make_float3(s_r.a[e].z, s_r.a[e].w, s_r.b[e].x); },
+                accum);
+        } else {
+            auto over_waves = [&](int k, int e, uint32_t on) -> float {
+                float v = 0.f;
+                for (; on; on &= on - 1u) v += s_g[__builtin_ctz(on)][k][e];
+                return v;
+            };
+            for (int q = tid; q < 9 * cnt; q += NT) {
+                const int e = q / 9, k = q - 9 * e;
+                float v = 0.f;
+                if (kOpacity || k != 5) {
+                    uint32_t on = 0u;
 #pragma unroll
-            for (int q = 0; q < NW; q++) on |= (uint32_t)((s_reach[q][e >> 6] >> (e & 63)) & 1ull) << q;
-            return on;
-        };
-        auto over_waves = [&](int k, int e, uint32_t on) -> float {
-            float v = 0.f;
-            for (; on; on &= on - 1u) v += s_g[__builtin_ctz(on)][k][e];
-            return v;
-        };
-        auto entry_term = [&](int k, int e, uint32_t on) -> float {
-            const float v = over_waves(k, e, on);
-            if (k <= 1) {
-                const float o = over_waves(1 - k, e, on);
-                const float4 w0 = s_r.a[e];
-                const float C = s_r.b[e].x;
-                return k == 0 ? w0.z * v + w0.w * o : w0.w * o + C * v;
+                    for (int u = 0; u < NW; u++) on |= (uint32_t)((s_reach[e >> 6][u] >> (e & 63)) & 1ull) << u;
+                    v = over_waves(k, e, on);
+                    if (k <= 1) {
+                        const float o = over_waves(1 - k, e, on);
+                        const float4 a = s_r.a[e];
+                        v = k == 0 ? a.z * v + a.w * o : a.w * o + s_r.b[e].x * v;
+                    } else {
+                        v *= kConicScale[k];
+                    }
+                }
+                const uint32_t widx = woff + (uint32_t)jb + e;   // compact index of this walked entry
+                if (widx < grec_cap)
+                    grec[(int64_t)k * grec_cap + widx] = v;
+                else if (v != 0.f)
+                    atomicAdd(accum + 9 * (int64_t)s_id[e] + k, v);
             }
-            return v * kConicScale[k];
-        };
-        for (int q = tid; q < 9 * cnt; q += NT) {
-            const int e = q / 9, k = q - 9 * e;
-            const bool none = !kOpacity && k == 5;
-            if (!kRecords && none) continue;
-            const uint32_t on = visited_by(e);
-            const float v = none ? 0.f : entry_term(k, e, on);
-            const uint32_t widx = woff + (uint32_t)jb + e;   // compact index of this walked entry
-            if (kRecords && widx < grec_cap)
-                grec[(int64_t)k * grec_cap + widx] = v;
-            else if (v != 0.f)
-                atomicAdd(accum + 9 * (int64_t)s_id[e] + k, v);
         }
         __syncthreads();
     }
@@ -1800,24 +1836,25 @@ void tile_order(const Launch& L, const uint2* ranges, const uint32_t* walk, int 
     if (L.prof) L.prof->end(L.st);
 }
 
-// Views of at most a tile per CU take the narrow blends.  Render / backward of
-// 50K surface Gaussians (us), 8 x 8 against narrow: 100 tiles 396 / 480
-// against 242 / 280, 256 tiles 290 / 336 against 192 / 202; of 50K uniform
-// ones: 100 tiles 150 / 94 against 120 / 82, 256 tiles 109 / 75 against 94 /
-// 60, but 400 tiles 108 / 71 against 114 / 88 and 1024 tiles 109 / 72 against
-// 150 / 147: with more tiles than CUs the 8 x 8 blends fill the SIMDs, and
-// evaluate a large Gaussian's pixels 64 at a time.
-bool narrow_tiles(int ntiles) { return ntiles <= 256; }
+// Views of at most two tiles per CU take the narrow blends.  Render / backward
+// of 50K surface Gaussians (us), 8 x 8 against narrow: 100 tiles 383 / 450
+// against 165 / 180, 256 tiles 276 / 320 against 132 / 126, 529 tiles 200 / 209
+// against 117 / 92; of 50K uniform ones: 256 tiles 96 / 69 against 84 / 46, 529
+// tiles 91 / 65 against 96 / 57, 784 tiles 91 / 62 against 106 / 70, 1620
+// tiles 105 / 83 against 148 / 130: with many tiles of like lists the 8 x 8
+// blends fill the SIMDs, and evaluate a large Gaussian's pixels 64 at a time.
+// With gradient records the backward keeps a tile to a workgroup: at most one
+// per CU (400 uniform tiles 108 / 71 against 114 / 88).
+bool narrow_tiles(int ntiles, bool records) { return ntiles <= (records ? kNarrowTiles / 2 : kNarrowTiles); }
 
 void blend_forward(const Launch& L, const CamDev& cam, const uint2* ranges, const uint32_t* vals, const float4* rec,
                    float* image, float* T_final, uint32_t* last, uint32_t* tile_walk, const int* order, uint64_t* taken,
-                   const SuperDev* supers) {
+                   const SuperDev* supers, bool narrow) {
     const int ntiles = cam.tiles_x * cam.tiles_y;
     if (L.prof) L.prof->begin("blend_fwd", L.st);
-    if (narrow_tiles(ntiles)) {
-        hipLaunchKernelGGL(supers ? k_blend_fwd_narrow<true> : k_blend_fwd_narrow<false>, dim3((unsigned)ntiles),
-                           dim3(kNarrowThreads), 0, L.st, cam, ntiles, ranges, vals, rec, image, T_final, last,
-                           tile_walk, supers ? *supers : SuperDev{});
+    if (narrow) {
+        hipLaunchKernelGGL(k_blend_fwd_narrow, dim3(4u * (unsigned)ntiles), dim3(kQuarterThreads), 0, L.st, cam, ranges,
+                           vals, rec, image, T_final, last, tile_walk);
     } else if (supers) {
         const int nsuper = supers->supers_x * super_count_of(cam.tiles_y);
         const unsigned grid = (unsigned)((nsuper + 7) / 8 * 8 * kSuperDim * kSuperDim);
@@ -1833,18 +1870,17 @@ void blend_forward(const Launch& L, const CamDev& cam, const uint2* ranges, cons
 
 void blend_backward(const Launch& L, const CamDev& cam, const uint2* ranges, const uint32_t* vals, const float4* rec,
                     const float* d_image, const float* T_final, const uint32_t* last, const GatherDev& ga,
-                    float* accum, bool want_opacity, const int* order, const uint64_t* taken, const SuperDev* supers) {
+                    float* accum, bool want_opacity, const int* order, const uint64_t* taken, const SuperDev* supers,
+                    bool narrow) {
     const int ntiles = cam.tiles_x * cam.tiles_y;
     if (L.prof) L.prof->begin("blend_bwd", L.st);
     const bool records = ga.grec_cap > 0;
-    if (narrow_tiles(ntiles)) {
-        auto kern =
-            supers ? (want_opacity ? k_blend_bwd_narrow<true, false, true> : k_blend_bwd_narrow<true, false, false>)
-            : records ? (want_opacity ? k_blend_bwd_narrow<false, true, true> : k_blend_bwd_narrow<false, true, false>)
-                      : (want_opacity ? k_blend_bwd_narrow<false, false, true> : k_blend_bwd_narrow<false, false, false>);
-        hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(kNarrowThreads), 0, L.st, cam, ntiles, ranges, vals, rec,
-                           d_image, T_final, last, ga.tile_walk, ga.walk_off, ga.grec, (uint32_t)ga.grec_cap, accum,
-                           supers ? *supers : SuperDev{});
+    if (narrow) {
+        auto kern = records ? (want_opacity ? k_blend_bwd_narrow<true, true> : k_blend_bwd_narrow<true, false>)
+                            : (want_opacity ? k_blend_bwd_narrow<false, true> : k_blend_bwd_narrow<false, false>);
+        hipLaunchKernelGGL(kern, dim3((records ? 1u : 4u) * (unsigned)ntiles),
+                           dim3(records ? kNarrowThreads : kQuarterThreads), 0, L.st, cam, ranges, vals, rec, d_image,
+                           T_final, last, ga.walk_off, ga.grec, (uint32_t)ga.grec_cap, accum);
         if (L.prof) L.prof->end(L.st);
         return;
     }

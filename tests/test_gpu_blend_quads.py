@@ -78,7 +78,11 @@ def blend_records(key, box, rec, width, height, bg):
                                                  # past 256 tiles: the 8 x 8 quadrants
                                                  ("thin", 2000, 257, 256), ("tiny", 3000, 300, 290),
                                                  ("faint", 1500, 262, 259), ("long", 300, 272, 257),
-                                                 ("usual", 1000, 256, 256), ("usual", 1000, 258, 270)])
+                                                 ("usual", 1000, 256, 256), ("usual", 1000, 258, 270),
+                                                 # 512 tiles and past them
+                                                 ("usual", 1500, 512, 256), ("thin", 2000, 400, 340),
+                                                 ("tiny", 3000, 513, 256), ("faint", 1500, 371, 369),
+                                                 ("long", 300, 392, 350), ("usual", 1500, 390, 352)])
 def test_quadrants_take_every_contributor(kind, n, width, height):
     from paper_2403_01444_amd import gs3
     g = scene(kind, n, n)
@@ -118,7 +122,9 @@ def test_quadrants_take_every_contributor(kind, n, width, height):
 @pytest.mark.parametrize("log2", [0, 18])
 @pytest.mark.parametrize("scene_name,n,width,height", [("surfaces", 6000, 330, 300), ("usual", 3000, 330, 300),
                                                        ("wall", 900, 330, 300), ("thin", 900, 330, 300),
-                                                       ("surfaces", 6000, 120, 100), ("wall", 300, 120, 100)])
+                                                       ("surfaces", 6000, 120, 100), ("wall", 300, 120, 100),
+                                                       ("surfaces", 6000, 390, 340), ("usual", 3000, 390, 340),
+                                                       ("wall", 1200, 390, 340)])
 def test_blends_read_only_what_they_stage(scene_name, n, width, height, log2):
     """The blends do not depend on what earlier kernels left in LDS: with LDS
     full of NaN (the loss of NaN images leaves them there) the image and the

@@ -67,6 +67,25 @@ def test_supers_match_the_sorted_pairs(n, width, height, offset, pairs):
         assert np.abs(ga[k] - gb[k]).max() <= 2e-4 * np.abs(gb[k]).max(), k
 
 
+@pytest.mark.parametrize("width,height", [(500, 330)])
+def test_wide_views_report_an_overflow_and_stay_in_bounds(width, height):
+    """The same for a view of many tiles, whose forward keeps the blocks it walks."""
+    from paper_2403_01444_amd import gs3
+    g = synth.make_gaussians(4000, 0, 5)
+    cam = synth.look_at_camera(width, height)
+    full = gs3.Context(g.n, 1 << 22, width, height)
+    gg = gs3.GaussiansGPU.from_host(g)
+    full.render(gg, cam)
+    K, _ = full.debug_counts()
+    full.check_flags()
+    small = gs3.Context(g.n, K // 50, width, height)
+    img = small.render(gg, cam)
+    small.render_backward(torch.ones_like(img), {"d_uv": small.zeros(g.n, 2)})
+    assert small.debug_counts() == (K, 1)
+    full.close()
+    small.close()
+
+
 def test_supers_report_an_overflow_and_stay_in_bounds():
     """More pairs than the capacity: reported like before, the render and its
     backward stay in bounds, and the pair count is still the true one."""
