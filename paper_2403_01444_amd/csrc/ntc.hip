@@ -12,8 +12,9 @@
 // own batch; then the four waves accumulate the weight gradients of the
 // four batches with MFMA (contraction over each batch's 16 points) in FP32
 // registers, each wave a quarter of the weight tiles; the encoding gradient
-// goes to the per-entry gather of the table gradient, or is scatter-added
-// into it with global atomics.
+// goes to the per-entry sums of the table gradient over the prepared lists, or
+// is added to the table's parts in LDS (very large tables: with global
+// atomics).
 //
 // Half-precision backward: each activation-gradient stage is rescaled by a
 // power of two so that its largest magnitude in the batch sits near 2^13
@@ -1135,8 +1136,9 @@ __global__ __launch_bounds__(1024) void k_csr_chunk(NtcDev nd, int64_t n, int sl
     float2* const out = part + slice * entries + nd.off[lv];
     // the waves take equal parts of the list, in whole rounds
     constexpr uint32_t kRound = 64 * kRun;
-    const uint32_t A = st[0], B = st[size], perw = (B - A + NW * kRound - 1) / (NW * kRound) * kRound;
-    const uint32_t a = min(B, A + w * perw), b = min(B, a + perw);
+    const uint32_t total = st[size] - st[0], perw = (total + NW * kRound - 1) / (NW * kRound) * kRound;
+    const uint32_t a = min(total, w * perw), b = min(total, a + perw);
+    const uint2* const list = pw + st[0];
     uint32_t nx[kRun];
     float nw[kRun];
     auto load = [&](uint32_t r) {   // the lane's contributions of the round at r
@@ -1144,7 +1146,7 @@ __global__ __launch_bounds__(1024) void k_csr_chunk(NtcDev nd, int64_t n, int sl
         if (k + kRun <= b) {
 #pragma unroll
             for (int i = 0; i < kRun; i += 2) {
-                const pw2 v = *reinterpret_cast<const pw2*>(pw + k + i);
+                const pw2 v = *reinterpret_cast<const pw2*>(list + k + i);
                 nx[i] = v.x;
                 nw[i] = __uint_as_float(v.y);
                 nx[i + 1] = v.z;
@@ -1154,7 +1156,7 @@ __global__ __launch_bounds__(1024) void k_csr_chunk(NtcDev nd, int64_t n, int sl
 #pragma unroll
             for (int i = 0; i < kRun; i++) {
                 const bool in = k + i < b;
-                const uint2 v = in ? pw[k + i] : make_uint2(chunk_word(kNoEntry, 0u), 0u);
+                const uint2 v = in ? list[k + i] : make_uint2(chunk_word(kNoEntry, 0u), 0u);
                 nx[i] = v.x;
                 nw[i] = __uint_as_float(v.y);
             }

@@ -196,7 +196,7 @@ __global__ __launch_bounds__(kThreads) void k_scan_single(const uint32_t* __rest
     if (threadIdx.x == 0) *total = carry;
 }
 
-// Tile ranges of the chunk-major pair list from the pairs per tile: one
+// Tile ranges of a tile-major pair list from the pairs per tile: one
 // block walks the counts with a running carry (as k_scan_single) and writes
 // ranges[t] = [start, start + len[t]) clamped to cap; the first thread also
 // flags an overflow when the list's total exceeds cap.
