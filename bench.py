@@ -642,10 +642,10 @@ def main():
 
         csr = {k: round(kernels[k]["ms_per_launch"] * kernels[k]["launches_per_step"], 4)
                for k in ("ntc_fwd", "ntc_bwd", "ntc_scatter") if k in kernels}
-        atom = {k: round(per_step(k), 4) for k in ("ntc_fwd", "ntc_bwd")}
+        atom = {k: round(per_step(k), 4) for k in ("ntc_fwd", "ntc_bwd", "ntc_scatter")}
         table_grad = {"csr_gather_ms_per_step": csr, "csr_gather_backward_ms": round(csr["ntc_bwd"] +
                                                                                     csr.get("ntc_scatter", 0.0), 4),
-                      "atomic_ms_per_step": atom, "atomic_backward_ms": atom["ntc_bwd"],
+                      "atomic_ms_per_step": atom, "atomic_backward_ms": round(atom["ntc_bwd"] + atom["ntc_scatter"], 4),
                       "used": "csr_gather"}
         ctx.ntc_load(params_warm)
 
