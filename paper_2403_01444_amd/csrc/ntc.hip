@@ -771,18 +771,21 @@ static bool table_parts(const NtcDev& nd, int part, TableParts& tp) {
 // into the entries of one part of the table in LDS, the counts of (slice,
 // entry) are turned into first slots (entry by entry, slice by slice), and a
 // workgroup per (part, slice) walks its points in order with the slots in LDS
-// and stores each contribution where its entry's counter says.  Its four
-// waves compute the corners of 256 points side by side and then take their
-// slots one wave after the other; a wave's LDS operations are done in order,
-// so a list is ordered by groups of 64 points, then corner, then the order in
-// which the LDS serves the lanes of one instruction, which depends on the
-// addresses alone: the same means give the same lists.  Bound by the
-// scattered 8-byte stores: an entry's list is one of 32768 that a workgroup
-// appends to, more lines than an L2 holds.  300K points, T =
-// 2^15, with the means' Morton reorder: 1.85 ms with a radix sort of (entry,
-// contribution) pairs -> 0.53 ms (parts of 8192 entries and a wave each, the
-// points read four times as often: 0.83 ms).  Tables of more than kLdsParts
-// parts (T above 2^18) still take the sort.
+// and stores each contribution where its entry's counter says.  Its sixteen
+// waves take a group of 64 points each and compute its corners and store on
+// their own; only the slots are taken in turn, group after group (s_turn).  A
+// wave's LDS operations are done in order, so a list is ordered by groups of 64
+// points, then corner, then the order in which the LDS serves the lanes of one
+// instruction, which depends on the addresses alone: the same means give the
+// same lists.  Bound by the scattered 8-byte stores (an entry's list is one of
+// 32768 that a workgroup appends to, more lines than an L2 holds) and, with
+// points in spatial order, by the atomics of lanes on one entry.  300K points,
+// T = 2^15, with the means' Morton reorder: 1.85 ms with a radix sort of (entry,
+// contribution) pairs -> 0.53 ms.  The placing alone, against four waves that
+// meet at a barrier for every turn: 284 -> 256 us (random order 474 -> 456), 2000
+// points 44 -> 19.  Lanes of one entry counted as one: 256 -> 538; the table in
+// two passes of half the entries: 315.  Tables of more than kLdsParts parts (T
+// above 2^18) still take the sort.
 // ---------------------------------------------------------------------------
 // Points from which the lists are kept slice by slice (backward of points in
 // Morton order all over the box, on surfaces, and in random order; entry by
@@ -852,18 +855,24 @@ __global__ __launch_bounds__(256) void k_csr_slots(uint32_t* __restrict__ cnt, i
     rows[e] = make_uint2(begin, run);
 }
 
-__global__ __launch_bounds__(256) void k_csr_place(NtcDev nd, TableParts tp, const float* __restrict__ means, int64_t n,
-                                                   int slices, int64_t entries, const uint32_t* __restrict__ slot,
-                                                   bool chunked, uint2* __restrict__ pw) {
+constexpr int kPlaceThreads = 1024;
+__global__ __launch_bounds__(kPlaceThreads) void k_csr_place(NtcDev nd, TableParts tp, const float* __restrict__ means,
+                                                             int64_t n, int slices, int64_t entries,
+                                                             const uint32_t* __restrict__ slot, bool chunked,
+                                                             uint2* __restrict__ pw) {
+    constexpr int NW = kPlaceThreads / 64;
     __shared__ uint32_t s_at[kListEntries];
+    __shared__ int s_turn;   // the group of 64 points that takes its slots next
     const int part = blockIdx.x / slices, slice = blockIdx.x % slices;
     const int lv = tp.level[part], size = tp.size[part];
     const uint32_t first = (uint32_t)nd.off[lv] + (uint32_t)tp.first[part];
     const uint32_t* src = slot + (int64_t)slice * entries + first;
-    for (int k = threadIdx.x; k < size; k += 256) s_at[k] = src[k];
+    for (int k = threadIdx.x; k < size; k += kPlaceThreads) s_at[k] = src[k];
+    if (threadIdx.x == 0) s_turn = 0;
     __syncthreads();
     const int64_t per = csr_slice(n, slices), p0 = slice * per, p1 = min(n, p0 + per);
-    const int w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int groups = p1 > p0 ? (int)((p1 - p0 + 63) / 64) : 0;
     float mu[3] = {0.f, 0.f, 0.f};
     auto load = [&](int64_t pt) {
         if (pt < p1) {
@@ -872,27 +881,31 @@ __global__ __launch_bounds__(256) void k_csr_place(NtcDev nd, TableParts tp, con
             mu[2] = means[3 * pt + 2];
         }
     };
-    load(p0 + threadIdx.x);
-    for (int64_t b = p0; b < p1; b += 256) {
-        const int64_t pt = b + threadIdx.x;
+    load(p0 + 64 * w + lane);
+    for (int g = w; g < groups; g += NW) {
+        const int64_t pt = p0 + 64 * (int64_t)g + lane;
         float x[3];
         const bool in = ntc_normalise(nd, mu, x) && pt < p1;
-        load(pt + 256);   // the next group's means arrive during this one's work
+        load(pt + 64 * NW);   // the next group's means arrive during this one's work
         uint32_t ent[8];
         float wt[8];
         ntc_corners(nd, lv, x, ent, wt);
+        // the groups' turns come in order, each ends before the next begins,
+        // and the wave of every group is on the CU: the wait ends
+        while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(&s_turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != g)
+            __builtin_amdgcn_s_sleep(1);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         uint32_t at[8];
-        for (int turn = 0; turn < 4; turn++) {
-            if (w == turn) {
 #pragma unroll
-                for (int c = 0; c < 8; c++) {
-                    const uint32_t k = ent[c] - first;
-                    at[c] = 0u;
-                    if (in && k < (uint32_t)size) at[c] = atomicAdd(&s_at[k], 1u);
-                }
-            }
-            __syncthreads();   // waits for the wave's LDS operations
+        for (int c = 0; c < 8; c++) {
+            const uint32_t k = ent[c] - first;
+            at[c] = 0u;
+            if (in && k < (uint32_t)size) at[c] = atomicAdd(&s_at[k], 1u);
         }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // the wave's LDS operations are done
+        if (lane == 0) __hip_atomic_store(&s_turn, g + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        // the means are waited for here: behind the stores, the wait would be theirs too
+        asm volatile("" : "+v"(mu[0]), "+v"(mu[1]), "+v"(mu[2]));
 #pragma unroll
         for (int c = 0; c < 8; c++) {
             const uint32_t k = ent[c] - first;
@@ -1648,7 +1661,7 @@ void ntc_csr_build(const Launch& L, const NtcDev& nd, const float* means, int64_
             hipLaunchKernelGGL(k_csr_slots, dim3(nblk(csr.entries, 256)), dim3(256), 0, L.st, w.cnt, slices,
                                csr.entries, w.first, csr.rows);
         }
-        hipLaunchKernelGGL(k_csr_place, dim3(grid), dim3(256), 0, L.st, nd, tp, means, n, slices, csr.entries, w.cnt,
+        hipLaunchKernelGGL(k_csr_place, dim3(grid), dim3(kPlaceThreads), 0, L.st, nd, tp, means, n, slices, csr.entries, w.cnt,
                            csr.slices > 0, csr.pw);
         if (L.prof) L.prof->end(L.st);
         return;
