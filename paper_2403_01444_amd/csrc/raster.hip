@@ -748,7 +748,7 @@ static_assert(kBwdGroup % 2 == 0, "entries are reduced two at a time");
 __constant__ float kConicScale[9] = {1.f, 1.f, -0.5f, -1.f, -0.5f, 1.f, 1.f, 1.f, 1.f};
 
 // A batch's sums of the waves (s_g, [wave][term][entry]; on: the entries each
-// wave visited, [word][wave]) added to accum.  A lane has one term of an entry
+// wave visited, [word][wave]): out(entry, term, sum).  A lane has one term of an entry
 // throughout and a wave seven entries at a time, so the rounds need no
 // divisions, a round's LDS reads are independent, and an entry's nine atomics
 // are adjacent lanes on adjacent addresses (one or two cache lines).  The mean
@@ -757,14 +757,14 @@ __constant__ float kConicScale[9] = {1.f, 1.f, -0.5f, -1.f, -0.5f, 1.f, 1.f, 1.f
 // and a branch for the mean terms in every round, the whole backward went from
 // 156 to 128 us at 50K Gaussians and 256 x 256, from 220 to 208 at 300K and
 // 1352 x 1014, from 295 to 288 at 502K and 1080p (rounds unrolled: 214 and
-// 305, for the registers).
-template <int NW, int KB, bool kOpacity, class Conic>
-__device__ __forceinline__ void add_batch(int cnt, int w, int lane, const uint64_t (&on)[2][NW],
-                                          const float (&s_g)[NW][9][KB + 1], const uint32_t* s_id, Conic conic,
-                                          float* __restrict__ accum) {
+// 305, for the registers); the narrow backward with records from 54 to 52 at 5K
+// and 200 x 152.
+template <int NW, int KB, bool kOpacity, class Conic, class Out>
+__device__ __forceinline__ void sum_batch(int cnt, int w, int lane, const uint64_t (&on)[2][NW],
+                                          const float (&s_g)[NW][9][KB + 1], Conic conic, Out out) {
     constexpr int kPer = 7, kRounds = (KB + kPer * NW - 1) / (kPer * NW);
     const int l = min(lane, 62) / 9, k = min(lane, 62) - 9 * l;
-    const bool mine = lane < 63 && (kOpacity || k != 5);
+    const bool none = !kOpacity && k == 5;
     const float scale = kConicScale[k];
     const int other = k == 0 ? lane + 1 : k == 1 ? lane - 1 : lane;
 #pragma unroll 1
@@ -781,8 +781,8 @@ __device__ __forceinline__ void add_batch(int cnt, int w, int lane, const uint64
         const float o = __shfl(v, other);
         const float3 c = conic(e);
         const float m = c.y * o + (k == 0 ? c.x : c.z) * v;
-        v = k <= 1 ? m : v * scale;
-        if (mine && e0 < cnt && v != 0.f) atomicAdd(accum + 9 * (int64_t)s_id[e] + k, v);
+        v = none ? 0.f : k <= 1 ? m : v * scale;
+        if (lane < 63 && e0 < cnt) out(e, k, v);
     }
 }
 
@@ -1023,9 +1023,11 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend_bwd(CamDev cam, int nti
                 }
             }
         } else {
-            add_batch<NW, KB, kOpacity>(
-                cnt, w, lane, s_taken, s_g, s_id, [&](int e) { return make_float3(s_w0[e].z, s_w0[e].w, s_w1[e].x); },
-                accum);
+            sum_batch<NW, KB, kOpacity>(
+                cnt, w, lane, s_taken, s_g, [&](int e) { return make_float3(s_w0[e].z, s_w0[e].w, s_w1[e].x); },
+                [&](int e, int k, float v) {
+                    if (v != 0.f) atomicAdd(accum + 9 * (int64_t)s_id[e] + k, v);
+                });
         }
         __syncthreads();
     }
@@ -1474,39 +1476,15 @@ __global__ __launch_bounds__(kRecords ? kNarrowThreads : kQuarterThreads) void k
             if (kOpacity && pix == 1) s_g[w][5][cur.j] = redop;
         }
         __syncthreads();
-        if constexpr (!kRecords) {
-            add_batch<NW, KB, kOpacity>(
-                cnt, w, lane, s_reach, s_g, s_id, [&](int e) { return make_float3(s_r.a[e].z, s_r.a[e].w, s_r.b[e].x); },
-                accum);
-        } else {
-            auto over_waves = [&](int k, int e, uint32_t on) -> float {
-                float v = 0.f;
-                for (; on; on &= on - 1u) v += s_g[__builtin_ctz(on)][k][e];
-                return v;
-            };
-            for (int q = tid; q < 9 * cnt; q += NT) {
-                const int e = q / 9, k = q - 9 * e;
-                float v = 0.f;
-                if (kOpacity || k != 5) {
-                    uint32_t on = 0u;
-#pragma unroll
-                    for (int u = 0; u < NW; u++) on |= (uint32_t)((s_reach[e >> 6][u] >> (e & 63)) & 1ull) << u;
-                    v = over_waves(k, e, on);
-                    if (k <= 1) {
-                        const float o = over_waves(1 - k, e, on);
-                        const float4 a = s_r.a[e];
-                        v = k == 0 ? a.z * v + a.w * o : a.w * o + s_r.b[e].x * v;
-                    } else {
-                        v *= kConicScale[k];
-                    }
-                }
+        sum_batch<NW, KB, kOpacity>(
+            cnt, w, lane, s_reach, s_g, [&](int e) { return make_float3(s_r.a[e].z, s_r.a[e].w, s_r.b[e].x); },
+            [&](int e, int k, float v) {
                 const uint32_t widx = woff + (uint32_t)jb + e;   // compact index of this walked entry
-                if (widx < grec_cap)
+                if (kRecords && widx < grec_cap)
                     grec[(int64_t)k * grec_cap + widx] = v;
                 else if (v != 0.f)
                     atomicAdd(accum + 9 * (int64_t)s_id[e] + k, v);
-            }
-        }
+            });
         __syncthreads();
     }
 }
@@ -1524,9 +1502,10 @@ __device__ __forceinline__ void quat_rot_adj(const float q[4], const float g[9],
 // inverse, EWA (with J depending on the camera-space mean), the covariance,
 // the colour (SH and its view direction) and the transform.
 // ---------------------------------------------------------------------------
+template <bool kRecords>
 __global__ __launch_bounds__(256) void k_preprocess_bwd(GaussDev g, CamDev cam, float* __restrict__ accum,
                                                         GatherDev ga, GradsDev out) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= g.n) return;
     // the blend's sums, left zero for the next backward
     float a9[9];
@@ -1538,20 +1517,42 @@ __global__ __launch_bounds__(256) void k_preprocess_bwd(GaussDev g, CamDev cam, 
     colour_forward(g, cam, i, o, cc);
     // the nine 2D gradient terms: the sums (records: those past the buffer)
     // plus this Gaussian's walked entries, visited in its tile-rectangle order
-    if (ga.grec_cap > 0) {
+    if constexpr (kRecords) {
+        // four entries at a time, whose chains of loads run side by side (5K
+        // Gaussians at 200 x 152, with a wave a workgroup: 29 -> 22 us)
+        constexpr int U = 4;
         const uint2 r = ga.rect[i];
         const int tx0 = r.x & 0xFFFF, ty0 = r.x >> 16, tx1 = r.y & 0xFFFF, ty1 = r.y >> 16;
-        uint64_t k = ga.goff[i];
-        for (int ty = ty0; ty <= ty1; ty++)
-            for (int tx = tx0; tx <= tx1; tx++, k++) {
-                if (k >= ga.cap) continue;
-                const int t = ty * cam.tiles_x + tx;
-                const uint32_t rel = ga.gpos[k] - ga.ranges[t].x;
-                if (rel >= ga.tile_walk[t]) continue;
-                const uint32_t widx = ga.walk_off[t] + rel;
-                if (widx >= ga.grec_cap) continue;
-                for (int c = 0; c < 9; c++) a9[c] += ga.grec[(int64_t)c * ga.grec_cap + widx];
+        const uint64_t k0 = ga.goff[i];
+        const int n = (tx1 - tx0 + 1) * (ty1 - ty0 + 1);
+        int tx = tx0, ty = ty0;
+        for (int e = 0; e < n; e += U) {
+            uint32_t widx[U];
+            bool on[U];
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const int t = ty * cam.tiles_x + tx;   // past the rectangle: its last tile
+                on[u] = e + u < n && k0 + e + u < ga.cap;
+                const uint32_t rel = (on[u] ? ga.gpos[k0 + e + u] : 0u) - ga.ranges[t].x;
+                on[u] = on[u] && rel < ga.tile_walk[t];
+                widx[u] = ga.walk_off[t] + rel;
+                on[u] = on[u] && widx[u] < ga.grec_cap;
+                const bool wrap = tx == tx1;
+                if (!(wrap && ty == ty1)) {
+                    tx = wrap ? tx0 : tx + 1;
+                    ty += wrap ? 1 : 0;
+                }
             }
+            float v[U][9];
+#pragma unroll
+            for (int u = 0; u < U; u++)
+#pragma unroll
+                for (int c = 0; c < 9; c++) v[u][c] = ga.grec[(int64_t)c * ga.grec_cap + (on[u] ? widx[u] : 0u)];
+#pragma unroll
+            for (int u = 0; u < U; u++)
+#pragma unroll
+                for (int c = 0; c < 9; c++) a9[c] = on[u] ? a9[c] + v[u][c] : a9[c];
+        }
     }
     const float du = a9[0], dv = a9[1], dA = a9[2], dB = a9[3], dC = a9[4], dop = a9[5];
     const float drgb[3] = {a9[6], a9[7], a9[8]};
@@ -1898,7 +1899,10 @@ void preprocess_backward(const Launch& L, const GaussDev& g, const CamDev& cam, 
                          const GatherDev& ga, const GradsDev& out) {
     if (g.n <= 0) return;
     if (L.prof) L.prof->begin("preprocess_bwd", L.st);
-    hipLaunchKernelGGL(k_preprocess_bwd, dim3(blocks_for(g.n, 256)), dim3(256), 0, L.st, g, cam, accum, ga, out);
+    // a wave a workgroup where there are too few for every CU
+    const int nt = g.n < 256 * 256 ? 64 : 256;
+    hipLaunchKernelGGL(ga.grec_cap > 0 ? k_preprocess_bwd<true> : k_preprocess_bwd<false>, dim3(blocks_for(g.n, nt)),
+                       dim3(nt), 0, L.st, g, cam, accum, ga, out);
     if (L.prof) L.prof->end(L.st);
 }
 
