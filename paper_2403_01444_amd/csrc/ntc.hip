@@ -991,6 +991,41 @@ struct GatherLevels {
 };
 
 
+// The per-workgroup weight-gradient rows summed into dst: workgroup b of 256
+// takes a range of columns of a slice of the rows, one atomic per (slice,
+// column).  The kernels over the prepared lists end with these workgroups, for
+// both only wait for the backward and a launch of its own costs 4-5 us.
+constexpr int kPartSlice = 32;
+struct PartSums {
+    const float* part;
+    int nparts;
+    float* dst;
+    int64_t first;   // the launch's first workgroup of them
+    __host__ __device__ static constexpr int cols() { return (kMlpParams + 255) / 256; }
+    int64_t blocks() const { return (int64_t)cols() * ((nparts + kPartSlice - 1) / kPartSlice); }
+};
+
+__device__ __forceinline__ void sum_parts(const PartSums& ps, int b) {
+    const int k = b % PartSums::cols() * 256 + threadIdx.x;
+    if (k >= kMlpParams) return;
+    const int b0 = b / PartSums::cols() * kPartSlice;
+    const int b1 = min(b0 + kPartSlice, ps.nparts);
+    // eight loads in flight, summed in order
+    float s = 0.f;
+    int r = b0;
+    for (; r + 8 <= b1; r += 8) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) v[u] = ps.part[(int64_t)(r + u) * kMlpParams + k];
+#pragma unroll
+        for (int u = 0; u < 8; u++) s += v[u];
+    }
+    for (; r < b1; r++) s += ps.part[(int64_t)r * kMlpParams + k];
+    atomicAdd(ps.dst + k, s);
+}
+
+__global__ __launch_bounds__(256) void k_reduce_parts(PartSums ps) { sum_parts(ps, blockIdx.x); }
+
 // The weighted encoding gradients of contributions k, k + G, ... below end,
 // four independent loads in flight per lane.
 template <int G>
@@ -1045,7 +1080,11 @@ static int64_t gather_blocks(const GatherLevels& gl, int lv) {
 
 __global__ __launch_bounds__(256) void k_csr_gather(GatherLevels gl, const uint2* __restrict__ rows,
                                                     const uint2* __restrict__ pw, const float* __restrict__ denc,
-                                                    int64_t n, float* __restrict__ g_table) {
+                                                    int64_t n, float* __restrict__ g_table, PartSums ps) {
+    if ((int64_t)blockIdx.x >= ps.first) {
+        sum_parts(ps, (int)(blockIdx.x - ps.first));
+        return;
+    }
     const int x = (int)(blockIdx.x % kXcds);
     int64_t j = blockIdx.x / kXcds;   // this workgroup's place among its XCD's
     int lv = x;
@@ -1081,7 +1120,11 @@ constexpr int64_t kShortMean = 2;   // mean contributions of an entry up to whic
 constexpr int kShortEntries = 16;   // entries of a wave
 __global__ __launch_bounds__(256) void k_csr_gather_short(int64_t entries, const uint2* __restrict__ rows,
                                                           const uint2* __restrict__ pw, const float* __restrict__ denc,
-                                                          int64_t n, float* __restrict__ g_table) {
+                                                          int64_t n, float* __restrict__ g_table, PartSums ps) {
+    if ((int64_t)blockIdx.x >= ps.first) {
+        sum_parts(ps, (int)(blockIdx.x - ps.first));
+        return;
+    }
     const int lane = threadIdx.x & 63;
     const int64_t e0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kShortEntries, e = e0 + lane;
     const uint2 r = lane < kShortEntries && e < entries ? rows[e] : make_uint2(0u, 0u);
@@ -1278,7 +1321,11 @@ __global__ __launch_bounds__(1024) void k_csr_chunk(NtcDev nd, int64_t n, int sl
 
 // The slices' sums added to the table gradient, slice by slice.
 __global__ __launch_bounds__(256) void k_chunk_sum(const float2* __restrict__ part, int slices, int64_t entries,
-                                                   float2* __restrict__ g_table) {
+                                                   float2* __restrict__ g_table, PartSums ps) {
+    if ((int64_t)blockIdx.x >= ps.first) {
+        sum_parts(ps, (int)(blockIdx.x - ps.first));
+        return;
+    }
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= entries) return;
     float2 a = make_float2(0.f, 0.f);
@@ -1373,29 +1420,6 @@ __global__ __launch_bounds__(256) void k_table_scatter(NtcDev nd, const float* _
         atomicAdd(g_table + 2 * (int64_t)ent[c], wt[c] * e.x);
         atomicAdd(g_table + 2 * (int64_t)ent[c] + 1, wt[c] * e.y);
     }
-}
-
-// Sum the per-workgroup weight-gradient rows: blockIdx.y takes a slice of
-// the rows, blockIdx.x a range of columns; one atomic per (slice, column).
-constexpr int kPartSlice = 32;
-__global__ __launch_bounds__(256) void k_reduce_parts(const float* __restrict__ part, int nparts, int len,
-                                                      float* __restrict__ dst) {
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= len) return;
-    const int b0 = blockIdx.y * kPartSlice;
-    const int b1 = min(b0 + kPartSlice, nparts);
-    // eight loads in flight, summed in order
-    float s = 0.f;
-    int b = b0;
-    for (; b + 8 <= b1; b += 8) {
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; u++) v[u] = part[(int64_t)(b + u) * len + k];
-#pragma unroll
-        for (int u = 0; u < 8; u++) s += v[u];
-    }
-    for (; b < b1; b++) s += part[(int64_t)b * len + k];
-    atomicAdd(dst + k, s);
 }
 
 template <class P>
@@ -1522,10 +1546,14 @@ void fwd_impl(const Launch& L, const NtcDev& nd, const void* table, const void* 
     hipLaunchKernelGGL((k_ntc_fwd<P, false>), grid(n), dim3(256), 0, L.st, nd, t, w, means, n, dmu, dq, (S*)enc_out);
 }
 
-// Table gradient from the encoding gradient: per entry over the prepared
-// lists, or scattered.
+// Table gradient from the encoding gradient, per entry over the prepared lists
+// or scattered, and the sums of the weight-gradient rows.
 void table_grad(const Launch& L, const NtcDev& nd, const float* means, int64_t n, const NtcCsr* csr, const float* denc,
-                float* g_table) {
+                float* g_table, PartSums ps) {
+    const auto with_parts = [&](int64_t blocks) {
+        ps.first = blocks;
+        return dim3((unsigned)(blocks + ps.blocks()));
+    };
     if (!csr) {
         TableParts tp;
         const bool fits = table_parts(nd, kLdsEntries, tp);
@@ -1543,18 +1571,22 @@ void table_grad(const Launch& L, const NtcDev& nd, const float* means, int64_t n
             hipLaunchKernelGGL(k_table_scatter, dim3((unsigned)((16 * n + 255) / 256)), dim3(256), 0, L.st, nd, means, n,
                                denc, g_table);
         }
+        ps.first = 0;
+        hipLaunchKernelGGL(k_reduce_parts, dim3((unsigned)ps.blocks()), dim3(256), 0, L.st, ps);
         return;
     }
     if (csr->slices > 0) {
         hipLaunchKernelGGL(k_csr_chunk, dim3((unsigned)(16 * csr->slices)), dim3(1024), 0, L.st, nd, n, csr->slices,
                            csr->entries, csr->starts, csr->pw, denc, csr->part);
-        hipLaunchKernelGGL(k_chunk_sum, dim3(nblk(csr->entries, 256)), dim3(256), 0, L.st, csr->part, csr->slices,
-                           csr->entries, reinterpret_cast<float2*>(g_table));
+        const dim3 grid = with_parts(nblk(csr->entries, 256));
+        hipLaunchKernelGGL(k_chunk_sum, grid, dim3(256), 0, L.st, csr->part, csr->slices, csr->entries,
+                           reinterpret_cast<float2*>(g_table), ps);
         return;
     }
     if (128 * n <= kShortMean * csr->entries) {
-        hipLaunchKernelGGL(k_csr_gather_short, dim3(nblk(csr->entries, 4 * kShortEntries)), dim3(256), 0, L.st, csr->entries, csr->rows,
-                           csr->pw, denc, n, g_table);
+        const dim3 grid = with_parts(nblk(csr->entries, 4 * kShortEntries));
+        hipLaunchKernelGGL(k_csr_gather_short, grid, dim3(256), 0, L.st, csr->entries, csr->rows, csr->pw, denc, n, g_table,
+                           ps);
         return;
     }
     GatherLevels gl;
@@ -1564,8 +1596,8 @@ void table_grad(const Launch& L, const NtcDev& nd, const float* means, int64_t n
     }
     int64_t per_xcd = 0;
     for (int x = 0; x < kXcds; x++) per_xcd = std::max(per_xcd, gather_blocks(gl, x) + gather_blocks(gl, 15 - x));
-    hipLaunchKernelGGL(k_csr_gather, dim3((unsigned)(per_xcd * kXcds)), dim3(256), 0, L.st, gl, csr->rows, csr->pw, denc,
-                       n, g_table);
+    const dim3 grid = with_parts(per_xcd * kXcds);
+    hipLaunchKernelGGL(k_csr_gather, grid, dim3(256), 0, L.st, gl, csr->rows, csr->pw, denc, n, g_table, ps);
 }
 
 template <class P>
@@ -1581,9 +1613,7 @@ void bwd_impl(const Launch& L, const NtcDev& nd, const void* table, const void* 
                        (const typename P::S*)mlp, means, n, d_dmu, d_dq, g_part, denc, (const typename P::S*)enc_in);
     if (L.prof) L.prof->end(L.st);
     if (L.prof) L.prof->begin("ntc_scatter", L.st);
-    table_grad(L, nd, means, n, csr, denc, g_table);
-    hipLaunchKernelGGL(k_reduce_parts, dim3(nblk(kMlpParams, 256), (grid + kPartSlice - 1) / kPartSlice), dim3(256), 0,
-                       L.st, g_part, (int)grid, kMlpParams, g_mlp);
+    table_grad(L, nd, means, n, csr, denc, g_table, PartSums{g_part, (int)grid, g_mlp, 0});
     if (L.prof) L.prof->end(L.st);
 }
 
