@@ -447,6 +447,13 @@ __device__ __forceinline__ float4 blend_stage_w2(const float4& w2, int tx0p, int
     return make_float4(w2.x, w2.w - 1e-4f, w2.w + 1e-4f, __uint_as_float(cm | (rm << 16)));
 }
 
+// Whether a record's colour (each channel >= 0) is so large that it may be
+// infinite: the blends then keep it from pixels that do not take the entry,
+// for which weight zero is not enough.
+__device__ __forceinline__ bool colour_overflows(const float4& w1, const float4& w2) {
+    return w1.z + w1.w + w2.x > 3e38f;
+}
+
 // First word of a tile's taken bits in a tile-major list that starts at slot
 // `start`: 64 entries a word, every tile's words its own.
 __device__ __forceinline__ int64_t taken_word(uint32_t start, int tile) { return (int64_t)(start >> 6) + tile; }

@@ -495,6 +495,7 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
     __shared__ uint64_t s_reach[NW][NW];            // [quadrant][word]: staged entries that can reach its pixels
     __shared__ uint64_t s_taken[NW][NW];            // [word][quadrant]: entries a pixel of the quadrant took
     __shared__ uint32_t s_live[NW], s_blk;           // bit 0: pixels left, bit 1: took an entry of the batch
+    __shared__ uint32_t s_over[NW];                  // colours of the batch that have overflowed
     const int tx0p = tx * kTile, ty0p = ty * kTile;
     // wave w: the 8 x 8 quadrant (w & 1, w >> 1) of the tile
     const int lx = quad_x(w, lane), ly = quad_y(w, lane);
@@ -562,6 +563,7 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
             c += cnt_u;
         }
         uint32_t reach = 0u;   // quadrants this thread's entry can reach
+        bool over = false;
         if ((uint32_t)tid < cnt_u) {
             const float4 r0 = rec[3 * (int64_t)myid + 0], r1 = rec[3 * (int64_t)myid + 1];
             const float4 r2 = rec[3 * (int64_t)myid + 2];
@@ -569,7 +571,10 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
             s_w1[tid] = r1;
             s_w2[tid] = blend_stage_w2(r2, tx0p, ty0p);
             reach = quads_reached(r0, r1, r2, tx0p, ty0p);
+            over = colour_overflows(r1, r2);
         }
+        const uint64_t overb = __builtin_amdgcn_ballot_w64(over);
+        if (lane == 0) s_over[w] = overb != 0ull ? 1u : 0u;
 #pragma unroll
         for (int q = 0; q < NW; q++) {
             const uint64_t b = __builtin_amdgcn_ballot_w64((reach >> q) & 1u);
@@ -636,15 +641,19 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
                     set_bit(tk, tj);
                     alive &= ~stop;
                     const float wgt = take ? alpha[i] * T : 0.0f;
-                    c0 += wgt * w1[i].z;
-                    c1 += wgt * w1[i].w;
-                    c2 += wgt * cb[i];
+                    // an entry by itself may have an infinite colour, which weight zero does not take away
+                    const float n0 = c0 + wgt * w1[i].z, n1 = c1 + wgt * w1[i].w, n2 = c2 + wgt * cb[i];
+                    c0 = kG > 1 || take ? n0 : c0;
+                    c1 = kG > 1 || take ? n1 : c1;
+                    c2 = kG > 1 || take ? n2 : c2;
                     T = take ? Tn : T;
                     last = take ? eb + (uint32_t)j[i] + 1u : last;
                 }
             };
             // the entries that can reach the wave's pixels, in order; the
-            // wave leaves once all its pixels have stopped
+            // wave leaves once all its pixels have stopped.  One by one in a
+            // batch with an infinite colour
+            const int group = __builtin_amdgcn_readfirstlane(s_over[0] | s_over[1] | s_over[2] | s_over[3]) ? NT : kFwdGroup;
 #pragma unroll 1
             for (int q = 0; q < NW; q++) {
                 tk = 0ull;
@@ -659,7 +668,7 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
                 };
                 int left = __popcll(m);
 #pragma unroll 1
-                for (; left >= kFwdGroup && alive; left -= kFwdGroup) {
+                for (; left >= group && alive; left -= kFwdGroup) {
                     int j[kFwdGroup];
 #pragma unroll
                     for (int i = 0; i < kFwdGroup; i++) j[i] = next();
@@ -807,6 +816,7 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend_bwd(CamDev cam, int nti
     __shared__ float4 s_w2[KB];   // blend_stage_w2 form
     __shared__ uint32_t s_id[KB];
     __shared__ uint64_t s_taken[2][NW];    // the batch's taken bits, [word][quadrant]
+    __shared__ uint32_t s_over[2];         // colours of the batch that have overflowed
     __shared__ float s_g[NW][9][KB + 1];   // per-wave sums, [wave][term][entry] (padded: term rows on distinct banks)
     const int tile = order ? order[blockIdx.x] : tile_of_block(blockIdx.x, ntiles);
     if (tile >= ntiles) return;
@@ -845,14 +855,18 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend_bwd(CamDev cam, int nti
     const int my_slot = my_term < 5 ? my_term : my_term + 1;   // index in the nine-term layout
     for (int64_t jb = ((int64_t)(maxlast - 1) / KB) * KB; jb >= 0; jb -= KB) {
         const uint32_t e = (uint32_t)jb + tid;
+        bool over = false;
         if (tid < KB && e < maxlast) {
             const uint32_t id = kSuper ? sd.walked[(int64_t)blk * kWalkBlock + (e % kWalkBlock)] : vals[start + e];
-            const float4 r0 = rec[3 * (int64_t)id + 0], r1 = rec[3 * (int64_t)id + 1];
+            const float4 r0 = rec[3 * (int64_t)id + 0], r1 = rec[3 * (int64_t)id + 1], r2 = rec[3 * (int64_t)id + 2];
             s_id[tid] = id;
             s_w0[tid] = r0;
             s_w1[tid] = r1;
-            s_w2[tid] = blend_stage_w2(rec[3 * (int64_t)id + 2], tx0p, ty0p);
+            s_w2[tid] = blend_stage_w2(r2, tx0p, ty0p);
+            over = colour_overflows(r1, r2);
         }
+        const uint64_t overb = __builtin_amdgcn_ballot_w64(over);
+        if (lane == 0 && w < 2) s_over[w] = overb != 0ull ? 1u : 0u;
         if (tid >= KB && tid < KB + 2 * NW) {
             const int t = tid - KB, wd = t / NW;
             const int64_t word = (kSuper ? (int64_t)blk * (kWalkBlock / 64) + ((jb % kWalkBlock) >> 6)
@@ -919,7 +933,8 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend_bwd(CamDev cam, int nti
                 const float wgt = aok * T;
                 const float d = (g0 * w1[i].z + g1 * w1[i].w + g2 * cb[i]) - gb;
                 const float dal = T * d;
-                gb += aok * d;
+                const float gn = gb + aok * d;
+                gb = kG > 1 || ok ? gn : gb;   // see the forward: opacity zero does not take an infinite colour away
                 const bool unclamped =
                     __builtin_amdgcn_inverse_ballot_w64(okm[i] & __builtin_amdgcn_ballot_w64(raw[i] < 0.99f));
                 const float dp = unclamped ? dal * raw[i] : 0.0f;
@@ -957,6 +972,7 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend_bwd(CamDev cam, int nti
                 }
             }
         };
+        const int group = __builtin_amdgcn_readfirstlane(s_over[0] | s_over[1]) ? KB : kBwdGroup;
 #pragma unroll 1
         for (int wd = 1; wd >= 0; wd--) {
             uint64_t m = uniform64(s_taken[wd][w]);
@@ -967,7 +983,7 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend_bwd(CamDev cam, int nti
             };
             int left = __popcll(m);
 #pragma unroll 1
-            for (; left >= kBwdGroup; left -= kBwdGroup) {
+            for (; left >= group; left -= kBwdGroup) {
                 int j[kBwdGroup];
 #pragma unroll
                 for (int i = 0; i < kBwdGroup; i++) j[i] = next();
@@ -1160,6 +1176,7 @@ __global__ __launch_bounds__(kQuarterThreads) void k_blend_fwd_narrow(CamDev cam
     __shared__ NarrowRecs<NB> s_r;
     __shared__ __align__(8) uint16_t s_list[NW][NB + 3 * kSlots];   // entries that reach the wave's block, in order
     __shared__ uint32_t s_live[2];
+    __shared__ uint32_t s_over[NW];   // colours of the batch that have overflowed
     const int tx0p = tx * kTile, ty0p = ty * kTile;
     const int row = lane >> 4, pix = lane & 15, block = quarter_block(quarter, w);
     const int lx = 4 * (block & 3) + (pix & 3), ly = 4 * (block >> 2) + (pix >> 2);
@@ -1182,7 +1199,13 @@ __global__ __launch_bounds__(kQuarterThreads) void k_blend_fwd_narrow(CamDev cam
     int par = 0;
     for (uint32_t eb = 0; eb < n; eb += NB, par ^= 1) {
         const uint32_t cnt_u = min((uint32_t)NB, n - eb);
-        if ((uint32_t)tid < cnt_u) s_r.put(tid, ahead.r0, ahead.r1, ahead.r2, tx0p, ty0p);
+        bool over = false;
+        if ((uint32_t)tid < cnt_u) {
+            s_r.put(tid, ahead.r0, ahead.r1, ahead.r2, tx0p, ty0p);
+            over = colour_overflows(ahead.r1, ahead.r2);
+        }
+        const uint64_t overb = __builtin_amdgcn_ballot_w64(over);
+        if (lane == 0) s_over[w] = overb != 0ull ? 1u : 0u;
         if (tid == 0) s_live[par] = 0u;
         if (eb + NB + tid < n) {
             ahead.id = ahead.next;
@@ -1251,6 +1274,8 @@ __global__ __launch_bounds__(kQuarterThreads) void k_blend_fwd_narrow(CamDev cam
             };
             Rec ahead4 = load(four_at(0));
             uint64_t l = four_at(kSlots);
+            // an infinite colour in the batch, which weight zero does not take away
+            const bool any_over = __builtin_amdgcn_readfirstlane(s_over[0] | s_over[1] | s_over[2] | s_over[3]) != 0u;
 #pragma unroll 1
             for (int g = 0; g < listed && alive; g += kSlots) {
                 const Four cur = eval(ahead4);
@@ -1264,11 +1289,11 @@ __global__ __launch_bounds__(kQuarterThreads) void k_blend_fwd_narrow(CamDev cam
 #pragma unroll
                 for (int s = 0; s < kSlots; s++) Ts[s + 1] = Ts[s] * (1.0f - cur.as[s]);
                 uint64_t own = cur.ok;   // lanes whose own slot's entry is taken
-                if ((alive & __builtin_amdgcn_ballot_w64(Ts[kSlots] < 1e-4f)) == 0ull) {
+                if ((alive & __builtin_amdgcn_ballot_w64(Ts[kSlots] < 1e-4f)) == 0ull && !any_over) {
 #pragma unroll
                     for (int s = 0; s < kSlots; s++) c += (cur.as[s] * Ts[s]) * cur.col[s];
                     T = Ts[kSlots];
-                } else {   // a pixel stops among the four
+                } else {   // a pixel stops among the four, or may meet an infinite colour
                     uint64_t taken = 0ull;
 #pragma unroll
                     for (int s = 0; s < kSlots; s++) {
@@ -1276,8 +1301,8 @@ __global__ __launch_bounds__(kQuarterThreads) void k_blend_fwd_narrow(CamDev cam
                         const uint64_t stop = alive & __builtin_amdgcn_ballot_w64(Tn < 1e-4f);
                         const uint64_t takem = alive & ~stop;
                         const bool take = __builtin_amdgcn_inverse_ballot_w64(takem);
-                        const float wgt = take ? cur.as[s] * T : 0.0f;
-                        c += wgt * cur.col[s];
+                        const float cn = c + (cur.as[s] * T) * cur.col[s];
+                        c = take && cur.as[s] != 0.0f ? cn : c;
                         T = take ? Tn : T;
                         alive = takem;
                         taken |= takem & (0xFFFFull << (16 * s));
@@ -1434,7 +1459,8 @@ __global__ __launch_bounds__(kRecords ? kNarrowThreads : kQuarterThreads) void k
             v.raw = rb.y * v.G;
             v.al = __builtin_amdgcn_inverse_ballot_w64(v.ok) ? fminf(0.99f, v.raw) : 0.0f;
             rows_all(v.al, v.as);
-            rows_all(g0 * rc.x + g1 * rc.y + g2 * rc.z, v.ds);
+            // zero where the entry is not taken: opacity zero does not take an infinite colour away
+            rows_all(__builtin_amdgcn_inverse_ballot_w64(v.ok) ? g0 * rc.x + g1 * rc.y + g2 * rc.z : 0.0f, v.ds);
             return v;
         };
         Rec ahead4 = load(s_list[w][row]);
