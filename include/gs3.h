@@ -148,7 +148,11 @@ void gs3_destroy(gs3_ctx* ctx);
 const char* gs3_last_error(const gs3_ctx* ctx);
 
 /* Launch all further work of this context on `hip_stream` (a hipStream_t;
- * NULL = the default stream). */
+ * NULL = the default stream).  The calls share the context's workspaces:
+ * work issued to different streams is to be ordered by the caller (events or
+ * synchronisation).  gs3_ntc_forward without a token writes only its outputs,
+ * so such calls may overlap each other and anything that leaves the
+ * parameters as they are. */
 gs3_status gs3_set_stream(gs3_ctx* ctx, void* hip_stream);
 
 /* ---- Per-frame setup ------------------------------------------------------ */

@@ -550,7 +550,7 @@ gs3_status gs3_ntc_forward(gs3_ctx* c, const float* means, int64_t n, uint64_t t
     // on the prepared means the forward keeps the encoding for the backward
     const bool prepared = token != 0 && n > 0;
     ntc_forward(c->L(), c->cfg.ntc.precision, c->nd, table, mlp, means, n, dmu, dq,
-                prepared ? c->enc_cache : nullptr, c->scatter_denc);
+                prepared ? c->enc_cache : nullptr);
     if (prepared) c->enc_valid = true;
     return c->check_launch("ntc_forward");
 }

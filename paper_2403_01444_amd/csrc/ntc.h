@@ -51,10 +51,9 @@ int64_t ntc_csr_slices(const NtcDev& nd, int64_t n);
 bool ntc_csr_chunked(const NtcDev& nd, int64_t n);   // lists slice by slice
 void ntc_csr_build(const Launch& L, const NtcDev& nd, const float* means, int64_t n, NtcCsr& csr, const CsrScratch& w);
 // enc_out (optional, n x 32 values of the working precision): the forward
-// also stores the points' encoding there, in the order that the backward reads;
-// without it, scratch (min(n, kScatterPoints) x 32 floats) takes it for the call
+// also stores the points' encoding there, in the order that the backward reads
 void ntc_forward(const Launch& L, int precision, const NtcDev& nd, const void* table, const void* mlp,
-                 const float* means, int64_t n, float* dmu, float* dq, void* enc_out, void* scratch);
+                 const float* means, int64_t n, float* dmu, float* dq, void* enc_out);
 // g_part holds max_parts x ntc_mlp_params() floats; without csr, scratch holds
 // min(n, kScatterPoints) x 32 floats; enc_in (optional, with csr): the
 // encoding a forward with the same parameters and means stored, used instead

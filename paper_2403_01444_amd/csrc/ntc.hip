@@ -1508,10 +1508,14 @@ __global__ __launch_bounds__(256) void k_warmup_finalize(const double* __restric
 
 inline unsigned nblk(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
-// Whether the encoding gets a launch of its own: the half types' levels, where
+// Whether the encoding of prepared means, which the forward keeps for the
+// backward anyway, gets a launch of its own: the half types' levels, where
 // they fit in its LDS, from so many points that the loads of the tables and
 // the launch pay (fp16, random and Morton order: 8192 points 11 and 10 us in
-// one launch, 11 in two; 20,011 16 and 13, 12 in two).
+// one launch, 11 in two; 20,011 16 and 13, 12 in two).  Without preparation
+// there is no place for it but a workspace of the context, and such forwards
+// write none: they may run beside each other and beside backwards, on other
+// streams (300K points in Morton order 58 us so, 44 in two launches).
 constexpr int64_t kEncPoints = 16384;
 bool encode_apart(const NtcDev& nd, int64_t n) {
     bool fits = n >= kEncPoints;
@@ -1521,29 +1525,23 @@ bool encode_apart(const NtcDev& nd, int64_t n) {
 
 template <class P>
 void fwd_impl(const Launch& L, const NtcDev& nd, const void* table, const void* mlp, const float* means, int64_t n,
-              float* dmu, float* dq, void* enc_out, void* scratch) {
+              float* dmu, float* dq, void* enc_out) {
     using S = typename P::S;
     const S* t = (const S*)table;
     const S* w = (const S*)mlp;
     // four workgroups per CU are resident (LDS-bound) on 256 CUs: one round of
     // workgroups, each looping over its share of the batches
-    auto grid = [](int64_t m) { return dim3((unsigned)std::min<int64_t>((m + kPts * kWaves - 1) / (kPts * kWaves), 1024)); };
+    const dim3 grid((unsigned)std::min<int64_t>((n + kPts * kWaves - 1) / (kPts * kWaves), 1024));
     if constexpr (sizeof(S) == 2) {
-        if (encode_apart(nd, n)) {
+        if (enc_out && encode_apart(nd, n)) {
             constexpr int kSlices = 16;   // times 16 levels: one workgroup per CU (the LDS holds one)
-            const int64_t step = enc_out ? n : 2 * kScatterPoints;
-            S* enc = (S*)(enc_out ? enc_out : scratch);
-            for (int64_t p0 = 0; p0 < n; p0 += step) {
-                const int64_t m = std::min(step, n - p0);
-                hipLaunchKernelGGL((k_ntc_encode<P>), dim3(16 * kSlices), dim3(1024), 0, L.st, nd, t, means + 3 * p0, m,
-                                   kSlices, enc);
-                hipLaunchKernelGGL((k_ntc_fwd<P, true>), grid(m), dim3(256), 0, L.st, nd, t, w, means + 3 * p0, m,
-                                   dmu + 3 * p0, dq + 4 * p0, enc);
-            }
+            hipLaunchKernelGGL((k_ntc_encode<P>), dim3(16 * kSlices), dim3(1024), 0, L.st, nd, t, means, n, kSlices,
+                               (S*)enc_out);
+            hipLaunchKernelGGL((k_ntc_fwd<P, true>), grid, dim3(256), 0, L.st, nd, t, w, means, n, dmu, dq, (S*)enc_out);
             return;
         }
     }
-    hipLaunchKernelGGL((k_ntc_fwd<P, false>), grid(n), dim3(256), 0, L.st, nd, t, w, means, n, dmu, dq, (S*)enc_out);
+    hipLaunchKernelGGL((k_ntc_fwd<P, false>), grid, dim3(256), 0, L.st, nd, t, w, means, n, dmu, dq, (S*)enc_out);
 }
 
 // Table gradient from the encoding gradient, per entry over the prepared lists
@@ -1622,15 +1620,15 @@ void bwd_impl(const Launch& L, const NtcDev& nd, const void* table, const void* 
 int ntc_mlp_params() { return kMlpParams; }
 
 void ntc_forward(const Launch& L, int precision, const NtcDev& nd, const void* table, const void* mlp,
-                 const float* means, int64_t n, float* dmu, float* dq, void* enc_out, void* scratch) {
+                 const float* means, int64_t n, float* dmu, float* dq, void* enc_out) {
     if (n <= 0) return;
     if (L.prof) L.prof->begin("ntc_fwd", L.st);
     if (precision == 1)
-        fwd_impl<PF16>(L, nd, table, mlp, means, n, dmu, dq, enc_out, scratch);
+        fwd_impl<PF16>(L, nd, table, mlp, means, n, dmu, dq, enc_out);
     else if (precision == 2)
-        fwd_impl<PBF16>(L, nd, table, mlp, means, n, dmu, dq, enc_out, scratch);
+        fwd_impl<PBF16>(L, nd, table, mlp, means, n, dmu, dq, enc_out);
     else
-        fwd_impl<PF32>(L, nd, table, mlp, means, n, dmu, dq, enc_out, scratch);
+        fwd_impl<PF32>(L, nd, table, mlp, means, n, dmu, dq, enc_out);
     if (L.prof) L.prof->end(L.st);
 }
 
