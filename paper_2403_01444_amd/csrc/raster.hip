@@ -495,7 +495,7 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
     __shared__ uint64_t s_reach[NW][NW];            // [quadrant][word]: staged entries that can reach its pixels
     __shared__ uint64_t s_taken[NW][NW];            // [word][quadrant]: entries a pixel of the quadrant took
     __shared__ uint32_t s_live[NW], s_blk;           // bit 0: pixels left, bit 1: took an entry of the batch
-    __shared__ uint32_t s_over[NW];                  // colours of the batch that have overflowed
+    __shared__ uint64_t s_over[NW];                 // [word]: staged entries with an infinite colour
     const int tx0p = tx * kTile, ty0p = ty * kTile;
     // wave w: the 8 x 8 quadrant (w & 1, w >> 1) of the tile
     const int lx = quad_x(w, lane), ly = quad_y(w, lane);
@@ -574,7 +574,7 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
             over = colour_overflows(r1, r2);
         }
         const uint64_t overb = __builtin_amdgcn_ballot_w64(over);
-        if (lane == 0) s_over[w] = overb != 0ull ? 1u : 0u;
+        if (lane == 0) s_over[w] = overb;
 #pragma unroll
         for (int q = 0; q < NW; q++) {
             const uint64_t b = __builtin_amdgcn_ballot_w64((reach >> q) & 1u);
@@ -651,13 +651,13 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
                 }
             };
             // the entries that can reach the wave's pixels, in order; the
-            // wave leaves once all its pixels have stopped.  One by one in a
-            // batch with an infinite colour
-            const int group = __builtin_amdgcn_readfirstlane(s_over[0] | s_over[1] | s_over[2] | s_over[3]) ? NT : kFwdGroup;
+            // wave leaves once all its pixels have stopped.  One by one where
+            // an infinite colour is among them
 #pragma unroll 1
             for (int q = 0; q < NW; q++) {
                 tk = 0ull;
                 uint64_t m = uniform64(alive ? s_reach[w][q] : 0ull);
+                const int group = (m & uniform64(s_over[q])) ? NT : kFwdGroup;
                 // the last entry taken; until there is one, the first visited
                 // (a bit too many costs the backward a visit)
                 int tj = __builtin_ctzll(m | (1ull << 63));
@@ -1132,7 +1132,9 @@ __device__ __forceinline__ bool block_reached(const float4& a, const float4& b, 
 
 // The records of the narrow blends in LDS: (u, v, A, B), (C, opacity, band
 // lower edge, band upper edge), colour, box mask; one past the last is an
-// entry no pixel takes.
+// entry no pixel takes.  The opacity of an entry whose colour may be infinite is
+// negated: the lists' builders read that word anyway, and its magnitude is
+// free (a flag of the batch beside the records cost the forward 5% on long lists).
 template <int N>
 struct NarrowRecs {
     float4 a[N + 1], b[N + 1], col[N + 1];
@@ -1140,7 +1142,7 @@ struct NarrowRecs {
     __device__ __forceinline__ void put(int j, const float4& r0, const float4& r1, const float4& r2, int tx0p, int ty0p) {
         const float4 w2 = blend_stage_w2(r2, tx0p, ty0p);
         a[j] = r0;
-        b[j] = make_float4(r1.x, r1.y, w2.y, w2.z);
+        b[j] = make_float4(r1.x, colour_overflows(r1, r2) ? -r1.y : r1.y, w2.y, w2.z);
         col[j] = make_float4(r1.z, r1.w, w2.x, 0.f);
         box[j] = __float_as_uint(w2.w);
     }
@@ -1176,7 +1178,6 @@ __global__ __launch_bounds__(kQuarterThreads) void k_blend_fwd_narrow(CamDev cam
     __shared__ NarrowRecs<NB> s_r;
     __shared__ __align__(8) uint16_t s_list[NW][NB + 3 * kSlots];   // entries that reach the wave's block, in order
     __shared__ uint32_t s_live[2];
-    __shared__ uint32_t s_over[NW];   // colours of the batch that have overflowed
     const int tx0p = tx * kTile, ty0p = ty * kTile;
     const int row = lane >> 4, pix = lane & 15, block = quarter_block(quarter, w);
     const int lx = 4 * (block & 3) + (pix & 3), ly = 4 * (block >> 2) + (pix >> 2);
@@ -1199,13 +1200,7 @@ __global__ __launch_bounds__(kQuarterThreads) void k_blend_fwd_narrow(CamDev cam
     int par = 0;
     for (uint32_t eb = 0; eb < n; eb += NB, par ^= 1) {
         const uint32_t cnt_u = min((uint32_t)NB, n - eb);
-        bool over = false;
-        if ((uint32_t)tid < cnt_u) {
-            s_r.put(tid, ahead.r0, ahead.r1, ahead.r2, tx0p, ty0p);
-            over = colour_overflows(ahead.r1, ahead.r2);
-        }
-        const uint64_t overb = __builtin_amdgcn_ballot_w64(over);
-        if (lane == 0) s_over[w] = overb != 0ull ? 1u : 0u;
+        if ((uint32_t)tid < cnt_u) s_r.put(tid, ahead.r0, ahead.r1, ahead.r2, tx0p, ty0p);
         if (tid == 0) s_live[par] = 0u;
         if (eb + NB + tid < n) {
             ahead.id = ahead.next;
@@ -1215,12 +1210,14 @@ __global__ __launch_bounds__(kQuarterThreads) void k_blend_fwd_narrow(CamDev cam
         __syncthreads();
         if (alive) {
             int listed = 0;
+            uint64_t over = 0ull;   // listed entries with an infinite colour, which weight zero does not take away
 #pragma unroll
             for (int q = 0; q < NB / 64; q++) {
                 const int j = 64 * q + lane;
                 const float4 ra = s_r.a[j], rb = s_r.b[j];
                 const uint64_t m = __builtin_amdgcn_ballot_w64((uint32_t)j < cnt_u &&
                                                                block_reached(ra, rb, s_r.box[j], block, tx0p, ty0p));
+                over |= m & __builtin_amdgcn_ballot_w64(rb.y < 0.0f);
                 if ((m >> lane) & 1ull) s_list[w][listed + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)j;
                 listed += __popcll(m);
             }
@@ -1268,14 +1265,14 @@ __global__ __launch_bounds__(kQuarterThreads) void k_blend_fwd_narrow(CamDev cam
                                     __builtin_amdgcn_ballot_w64(power >= rb.z);
                 const uint64_t bm = pm & __builtin_amdgcn_ballot_w64(power < rb.w);
                 v.ok = pm & ~bm;
-                if (bm) v.ok |= bm & __builtin_amdgcn_ballot_w64(blend_exact_test(power, rb.y));
-                rows_all(__builtin_amdgcn_inverse_ballot_w64(v.ok) ? fminf(0.99f, rb.y * __expf(power)) : 0.0f, v.as);
+                if (bm) v.ok |= bm & __builtin_amdgcn_ballot_w64(blend_exact_test(power, fabsf(rb.y)));
+                rows_all(__builtin_amdgcn_inverse_ballot_w64(v.ok) ? fminf(0.99f, fabsf(rb.y) * __expf(power)) : 0.0f, v.as);
                 return v;
             };
             Rec ahead4 = load(four_at(0));
             uint64_t l = four_at(kSlots);
-            // an infinite colour in the batch, which weight zero does not take away
-            const bool any_over = __builtin_amdgcn_readfirstlane(s_over[0] | s_over[1] | s_over[2] | s_over[3]) != 0u;
+            // with one, every group takes the branch that selects
+            const float stop_below = over ? __builtin_huge_valf() : 1e-4f;
 #pragma unroll 1
             for (int g = 0; g < listed && alive; g += kSlots) {
                 const Four cur = eval(ahead4);
@@ -1289,7 +1286,7 @@ __global__ __launch_bounds__(kQuarterThreads) void k_blend_fwd_narrow(CamDev cam
 #pragma unroll
                 for (int s = 0; s < kSlots; s++) Ts[s + 1] = Ts[s] * (1.0f - cur.as[s]);
                 uint64_t own = cur.ok;   // lanes whose own slot's entry is taken
-                if ((alive & __builtin_amdgcn_ballot_w64(Ts[kSlots] < 1e-4f)) == 0ull && !any_over) {
+                if ((alive & __builtin_amdgcn_ballot_w64(Ts[kSlots] < stop_below)) == 0ull) {
 #pragma unroll
                     for (int s = 0; s < kSlots; s++) c += (cur.as[s] * Ts[s]) * cur.col[s];
                     T = Ts[kSlots];
@@ -1454,9 +1451,9 @@ __global__ __launch_bounds__(kRecords ? kNarrowThreads : kQuarterThreads) void k
                                 __builtin_amdgcn_ballot_w64(power <= 0.0f) & __builtin_amdgcn_ballot_w64(power >= rb.z);
             const uint64_t bm = pm & __builtin_amdgcn_ballot_w64(power < rb.w);
             v.ok = pm & ~bm;
-            if (bm) v.ok |= bm & __builtin_amdgcn_ballot_w64(blend_exact_test(power, rb.y));
+            if (bm) v.ok |= bm & __builtin_amdgcn_ballot_w64(blend_exact_test(power, fabsf(rb.y)));
             v.G = __expf(power);
-            v.raw = rb.y * v.G;
+            v.raw = fabsf(rb.y) * v.G;
             v.al = __builtin_amdgcn_inverse_ballot_w64(v.ok) ? fminf(0.99f, v.raw) : 0.0f;
             rows_all(v.al, v.as);
             // zero where the entry is not taken: opacity zero does not take an infinite colour away
