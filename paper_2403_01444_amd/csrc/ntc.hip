@@ -497,13 +497,20 @@ __device__ __forceinline__ int clamp_exp(int k) { return k < -126 ? -126 : (k > 
 // copy, a lane keeps its activations for the masks, and with two waves to a
 // SIMD the accumulators need no AGPRs (184 moves from them): 300K points fp16
 // 62 -> 47 us, 20,011 bf16 with the encoding 22 -> 19.
-template <class P>
+//
+// kScatter (means without lists, tables of more than kLdsParts parts): a lane
+// adds the gradients of its four levels to the table with global atomics, whose
+// rate of some 20 per ns bounds the launch; the rest hides behind them (a
+// launch of their own for the atomics, on the stored encoding gradient: 300K
+// points at T = 2^17 4.19 for 3.91 ms, at 2^19 4.23 for 3.92).
+template <class P, bool kScatter>
 __global__ __launch_bounds__(256, 2) void k_ntc_bwd(NtcDev nd, const typename P::S* __restrict__ table,
                                                  const typename P::S* __restrict__ mlp, const float* __restrict__ means,
                                                  int64_t n, const float* __restrict__ d_dmu,
                                                  const float* __restrict__ d_dq, float* __restrict__ g_part,
                                                  float* __restrict__ denc,
-                                                 const typename P::S* __restrict__ enc_in) {
+                                                 const typename P::S* __restrict__ enc_in,
+                                                 float* __restrict__ g_table) {
     using S = typename P::S;
     constexpr bool kCopies = P::KPL == 1;   // transposed copies of W1 and W2: see layer_tile_t
     constexpr int kWElems = 64 * LD32 + 64 * LD64 + 64 * LD16 + (kCopies ? 32 * LD64 + 64 * LD64 : 0);
@@ -669,9 +676,24 @@ __global__ __launch_bounds__(256, 2) void k_ntc_bwd(NtcDev nd, const typename P:
 #pragma unroll
             for (int mt = 0; mt < 2; mt++) {
                 const f4v e = layer_tile_t<P, 64>(sW1, LD32, sW1t, LD64, mt * 16, D1, LD64, lane);
-                // level-major [level][point][2]: one level's slice (8 n bytes)
-                // stays cache-resident while the gather walks that level
-                if (valid) {
+                if constexpr (kScatter) {
+                    if (in) {
+#pragma unroll
+                        for (int j = 0; j < 2; j++) {
+                            uint32_t ent[8];
+                            float wt[8];
+                            ntc_corners(nd, 8 * mt + 2 * g + j, x, ent, wt);
+                            const float e0 = e[2 * j] * inv, e1 = e[2 * j + 1] * inv;
+#pragma unroll
+                            for (int c = 0; c < 8; c++) {
+                                atomicAdd(g_table + 2 * (int64_t)ent[c], wt[c] * e0);
+                                atomicAdd(g_table + 2 * (int64_t)ent[c] + 1, wt[c] * e1);
+                            }
+                        }
+                    }
+                } else if (valid) {
+                    // level-major [level][point][2]: one level's slice (8 n bytes)
+                    // stays cache-resident while the gather walks that level
                     float2* d = dlev[mt] + pt;
                     d[0] = make_float2(e[0] * inv, e[1] * inv);
                     d[n] = make_float2(e[2] * inv, e[3] * inv);   // level lv + 1
@@ -1401,27 +1423,6 @@ __global__ __launch_bounds__(1024) void k_table_lds(NtcDev nd, TableParts tp, co
     }
 }
 
-// The same with global atomics, for tables of more than kLdsParts parts.
-__global__ __launch_bounds__(256) void k_table_scatter(NtcDev nd, const float* __restrict__ means, int64_t n,
-                                                       const float* __restrict__ denc, float* __restrict__ g_table) {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;   // (level, point)
-    if (t >= 16 * n) return;
-    const int lv = (int)(t / n);
-    const int64_t pt = t - lv * n;
-    const float mu[3] = {means[3 * pt], means[3 * pt + 1], means[3 * pt + 2]};
-    float xn[3];
-    if (!ntc_normalise(nd, mu, xn)) return;
-    const float2 e = reinterpret_cast<const float2*>(denc)[t];
-    uint32_t ent[8];
-    float wt[8];
-    ntc_corners(nd, lv, xn, ent, wt);
-#pragma unroll
-    for (int c = 0; c < 8; c++) {
-        atomicAdd(g_table + 2 * (int64_t)ent[c], wt[c] * e.x);
-        atomicAdd(g_table + 2 * (int64_t)ent[c] + 1, wt[c] * e.y);
-    }
-}
-
 template <class P>
 __global__ __launch_bounds__(256) void k_ntc_adam(float* __restrict__ p, float* __restrict__ gr, float* __restrict__ m,
                                                   float* __restrict__ v, typename P::S* __restrict__ work, int64_t n,
@@ -1554,8 +1555,7 @@ void table_grad(const Launch& L, const NtcDev& nd, const float* means, int64_t n
     };
     if (!csr) {
         TableParts tp;
-        const bool fits = table_parts(nd, kLdsEntries, tp);
-        if (fits) {
+        if (table_parts(nd, kLdsEntries, tp)) {   // else the backward has scattered it
             // about one workgroup per CU (the LDS holds one) for few points,
             // a slice per 8192 points for many, so that the coarse levels'
             // workgroups, whose atomics queue up, do not trail the launch
@@ -1565,9 +1565,6 @@ void table_grad(const Launch& L, const NtcDev& nd, const float* means, int64_t n
             const int slices = (int)std::max<int64_t>(std::max<int64_t>(few, n / 8192), 1);
             hipLaunchKernelGGL(k_table_lds, dim3((unsigned)(tp.count * slices)), dim3(1024), 0, L.st, nd, tp, means, n,
                                slices, denc, g_table);
-        } else {
-            hipLaunchKernelGGL(k_table_scatter, dim3((unsigned)((16 * n + 255) / 256)), dim3(256), 0, L.st, nd, means, n,
-                               denc, g_table);
         }
         ps.first = 0;
         hipLaunchKernelGGL(k_reduce_parts, dim3((unsigned)ps.blocks()), dim3(256), 0, L.st, ps);
@@ -1607,8 +1604,9 @@ void bwd_impl(const Launch& L, const NtcDev& nd, const void* table, const void* 
     // on a CU, the float32 one (twice the LDS) one
     const int parts = sizeof(typename P::S) == 4 ? max_parts / 2 : max_parts;
     const unsigned grid = (unsigned)std::min<int64_t>((nb + kWaves - 1) / kWaves, parts);
-    hipLaunchKernelGGL((k_ntc_bwd<P>), dim3(grid), dim3(256), 0, L.st, nd, (const typename P::S*)table,
-                       (const typename P::S*)mlp, means, n, d_dmu, d_dq, g_part, denc, (const typename P::S*)enc_in);
+    auto kern = denc ? k_ntc_bwd<P, false> : k_ntc_bwd<P, true>;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, L.st, nd, (const typename P::S*)table, (const typename P::S*)mlp,
+                       means, n, d_dmu, d_dq, g_part, denc, (const typename P::S*)enc_in, g_table);
     if (L.prof) L.prof->end(L.st);
     if (L.prof) L.prof->begin("ntc_scatter", L.st);
     table_grad(L, nd, means, n, csr, denc, g_table, PartSums{g_part, (int)grid, g_mlp, 0});
@@ -1636,11 +1634,14 @@ void ntc_backward(const Launch& L, int precision, const NtcDev& nd, const void* 
                   const float* means, int64_t n, const float* d_dmu, const float* d_dq, float* g_table, float* g_mlp,
                   float* g_part, int max_parts, const NtcCsr* csr, float* scratch, const void* enc_in) {
     if (n <= 0) return;
-    // without preparation the points go through the scratch a part at a time
-    const int64_t step = csr ? n : kScatterPoints;
+    // without preparation the points go through the scratch a part at a time,
+    // or their gradients straight to a large table
+    TableParts tp;
+    const bool scatter = !csr && !table_parts(nd, kLdsEntries, tp);
+    const int64_t step = csr || scatter ? n : kScatterPoints;
     for (int64_t p0 = 0; p0 < n; p0 += step) {
         const int64_t m = std::min(step, n - p0);
-        float* denc = csr ? csr->denc : scratch;
+        float* denc = csr ? csr->denc : scatter ? nullptr : scratch;
         if (L.prof) L.prof->begin("ntc_bwd", L.st);
         if (precision == 1)
             bwd_impl<PF16>(L, nd, table, mlp, means + 3 * p0, m, d_dmu + 3 * p0, d_dq + 4 * p0, g_table, g_mlp, g_part,
