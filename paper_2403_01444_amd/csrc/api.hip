@@ -238,7 +238,7 @@ gs3_status gs3_create(const gs3_config* cfg, gs3_ctx** out) {
     bool ok = true;
     c->slots.resize(cfg->num_slots);
     for (auto& s : c->slots) {
-        ok = ok && c->alloc(&s.rec, 3 * N) && c->alloc(&s.key, N) && c->alloc(&s.rect, N) && c->alloc(&s.count, N) &&
+        ok = ok && c->alloc(&s.rec, 3 * N) && c->alloc(&s.key, N) && c->alloc(&s.rect, N) && (supers || c->alloc(&s.count, N)) &&
              c->alloc(&s.vals[0], PK) && c->alloc(&s.ranges, c->max_tiles) && c->alloc(&s.T_final, PX) &&
              c->alloc(&s.last, PX) && c->alloc(&s.total, 1) && c->alloc(&s.goff, N) &&
              c->alloc(&s.gpos, cfg->grad_record_log2 > 0 ? PK : 1) && c->alloc(&s.tile_walk, c->max_tiles) &&

@@ -55,6 +55,7 @@ void iota_u32(const Launch& L, uint32_t* p, int64_t n);
 void sum_u32(const Launch& L, const uint32_t* a, int64_t n, uint64_t* out);
 
 // ---- rasterizer (raster.hip) -------------------------------------------------
+// count (optional): tiles of each Gaussian's rectangle
 void preprocess(const Launch& L, const GaussDev& g, const CamDev& cam, float4* rec, uint32_t* key, uint2* rect,
                 uint32_t* count);
 // radix64 path: keys/vals of every pair in Gaussian order from exclusive offsets
@@ -171,7 +172,7 @@ bool narrow_tiles(int ntiles, bool records);
 constexpr int kNarrowTiles = 512;
 // supers: the supers' lists (order then maps places to supers), or NULL for a
 // tile-major list read through ranges (order maps workgroups to tiles).
-// `order` is optional.  taken: for every 64 entries of a tile's list four
+// narrow needs no order.  taken: for every 64 entries of a tile's list four
 // words, one per quadrant of the tile (quad_x), with a bit for each entry a
 // pixel of the quadrant took; at the walked blocks' places (kWalkBlock / 64
 // each), or at taken_word of a tile-major list.  The words up to the tile's

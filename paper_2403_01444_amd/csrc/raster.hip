@@ -23,7 +23,7 @@ __global__ __launch_bounds__(256) void k_preprocess(GaussDev g, CamDev cam, floa
     Geo o;
     if (!geo_forward(g, cam, i, o)) {
         key[i] = 0xFFFFFFFFu;
-        count[i] = 0;
+        if (count) count[i] = 0;
         rect[i] = make_uint2(1u, 0u);
         rec[3 * i + 0] = make_float4(0.f, 0.f, 0.f, 0.f);
         rec[3 * i + 1] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -40,7 +40,7 @@ __global__ __launch_bounds__(256) void k_preprocess(GaussDev g, CamDev cam, floa
                                  __uint_as_float(pack16(o.x1, o.y1)), -logf(255.0f * op));
     const int tx0 = o.x0 / kTile, ty0 = o.y0 / kTile, tx1 = o.x1 / kTile, ty1 = o.y1 / kTile;
     rect[i] = make_uint2(pack16(tx0, ty0), pack16(tx1, ty1));
-    count[i] = (uint32_t)((tx1 - tx0 + 1) * (ty1 - ty0 + 1));
+    if (count) count[i] = (uint32_t)((tx1 - tx0 + 1) * (ty1 - ty0 + 1));
     key[i] = __float_as_uint(o.t[2]);
 }
 
@@ -393,16 +393,6 @@ __global__ __launch_bounds__(256) void k_ranges_from_hist(const uint32_t* __rest
     ranges[t] = make_uint2(s, e);
 }
 
-// XCD-aware tile order: consecutive workgroups are dealt round-robin to the
-// eight XCDs, so give each XCD a contiguous band of tiles (neighbouring tiles
-// share most of their Gaussians and hit the same L2).
-__device__ __forceinline__ int tile_of_block(int b, int ntiles) {
-    const int per = (ntiles + 7) / 8;
-    const int xcd = b & 7, k = b >> 3;
-    const int t = xcd * per + k;
-    return t;
-}
-
 // Longest-first tile schedule: tiles bucketed by the work they carry (list
 // length for the forward, walked entries for the backward) on a half-octave
 // scale, heaviest bucket first, so the long tiles start in the first wave of
@@ -457,7 +447,7 @@ __global__ __launch_bounds__(1024) void k_tile_order(const uint2* __restrict__ r
 // ---------------------------------------------------------------------------
 constexpr int kFwdGroup = 4;   // entries whose exponents are evaluated together
 template <bool kSuper>
-__global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int ntiles, const uint2* __restrict__ ranges,
+__global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, const uint2* __restrict__ ranges,
                                                              const uint32_t* __restrict__ vals,
                                                              const float4* __restrict__ rec, float* __restrict__ image,
                                                              float* __restrict__ T_final, uint32_t* __restrict__ last_out,
@@ -475,14 +465,13 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, int 
         const int x = blockIdx.x & 7, k = blockIdx.x >> 3;
         const int place = (k / T) * 8 + x, local = k % T;
         if (place >= nsuper) return;
-        sup = order ? order[place] : place;
+        sup = order[place];
         tx = (sup % sd.supers_x) * kSuperDim + local % kSuperDim;
         ty = (sup / sd.supers_x) * kSuperDim + local / kSuperDim;
         if (tx >= cam.tiles_x || ty >= cam.tiles_y) return;
         tile = ty * cam.tiles_x + tx;
     } else {
-        tile = order ? order[blockIdx.x] : tile_of_block(blockIdx.x, ntiles);
-        if (tile >= ntiles) return;
+        tile = order[blockIdx.x];
         tx = tile % cam.tiles_x;
         ty = tile / cam.tiles_x;
     }
@@ -796,7 +785,7 @@ __device__ __forceinline__ void sum_batch(int cnt, int w, int lane, const uint64
 }
 
 template <bool kSuper, bool kRecords, bool kOpacity>
-__global__ __launch_bounds__(kBlendThreads) void k_blend_bwd(CamDev cam, int ntiles, const uint2* __restrict__ ranges,
+__global__ __launch_bounds__(kBlendThreads) void k_blend_bwd(CamDev cam, const uint2* __restrict__ ranges,
                                                              const uint32_t* __restrict__ vals,
                                                              const float4* __restrict__ rec,
                                                              const float* __restrict__ d_image,
@@ -818,8 +807,7 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend_bwd(CamDev cam, int nti
     __shared__ uint64_t s_taken[2][NW];    // the batch's taken bits, [word][quadrant]
     __shared__ uint32_t s_over[2];         // colours of the batch that have overflowed
     __shared__ float s_g[NW][9][KB + 1];   // per-wave sums, [wave][term][entry] (padded: term rows on distinct banks)
-    const int tile = order ? order[blockIdx.x] : tile_of_block(blockIdx.x, ntiles);
-    if (tile >= ntiles) return;
+    const int tile = order[blockIdx.x];
     const uint32_t maxlast = tile_walk[tile];
     if (maxlast == 0) return;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -1852,8 +1840,6 @@ void ranges_from_hist(const Launch& L, const uint32_t* base, const uint64_t* tot
 }
 
 
-static unsigned blend_grid(int ntiles) { return (unsigned)(((ntiles + 7) / 8) * 8); }
-
 void tile_order(const Launch& L, const uint2* ranges, const uint32_t* walk, int ntiles, int* order) {
     if (L.prof) L.prof->begin("tile_order", L.st);
     hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(1024), 0, L.st, ranges, walk, ntiles, order);
@@ -1882,12 +1868,11 @@ void blend_forward(const Launch& L, const CamDev& cam, const uint2* ranges, cons
     } else if (supers) {
         const int nsuper = supers->supers_x * super_count_of(cam.tiles_y);
         const unsigned grid = (unsigned)((nsuper + 7) / 8 * 8 * kSuperDim * kSuperDim);
-        hipLaunchKernelGGL((k_blend_fwd<true>), dim3(grid), dim3(kBlendThreads), 0, L.st, cam, ntiles, ranges, vals,
-                           rec, image, T_final, last, tile_walk, order, taken, *supers, nsuper);
+        hipLaunchKernelGGL((k_blend_fwd<true>), dim3(grid), dim3(kBlendThreads), 0, L.st, cam, ranges, vals, rec, image,
+                           T_final, last, tile_walk, order, taken, *supers, nsuper);
     } else {
-        hipLaunchKernelGGL((k_blend_fwd<false>), dim3(order ? (unsigned)ntiles : blend_grid(ntiles)),
-                           dim3(kBlendThreads), 0, L.st, cam, ntiles, ranges, vals, rec, image, T_final, last,
-                           tile_walk, order, taken, SuperDev{}, 0);
+        hipLaunchKernelGGL((k_blend_fwd<false>), dim3((unsigned)ntiles), dim3(kBlendThreads), 0, L.st, cam, ranges, vals,
+                           rec, image, T_final, last, tile_walk, order, taken, SuperDev{}, 0);
     }
     if (L.prof) L.prof->end(L.st);
 }
@@ -1912,8 +1897,7 @@ void blend_backward(const Launch& L, const CamDev& cam, const uint2* ranges, con
     auto kern = supers ? (want_opacity ? k_blend_bwd<true, false, true> : k_blend_bwd<true, false, false>)
                 : records ? (want_opacity ? k_blend_bwd<false, true, true> : k_blend_bwd<false, true, false>)
                           : (want_opacity ? k_blend_bwd<false, false, true> : k_blend_bwd<false, false, false>);
-    hipLaunchKernelGGL(kern, dim3(order ? (unsigned)ntiles : blend_grid(ntiles)), dim3(kBlendThreads), 0, L.st, cam,
-                       ntiles, ranges, vals, rec, d_image, T_final, last, ga.tile_walk, ga.walk_off, ga.grec,
+    hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(kBlendThreads), 0, L.st, cam, ranges, vals, rec, d_image, T_final, last, ga.tile_walk, ga.walk_off, ga.grec,
                        (uint32_t)ga.grec_cap, accum, order, taken, supers ? *supers : SuperDev{});
     if (L.prof) L.prof->end(L.st);
 }
