@@ -166,8 +166,9 @@ void super_pairs(const Launch& L, const SuperDev& sd, int tiles_x, int tiles_y, 
 // Longest-first launch order of the tiles: by list length (walk == nullptr)
 // or by walked entries.  `order` holds ntiles ints.
 void tile_order(const Launch& L, const uint2* ranges, const uint32_t* walk, int ntiles, int* order);
-// Whether a view of ntiles tiles takes the narrow blends, whose workgroups
-// are all in flight at once: no order of the tiles is needed then.
+// Whether a view of ntiles tiles takes the narrow blends, which need no order of
+// the tiles: their workgroups, quarters of a tile, are all in flight at once or
+// nearly so.
 bool narrow_tiles(int ntiles, bool records);
 constexpr int kNarrowTiles = 512;
 // supers: the supers' lists (order then maps places to supers), or NULL for a

@@ -1038,9 +1038,9 @@ __global__ __launch_bounds__(kBlendThreads) void k_blend_bwd(CamDev cam, const u
 }
 
 // ---------------------------------------------------------------------------
-// Narrow blends, for views of few tiles.  With a tile to a CU or fewer, the
-// 8 x 8 blends above leave one wave to a SIMD and run at the latency of its
-// chain, entry after entry.  Here a tile has 16 waves: a wave takes a block of
+// Narrow blends, for views of few tiles.  With a tile or two to a CU, the
+// 8 x 8 blends above leave one wave or two to a SIMD and run at the latency of
+// its chain, entry after entry.  Here a tile has 16 waves: a wave takes a block of
 // 4 x 4 pixels, and its four 16-lane rows evaluate four entries (slots) at a
 // time, one entry to a row, each lane one pixel of it.  The opacities of the
 // four slots are then exchanged between the rows (permlane swaps), and every
@@ -1854,7 +1854,13 @@ void tile_order(const Launch& L, const uint2* ranges, const uint32_t* walk, int 
 // tiles 105 / 83 against 148 / 130: with many tiles of like lists the 8 x 8
 // blends fill the SIMDs, and evaluate a large Gaussian's pixels 64 at a time.
 // With gradient records the backward keeps a tile to a workgroup: at most one
-// per CU (400 uniform tiles 108 / 71 against 114 / 88).
+// per CU (400 uniform tiles 108 / 71 against 114 / 88).  Without, the backward's
+// LDS lets six workgroups share a CU, 384 tiles in all; the quarters past those
+// start in raster order as others end.  Even where the longest tiles come last
+// that costs less than 8 x 8 blends, longest first: surfaces in the far corner of
+// the view, 50K at 400, 480 and 512 tiles 487 / 570, 470 / 523 and 159 / 162
+// against 193 / 236, 193 / 237 and 109 / 81, 200K at 506 tiles 1177 / 1480
+// against 403 / 640.
 bool narrow_tiles(int ntiles, bool records) { return ntiles <= (records ? kNarrowTiles / 2 : kNarrowTiles); }
 
 void blend_forward(const Launch& L, const CamDev& cam, const uint2* ranges, const uint32_t* vals, const float4* rec,
