@@ -1530,7 +1530,10 @@ __global__ __launch_bounds__(256) void k_preprocess_bwd(GaussDev g, CamDev cam, 
     // plus this Gaussian's walked entries, visited in its tile-rectangle order
     if constexpr (kRecords) {
         // four entries at a time, whose chains of loads run side by side (5K
-        // Gaussians at 200 x 152, with a wave a workgroup: 29 -> 22 us)
+        // Gaussians at 200 x 152, with a wave a workgroup: 29 -> 20 us).  Bound by
+        // the lanes' lines where rectangles are large, so a lane loads for an entry
+        // that was walked only: 40K Gaussians at 1920 x 1080, one pair in fifteen
+        // walked, 920 us with every lane loading, 786 so, 814 one at a time
         constexpr int U = 4;
         const uint2 r = ga.rect[i];
         const int tx0 = r.x & 0xFFFF, ty0 = r.x >> 16, tx1 = r.y & 0xFFFF, ty1 = r.y >> 16;
@@ -1546,7 +1549,7 @@ __global__ __launch_bounds__(256) void k_preprocess_bwd(GaussDev g, CamDev cam, 
                 on[u] = e + u < n && k0 + e + u < ga.cap;
                 const uint32_t rel = (on[u] ? ga.gpos[k0 + e + u] : 0u) - ga.ranges[t].x;
                 on[u] = on[u] && rel < ga.tile_walk[t];
-                widx[u] = ga.walk_off[t] + rel;
+                widx[u] = on[u] ? ga.walk_off[t] + rel : 0u;
                 on[u] = on[u] && widx[u] < ga.grec_cap;
                 const bool wrap = tx == tx1;
                 if (!(wrap && ty == ty1)) {
@@ -1556,9 +1559,12 @@ __global__ __launch_bounds__(256) void k_preprocess_bwd(GaussDev g, CamDev cam, 
             }
             float v[U][9];
 #pragma unroll
-            for (int u = 0; u < U; u++)
+            for (int u = 0; u < U; u++) {
+                if (on[u]) {
 #pragma unroll
-                for (int c = 0; c < 9; c++) v[u][c] = ga.grec[(int64_t)c * ga.grec_cap + (on[u] ? widx[u] : 0u)];
+                    for (int c = 0; c < 9; c++) v[u][c] = ga.grec[(int64_t)c * ga.grec_cap + widx[u]];
+                }
+            }
 #pragma unroll
             for (int u = 0; u < U; u++)
 #pragma unroll
