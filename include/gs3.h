@@ -224,17 +224,22 @@ gs3_status gs3_ntc_forward(gs3_ctx* ctx, const float* means, int64_t n, uint64_t
  * <d_dmu, dmu> + <d_dq, dq> for the same means (adjoint of Eq. 5: MLP
  * backward, then the hash-table scatter-add).  token as for
  * gs3_ntc_forward: with a token the table gradient is the per-entry sum over
- * the prepared contribution lists (no atomics, fixed order) and the encoding
- * of the last forward with that token is reused when no gs3_ntc_step,
- * gs3_ntc_init or load came in between; with 0 the table gradient is
- * scattered with atomics. */
+ * the prepared contribution lists (no atomics, in the lists' order: see
+ * gs3_ntc_prepare) and the encoding of the last forward with that token is
+ * reused when no gs3_ntc_step, gs3_ntc_init or load came in between; with 0 the
+ * table gradient is scattered with atomics. */
 gs3_status gs3_ntc_backward(gs3_ctx* ctx, const float* means, int64_t n, uint64_t token,
                             const float* d_dmu, const float* d_dq);
 
 /* Per-frame setup for gs3_ntc_backward on frozen means (Stage 1 keeps the
  * previous frame's Gaussians frozen, Sec. 4.1): for every (mean, level,
  * corner) the table entry and trilinear weight are computed once and the
- * contributions are sorted by entry.  *token receives a new nonzero token
+ * contributions are sorted by entry.  With T above 2^18 an entry's
+ * contributions are ordered by mean, then corner; else by groups of 64 means,
+ * then corner, and inside of those as the LDS of gfx950 serves the lanes of one
+ * atomic instruction, which its ISA leaves open but no timing enters: the same
+ * means have given the same lists, and gradients bit for bit, in every run.
+ * *token receives a new nonzero token
  * that names this preparation; forward and backward calls pass it to use
  * the prepared lists.  The caller guarantees that the contents of `means`
  * do not change while the token is in use; a later gs3_ntc_prepare makes

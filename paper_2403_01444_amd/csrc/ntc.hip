@@ -492,7 +492,8 @@ __device__ __forceinline__ int clamp_exp(int k) { return k < -126 ? -126 : (k > 
 // holds 7 accumulator tiles instead of 28 and the register file leaves room
 // for more than one wave per SIMD.
 // Two workgroups' registers per SIMD and LDS per CU; bound by instructions
-// issued, so fragments strided in the points are read transposed (four 2-byte
+// issued (by either of a SIMD's two waves in 7 cycles of 10, the vector ALU in 4),
+// so fragments strided in the points are read transposed (four 2-byte
 // reads and their packing each, else), W1 and W2 are read either way from one
 // copy, a lane keeps its activations for the masks, and with two waves to a
 // SIMD the accumulators need no AGPRs (184 moves from them): 300K points fp16
@@ -798,8 +799,9 @@ static bool table_parts(const NtcDev& nd, int part, TableParts& tp) {
 // their own; only the slots are taken in turn, group after group (s_turn).  A
 // wave's LDS operations are done in order, so a list is ordered by groups of 64
 // points, then corner, then the order in which the LDS serves the lanes of one
-// instruction, which depends on the addresses alone: the same means give the
-// same lists.  Bound by the scattered 8-byte stores (an entry's list is one of
+// instruction.  The ISA leaves that order open; no other wave has a part in it,
+// and on this chip it depends on the addresses alone: the same means give the
+// same lists (the sort below orders them by construction).  Bound by the scattered 8-byte stores (an entry's list is one of
 // 32768 that a workgroup appends to, more lines than an L2 holds) and, with
 // points in spatial order, by the atomics of lanes on one entry.  300K points,
 // T = 2^15, with the means' Morton reorder: 1.85 ms with a radix sort of (entry,
