@@ -255,33 +255,50 @@ def stream(args):
 
 
 # Per-unit algorithmic work of each kernel.  The blend kernels are bound by
-# vector ALU work.  The reported count is about 25 operations per evaluated
-# (pixel, tile-list entry) pair, where a tile evaluates 256 x its longest
-# walk (the 16 x 16 pixels of a tile run in lockstep up to the last
-# contributor of any of them): evaluated pairs = 256 x sum over tiles of the
-# longest walk.  The build's own per-operation counts of the two kernels'
-# formulas (29 forward, 71 backward per pixel's own walked entries: Eq. 4 and
-# its adjoint, add / mul / compare / min / exp 1, fused multiply-add 2, the
-# backward with the 9 adds into the Gaussian's gradient terms) are reported
-# beside it, never as the roofline.
+# vector ALU work.  The reported count is nominal: about 25 operations per
+# (pixel, tile-list entry) pair with every one of a tile's 16 x 16 pixels
+# taken through the tile's list up to the last contributor of any of them,
+# pairs = 256 x sum over tiles of the longest walk.  The kernels leave out
+# entries that cannot reach a wave's pixels, so they evaluate fewer.  The
+# per-operation counts of the two kernels' formulas (29 forward, 71 backward
+# per pixel's own walked entries: Eq. 4 and its adjoint, add / mul / compare /
+# min / exp 1, fused multiply-add 2, the backward with the 9 adds into the
+# Gaussian's gradient terms) are reported beside it, never as the roofline.
 OPS_PER_EVALUATED_PAIR = 25
 BLEND_FWD_FLOP = 29
 BLEND_BWD_FLOP = 71
 FP32_VECTOR_PEAK_TFLOPS = 157.3
 
-# Algorithmic HBM bytes of the rasterizer (preprocess, prefix sum, keys, sort,
-# ranges, both blends, preprocess backward) per unit: per Gaussian the
-# preprocess reads 72 + 4S and writes 52 bytes, the scan moves 8, the
-# accumulators are zeroed (36) and the preprocess backward reads 36 + 72 + 4S
-# and writes 28; per pair 52 bytes (emit 12, one sort read and write 24,
-# ranges 8, one list read in each blend 4 + 4); per pixel 20 written by the
-# forward and 20 read by the backward.  (S: SH floats per Gaussian.)
+# Nominal HBM bytes of the rasterizer when every (Gaussian, tile) pair is
+# emitted and sorted (preprocess, prefix sum, keys, sort, ranges, both blends,
+# preprocess backward) per unit: per Gaussian the preprocess reads 72 + 4S and
+# writes 52 bytes, the scan moves 8, the accumulators are zeroed (36) and the
+# preprocess backward reads 36 + 72 + 4S and writes 28; per pair 52 bytes (emit
+# 12, one sort read and write 24, ranges 8, one list read in each blend 4 + 4);
+# per pixel 20 written by the forward and 20 read by the backward.  (S: SH
+# floats per Gaussian.)  No pair is written by the depth-first binning: see
+# binned_bytes for what its kernels move.
 RASTER_KERNELS = ("preprocess_fwd", "radix_pass", "bin_gather", "bin_count", "scan", "bin_scatter", "tile_ranges",
                   "tile_order", "blend_fwd", "blend_bwd", "preprocess_bwd")
 
 
 def raster_bytes(n, K, P, S):
     return n * (72 + 4 * S + 52 + 8 + 36 + 36 + 72 + 4 * S + 28) + K * 52 + P * (20 + 20)
+
+
+def binned_bytes(st):
+    """HBM bytes of the rasterizer's kernels as they are (depth-first, no
+    gradient records), each input read once and each output written once:
+    per Gaussian the preprocess (72 + 4S read, 60 written), four passes of the
+    depth order (counting 4, moving 8 + 8, the first without positions to
+    read), counting (order 4, rectangle 8, its copy 8), the scatter (12), a
+    48-byte record read by each blend, the gradient sums (36 read, 36 cleared)
+    and the preprocess backward (72 + 4S read, 28 written); per super entry 6
+    bytes written and 6 read; per walked entry its id (4) and a taken bit of
+    each quadrant (0.5), written and read; per pixel 20 written and 20 read."""
+    n, S = st["n"], st["sh_floats"]
+    return int(n * (72 + 4 * S + 60 + 4 * 20 - 4 + 20 + 12 + 2 * 48 + 72 + 72 + 4 * S + 28) + st["super_entries"] * 12 +
+               st["walked"] * 9 + st["pixels"] * 40)
 
 
 def algorithmic_work(name, st):
@@ -302,15 +319,24 @@ def algorithmic_work(name, st):
     if name == "ntc_bwd":
         return "hbm", n * (12 + 28) + st["table_bytes"], "byte"
     if name == "ntc_scatter":
-        # each contribution read once (entry weight and feature gradient), each table gradient written once
-        return "hbm", st["contribs"] * (4 + 8) + 4 * st["table_entries"] * 2, "byte"
+        # each contribution (place and weight, 8 bytes) and each point's encoding gradient read
+        # once, each table gradient read and written once
+        return "hbm", st["contribs"] * 8 + n * 128 + 16 * st["table_entries"], "byte"
     if name == "loss":
         return "hbm", P * (12 + 12 + 12) + P * 36 * 2, "byte"
     if name == "bin_scatter":
-        return "hbm", n * 16 + st["K"] * 4, "byte"
+        # order and rectangle read; an id and a tile mask written per super entry
+        return "hbm", n * 12 + st["super_entries"] * 6, "byte"
     if name == "bin_count":
-        return "hbm", n * 16, "byte"
+        return "hbm", n * 20, "byte"
     return None
+
+
+def super_entries(box, key):
+    """Entries of the lists of supers (64 x 64 pixels): the supers that the
+    pixel boxes (n, 4: x0, y0, x1, y1) of the visible Gaussians meet."""
+    b = box.cpu().numpy()[(key != -1).cpu().numpy()].astype(np.int64) // 64
+    return int(((b[:, 2] - b[:, 0] + 1) * (b[:, 3] - b[:, 1] + 1)).sum())
 
 
 def measured_traffic(kernel, workload):
@@ -486,16 +512,18 @@ def main():
     mem = {"context_workspace_bytes": ctx.workspace_bytes(), "device_in_use_bytes": int(total_b - free_b),
            "torch_peak_allocated_bytes": int(torch.cuda.max_memory_allocated())}
 
-    # pairs, walked list entries and per-pixel evaluations, averaged over the
-    # training views with the final transform
+    # pairs, super entries, walked list entries and per-pixel evaluations,
+    # averaged over the training views with the final transform
     dmu_f, dq_f = st1.transform()
-    Ks, walks, evals = [], [], []
+    Ks, walks, evals, supers = [], [], [], []
     for cam in cams:
         ctx.render(gg, cam, dmu_f, dq_f)
         sc, wk = ctx.debug_sums()          # sum of n_contrib; sum over tiles of the longest walk
         walks.append(wk)
         evals.append(sc)
         Ks.append(ctx.debug_counts()[0])
+        key, box, _ = ctx.debug_gaussians(g.n)
+        supers.append(super_entries(box, key))
     K0, walked, n_evals = int(np.mean(Ks)), int(np.mean(walks)), int(np.mean(evals))
 
     # s/frame: per-frame setup (Morton order of the frozen Gaussians, NTC
@@ -577,7 +605,7 @@ def main():
     # roofline of the dominant kernel (by device time per step)
     n_table_entries = cfg.num_table_params() // 2
     st = dict(n=g.n, pixels=cams[0].width * cams[0].height, walked=walked, evals=n_evals,
-              sh_floats=3 * (g.sh_degree + 1) ** 2, K=K0, contribs=8 * cfg.levels * g.n,
+              sh_floats=3 * (g.sh_degree + 1) ** 2, super_entries=int(np.mean(supers)), contribs=8 * cfg.levels * g.n,
               table_bytes=n_table_entries * 2 * (4 if args.precision == "f32" else 2),
               table_entries=n_table_entries)
     roof = None
@@ -597,16 +625,19 @@ def main():
                     "algorithmic_unit": unit, "ms_per_launch": round(dom_ms, 5)}
     if roof is not None and dom in ("blend_fwd", "blend_bwd"):
         per = BLEND_FWD_FLOP if dom == "blend_fwd" else BLEND_BWD_FLOP
-        roof["count"] = (f"{OPS_PER_EVALUATED_PAIR} ops x 256 x {walked} (sum over tiles of the longest walk) "
-                         f"evaluated pairs")
+        roof["count"] = (f"nominal: {OPS_PER_EVALUATED_PAIR} ops x 256 x {walked} (sum over tiles of the longest walk) "
+                         f"pairs; entries that cannot reach a quadrant of a tile are not evaluated")
         roof["builder_op_count"] = {"ops_per_pixel_entry": per, "pixel_entries": n_evals,
                                     "tflops": round(per * n_evals / (dom_ms * 1e-3) / 1e12, 3),
                                     "frac": round(per * n_evals / (dom_ms * 1e-3) / 1e12 / FP32_VECTOR_PEAK_TFLOPS, 4)}
     r_ms = sum(kernels[k]["ms_per_launch"] * kernels[k]["launches_per_step"] for k in RASTER_KERNELS if k in kernels)
     r_bytes = raster_bytes(g.n, K0, cams[0].width * cams[0].height, 3 * (g.sh_degree + 1) ** 2)
-    raster_hbm = {"kernels": list(RASTER_KERNELS), "ms_per_step": round(r_ms, 4), "algorithmic_bytes": int(r_bytes),
-                  "achieved_gbs": round(r_bytes / (r_ms * 1e-3) / 1e9, 1),
-                  "frac_of_8tbs": round(r_bytes / (r_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
+    # pair lists (radix64): the nominal bytes are those the kernels move
+    moved = binned_bytes(st) if args.sort_mode == "depth_first" else r_bytes
+    raster_hbm = {"kernels": list(RASTER_KERNELS), "ms_per_step": round(r_ms, 4), "algorithmic_bytes": int(moved),
+                  "achieved_gbs": round(moved / (r_ms * 1e-3) / 1e9, 1),
+                  "frac_of_8tbs": round(moved / (r_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
+                  "nominal_pair_list_bytes": int(r_bytes)}
     all_roof = {}
     for k, v in kernels.items():
         w = algorithmic_work(k, st)
@@ -617,10 +648,10 @@ def main():
         all_roof[k] = (round(amount / sec / 1e12 / FP32_VECTOR_PEAK_TFLOPS, 4) if bound == "alu"
                        else round(amount / sec / 1e9 / HBM_PEAK_GBS, 4))
 
-    # the NTC table gradient two ways on the same loop: the CSR gather over
-    # the per-frame contribution lists (the step above) and per-point float
-    # atomics into the table (token 0: no contribution lists, and the
-    # backward gathers the encoding again)
+    # the NTC table gradient two ways on the same loop: sums over the per-frame
+    # contribution lists (the step above) and atomics, into the table's parts in
+    # LDS or the table itself (token 0: no contribution lists, and the backward
+    # gathers the encoding again)
     table_grad = None
     if "ntc_bwd" in kernels:
         tok = st1.token
@@ -676,7 +707,7 @@ def main():
         "direct_f32_iters_per_s": None if direct is None else round(direct, 3),
         "iters_per_s_by_ntc_precision": by_precision, "multi_view_batch": multi_view,
         "pairs_per_view": int(K0), "sum_n_contrib": n_evals, "walked_entries": walked,
-        "evaluated_pairs": 256 * walked, "pixel_evals": n_evals,
+        "super_entries": st["super_entries"], "nominal_pairs": 256 * walked, "pixel_evals": n_evals,
         "device_memory": mem,
         "heldout_psnr_after_steps": round(psnr_ntc, 3),
         "warmup_s": round(t_warm, 3), "warmup_iters": args.warmup_iters, "frame_setup_s": round(t_prepare + t_reorder, 4),
