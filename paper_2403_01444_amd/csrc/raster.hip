@@ -434,9 +434,9 @@ __global__ __launch_bounds__(1024) void k_tile_order(const uint2* __restrict__ r
 // (fewer at the end of the list).  Each batch's indices are kept in a walked
 // block for the backward.  Otherwise the entries are vals[ranges[tile]).
 //
-// Bound by VALU issue where the launch fills the chip (0.77 of the cycles at 300K
-// uniform and 1352 x 1014, and as much again of scalar instructions) and by the
-// latency of one wave's chain where it does not.  So a wave takes a square of 8 x 8
+// Bound by instruction issue where the launch fills the chip (300K uniform at 1352 x
+// 1014: the vector ALUs in 0.69 of the cycles, and three scalar instructions for
+// four of theirs) and by the latency of one wave's chain where it does not.  So a wave takes a square of 8 x 8
 // pixels and evaluates only the staged entries that can reach it
 // (quads_reached, a bit per entry and quadrant: at the benchmark scene less
 // than half of the (wave, entry) visits of 16 x 4 pixels without the test),
@@ -723,7 +723,7 @@ __global__ __launch_bounds__(kBlendThreads, 7) void k_blend_fwd(CamDev cam, cons
 // terms over a wave's pixels (reduce-scatter), then over the tile's waves in
 // LDS, before one global atomic per term and tile.
 //
-// Bound by VALU issue on large views (every cycle, at 300K uniform and 1352 x
+// Bound by VALU issue on large views (0.95 of the cycles, 300K uniform at 1352 x
 // 1014).  Each wave has the forward's 8 x 8
 // quadrant and visits exactly the entries of which the forward noted that a
 // pixel of the quadrant took them (`taken`, a bit per entry and quadrant), so
